@@ -220,28 +220,24 @@ typedef struct {
   int32_t status;   /* VP_OK or the job's error code */
   uint64_t t_submit, t_admit, t_start, t_done; /* CLOCK_MONOTONIC ns, as the scheduler thread saw them */
   /* device wall clock (ticks of hipDeviceAttributeWallClockRate, one clock per
-   * device) when the job's first tile started and when its last tile ended;
-   * comparable between jobs of one context; 0 for a job that ran no tile */
+   * device) just before the job's first kernel and just after its last;
+   * comparable between jobs of one context; 0 for a job that ran none */
   uint64_t dev_first_tile, dev_last_tile;
 } vp_job_result;
 
 /* Enqueue a job; returns a ticket.  The caller's writes to job->vis_dev (the
  * data of a subtract job) must be complete, i.e. the writing stream
- * synchronised, before the call.  Only VP_PREC_MIXED is served: the
- * persistent kernels that run every admitted job's tiles are compiled
- * instances of the mixed path, and their register use sets the occupancy
- * that all jobs share (FP64 instances beside them would run at lower
- * occupancy and serialise against them); FP64 work goes through vp_predict /
- * vp_subtract on a caller stream, which may run beside serving.  The job is
+ * synchronised, before the call.  Only VP_PREC_MIXED is served; FP64 work
+ * goes through vp_predict / vp_subtract on a caller stream, which may run
+ * beside serving.  The job is
  * admitted when its HBM footprint fits the budget minus what admitted jobs
- * hold, in FIFO order, and a job slot and ring space are free; an admitted
- * job's tiles (its tables first, when its sky and observation have none yet)
- * are run by two persistent device kernels, one for the point/Gaussian pass
- * and one for the shapelet pass, together with the tiles of other admitted
- * jobs.  A failure of the job's own admission (e.g. its table allocation)
- * ends that job alone; a device failure ends every running job.  Errors:
- * VP_EINVAL, VP_ECAPACITY if the footprint exceeds the whole budget or the job
- * has more tiles than a serving ring holds.  Thread-safe. */
+ * hold, in FIFO order, and a job slot is free; an admitted job's kernels (its
+ * tables first, when its sky and observation have none yet) are those of
+ * vp_predict / vp_subtract, enqueued on one of a few library streams beside
+ * those of other admitted jobs.  A failure of the job's own admission (e.g.
+ * its table allocation) ends that job alone; a device failure ends every
+ * running job.  Errors: VP_EINVAL, VP_ECAPACITY if the footprint exceeds the
+ * whole budget.  Thread-safe. */
 int vp_submit(vp_ctx *ctx, const vp_job *job, uint64_t *ticket);
 
 /* Non-blocking: VP_OK with *res filled when the job is done (res->status holds
@@ -250,11 +246,11 @@ int vp_submit(vp_ctx *ctx, const vp_job *job, uint64_t *ticket);
  * poll.  Thread-safe. */
 int vp_poll(vp_ctx *ctx, uint64_t ticket, vp_job_result *res);
 
-/* Serving measurement: the number of completed launches of the persistent
- * serving kernels since the context's first vp_submit and the total duration
- * in ms of their launch groups (HIP events around each group on the kernels'
- * stream; a group still running is not counted).  Zeros before the first
- * vp_submit.  Errors: VP_EINVAL. */
+/* Serving measurement: the number of kernels that finished jobs have launched
+ * since the context's first vp_submit and the time in ms during which at least
+ * one job was on the device (the union of their device intervals; jobs still
+ * running are not counted).  Zeros before the first vp_submit.  Errors:
+ * VP_EINVAL. */
 int vp_serve_stats(vp_ctx *ctx, uint64_t *launches, double *resident_ms);
 
 /* HBM footprint (bytes) that admission charges for `job`.  Errors: VP_EINVAL. */

@@ -1,7 +1,7 @@
 // serve_core.h -- the serving scheduler's policy, free of any device code:
 // FIFO admission by HBM footprint, tickets, completion bookkeeping and the
-// scheduler thread.  What a job does on the device (publishing its work,
-// launching the persistent kernel, reading completion flags) sits behind
+// scheduler thread.  What a job does on the device (launching its kernels,
+// reading completion marks) sits behind
 // ServeExecutor; libvp's executor lives in vp_serve.cpp, and the tests drive
 // the core with a mock executor on the CPU (also under ThreadSanitizer).
 #ifndef VP_SERVE_CORE_H

@@ -9,10 +9,8 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
-#include <chrono>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <utility>
 #include <vector>
 
@@ -120,83 +118,49 @@ FluxArgs make_flux_args(const vp_sky *sky, const vp_obs *obs, const Derived &d) 
   return fa;
 }
 
-int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t stream, DerivedEntry **out) {
+int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t stream, bool serving,
+                DerivedEntry **out, bool *built) {
   const auto key = std::make_pair(sky->id, obs->id);
-  for (;;) {
-    std::unique_lock<std::mutex> lk(ctx->mu);
-    auto it = ctx->derived.find(key);
-    if (it != ctx->derived.end()) {
-      DerivedEntry *d = it->second;
-      if (d->building) {  // being built by the serving kernel
-        lk.unlock();
-        std::this_thread::sleep_for(std::chrono::microseconds(50));
-        continue;
-      }
-      if (d->ready && d->ready_stream != stream) {
-        hipError_t e = hipStreamWaitEvent(stream, d->ready, 0);
-        if (e != hipSuccess) return hip_error(e, "hipStreamWaitEvent");
-      }
-      d->serve_built = false;  // a direct call's kernels may read it from now on: never evicted by serving
-      *out = d;
-      return VP_OK;
-    }
-    DerivedEntry *d = nullptr;
-    int rc = alloc_derived(sky, obs, &d);
-    if (rc != VP_OK) return rc;
-    hipError_t e = hipEventCreateWithFlags(&d->ready, hipEventDisableTiming);
-    if (e == hipSuccess) {
-      ProfScope ps(ctx, stream, 0);
-      e = launch_derive(make_derive_args(sky, obs, d->d), stream);
-      if (e == hipSuccess) e = launch_flux(make_flux_args(sky, obs, d->d), stream);
-      ps.end();
-    }
-    if (e == hipSuccess) e = hipEventRecord(d->ready, stream);
-    if (e != hipSuccess) {
-      if (d->ready) (void)hipEventDestroy(d->ready);
-      d->mem.release();
-      delete d;
-      return hip_error(e, "building per-(sky, observation) tables");
-    }
-    d->ready_stream = stream;
-    ctx->derived[key] = d;
-    ctx->lib_bytes += d->mem.total;
-    *out = d;
-    return VP_OK;
-  }
-}
-
-int serve_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, DerivedEntry **out, bool *build) {
   std::lock_guard<std::mutex> lk(ctx->mu);
-  const auto key = std::make_pair(sky->id, obs->id);
   auto it = ctx->derived.find(key);
+  if (built) *built = it == ctx->derived.end();
   if (it != ctx->derived.end()) {
-    it->second->serve_users += 1;
-    *out = it->second;
-    *build = false;
+    DerivedEntry *d = it->second;
+    if (d->ready && d->ready_stream != stream) {
+      hipError_t e = hipStreamWaitEvent(stream, d->ready, 0);
+      if (e != hipSuccess) return hip_error(e, "hipStreamWaitEvent");
+    }
+    if (serving)
+      d->serve_users += 1;
+    else
+      d->serve_built = false;  // a direct call's kernels may read it from now on: never evicted by serving
+    *out = d;
     return VP_OK;
   }
   DerivedEntry *d = nullptr;
   int rc = alloc_derived(sky, obs, &d);
   if (rc != VP_OK) return rc;
-  d->building = true;
-  d->serve_built = true;
-  d->serve_users = 1;
+  hipError_t e = hipEventCreateWithFlags(&d->ready, hipEventDisableTiming);
+  if (e == hipSuccess) {
+    ProfScope ps(serving ? nullptr : ctx, stream, 0);
+    e = launch_derive(make_derive_args(sky, obs, d->d), stream);
+    if (e == hipSuccess) e = launch_flux(make_flux_args(sky, obs, d->d), stream);
+    ps.end();
+  }
+  if (e == hipSuccess) e = hipEventRecord(d->ready, stream);
+  if (e != hipSuccess) {
+    if (d->ready) (void)hipEventDestroy(d->ready);
+    d->mem.release();
+    delete d;
+    return hip_error(e, "building per-(sky, observation) tables");
+  }
+  d->ready_stream = stream;
+  d->serve_built = serving;
+  d->serve_users = serving ? 1 : 0;
   ctx->derived[key] = d;
   ctx->lib_bytes += d->mem.total;
   *out = d;
-  *build = true;
   return VP_OK;
-}
-
-bool derived_ready(vp_ctx *ctx, DerivedEntry *d) {
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  if (d->building) return false;
-  return !d->ready || hipEventQuery(d->ready) == hipSuccess;
-}
-
-void derived_built(vp_ctx *ctx, DerivedEntry *d) {
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  d->building = false;
 }
 
 static void free_entry(vp_ctx *ctx, DerivedEntry *d) {
@@ -230,7 +194,7 @@ uint64_t serve_evictable_bytes(vp_ctx *ctx) {
   std::lock_guard<std::mutex> lk(ctx->mu);
   uint64_t b = 0;
   for (auto &kv : ctx->derived)
-    if (kv.second->serve_built && kv.second->serve_users == 0 && !kv.second->building) b += kv.second->mem.total;
+    if (kv.second->serve_built && kv.second->serve_users == 0) b += kv.second->mem.total;
   return b;
 }
 
@@ -238,7 +202,7 @@ void serve_evict(vp_ctx *ctx) {
   std::lock_guard<std::mutex> lk(ctx->mu);
   for (auto it = ctx->derived.begin(); it != ctx->derived.end();) {
     DerivedEntry *d = it->second;
-    if (d->serve_built && d->serve_users == 0 && !d->building) {
+    if (d->serve_built && d->serve_users == 0) {
       it = ctx->derived.erase(it);
       free_entry(ctx, d);
     } else {
@@ -331,11 +295,8 @@ static int get_lut(vp_ctx *ctx, hipStream_t stream, const float **out) {
   return VP_OK;
 }
 
-// Launch the point/Gaussian and shapelet passes over the visibility tiles
-// with the pair's tables `d`.  prof: the context whose profiling records the
-// launches, or null.
-static int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
-                         int subtract, hipStream_t stream, const Derived &d, const float *lut) {
+int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
+                  int subtract, hipStream_t stream, const Derived &d, const float *lut, int *kernels) {
   TileArgs a;
   a.nrows = (int64_t)obs->T * obs->B;
   a.K = obs->K;
@@ -362,12 +323,14 @@ static int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int
   if (pg_pass) {
     ProfScope ps(prof, stream, 1);
     e = launch_pg(a, precision, stream);
+    if (kernels) ++*kernels;
   }
   if (e != hipSuccess) return hip_error(e, "launching the point/Gaussian kernel");
   if (sky->S > 0) {
     a.n_cb = (obs->K + kShpChan - 1) / kShpChan;
     ProfScope ps(prof, stream, 2);
     e = launch_shp(a, precision, sky->max_nmax, stream);
+    if (kernels) ++*kernels;
     if (e == hipErrorNotSupported) return set_error(VP_EINVAL, "precision %d has no shapelet kernel", precision);
     if (e != hipSuccess) return hip_error(e, "launching the shapelet kernel");
   }
@@ -377,7 +340,7 @@ static int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int
 int run_tiles(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
               int subtract, hipStream_t stream) {
   DerivedEntry *d = nullptr;
-  int rc = get_derived(ctx, sky, obs, stream, &d);
+  int rc = get_derived(ctx, sky, obs, stream, false, &d);
   if (rc != VP_OK) return rc;
   const float *lut = nullptr;
   if (precision == kLut && sky->S > 0) {

@@ -46,9 +46,8 @@ struct PeelWork {
 struct DerivedEntry {
   Derived d{};
   DeviceMem mem;
-  hipEvent_t ready = nullptr;  // recorded after kernels built the tables (null when the serving kernel did)
+  hipEvent_t ready = nullptr;  // recorded after the kernels that build the tables
   hipStream_t ready_stream = nullptr;
-  bool building = false;       // true while the serving kernel builds the tables (guarded by ctx->mu)
   bool serve_built = false;    // built for serving and not handed to a direct call since (guarded by ctx->mu)
   int serve_users = 0;         // admitted serving jobs that use the tables (guarded by ctx->mu)
 };
@@ -94,20 +93,22 @@ int run_tiles(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *ob
               void *vis, int subtract, hipStream_t stream);
 int check_call(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
                void *vis);
+// Launch the passes over the visibility tiles with the pair's tables `d`.
+// prof: the context whose profiling records the launches, or null; *kernels
+// (when given) grows by the number of kernels launched.
+int launch_passes(vp_ctx *prof, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
+                  void *vis, int subtract, hipStream_t stream, const Derived &d, const float *lut,
+                  int *kernels = nullptr);
 // Per-(sky, observation) tables, built on `stream` at first use and cached;
-// later callers on other streams wait for the build.
-int get_derived(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, hipStream_t stream,
-                DerivedEntry **out);
-// Serving: find the pair's tables, or allocate them unbuilt (*build = true:
-// the caller builds them and calls derived_built).
-int serve_derived(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, DerivedEntry **out,
-                  bool *build);
-bool derived_ready(vp_ctx *ctx, DerivedEntry *d);
-void derived_built(vp_ctx *ctx, DerivedEntry *d);
+// later callers on other streams wait for the build.  serving: the caller is
+// an admitted job, counted in the entry's users until serve_release_derived.
+// *built (when given): whether this call enqueued the build.
+int get_derived(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, hipStream_t stream, bool serving,
+                DerivedEntry **out, bool *built = nullptr);
 // A serving job is done with the pair's tables.
 void serve_release_derived(vp_ctx *ctx, DerivedEntry *d);
-// The tables a serving job was to build were never built (its work was
-// abandoned): drop them, so that no later call finds them ready.
+// The tables a serving job was to build may never have been built (its work
+// was abandoned): drop them, so that no later call finds them ready.
 void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d);
 // Bytes of tables that serving jobs built and no admitted job or direct call
 // uses, and their release (hipFree: waits for the device).

@@ -236,7 +236,7 @@ def vp_submit(ctx: int, kind: int, sky: int, obs: int, precision: int, dtype: in
 
 
 def vp_serve_stats(ctx: int):
-    """(launches, resident_ms) of the persistent serving kernel."""
+    """(kernels of finished jobs, ms with a job on the device)."""
     n, ms = ctypes.c_uint64(), ctypes.c_double()
     _check(load().vp_serve_stats(ctx, ctypes.byref(n), ctypes.byref(ms)))
     return int(n.value), float(ms.value)
