@@ -10,11 +10,13 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
 
 #include "../../include/vp.h"
+#include "ant_layout.h"
 #include "vp_internal.h"
 #include "vp_objects.h"
 
@@ -77,6 +79,43 @@ void DeviceMem::release() {
 // derived (sky, obs) tables
 // ---------------------------------------------------------------------------
 
+// Points by antenna: whole blocks of 32 points.
+int ant_jp(const vp_sky *sky) { return (sky->P + 31) / 32 * 32; }
+
+bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
+  if (obs->ant_n == 0 || sky->P < kAntMinPoints) return false;
+  // The factors are FP16 pairs (2^-24 .. 2^16): sqrt|S| is scaled so that the
+  // largest stays below 2^13.  The bound on the largest flux takes the largest
+  // S_ref and the largest spectral index together (the beam is at most 1);
+  // where that leaves the true one further than 2^20 behind, the headroom is
+  // gone and the vector path takes the points.
+  const double x = std::max(std::fabs(std::log(obs->f_lo / sky->nu_ref)), std::fabs(std::log(obs->f_hi / sky->nu_ref)));
+  const double grow = std::exp(sky->p_amax * x);
+  const double top = sky->p_smax * grow;
+  if (!(sky->p_smax >= 1e-30) || !(top <= 1e30) || !(grow <= 1048576.0)) return false;
+  if (scale) *scale = std::ldexp(1.0, 13 - (int)std::ceil(std::log2(std::sqrt(top))) - 1);
+  return true;
+}
+
+// Whether a call takes the points by antenna: the mixed paths, where the
+// antennas agree with the rows to 1e-10 turns (the path's own phases are good
+// to 3e-8) and lie within 2^17 wavelengths (fixed-point phases hold 2^19 turns;
+// |n - 1| <= 2), and the matrix kernel is the faster.  Its time goes by blocks
+// of 32 points and rounds of one workgroup per CU, a workgroup being a (time,
+// channels, macro): 2.2 us each, measured at 128 antennas x 448 workgroups and
+// 256 x 1,536.  The vector kernel's goes by points and rounds of three tiles
+// per CU: 0.32 us (128 antennas, 1,780 tiles), and not below 0.18 us for a few
+// tiles.
+static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision) {
+  if (precision != kMixed && precision != kMixedBf16 && precision != kMixedBf16x2) return false;
+  if (!ant_pair(sky, obs) || !(obs->ant_dev <= 1e-10) || !(obs->ant_reach <= 131072.0)) return false;
+  const double wgs = (double)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac;
+  const double ant_us = std::ceil(wgs / 256.0) * ant_jp(sky) / 32.0 * 2.2 + 8.0;
+  const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
+  const double vec_us = std::max(0.18, 0.32 * tiles / 768.0) * sky->P;
+  return ant_us < vec_us;
+}
+
 static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **out) {
   DerivedEntry *d = new DerivedEntry();
   const int J = sky->P + sky->G + sky->S;
@@ -86,6 +125,8 @@ static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **ou
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.sframe, sizeof(double) * 12 * Sc);
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.flux32, sizeof(float) * (size_t)Jc * obs->Kpad);
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.flux64, sizeof(double) * (size_t)Jc * obs->Kpad);
+  if (e == hipSuccess && ant_pair(sky, obs))
+    e = d->mem.alloc((void **)&d->d.amp, sizeof(float) * (size_t)ant_jp(sky) * obs->Kpad);
   if (e != hipSuccess) {
     d->mem.release();
     delete d;
@@ -118,6 +159,15 @@ FluxArgs make_flux_args(const vp_sky *sky, const vp_obs *obs, const Derived &d) 
   return fa;
 }
 
+static hipError_t build_amp(const vp_sky *sky, const vp_obs *obs, const Derived &d, hipStream_t stream) {
+  AntAmpArgs a;
+  if (!d.amp || !ant_pair(sky, obs, &a.scale)) return hipSuccess;
+  a.J = sky->P; a.Jp = ant_jp(sky); a.Kpad = obs->Kpad;
+  a.flux64 = d.flux64;
+  a.amp = d.amp;
+  return launch_ant_amp(a, stream);
+}
+
 int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t stream, bool serving,
                 DerivedEntry **out, bool *built) {
   const auto key = std::make_pair(sky->id, obs->id);
@@ -145,6 +195,7 @@ int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t s
     ProfScope ps(serving ? nullptr : ctx, stream, 0);
     e = launch_derive(make_derive_args(sky, obs, d->d), stream);
     if (e == hipSuccess) e = launch_flux(make_flux_args(sky, obs, d->d), stream);
+    if (e == hipSuccess) e = build_amp(sky, obs, d->d, stream);
     ps.end();
   }
   if (e == hipSuccess) e = hipEventRecord(d->ready, stream);
@@ -317,9 +368,31 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   a.uniform = precision == kFP64 || precision == kLut ? obs->uniform64 : obs->uniform;
   // A sky of shapelets only skips the point/Gaussian pass, which would only
   // write zeros (predict) or rewrite the data unchanged (subtract).
-  const bool pg_pass = sky->P + sky->G > 0 || sky->S == 0;
-  a.fresh = !pg_pass && !subtract;
+  const bool ant = d.amp && use_ant(sky, obs, precision);
+  const bool pg_pass = ant ? sky->G > 0 : sky->P + sky->G > 0 || sky->S == 0;
+  a.skip_points = ant;
+  a.fresh = !pg_pass && !ant && !subtract;
   hipError_t e = hipSuccess;
+  if (ant) {
+    AntArgs p;
+    double scale = 1.0;
+    ant_pair(sky, obs, &scale);
+    p.T = obs->T; p.B = obs->B; p.K = obs->K;
+    p.npad = obs->ant_npad;
+    p.J = sky->P; p.Jp = ant_jp(sky);
+    p.nmac = obs->ant_nmac; p.max_sup = obs->ant_max_sup;
+    p.kpack = obs->ant_kpack; p.nkb = (obs->K + p.kpack - 1) / p.kpack;
+    p.mac = obs->ant_mac; p.xyz = obs->ant_xyz; p.rowmap = obs->ant_rowmap;
+    p.fk = obs->fk; p.pos = d.pos; p.amp = d.amp;
+    p.unscale = 1.0 / (scale * scale);
+    p.neg = sky->p_neg;
+    p.fine = !obs->uniform;
+    p.vis = vis; p.c64 = a.c64; p.conj = a.conj; p.subtract = subtract;
+    ProfScope ps(prof, stream, 1);
+    e = launch_ant(p, stream);
+    if (kernels) ++*kernels;
+  }
+  if (e != hipSuccess) return hip_error(e, "launching the kernel of the points by antenna");
   if (pg_pass) {
     ProfScope ps(prof, stream, 1);
     e = launch_pg(a, precision, stream);
@@ -431,6 +504,44 @@ int vp_destroy_ctx(vp_ctx *ctx) {
   return VP_OK;
 }
 
+// The antennas behind the rows, if there are any (see ant_layout.h), and the
+// tables by which the kernels work on them.
+static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
+  // a complete list of n antennas has B = n (n - 1) / 2 rows; half of them
+  // flagged, n = 2 sqrt(B)
+  const int max_n = std::min(kAntMaxN, (int)(2.2 * std::sqrt((double)o->B)) + 8);
+  const double f = o->f_hi / kLightSpeed;
+  if (o->B > (int64_t)kAntMaxN * (kAntMaxN + 1) / 2) return hipSuccess;
+  const AntLayout L = find_antennas(o->T, o->B, uvw, 1e-10 / f, max_n);
+  const int np = (L.n + kAntBlk - 1) / kAntBlk * kAntBlk;
+  // (few baselines over very many times: the padding would outgrow the uvw)
+  if (L.n == 0 || (np > o->B && (int64_t)o->T * np > 1 << 20)) return hipSuccess;
+  const std::vector<AntMacro> mac = ant_macros(L.n, &o->ant_kpack);
+  std::vector<int32_t> map((size_t)np * np, 0);
+  for (int b = 0; b < o->B; ++b) {
+    const int p = L.p[b], q = L.q[b];
+    if (p <= q)
+      map[(size_t)p * np + q] = b + 1;
+    else
+      map[(size_t)q * np + p] = -(b + 1);
+  }
+  std::vector<double> xyz((size_t)o->T * np * 3, 0.0);
+  for (int t = 0; t < o->T; ++t)
+    std::copy(&L.xyz[(size_t)t * L.n * 3], &L.xyz[(size_t)t * L.n * 3] + 3 * (size_t)L.n, &xyz[(size_t)t * np * 3]);
+  hipError_t e = upload(&o->ant_xyz, xyz.data(), (int64_t)xyz.size(), o->mem);
+  if (e == hipSuccess) e = upload(&o->ant_rowmap, map.data(), (int64_t)map.size(), o->mem);
+  if (e == hipSuccess) e = upload(&o->ant_mac, mac.data(), (int64_t)mac.size(), o->mem);
+  if (e != hipSuccess) return e;
+  o->ant_n = L.n;
+  o->ant_npad = np;
+  o->ant_nmac = (int)mac.size();
+  for (const AntMacro &m : mac) o->ant_max_sup = std::max(o->ant_max_sup, (int)m.nsup);
+  o->ant_dev = L.dev * f;
+  for (size_t i = 0; i < L.xyz.size(); i += 3)
+    o->ant_reach = std::max(o->ant_reach, f * (std::fabs(L.xyz[i]) + std::fabs(L.xyz[i + 1]) + std::fabs(L.xyz[i + 2])));
+  return hipSuccess;
+}
+
 int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out) {
   if (!ctx || !desc || !out) return set_error(VP_EINVAL, "NULL argument");
   if (desc->n_time <= 0 || desc->n_bl <= 0 || desc->n_chan <= 0)
@@ -463,6 +574,8 @@ int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out) {
   o->beam_fwhm = desc->beam_fwhm_rad;
   o->beam_nu_ref = desc->beam_nu_ref_hz;
   o->h_freq.assign(desc->freq_hz, desc->freq_hz + desc->n_chan);
+  o->f_lo = *std::min_element(o->h_freq.begin(), o->h_freq.end());
+  o->f_hi = *std::max_element(o->h_freq.begin(), o->h_freq.end());
   std::vector<double> fk(o->Kpad);
   for (int k = 0; k < o->Kpad; ++k) fk[k] = desc->freq_hz[std::min(k, o->K - 1)] / kLightSpeed;
   if (o->K >= 2) {
@@ -481,6 +594,11 @@ int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out) {
   hipError_t e = upload(&o->uvw, desc->uvw_m, 3 * nrows, o->mem);
   if (e == hipSuccess) e = upload(&o->freq, desc->freq_hz, (int64_t)o->K, o->mem);
   if (e == hipSuccess) e = upload(&o->fk, fk.data(), (int64_t)o->Kpad, o->mem);
+  try {
+    if (e == hipSuccess) e = upload_antennas(o, desc->uvw_m);
+  } catch (const std::bad_alloc &) {  // without the antennas, points go the vector path
+    o->ant_n = 0;
+  }
   if (e != hipSuccess) {
     o->mem.release();
     delete o;
@@ -506,6 +624,26 @@ int vp_destroy_obs(vp_obs *obs) {
   obs->mem.release();
   delete obs;
   return VP_OK;
+}
+
+// The points from bright to faint, to a quarter of an octave (a counting sort
+// on the leading bits; points of one bin keep their order).  The kernels sum
+// points in short FP32 groups, on the matrix cores with roundings of ~1.3 units
+// of the group's largest term: groups of one brightness keep a bright point's
+// rounding off the faint ones' sum (MWA-like points by antenna: 2.1e-7 of the
+// result's norm as given).
+static std::vector<int32_t> by_flux(const double *s, int n) {
+  constexpr int kBins = 2048 << 2;  // exponent and two bits of the mantissa
+  std::vector<int32_t> at(kBins + 1, 0), ord(n);
+  auto bin = [&](int i) {
+    uint64_t u;
+    std::memcpy(&u, &s[i], 8);
+    return kBins - 1 - (int)((u << 1) >> 51);
+  };
+  for (int i = 0; i < n; ++i) ++at[bin(i) + 1];
+  for (int b = 0; b < kBins; ++b) at[b + 1] += at[b];
+  for (int i = 0; i < n; ++i) ord[at[bin(i)]++] = i;
+  return ord;
 }
 
 int vp_create_sky(vp_ctx *ctx, const vp_sky_desc *d, vp_sky **out) {
@@ -583,7 +721,16 @@ int vp_create_sky(vp_ctx *ctx, const vp_sky_desc *d, vp_sky **out) {
   k->h_nmax = nmax;
   const int J = P + G + S;
   std::vector<double> ra(J), dec(J), sref(J), alpha(J), coeffs(ncoef), b1(S), b2(S), spa(S);
-  for (int i = 0; i < P; ++i) { ra[i] = d->p_ra[i]; dec[i] = d->p_dec[i]; sref[i] = d->p_sref[i]; alpha[i] = d->p_alpha[i]; }
+  for (int i = 0; i < P; ++i) {
+    k->p_smax = std::max(k->p_smax, std::fabs(d->p_sref[i]));
+    k->p_amax = std::max(k->p_amax, std::fabs(d->p_alpha[i]));
+    if (d->p_sref[i] < 0) k->p_neg = 1;
+  }
+  const std::vector<int32_t> ord = by_flux(d->p_sref, P);
+  for (int i = 0; i < P; ++i) {
+    const int j = ord[i];
+    ra[i] = d->p_ra[j]; dec[i] = d->p_dec[j]; sref[i] = d->p_sref[j]; alpha[i] = d->p_alpha[j];
+  }
   for (int i = 0; i < G; ++i) { ra[P + i] = d->g_ra[i]; dec[P + i] = d->g_dec[i]; sref[P + i] = d->g_sref[i]; alpha[P + i] = d->g_alpha[i]; }
   bool terms = false;
   for (int i = 0; i < S; ++i) {
@@ -718,11 +865,15 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
   d.sframe = (double *)(base + o_sf);
   d.flux32 = (float *)(base + o_f32);
   d.flux64 = (double *)(base + o_f64);
+  d.amp = ant_pair(sky, obs) && sizeof(float) * (uint64_t)ant_jp(sky) * Kp <= kNoAllocAmpBytes
+              ? (float *)(base + kNoAllocScratchBytes)
+              : nullptr;
   const hipStream_t stream = (hipStream_t)hip_stream;
   // every entry the tile kernels read is written here first (the flux table
   // includes its zero padding), so nothing is cleared
   hipError_t e = launch_derive(make_derive_args(sky, obs, d), stream);
   if (e == hipSuccess) e = launch_flux(make_flux_args(sky, obs, d), stream);
+  if (e == hipSuccess) e = build_amp(sky, obs, d, stream);
   if (e != hipSuccess) return hip_error(e, "building the tables in the scratch array");
   return launch_passes(nullptr, sky, obs, precision, dtype, vis_dev, 0, stream, d, nullptr);
 }

@@ -51,6 +51,7 @@ struct Derived {
   double *sframe; // [S][12] a-vector(3), b-vector(3), (l, m, n-1)(3), pad(3)
   float *flux32;  // [J][Kpad]
   double *flux64; // [J][Kpad]
+  float *amp;     // [Kpad][Jp] sign(S) sqrt|S| x scale of the points, by antenna (null: not taken by antenna)
 };
 
 // Shapelet coefficient tiles (depend on the sky only).
@@ -113,6 +114,7 @@ struct TileArgs {
   ShpTiles t;
   void *vis;           // output (predict) or data (subtract), [nrows][K] complex
   int subtract;        // 0: vis = V; 1: vis = vis - V
+  int skip_points;     // 1: the points were taken by antenna; the Gaussians add to vis (or subtract from it)
   int c64;             // 1: complex64, 0: complex128
   int conj;            // 1 when the exponent sign is -1
   const float *lut;    // basis table of the lookup-table variant, or null
@@ -120,6 +122,35 @@ struct TileArgs {
   int uniform;         // 1: channels uniformly spaced (the mixed path rotates phasors by dfk)
   int fresh;           // 1: the shapelet pass starts from zero instead of reading vis (a
                        //    predict with no point/Gaussian pass before it)
+};
+
+// Points by antenna (vp_ant.hip).
+constexpr int kAntMinPoints = 64;  // two blocks of 32 points: below, padding is most of the work
+constexpr int kAntMaxN = 1024;     // antennas (the pair map takes 4 n^2 bytes)
+struct AntMacro;
+struct AntArgs {
+  int T, B, K;            // time steps, baselines, channels
+  int npad;               // antennas padded to whole blocks
+  int J, Jp;              // points, padded to whole groups of blocks
+  int nmac, max_sup;      // macros and the most blocks one of them stages
+  int kpack, nkb;         // channels per workgroup, workgroups over the channels
+  const AntMacro *mac;
+  const double *xyz;      // [T][npad][3] antenna coordinates, metres (zero in the padding)
+  const int32_t *rowmap;  // [npad][npad] row of pair (p, q) + 1, negative: conjugated, 0: none
+  const double *fk;       // [Kpad] nu / c
+  const double4 *pos;     // [J] l, m, n - 1
+  const float *amp;       // [Kpad][Jp]
+  double unscale;         // 1 / (the amplitudes' scale)^2
+  int neg;                // 1: some fluxes are negative
+  int fine;               // 1: the more exact factors (irregular channels)
+  void *vis;              // [T][B][K]
+  int c64, conj, subtract;
+};
+struct AntAmpArgs {
+  int J, Jp, Kpad;
+  const double *flux64;   // [J][Kpad]
+  double scale;
+  float *amp;             // [Kpad][Jp]
 };
 
 // A serving job's mark: its sequence number, and the device wall clock when it
@@ -164,6 +195,10 @@ hipError_t device_init(int dev);
 void *noalloc_scratch(int dev);
 // Size of that array: per-(sky, observation) tables of vp_predict_noalloc.
 constexpr uint64_t kNoAllocScratchBytes = 64ull << 20;
+// A second part of the array, behind the first, holds the points' amplitudes
+// by antenna: 4 of the 12 bytes per (component, channel) above, and less than
+// twice the points in padding, so that no pair the first part takes exceeds it.
+constexpr uint64_t kNoAllocAmpBytes = 48ull << 20;
 
 // Host-side launchers (vp_kernels.hip).
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s);
@@ -172,6 +207,8 @@ hipError_t launch_tiles_build(const TileBuildArgs &a, int max_nmax, hipStream_t 
 hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s);
 hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s);
 hipError_t launch_lut_build(float *T, hipStream_t s);
+hipError_t launch_ant_amp(const AntAmpArgs &a, hipStream_t s);
+hipError_t launch_ant(const AntArgs &a, hipStream_t s);
 hipError_t launch_mark(ServeMark *m, uint64_t seq, hipStream_t s);
 hipError_t launch_gain(const GainArgs &a, hipStream_t s);
 hipError_t launch_gain_subtract(const GainArgs &a, hipStream_t s);

@@ -360,7 +360,7 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
   // uniform grid (also when they lie past the last channel)
   const double fa3 = fma(3.0, a.dfk, f[0]), fa6 = fma(6.0, a.dfk, f[0]);
 
-  const int J0[2] = {0, a.P};
+  const int J0[2] = {a.skip_points ? a.P : 0, a.P};
   const int JN[2] = {a.P, a.P + a.G};
 #pragma unroll
   for (int kind = 0; kind < 2; ++kind) {  // 0: points, 1: Gaussians
@@ -546,6 +546,9 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
       if (a.subtract) {
         const float2 d = *o;
         *o = make_float2(d.x - re, d.y - im);
+      } else if (a.skip_points) {
+        const float2 d = *o;
+        *o = make_float2((float)((double)d.x + tre), (float)((double)d.y + (a.conj ? -tim : tim)));
       } else {
         *o = make_float2(re, im);
       }
@@ -556,6 +559,9 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
       if (a.subtract) {
         const double2 d = *o;
         *o = make_double2(d.x - re, d.y - im);
+      } else if (a.skip_points) {
+        const double2 d = *o;
+        *o = make_double2(d.x + re, d.y + im);
       } else {
         *o = make_double2(re, im);
       }
@@ -1518,7 +1524,7 @@ static hipError_t init_constants() {
 // call), one array per device for the life of the process.  In host code the
 // name is only a stand-in: its device address, which differs per device, is
 // looked up once per device below and used everywhere instead.
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocAmpBytes];
 static void *g_scratch[kMaxDevices];
 
 hipError_t device_init(int dev) {

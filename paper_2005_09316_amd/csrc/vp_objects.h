@@ -114,6 +114,10 @@ void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d);
 // uses, and their release (hipFree: waits for the device).
 uint64_t serve_evictable_bytes(vp_ctx *ctx);
 void serve_evict(vp_ctx *ctx);
+// Whether the pair's points may be taken by antenna, on any path (a property of
+// the pair: its tables then hold the amplitudes, Jp x Kpad of them).
+bool ant_pair(const struct ::vp_sky *sky, const struct ::vp_obs *obs, double *scale = nullptr);
+int ant_jp(const struct ::vp_sky *sky);
 DeriveArgs make_derive_args(const struct ::vp_sky *sky, const struct ::vp_obs *obs, const Derived &d);
 FluxArgs make_flux_args(const struct ::vp_sky *sky, const struct ::vp_obs *obs, const Derived &d);
 void drop_derived(vp_ctx *ctx, uint64_t sky_id, uint64_t obs_id);
@@ -140,6 +144,14 @@ struct vp_obs {
   int uniform = 0;        // channels uniformly spaced (to 1e-12 of nu/c)
   int uniform64 = 0;      // ... to 1e-15 of nu/c (enough for the FP64 path)
   std::vector<double> h_freq;
+  double f_lo = 0, f_hi = 0;  // lowest and highest channel frequency, Hz
+  // antennas behind the baselines (ant_layout.h); ant_n 0: none found
+  int ant_n = 0, ant_npad = 0, ant_nmac = 0, ant_max_sup = 0, ant_kpack = 1;
+  double ant_dev = 0;           // their largest disagreement with a row, in turns at the highest frequency
+  double ant_reach = 0;         // largest antenna coordinate (a sum of magnitudes), in wavelengths at the highest frequency
+  double *ant_xyz = nullptr;    // device [T][npad][3]
+  int32_t *ant_rowmap = nullptr;  // device [npad][npad]
+  vp::AntMacro *ant_mac = nullptr;
   int jobs = 0;           // pending serving jobs using it (guarded by ctx->mu)
   vp::DeviceMem mem;
 };
@@ -151,6 +163,8 @@ struct vp_sky {
   double nu_ref = 0;
   int max_nmax = 0;
   std::vector<int32_t> h_nmax;
+  double p_smax = 0, p_amax = 0;  // points: largest |S_ref| and largest |spectral index|
+  int p_neg = 0;                  // points: 1 if an S_ref is negative
   double *ra = nullptr, *dec = nullptr, *sref = nullptr, *alpha = nullptr;  // device [J]
   double *g_maj = nullptr, *g_min = nullptr, *g_pa = nullptr;               // device [G]
   double *s_beta1 = nullptr, *s_beta2 = nullptr, *s_pa = nullptr;          // device [S]
