@@ -90,8 +90,8 @@ struct Pass {
           q = cur + 2;
         }
       }
-      // ... or any antennas found so far
-      for (int s = 0; s < n && q < 0; ++s) {
+      // ... or any antennas found so far (on a complete list, the next one at most)
+      for (int s = 0; s < (rows ? n : std::min(n, 2)) && q < 0; ++s) {
         p = cur + s < n ? cur + s : cur + s - n;
         ++looks;
         plus(places.at(p), d, y);
@@ -181,10 +181,15 @@ AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n) 
       const double g = s.via[a] >= 0 ? 1.0 : -1.0, *u = U + 3 * (size_t)(s.via[a] >= 0 ? s.via[a] : ~s.via[a]);
       for (int c = 0; c < 3; ++c) X[3 * a + c] = X[3 * s.from[a] + c] + g * u[c];
     }
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0;
     for (int b = 0; b < B; ++b) {
       const double *x = X + 3 * (size_t)P[b], *y = X + 3 * (size_t)Q[b], *u = U + 3 * (size_t)b;
-      for (int c = 0; c < 3; ++c) dev = std::max(dev, std::fabs(y[c] - x[c] - u[c]));
+      const double e0 = std::fabs(y[0] - x[0] - u[0]), e1 = std::fabs(y[1] - x[1] - u[1]), e2 = std::fabs(y[2] - x[2] - u[2]);
+      d0 = e0 > d0 ? e0 : d0;
+      d1 = e1 > d1 ? e1 : d1;
+      d2 = e2 > d2 ? e2 : d2;
     }
+    dev = std::max(dev, std::max(d0, std::max(d1, d2)));
     if (!(dev <= tol)) return r;
   }
   r.n = n;

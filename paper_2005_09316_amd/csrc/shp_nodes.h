@@ -1,0 +1,45 @@
+// shp_nodes.h -- how many frequencies determine a shapelet's envelope over a
+// band, free of any device code.
+//
+// Along a baseline the envelope is a function of frequency alone: the line
+// (a, b) = nu (a_m, b_m) / c through the origin of the Hermite plane.  Rotated
+// onto that line, a sum over n1 + n2 <= N is a combination of the Hermite
+// functions phi_n(x), n <= N, of x = nu |(a_m, b_m)| / c (the functions of one
+// order n1 + n2 are rotated among themselves).  phi_n oscillates at
+// sqrt(2 n + 1 - x^2) where it is not small, so over a band of relative width
+// its phase advances by at most x sqrt(2 n + 1 - x^2) <= n + 1/2 per unit of
+// ln nu, whatever the baseline's length: the envelope is entire, of bounded
+// bandwidth over the band, and a Chebyshev interpolation in nu converges as
+// (w/2)^M / M! with w = (N + 1/2) x the band's half-width over its lower end.
+#pragma once
+
+#include <cmath>
+
+namespace vp {
+
+constexpr int kNodesMax = 64;  // nodes a plan may have
+// Absolute errors of phi_n allowed to the interpolation: a hundredth of the
+// mixed path's own (its products carry FP32 sums), and below the rounding of
+// the FP64 recurrence.
+constexpr double kNodesTolMixed = 1e-10, kNodesTolFp64 = 2e-15;
+
+// The least number of Chebyshev nodes on [f_lo, f_hi] for order nmax, or 0
+// when kNodesMax do not suffice.  The series' leading term (damped as the
+// Bessel function J_M(w) it stands for) against the tolerance; the order is
+// raised by 6.5 for the functions' tails beyond their turning points, which
+// matter at low orders.  Against the largest Chebyshev coefficients of phi_n
+// over all n <= N and lines, N = 0 .. 96 and bands up to a factor of 2, it is
+// never less than enough, and 1.6 more on average.
+inline int shp_nodes(int nmax, double f_lo, double f_hi, double tol) {
+  if (!(f_lo > 0.0) || !(f_hi >= f_lo)) return 0;
+  const double w = (nmax + 7.0) * 0.5 * (f_hi - f_lo) / f_lo;
+  if (!(w <= kNodesMax)) return 0;
+  double t = 2.0;
+  for (int m = 1; m <= kNodesMax; ++m) {
+    t *= 0.5 * w / m;
+    if (m >= w && t * std::exp(-0.25 * w * w / (m + 1)) <= tol) return m;
+  }
+  return 0;
+}
+
+}  // namespace vp

@@ -51,6 +51,7 @@ struct Derived {
   double *sframe; // [S][12] a-vector(3), b-vector(3), (l, m, n-1)(3), pad(3)
   float *flux32;  // [J][Kpad]
   double *flux64; // [J][Kpad]
+  double *interp[2];  // shapelet nodes and interpolation of the mixed and the FP64 path (NodePlan), or null
   float *amp;     // [Kpad][Jp] sign(S) sqrt|S| x scale of the points, by antenna (null: not taken by antenna)
 };
 
@@ -66,12 +67,28 @@ struct ShpTiles {
   const int32_t *nmax;     // [S]
 };
 
+// Shapelets by nodes: the envelopes are evaluated at M Chebyshev nodes of the
+// band and interpolated to the channels (M = 0: evaluated at every channel).
+// Table: the nodes nu / c [kNodesStride], then the interpolation matrix as
+// operands of 16 channels x 4 nodes: [K / 16][M / 4][64], both rounded up, lane
+// l of a block holding channel 4 (l mod 4) + (l mod 16) / 4 and node l / 16 of it.
+struct NodePlan {
+  int M, Mp;                 // nodes, padded to a multiple of 4 (zero columns)
+  double mid, half;          // the band in nu / c
+};
+constexpr int kNodesStride = 64;
+inline size_t node_doubles(int K, int Mp) { return kNodesStride + (size_t)((K + 15) / 16) * 16 * Mp; }
+constexpr int kNodesMaxChan = 4096;
+
 struct DeriveArgs {
   int P, G, S;
   const double *ra, *dec;          // [J]
   const double *g_maj, *g_min, *g_pa;  // [G]
   const double *s_beta1, *s_beta2, *s_pa;  // [S]
   double ra0, dec0;
+  int K;                           // the interpolation tables (below), for plans with M > 0
+  const double *fk;                // [Kpad] nu / c
+  NodePlan plan[2];
   Derived d;
 };
 
@@ -199,6 +216,9 @@ constexpr uint64_t kNoAllocScratchBytes = 64ull << 20;
 // by antenna: 4 of the 12 bytes per (component, channel) above, and less than
 // twice the points in padding, so that no pair the first part takes exceeds it.
 constexpr uint64_t kNoAllocAmpBytes = 48ull << 20;
+// A third part holds the interpolation tables of both paths (at most
+// kNodesMaxChan channels x kNodesStride nodes each).
+constexpr uint64_t kNoAllocNodeBytes = 2ull * (kNodesMaxChan + 16) * kNodesStride * 8;
 
 // Host-side launchers (vp_kernels.hip).
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s);
@@ -206,6 +226,8 @@ hipError_t launch_flux(const FluxArgs &a, hipStream_t s);
 hipError_t launch_tiles_build(const TileBuildArgs &a, int max_nmax, hipStream_t s);
 hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s);
 hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s);
+hipError_t launch_shp_nodes(const TileArgs &a, const NodePlan &p, int prec, int max_nmax, hipStream_t s);
+bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp);
 hipError_t launch_lut_build(float *T, hipStream_t s);
 hipError_t launch_ant_amp(const AntAmpArgs &a, hipStream_t s);
 hipError_t launch_ant(const AntArgs &a, hipStream_t s);

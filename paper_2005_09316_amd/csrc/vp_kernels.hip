@@ -151,9 +151,56 @@ __device__ __forceinline__ void derive_one(const DeriveArgs &a, int j) {
   }
 }
 
-__global__ void k_derive(DeriveArgs a) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < a.P + a.G + a.S) derive_one(a, j);
+// Row k (a channel) of the interpolation matrix of plan i, one wave a row and
+// one lane a node: barycentric weights of the Chebyshev nodes, normalised; a
+// channel on a node takes that node alone.  Channels past the last and padding
+// nodes are zero.
+__device__ __forceinline__ void interp_row(const DeriveArgs &a, int i, int k) {
+  const NodePlan &p = a.plan[i];
+  const int m = threadIdx.x & 63;
+  double *tab = a.d.interp[i];
+  double sn, cs;
+  sincospi((2 * m + 1) / (2.0 * p.M), &sn, &cs);
+  const double fm = fma(p.half, cs, p.mid);
+  if (k == 0) tab[m] = m < p.M ? fm : p.mid;
+  double w = 0.0;
+  if (k < a.K) {
+    const double dx = a.fk[k] - fm;
+    const unsigned long long hit = __ballot(m < p.M && dx == 0.0);
+    if (hit)
+      w = m == __ffsll(hit) - 1 ? 1.0 : 0.0;
+    else if (m < p.M)
+      w = ((m & 1) ? -sn : sn) / dx;
+  }
+  double sum = w;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+  if (k < a.K) w /= sum;
+  const int c = k & 15;  // channel 4 g + r of its block is operand row 4 r + g
+  if (m < p.Mp)
+    tab[kNodesStride + ((size_t)(k >> 4) * (p.Mp >> 2) + (m >> 2)) * 64 + (m & 3) * 16 + 4 * (c & 3) + (c >> 2)] = w;
+}
+
+// Blocks of 128 threads: the components first, then two rows of the
+// interpolation tables each.
+__global__ __launch_bounds__(128) void k_derive(DeriveArgs a) {
+  const int J = a.P + a.G + a.S, nj = (J + 127) / 128;
+  if ((int)blockIdx.x < nj) {
+    const int j = blockIdx.x * 128 + threadIdx.x;
+    if (j < J) derive_one(a, j);
+    return;
+  }
+  int row = 2 * ((int)blockIdx.x - nj) + (int)(threadIdx.x >> 6);
+  const int K16 = (a.K + 15) / 16 * 16;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (a.plan[i].M == 0) continue;
+    if (row < K16) {
+      interp_row(a, i, row);
+      return;
+    }
+    row -= K16;
+  }
 }
 
 // S_j(nu_k) = S_ref (nu_k / nu_ref)^alpha * B_j(nu_k) for flat index
@@ -925,6 +972,152 @@ __device__ __forceinline__ void shp_group_mfma(const bf16x8 (&A)[3][2], const bf
   O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[0][1], Bg[0][1], O, 0, 0, 0);
 }
 
+// The envelope of one shapelet of order N at this lane's (xa, xb), with the
+// coefficient tiles Ab in LDS (parts part_stride apart); every lane of the wave
+// takes part.  See shp_tile_bf.
+template <int CM>
+__device__ __forceinline__ void shp_eval_bf(double xa, double xb, int N, const __bf16 *Ab, int part_stride, double &xr,
+                                            double &xi) {
+  constexpr int parts = CM == kCmBf16x3 ? 3 : 2;
+  const int q = N / 32;
+  double pb_m1 = 0, pb_n = shp_phi0<double>(xb) * c_sc[0];
+  const double ua0 = shp_phi0<double>(xa) * c_sc[0];
+  double sr[4] = {0, 0, 0, 0}, si[4] = {0, 0, 0, 0};
+  int pbase = 0;
+  for (int ch = 0; ch <= q; ++ch) {
+    const int nb8 = min(4, (N - 32 * ch) / 8 + 1);
+    // second-axis operands of both groups: Bv[group][part][parity]
+    bf16x8 Bv[2][3][2];
+    {
+      // pkb[part][parity][hc] element jj holds orders 16 hc + 4 jj +
+      // parity (low half) and 16 hc + 4 jj + 2 + parity (high half)
+      u32x4 pkb[3][2][2];
+      double prev = pb_m1, cur = pb_n;
+#pragma unroll
+      for (int s4 = 0; s4 < 8; ++s4) {
+        const int hc = s4 >> 2, jj = s4 & 3;
+        if (s4 < 2 * nb8) {
+          double v4[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            v4[t] = cur;
+            const double nx = psi_next<double>(xb, cur, prev, c_half[32 * ch + 4 * s4 + t]);
+            prev = cur;
+            cur = nx;
+          }
+#pragma unroll
+          for (int par = 0; par < 2; ++par) {
+            const double x0 = v4[par], x1 = v4[par + 2];
+            const float2v xf = {(float)x0, (float)x1};
+            const bf16x2v h = __builtin_convertvector(xf, bf16x2v);
+            const float2v hf = __builtin_convertvector(h, float2v);
+            const float2v rf = {(float)(x0 - (double)hf[0]), (float)(x1 - (double)hf[1])};
+            const bf16x2v m = __builtin_convertvector(rf, bf16x2v);
+            pkb[0][par][hc][jj] = __builtin_bit_cast(uint32_t, h);
+            pkb[1][par][hc][jj] = __builtin_bit_cast(uint32_t, m);
+            if (CM == kCmBf16x3) {
+              const bf16x2v l = __builtin_convertvector(rf - __builtin_convertvector(m, float2v), bf16x2v);
+              pkb[2][par][hc][jj] = __builtin_bit_cast(uint32_t, l);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int par = 0; par < 2; ++par) pkb[part][par][hc][jj] = 0u;
+        }
+      }
+      const double rs = ch < 3 ? c_sc[ch + 1] : 1.0;
+      pb_m1 = prev * rs;
+      pb_n = cur * rs;
+      // group 0's operand: orders 0-15 of the lower half's visibility in
+      // lanes 0-31, its orders 16-31 in lanes 32-63; group 1's likewise
+      // for the upper half's visibility
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+#pragma unroll
+        for (int par = 0; par < 2; ++par) {
+          u32x4 g0 = pkb[part][par][0], g1 = pkb[part][par][1];
+          if (part < parts) {
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+              if (jj < 2 * nb8) {  // else both registers are zero in every lane
+                uint32_t a0 = g0[jj], a1 = g1[jj];
+                half_swap(a0, a1);
+                g0[jj] = a0;
+                g1[jj] = a1;
+              }
+          }
+          Bv[0][part][par] = __builtin_bit_cast(bf16x8, g0);
+          Bv[1][part][par] = __builtin_bit_cast(bf16x8, g1);
+        }
+    }
+    const int nmb = q - ch + 1;
+    double prev = 0, cur = ua0;
+#pragma unroll
+    for (int mb = 0; mb < kMBMax; ++mb) {
+      if (mb >= nmb) break;
+      if (mb > 0) {  // the next block's base order
+        prev *= c_sc[mb];
+        cur *= c_sc[mb];
+      }
+      const int p = pbase + mb;
+      bf16x8 Av[3][2];  // [part][parity]
+      {
+        const int oe = p * kAbfPerPair + (threadIdx.x & 63) * 8, oo = oe + 64 * 8;
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+          const int pp = part < parts ? part : parts - 1;
+          Av[part][0] = *(const bf16x8 *)(Ab + pp * part_stride + oe);
+          Av[part][1] = *(const bf16x8 *)(Ab + pp * part_stride + oo);
+        }
+      }
+      floatx16 E0, O0, E1, O1;
+      shp_group_mfma<CM>(Av, Bv[0], E0, O0);
+      shp_group_mfma<CM>(Av, Bv[1], E1, O1);
+      // 8-row groups of this block inside the triangle
+      const int ng = min(4, (N - 32 * (ch + mb)) / 8 + 1);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if (g < ng) {
+          double ra[8];
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            ra[r] = cur;
+            const double nx = psi_next<double>(xa, cur, prev, 0.5 * (32 * mb + 8 * g + r));
+            prev = cur;
+            cur = nx;
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = 4 * g + r;
+            float e0 = E0[i], e1 = E1[i], o0 = O0[i], o1 = O1[i];
+            half_swap(e0, e1);
+            half_swap(o0, o1);
+            // rows 8 g + r (set 0) and 8 g + 4 + r (set 1), both of parity r % 2;
+            // four independent FP64 sums per part (set x row parity)
+            const int k = 2 * (r & 1);
+            if ((r & 1) == 0) {
+              sr[k] = fma(ra[r], (double)e0, sr[k]);
+              si[k] = fma(ra[r], (double)o0, si[k]);
+              sr[k + 1] = fma(ra[4 + r], (double)e1, sr[k + 1]);
+              si[k + 1] = fma(ra[4 + r], (double)o1, si[k + 1]);
+            } else {
+              sr[k] = fma(ra[r], (double)o0, sr[k]);
+              si[k] = fma(ra[r], (double)e0, si[k]);
+              sr[k + 1] = fma(ra[4 + r], (double)o1, sr[k + 1]);
+              si[k + 1] = fma(ra[4 + r], (double)e1, si[k + 1]);
+            }
+          }
+        }
+      }
+    }
+    pbase += nmb;
+  }
+  xr = (sr[0] + sr[1]) + (sr[2] + sr[3]);
+  xi = (si[0] + si[1]) + (si[2] + si[3]);
+}
+
 // One tile of the mixed path's shapelet pass: kTileRows rows x kShpChan
 // channels starting at channel block cb.  Lane l of wave w owns row 64 w + l
 // and runs both Hermite recurrences of its visibility in FP64 (rescaled,
@@ -1005,141 +1198,8 @@ __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, S
       const double f = a.fk[k0 + c];
       const double S = a.d.flux64[(int64_t)jg * a.Kpad + k0 + c];
       const double xa = am * f, xb = bm * f;
-      double pb_m1 = 0, pb_n = shp_phi0<double>(xb) * c_sc[0];
-      const double ua0 = shp_phi0<double>(xa) * c_sc[0];
-      double sr[4] = {0, 0, 0, 0}, si[4] = {0, 0, 0, 0};
-      int pbase = 0;
-      for (int ch = 0; ch <= q; ++ch) {
-        const int nb8 = min(4, (N - 32 * ch) / 8 + 1);
-        // second-axis operands of both groups: Bv[group][part][parity]
-        bf16x8 Bv[2][3][2];
-        {
-          // pkb[part][parity][hc] element jj holds orders 16 hc + 4 jj +
-          // parity (low half) and 16 hc + 4 jj + 2 + parity (high half)
-          u32x4 pkb[3][2][2];
-          double prev = pb_m1, cur = pb_n;
-#pragma unroll
-          for (int s4 = 0; s4 < 8; ++s4) {
-            const int hc = s4 >> 2, jj = s4 & 3;
-            if (s4 < 2 * nb8) {
-              double v4[4];
-#pragma unroll
-              for (int t = 0; t < 4; ++t) {
-                v4[t] = cur;
-                const double nx = psi_next<double>(xb, cur, prev, c_half[32 * ch + 4 * s4 + t]);
-                prev = cur;
-                cur = nx;
-              }
-#pragma unroll
-              for (int par = 0; par < 2; ++par) {
-                const double x0 = v4[par], x1 = v4[par + 2];
-                const float2v xf = {(float)x0, (float)x1};
-                const bf16x2v h = __builtin_convertvector(xf, bf16x2v);
-                const float2v hf = __builtin_convertvector(h, float2v);
-                const float2v rf = {(float)(x0 - (double)hf[0]), (float)(x1 - (double)hf[1])};
-                const bf16x2v m = __builtin_convertvector(rf, bf16x2v);
-                pkb[0][par][hc][jj] = __builtin_bit_cast(uint32_t, h);
-                pkb[1][par][hc][jj] = __builtin_bit_cast(uint32_t, m);
-                if (CM == kCmBf16x3) {
-                  const bf16x2v l = __builtin_convertvector(rf - __builtin_convertvector(m, float2v), bf16x2v);
-                  pkb[2][par][hc][jj] = __builtin_bit_cast(uint32_t, l);
-                }
-              }
-            } else {
-#pragma unroll
-              for (int part = 0; part < 3; ++part)
-#pragma unroll
-                for (int par = 0; par < 2; ++par) pkb[part][par][hc][jj] = 0u;
-            }
-          }
-          const double rs = ch < 3 ? c_sc[ch + 1] : 1.0;
-          pb_m1 = prev * rs;
-          pb_n = cur * rs;
-          // group 0's operand: orders 0-15 of the lower half's visibility in
-          // lanes 0-31, its orders 16-31 in lanes 32-63; group 1's likewise
-          // for the upper half's visibility
-#pragma unroll
-          for (int part = 0; part < 3; ++part)
-#pragma unroll
-            for (int par = 0; par < 2; ++par) {
-              u32x4 g0 = pkb[part][par][0], g1 = pkb[part][par][1];
-              if (part < parts) {
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-                  if (jj < 2 * nb8) {  // else both registers are zero in every lane
-                    uint32_t a0 = g0[jj], a1 = g1[jj];
-                    half_swap(a0, a1);
-                    g0[jj] = a0;
-                    g1[jj] = a1;
-                  }
-              }
-              Bv[0][part][par] = __builtin_bit_cast(bf16x8, g0);
-              Bv[1][part][par] = __builtin_bit_cast(bf16x8, g1);
-            }
-        }
-        const int nmb = q - ch + 1;
-        double prev = 0, cur = ua0;
-#pragma unroll
-        for (int mb = 0; mb < kMBMax; ++mb) {
-          if (mb >= nmb) break;
-          if (mb > 0) {  // the next block's base order
-            prev *= c_sc[mb];
-            cur *= c_sc[mb];
-          }
-          const int p = pbase + mb;
-          bf16x8 Av[3][2];  // [part][parity]
-          {
-            const int oe = p * kAbfPerPair + (tid & 63) * 8, oo = oe + 64 * 8;
-#pragma unroll
-            for (int part = 0; part < 3; ++part) {
-              const int pp = part < parts ? part : parts - 1;
-              Av[part][0] = *(const bf16x8 *)(Ab + pp * part_stride + oe);
-              Av[part][1] = *(const bf16x8 *)(Ab + pp * part_stride + oo);
-            }
-          }
-          floatx16 E0, O0, E1, O1;
-          shp_group_mfma<CM>(Av, Bv[0], E0, O0);
-          shp_group_mfma<CM>(Av, Bv[1], E1, O1);
-          // 8-row groups of this block inside the triangle
-          const int ng = min(4, (N - 32 * (ch + mb)) / 8 + 1);
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            if (g < ng) {
-              double ra[8];
-#pragma unroll
-              for (int r = 0; r < 8; ++r) {
-                ra[r] = cur;
-                const double nx = psi_next<double>(xa, cur, prev, 0.5 * (32 * mb + 8 * g + r));
-                prev = cur;
-                cur = nx;
-              }
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int i = 4 * g + r;
-                float e0 = E0[i], e1 = E1[i], o0 = O0[i], o1 = O1[i];
-                half_swap(e0, e1);
-                half_swap(o0, o1);
-                // rows 8 g + r (set 0) and 8 g + 4 + r (set 1), both of parity r % 2;
-                // four independent FP64 sums per part (set x row parity)
-                const int k = 2 * (r & 1);
-                if ((r & 1) == 0) {
-                  sr[k] = fma(ra[r], (double)e0, sr[k]);
-                  si[k] = fma(ra[r], (double)o0, si[k]);
-                  sr[k + 1] = fma(ra[4 + r], (double)e1, sr[k + 1]);
-                  si[k + 1] = fma(ra[4 + r], (double)o1, si[k + 1]);
-                } else {
-                  sr[k] = fma(ra[r], (double)o0, sr[k]);
-                  si[k] = fma(ra[r], (double)e0, si[k]);
-                  sr[k + 1] = fma(ra[4 + r], (double)o1, sr[k + 1]);
-                  si[k + 1] = fma(ra[4 + r], (double)e1, si[k + 1]);
-                }
-              }
-            }
-          }
-        }
-        pbase += nmb;
-      }
-      const double xr = (sr[0] + sr[1]) + (sr[2] + sr[3]), xi = (si[0] + si[1]) + (si[2] + si[3]);
+      double xr, xi;
+      shp_eval_bf<CM>(xa, xb, N, Ab, part_stride, xr, xi);
       double cs, sn;
       turns_sincos_f64(t0 * f, cs, sn);
       sm.acc_re[c][tid] += sgn * S * (xr * cs - xi * sn);
@@ -1251,6 +1311,106 @@ __device__ __forceinline__ void lut_chunk(const LutPos &q, int n0, float (&v)[32
 // chunk for the tile's four channels (4 x 16 FP64) stay in registers.
 constexpr int kF64Chunk = 16;
 
+// The envelopes of shapelet j (order N) at the four frequencies f4 (nu / c) of
+// this thread's row; sC: the workgroup's chunk of coefficients.  Every thread of
+// the workgroup takes part (barriers).
+__device__ __forceinline__ void shp_eval4_fp64(const ShpTiles &t, int j, int N, double am, double bm,
+                                               const double (&f4)[kShpChan], double *sC, double (&xr)[kShpChan],
+                                               double (&xi)[kShpChan]) {
+  constexpr int KB = kShpChan;
+  const int tid = threadIdx.x;
+  // The second axis in chunks of kF64Chunk orders (its recurrence carried
+  // across chunks, per channel); per chunk the first axis is walked from
+  // order 0 for all of the tile's channels at once, and each row n1 is
+  // dotted with the chunk's part of row n1 of the signed coefficient
+  // matrix.  Every coefficient read from LDS (a broadcast to all lanes)
+  // feeds the tile's four channels: with one channel per read the LDS
+  // return path, not the FP64 units, set the pace.  Channels past the
+  // last (a ragged tile) are computed on the padded frequency table and
+  // not used.
+  const double *C = t.c64 + t.c64_off[j];
+  const int ld = t.c64_ld[j];
+  double bn[KB], bm1[KB], pa0[KB];  // per channel
+#pragma unroll
+  for (int c = 0; c < KB; ++c) {
+    const double xb = f4[c] * bm, xa = f4[c] * am;
+    bn[c] = kPiM14 * exp(-0.5 * xb * xb);
+    pa0[c] = kPiM14 * exp(-0.5 * xa * xa);
+    bm1[c] = xr[c] = xi[c] = 0.0;
+  }
+  for (int ch = 0; kF64Chunk * ch <= N; ++ch) {
+    const int m0 = kF64Chunk * ch;
+    __syncthreads();  // the previous chunk is no longer read
+    for (int i = tid; i < (N - m0 + 1) * kF64Chunk; i += kTileRows) {
+      const int col = m0 + (i % kF64Chunk);
+      sC[i] = col < ld ? C[(int64_t)(i / kF64Chunk) * ld + col] : 0.0;
+    }
+    __syncthreads();
+    double pb[KB][kF64Chunk];
+#pragma unroll
+    for (int c = 0; c < KB; ++c) {
+      const double sxb = 1.41421356237309504880 * (f4[c] * bm);
+#pragma unroll
+      for (int i = 0; i < kF64Chunk; ++i) {
+        pb[c][i] = bn[c];
+        const double nx = herm_step<double>(sxb, bn[c], bm1[c], m0 + i);  // orders <= 127: table size
+        bm1[c] = bn[c];
+        bn[c] = nx;
+      }
+    }
+    double pa[KB], pam1[KB], sxa[KB];
+#pragma unroll
+    for (int c = 0; c < KB; ++c) {
+      pa[c] = pa0[c];
+      pam1[c] = 0.0;
+      sxa[c] = 1.41421356237309504880 * (f4[c] * am);
+    }
+    // one row n1: its dots with the chunk's second-axis values, folded
+    // with the first axis into the real or imaginary sums by the parity
+    // of n1 (rows are taken in pairs, so the parity is a constant)
+    auto row = [&](int n1, auto ODD) {
+      const double *Cr = sC + n1 * kF64Chunk;
+      double te[KB], to[KB];
+#pragma unroll
+      for (int b8 = 0; b8 < kF64Chunk / 8; ++b8) {
+        if (b8 == 0 || 8 * b8 <= N - m0 - n1) {
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) {
+            const double ce = Cr[8 * b8 + e], co = Cr[8 * b8 + e + 1];
+#pragma unroll
+            for (int c = 0; c < KB; ++c) {
+              if (b8 == 0 && e == 0) {
+                te[c] = ce * pb[c][0];
+                to[c] = co * pb[c][1];
+              } else {
+                te[c] = fma(ce, pb[c][8 * b8 + e], te[c]);
+                to[c] = fma(co, pb[c][8 * b8 + e + 1], to[c]);
+              }
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < KB; ++c) {
+        if constexpr (decltype(ODD)::value) {
+          xr[c] = fma(pa[c], to[c], xr[c]);
+          xi[c] = fma(pa[c], te[c], xi[c]);
+        } else {
+          xr[c] = fma(pa[c], te[c], xr[c]);
+          xi[c] = fma(pa[c], to[c], xi[c]);
+        }
+        const double nx = herm_step<double>(sxa[c], pa[c], pam1[c], n1);
+        pam1[c] = pa[c];
+        pa[c] = nx;
+      }
+    };
+    for (int n1 = 0; n1 <= N - m0; n1 += 2) {
+      row(n1, std::integral_constant<bool, false>());
+      if (n1 + 1 <= N - m0) row(n1 + 1, std::integral_constant<bool, true>());
+    }
+  }
+}
+
 template <bool LUT>
 __global__ __launch_bounds__(kTileRows) __attribute__((amdgpu_waves_per_eu(2))) void k_shp_fp64(TileArgs a) {
   constexpr int KB = kShpChan;
@@ -1278,97 +1438,10 @@ __global__ __launch_bounds__(kTileRows) __attribute__((amdgpu_waves_per_eu(2))) 
     const double bm = fma(fr[3], u, fma(fr[4], v, fr[5] * w));
     const double t0 = fma(fr[6], u, fma(fr[7], v, fr[8] * w));
     if constexpr (!LUT) {
-      // The second axis in chunks of kF64Chunk orders (its recurrence carried
-      // across chunks, per channel); per chunk the first axis is walked from
-      // order 0 for all of the tile's channels at once, and each row n1 is
-      // dotted with the chunk's part of row n1 of the signed coefficient
-      // matrix.  Every coefficient read from LDS (a broadcast to all lanes)
-      // feeds the tile's four channels: with one channel per read the LDS
-      // return path, not the FP64 units, set the pace.  Channels past the
-      // last (a ragged tile) are computed on the padded frequency table and
-      // not written.
-      const double *C = a.t.c64 + a.t.c64_off[j];
-      const int ld = a.t.c64_ld[j];
-      double bn[KB], bm1[KB], xr[KB], xi[KB], pa0[KB];  // per channel
+      double f4[KB], xr[KB], xi[KB];
 #pragma unroll
-      for (int c = 0; c < KB; ++c) {
-        const double f = a.fk[k0 + c];
-        const double xb = f * bm, xa = f * am;
-        bn[c] = kPiM14 * exp(-0.5 * xb * xb);
-        pa0[c] = kPiM14 * exp(-0.5 * xa * xa);
-        bm1[c] = xr[c] = xi[c] = 0.0;
-      }
-      for (int ch = 0; kF64Chunk * ch <= N; ++ch) {
-        const int m0 = kF64Chunk * ch;
-        __syncthreads();  // the previous chunk is no longer read
-        for (int i = tid; i < (N - m0 + 1) * kF64Chunk; i += kTileRows) {
-          const int col = m0 + (i % kF64Chunk);
-          sC[i] = col < ld ? C[(int64_t)(i / kF64Chunk) * ld + col] : 0.0;
-        }
-        __syncthreads();
-        double pb[KB][kF64Chunk];
-#pragma unroll
-        for (int c = 0; c < KB; ++c) {
-          const double sxb = 1.41421356237309504880 * (a.fk[k0 + c] * bm);
-#pragma unroll
-          for (int i = 0; i < kF64Chunk; ++i) {
-            pb[c][i] = bn[c];
-            const double nx = herm_step<double>(sxb, bn[c], bm1[c], m0 + i);  // orders <= 127: table size
-            bm1[c] = bn[c];
-            bn[c] = nx;
-          }
-        }
-        double pa[KB], pam1[KB], sxa[KB];
-#pragma unroll
-        for (int c = 0; c < KB; ++c) {
-          pa[c] = pa0[c];
-          pam1[c] = 0.0;
-          sxa[c] = 1.41421356237309504880 * (a.fk[k0 + c] * am);
-        }
-        // one row n1: its dots with the chunk's second-axis values, folded
-        // with the first axis into the real or imaginary sums by the parity
-        // of n1 (rows are taken in pairs, so the parity is a constant)
-        auto row = [&](int n1, auto ODD) {
-          const double *Cr = sC + n1 * kF64Chunk;
-          double te[KB], to[KB];
-#pragma unroll
-          for (int b8 = 0; b8 < kF64Chunk / 8; ++b8) {
-            if (b8 == 0 || 8 * b8 <= N - m0 - n1) {
-#pragma unroll
-              for (int e = 0; e < 8; e += 2) {
-                const double ce = Cr[8 * b8 + e], co = Cr[8 * b8 + e + 1];
-#pragma unroll
-                for (int c = 0; c < KB; ++c) {
-                  if (b8 == 0 && e == 0) {
-                    te[c] = ce * pb[c][0];
-                    to[c] = co * pb[c][1];
-                  } else {
-                    te[c] = fma(ce, pb[c][8 * b8 + e], te[c]);
-                    to[c] = fma(co, pb[c][8 * b8 + e + 1], to[c]);
-                  }
-                }
-              }
-            }
-          }
-#pragma unroll
-          for (int c = 0; c < KB; ++c) {
-            if constexpr (decltype(ODD)::value) {
-              xr[c] = fma(pa[c], to[c], xr[c]);
-              xi[c] = fma(pa[c], te[c], xi[c]);
-            } else {
-              xr[c] = fma(pa[c], te[c], xr[c]);
-              xi[c] = fma(pa[c], to[c], xi[c]);
-            }
-            const double nx = herm_step<double>(sxa[c], pa[c], pam1[c], n1);
-            pam1[c] = pa[c];
-            pa[c] = nx;
-          }
-        };
-        for (int n1 = 0; n1 <= N - m0; n1 += 2) {
-          row(n1, std::integral_constant<bool, false>());
-          if (n1 + 1 <= N - m0) row(n1 + 1, std::integral_constant<bool, true>());
-        }
-      }
+      for (int c = 0; c < KB; ++c) f4[c] = a.fk[k0 + c];
+      shp_eval4_fp64(a.t, j, N, am, bm, f4, sC, xr, xi);
 #pragma unroll
       for (int c = 0; c < KB; ++c) {
         if (c >= nc) break;
@@ -1488,6 +1561,190 @@ __global__ __launch_bounds__(kTileRows) __attribute__((amdgpu_waves_per_eu(2))) 
   }
 }
 
+// ---------------------------------------------------------------------------
+// shapelets by nodes
+// ---------------------------------------------------------------------------
+//
+// The envelope of a shapelet along a baseline is a smooth function of
+// frequency (see shp_nodes.h): it is evaluated at M Chebyshev nodes of the band
+// and interpolated to the channels, where flux and phase are applied as ever.
+// A workgroup takes R rows: the envelopes of every shapelet at the nodes go to
+// LDS (FP64), lanes holding (row, node) pairs, and then each wave forms 16 rows
+// x 16 channels at a time, the interpolation on v_mfma_f64_16x16x4f64 (the
+// matrix from global memory, 4 nodes a step) and the sums over the shapelets in
+// FP64 registers, one write per visibility.  What bounds it: the envelopes, M
+// in place of K of them; a channel then costs M / 4 FP64 MFMAs per 128 outputs
+// and ~35 vector instructions for its phase and flux, a fiftieth to a twentieth
+// of an envelope.
+typedef double double4w __attribute__((ext_vector_type(4)));
+
+// Doubles of LDS the node values of S shapelets take.
+__host__ __device__ inline size_t node_lds(int S, int Mp, int R) { return (size_t)S * 2 * Mp * R; }
+
+__device__ __forceinline__ void node_outputs(const TileArgs &a, int Mp, const double *tab, const double *xs, int R,
+                                             int64_t row0, int wave, int nwaves) {
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int ncb = (a.K + 15) / 16, ntask = (R / 16) * ncb, steps = Mp / 4;
+  for (int task = wave; task < ntask; task += nwaves) {
+    const int rg = task / ncb, cb = task - rg * ncb;
+    const int rr = rg * 16 + n, k = cb * 16 + 4 * g;  // this lane's row and first of four channels
+    const int64_t row = row0 + rr;
+    if (row0 + rg * 16 >= a.nrows) break;  // whole groups past the last row (wave-uniform)
+    const bool valid = row < a.nrows;
+    const int64_t rowc = valid ? row : a.nrows - 1;
+    const double u = a.uvw[3 * rowc], v = a.uvw[3 * rowc + 1], w = a.uvw[3 * rowc + 2];
+    double f[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) f[r] = a.fk[min(k + r, a.Kpad - 1)];
+    double sre[4] = {0, 0, 0, 0}, sim[4] = {0, 0, 0, 0};
+    for (int j = 0; j < a.S; ++j) {
+      const double *xr = xs + node_lds(j, Mp, R), *xi = xr + (size_t)Mp * R;
+      const double *L = tab + kNodesStride + (size_t)cb * steps * 64 + lane;
+      double4w er = {0, 0, 0, 0}, ei = {0, 0, 0, 0};
+      for (int s = 0; s < steps; ++s) {
+        const double l = L[64 * s];
+        const int at = (4 * s + g) * R + rr;
+        er = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xr[at], er, 0, 0, 0);
+        ei = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xi[at], ei, 0, 0, 0);
+      }
+      const double *fr = a.d.sframe + 12 * j;
+      const double t0 = fma(fr[6], u, fma(fr[7], v, fr[8] * w));
+      double c, s, cd = 0, sd = 0;
+      turns_sincos_f64(t0 * f[0], c, s);
+      if (a.uniform) turns_sincos_f64(t0 * a.dfk, cd, sd);
+      const double *fl = a.d.flux64 + (int64_t)(a.P + a.G + j) * a.Kpad;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (r > 0) {
+          if (a.uniform) {
+            const double cn = fma(c, cd, -s * sd);
+            s = fma(s, cd, c * sd);
+            c = cn;
+          } else {
+            turns_sincos_f64(t0 * f[r], c, s);
+          }
+        }
+        const double S = fl[min(k + r, a.Kpad - 1)];
+        sre[r] += S * (er[r] * c - ei[r] * s);
+        sim[r] += S * (er[r] * s + ei[r] * c);
+      }
+    }
+    if (!valid) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (k + r >= a.K) break;
+      const int64_t idx = row * a.K + k + r;
+      double re = a.subtract ? -sre[r] : sre[r], im = a.subtract ? -sim[r] : sim[r];
+      if (a.conj) im = -im;
+      if (a.c64) {
+        float2 *o = (float2 *)a.vis + idx;
+        if (!a.fresh) {
+          const float2 d = *o;
+          re += d.x;
+          im += d.y;
+        }
+        *o = make_float2((float)re, (float)im);
+      } else {
+        double2 *o = (double2 *)a.vis + idx;
+        if (!a.fresh) {
+          const double2 d = *o;
+          re += d.x;
+          im += d.y;
+        }
+        *o = make_double2(re, im);
+      }
+    }
+  }
+}
+
+constexpr int kNodeThreads = 256;
+
+template <int CM>
+__global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_shp_nodes(
+    TileArgs a, NodePlan p, const double *tab, int R, int a_bytes) {
+  extern __shared__ __align__(16) unsigned char node_sm[];
+  constexpr int parts = CM == kCmBf16x3 ? 3 : 2;
+  uint4 *sA = (uint4 *)node_sm;
+  double *xs = (double *)(node_sm + a_bytes);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * R;
+  // padding nodes (zero columns of the matrix) hold zeros
+  for (int i = tid; i < a.S * 2 * (p.Mp - p.M) * R; i += kNodeThreads) {
+    const int c = i / ((p.Mp - p.M) * R), e = i % ((p.Mp - p.M) * R);
+    xs[(size_t)c * p.Mp * R + (size_t)p.M * R + e] = 0.0;
+  }
+  const int lr = R < 64 ? R : 64;                    // rows of a wave's share
+  const int per = 64 / lr, groups = R / lr;          // nodes of it, row groups
+  const int items = groups * ((p.M + per - 1) / per);
+  for (int j = 0; j < a.S; ++j) {
+    const int N = a.t.nmax[j];
+    const int npairs = shp_pairs(N);
+    __syncthreads();  // the previous shapelet's blocks are no longer read
+    {
+      const uint4 *src = (const uint4 *)(a.t.abf + a.t.abf_off[j]);
+      for (int i = tid; i < parts * npairs * kAbfPerPair / 8; i += kNodeThreads) sA[i] = src[i];
+    }
+    __syncthreads();
+    const double *fr = a.d.sframe + 12 * j;
+    double *xr_s = xs + node_lds(j, p.Mp, R), *xi_s = xr_s + (size_t)p.Mp * R;
+    for (int it = wave; it < items; it += kNodeThreads / 64) {
+      const int rr = (it % groups) * lr + lane % lr, m = (it / groups) * per + lane / lr;
+      const int64_t row = min(row0 + rr, a.nrows - 1);
+      const double f = tab[min(m, p.M - 1)];
+      const double u = a.uvw[3 * row], v = a.uvw[3 * row + 1], w = a.uvw[3 * row + 2];
+      const double am = fma(fr[0], u, fma(fr[1], v, fr[2] * w));
+      const double bm = fma(fr[3], u, fma(fr[4], v, fr[5] * w));
+      double xr, xi;
+      shp_eval_bf<CM>(am * f, bm * f, N, (const __bf16 *)sA, npairs * kAbfPerPair, xr, xi);
+      if (m < p.M) {
+        xr_s[m * R + rr] = xr;
+        xi_s[m * R + rr] = xi;
+      }
+    }
+  }
+  __syncthreads();
+  node_outputs(a, p.Mp, tab, xs, R, row0, wave, kNodeThreads / 64);
+}
+
+// The FP64 path: four nodes of one row a thread (padding nodes repeat the
+// middle of the band), as many passes as the workgroup's R rows x M / 4 need.
+__global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_shp_nodes64(
+    TileArgs a, NodePlan p, const double *tab, int R) {
+  extern __shared__ __align__(16) unsigned char node_sm[];
+  double *sC = (double *)node_sm;
+  double *xs = sC + (kNmaxLimit + 1) * kF64Chunk;
+  const int tid = threadIdx.x;
+  const int64_t row0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * R;
+  const int quads = p.Mp / 4;
+  for (int j = 0; j < a.S; ++j) {
+    const int N = a.t.nmax[j];
+    const double *fr = a.d.sframe + 12 * j;
+    double *xr_s = xs + node_lds(j, p.Mp, R), *xi_s = xr_s + (size_t)p.Mp * R;
+    for (int i0 = 0; i0 < R * quads; i0 += kNodeThreads) {
+      const int i = min(i0 + tid, R * quads - 1);
+      const int rr = i % R, q = i / R;
+      const int64_t row = min(row0 + rr, a.nrows - 1);
+      const double u = a.uvw[3 * row], v = a.uvw[3 * row + 1], w = a.uvw[3 * row + 2];
+      const double am = fma(fr[0], u, fma(fr[1], v, fr[2] * w));
+      const double bm = fma(fr[3], u, fma(fr[4], v, fr[5] * w));
+      double f4[kShpChan], xr[kShpChan], xi[kShpChan];
+#pragma unroll
+      for (int c = 0; c < kShpChan; ++c) f4[c] = tab[4 * q + c];
+      shp_eval4_fp64(a.t, j, N, am, bm, f4, sC, xr, xi);
+      if (i0 + tid < R * quads) {
+#pragma unroll
+        for (int c = 0; c < kShpChan; ++c) {
+          xr_s[(4 * q + c) * R + rr] = xr[c];
+          xi_s[(4 * q + c) * R + rr] = xi[c];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  node_outputs(a, p.Mp, tab, xs, R, row0, __builtin_amdgcn_readfirstlane(tid >> 6), kNodeThreads / 64);
+}
+
 // A serving job's mark on its stream (see ServeMark): the clock, then the
 // sequence number that tells the host that the clock is there.
 __global__ void k_mark(ServeMark *m, uint64_t seq) {
@@ -1524,7 +1781,7 @@ static hipError_t init_constants() {
 // call), one array per device for the life of the process.  In host code the
 // name is only a stand-in: its device address, which differs per device, is
 // looked up once per device below and used everywhere instead.
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocAmpBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocAmpBytes + kNoAllocNodeBytes];
 static void *g_scratch[kMaxDevices];
 
 hipError_t device_init(int dev) {
@@ -1557,7 +1814,8 @@ static hipError_t upload_tables() {
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s) {
   const int J = a.P + a.G + a.S;
   if (J == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_derive, dim3((J + 127) / 128), dim3(128), 0, s, a);
+  const int rows = ((a.plan[0].M > 0) + (a.plan[1].M > 0)) * ((a.K + 15) / 16 * 16);
+  hipLaunchKernelGGL(k_derive, dim3((J + 127) / 128 + (rows + 1) / 2), dim3(128), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1632,6 +1890,52 @@ hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s) 
       return hipErrorNotSupported;
   }
   return hipGetLastError();
+}
+
+// LDS beside the node values: the mixed path's coefficient tiles, the FP64
+// path's chunk.
+static size_t node_base_bytes(int prec, int max_nmax) {
+  if (prec == kFP64) return (size_t)(kNmaxLimit + 1) * kF64Chunk * sizeof(double);
+  return (size_t)(prec == kMixedBf16x2 ? 2 : 3) * shp_pairs(max_nmax) * kAbfPerPair * sizeof(uint16_t);
+}
+
+// Rows of a workgroup: as many as leave two workgroups on a CU (half of its
+// LDS) and, of those, few enough for two workgroups per CU to be had; 16 rows
+// (the outputs' tile) with all of the LDS where half is too little.  0: not even
+// those.
+static int node_rows(int prec, int max_nmax, int S, int Mp, int64_t nrows) {
+  const size_t base = node_base_bytes(prec, max_nmax), half = 81920, all = 163840;
+  int R = 128;
+  while (R > 16 && base + node_lds(S, Mp, R) * sizeof(double) > half) R /= 2;
+  if (base + node_lds(S, Mp, R) * sizeof(double) > all) return 0;
+  while (R > 16 && (nrows + R - 1) / R < 512) R /= 2;
+  return R;
+}
+
+bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) { return node_rows(prec, max_nmax, S, Mp, 1 << 20) > 0; }
+
+template <typename K, typename... A>
+static hipError_t launch_node_kernel(K k, unsigned grid, size_t sm, hipStream_t s, A... args) {
+  hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3(grid), dim3(kNodeThreads), sm, s, args...);
+  return hipGetLastError();
+}
+
+hipError_t launch_shp_nodes(const TileArgs &a, const NodePlan &p, int prec, int max_nmax, hipStream_t s) {
+  hipError_t e = upload_tables();
+  if (e != hipSuccess) return e;
+  const int R = node_rows(prec, max_nmax, a.S, p.Mp, a.nrows);
+  if (R == 0 || p.M < 1 || p.M > p.Mp || p.Mp > kNodesStride || p.Mp % 4 || max_nmax < 0 || max_nmax > kNmaxLimit)
+    return hipErrorInvalidValue;
+  const int64_t nt = (a.nrows + R - 1) / R;
+  if (nt > 0x7fffffff) return hipErrorInvalidValue;
+  const size_t base = node_base_bytes(prec, max_nmax), sm = base + node_lds(a.S, p.Mp, R) * sizeof(double);
+  const double *tab = a.d.interp[prec == kFP64];
+  if (prec == kFP64) return launch_node_kernel(k_shp_nodes64, (unsigned)nt, sm, s, a, p, tab, R);
+  if (prec == kMixedBf16x2)
+    return launch_node_kernel(k_shp_nodes<kCmBf16x2>, (unsigned)nt, sm, s, a, p, tab, R, (int)base);
+  return launch_node_kernel(k_shp_nodes<kCmBf16x3>, (unsigned)nt, sm, s, a, p, tab, R, (int)base);
 }
 
 hipError_t launch_lut_build(float *T, hipStream_t s) {

@@ -114,6 +114,8 @@ void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d);
 // uses, and their release (hipFree: waits for the device).
 uint64_t serve_evictable_bytes(vp_ctx *ctx);
 void serve_evict(vp_ctx *ctx);
+// The pair's plan for shapelets by nodes: i = 0 mixed, 1 FP64 (M = 0: none).
+NodePlan node_plan(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int i);
 // Whether the pair's points may be taken by antenna, on any path (a property of
 // the pair: its tables then hold the amplitudes, Jp x Kpad of them).
 bool ant_pair(const struct ::vp_sky *sky, const struct ::vp_obs *obs, double *scale = nullptr);

@@ -33,12 +33,21 @@
 
 namespace vp {
 
+static uint64_t node_table_bytes(const vp_sky *sky, const vp_obs *obs) {
+  uint64_t b = 0;
+  for (int i = 0; i < 2; ++i) {
+    const NodePlan p = node_plan(sky, obs, i);
+    if (p.M > 0) b += sizeof(double) * node_doubles(obs->K, p.Mp);
+  }
+  return b;
+}
+
 uint64_t job_footprint(const vp_sky *sky, const vp_obs *obs, int dtype) {
   const uint64_t nvis = (uint64_t)obs->T * obs->B * obs->K;
   const uint64_t J = (uint64_t)sky->P + sky->G + sky->S;
   const uint64_t tables = 32 * (J ? J : 1) + 32 * (sky->G ? sky->G : 1) + 96 * (sky->S ? sky->S : 1) +
                           12 * (J ? J : 1) * (uint64_t)obs->Kpad +
-                          (ant_pair(sky, obs) ? 4 * (uint64_t)ant_jp(sky) * obs->Kpad : 0);
+                          node_table_bytes(sky, obs) + (ant_pair(sky, obs) ? 4 * (uint64_t)ant_jp(sky) * obs->Kpad : 0);
   return nvis * (dtype == VP_C64 ? 8 : 16) + tables;
 }
 
