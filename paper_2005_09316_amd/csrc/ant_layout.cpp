@@ -149,7 +149,7 @@ struct Pass {
 
 }  // namespace
 
-AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n) {
+AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n, bool check) {
   AntLayout r;
   if (T <= 0 || B <= 0 || max_n < 2 || !(tol > 0.0)) return r;
   // coordinates beyond this overflow the lookup's cells (and are no array's)
@@ -181,6 +181,7 @@ AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n) 
       const double g = s.via[a] >= 0 ? 1.0 : -1.0, *u = U + 3 * (size_t)(s.via[a] >= 0 ? s.via[a] : ~s.via[a]);
       for (int c = 0; c < 3; ++c) X[3 * a + c] = X[3 * s.from[a] + c] + g * u[c];
     }
+    if (t > 0 && !check) continue;
     double d0 = 0.0, d1 = 0.0, d2 = 0.0;
     for (int b = 0; b < B; ++b) {
       const double *x = X + 3 * (size_t)P[b], *y = X + 3 * (size_t)Q[b], *u = U + 3 * (size_t)b;

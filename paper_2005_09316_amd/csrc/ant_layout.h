@@ -30,8 +30,9 @@ struct AntLayout {
 // correlators write them) give the true antennas, and rows that cannot be
 // tied to antennas found before (a gap in the list) get further ones, which
 // are as exact.  At most max_n antennas; n = 0 when that does not suffice or
-// the rows do not agree over time.
-AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n);
+// the rows do not agree over time.  check = false: only the first time step is
+// looked at (dev is its own); whether the others agree is the caller's to find.
+AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n, bool check = true);
 
 // Tiling of the (p, q) plane for the kernels that form it: antennas in blocks
 // of 32, workgroups ("macros") of up to kAntWaves waves.  A macro stages up

@@ -133,13 +133,15 @@ __device__ __forceinline__ void ant_add(AntSum &s, const AntTile &t) {
 }
 
 // Writes one tile's visibilities: element i of lane l is (p0 + 4 (l / 16) + i,
-// q0 + l % 16); the map gives the row of each pair (+: as it is, -: conjugated).
+// q0 + l % 16), with F64 (the FP64 MFMA's layout) row p0 + 4 i + l / 16; the map
+// gives the row of each pair (+: as it is, -: conjugated).
+template <bool F64 = false>
 __device__ __forceinline__ void ant_store(const AntArgs &a, const AntSum &s, int p0, int q0, int64_t t, int k) {
   const int lane = threadIdx.x & 63;
   const int q = q0 + (lane & 15);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int p = p0 + 4 * (lane >> 4) + i;
+    const int p = p0 + (F64 ? 4 * i + (lane >> 4) : 4 * (lane >> 4) + i);
     const int m = a.rowmap[(int64_t)p * a.npad + q];
     if (m == 0) continue;
     const double re = s.re[i] * a.unscale, im0 = s.im[i] * a.unscale;
@@ -479,6 +481,348 @@ __global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// ---------------------------------------------------------------------------
+// FP64 path
+// ---------------------------------------------------------------------------
+//
+// The same product in FP64 on v_mfma_f64_16x16x4f64, 16 points at a time, from
+// faint points to bright, so that the running sums stay small for longest.  The
+// factors' phases are dots of
+// coordinates (wavelengths) with (l, m, n - 1): each product is taken with its
+// rounding error and reduced to a fraction of a turn before the sum, so that
+// the phase is good to an ulp of a turn and not of the whole phase (the error of
+// two factors would otherwise exceed that of the vector path's one phase).
+// What bounds it: the matrix cores (16 MFMAs per four tiles and 4 points, 60
+// TFLOP/s at best against 47 to 63 measured for plain products), with ~55
+// vector instructions per factor beside them.
+typedef double double4a __attribute__((ext_vector_type(4)));
+constexpr int kAntK64 = 16;  // points per block
+
+// Cosine and sine of the phase (xh + xl) l + (yh + yl) m + (zh + zl) n turns.
+struct AntXyz {
+  double xh, yh, zh, xl, yl, zl;
+};
+__device__ __forceinline__ void ant_sincos64(const AntXyz &X, double l, double m, double n, double &c, double &s) {
+  const double px = X.xh * l, py = X.yh * m, pz = X.zh * n;
+  double e = fma(X.xh, l, -px);
+  e = fma(X.xl, l, e);
+  e += fma(X.yl, m, fma(X.yh, m, -py));
+  e += fma(X.zl, n, fma(X.zh, n, -pz));
+  const double t = ((px - rint(px)) + (py - rint(py))) + ((pz - rint(pz)) + e);
+  // nearest quarter turn (its number modulo 4 in the low bits of u), |f| <= 1/8
+  const double u = t + 1688849860263936.0;  // 1.5 x 2^50
+  const uint32_t q = (uint32_t)__double_as_longlong(u);
+  const double f = t - (u - 1688849860263936.0), x = f * f;
+  // minimax fits of sin(2 pi f) / f (2e-17) and (cos(2 pi f) - 1) / f^2 (1e-19)
+  double ps = fma(3.7808689593022955184, x, -15.093804209987113512);
+  ps = fma(ps, x, 42.058685020160894047);
+  ps = fma(ps, x, -76.705859704274550647);
+  ps = fma(ps, x, 81.605249275948035209);
+  ps = fma(ps, x, -41.341702240399636207);
+  ps = fma(ps, x, 6.2831853071795864572) * f;
+  double pc = fma(-1.6990343940660636356, x, 7.9032069115696784291);
+  pc = fma(pc, x, -26.426253275854721364);
+  pc = fma(pc, x, 60.244641352702008933);
+  pc = fma(pc, x, -85.456817206643804246);
+  pc = fma(pc, x, 64.939394022668242743);
+  pc = fma(pc, x, -19.73920880217871723);
+  pc = fma(pc, x, 1.0);
+  const bool odd = q & 1;
+  const double a = odd ? ps : pc, b = odd ? pc : ps;
+  const uint32_t w = q << 30;
+  s = __longlong_as_double(__double_as_longlong(b) ^ ((int64_t)(w & 0x80000000u) << 32));
+  c = __longlong_as_double(__double_as_longlong(a) ^ ((int64_t)((w + 0x40000000u) & 0x80000000u) << 32));
+}
+
+struct AntPoints64 {
+  double x[2][kAntK64], y[2][kAntK64], z[2][kAntK64];
+  double am[4][kAntSup][kAntK64];  // sign(S) sqrt|S| per staged antenna block
+};
+
+// Antennas against rows, a workgroup per time step and 32 antennas: dev receives
+// the largest disagreement (as the bits of a non-negative double), and xyz_lo
+// what a row's average disagreement says an antenna lies beside xyz: the
+// least-squares correction for a complete list (sums over each antenna's rows,
+// of residuals formed without rounding; order fixed).  Rows are rounded to 1e-16
+// of their length; an antenna seen through one row alone would carry that
+// rounding into all of its baselines.  Once per observation; 25 us at 128
+// antennas x 14 times, bound by its dependent loads.
+__global__ __launch_bounds__(256) void k_ant_refine(int B, int n, int npad, const double *uvw, const int32_t *rowmap,
+                                                    const double *xyz, double *xyz_lo, unsigned long long *dev) {
+  const int64_t t = blockIdx.x;
+  const double *X = xyz + 3 * t * npad;
+  double worst = 0.0;
+  // 32 antennas x 8 shares of their rows
+  __shared__ double part[8][32][4];
+  const int a32 = threadIdx.x & 31, sh = threadIdx.x >> 5, p = blockIdx.y * 32 + a32;
+  double s[3] = {0, 0, 0};
+  {
+    int deg = 0;
+    for (int q = sh; q < n && p < n; q += 8) {
+      const int lo = min(p, q), hi = max(p, q);
+      const int m = rowmap[(int64_t)lo * npad + hi];
+      if (m == 0) continue;
+      ++deg;
+      const double *u = uvw + 3 * (t * B + (m < 0 ? -m : m) - 1);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double a = X[3 * hi + c], b = X[3 * lo + c], v = m < 0 ? -u[c] : u[c];
+        // a - b = d + r exactly
+        const double d = a - b, bb = d - a, r = (a - (d - bb)) - (b + bb);
+        const double e = (v - d) - r;
+        worst = fmax(worst, fabs(e));
+        s[c] += p == hi ? e : -e;
+      }
+    }
+    for (int c = 0; c < 3; ++c) part[sh][a32][c] = s[c];
+    part[sh][a32][3] = deg;
+  }
+  __syncthreads();
+  if (sh == 0) {
+    double d[4] = {0, 0, 0, 0};
+    for (int i = 0; i < 8; ++i)
+      for (int c = 0; c < 4; ++c) d[c] += part[i][a32][c];
+    for (int c = 0; c < 3; ++c) xyz_lo[3 * (t * npad + p) + c] = d[c] / (d[3] + 1.0);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) worst = fmax(worst, __shfl_xor(worst, o));
+  if ((threadIdx.x & 63) == 0) atomicMax(dev, (unsigned long long)__double_as_longlong(worst));
+}
+
+hipError_t launch_ant_refine(int T, int B, int n, int npad, const double *uvw, const int32_t *rowmap, const double *xyz,
+                             double *xyz_lo, unsigned long long *dev, hipStream_t s) {
+  if (T <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_ant_refine, dim3((unsigned)T, (unsigned)(npad / kAntBlk)), dim3(256), 0, s, B, n, npad, uvw,
+                     rowmap, xyz, xyz_lo, dev);
+  return hipGetLastError();
+}
+
+struct AntTile64 {
+  double4a re, im;
+};
+
+__device__ __forceinline__ double4a ant_mfma64(double a, double b, double4a c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ double ant_flip(double x, double sign_of) {
+  return __longlong_as_double(__double_as_longlong(x) ^ (__double_as_longlong(sign_of) & (int64_t)0x8000000000000000ull));
+}
+
+// The operands of one wave's tiles for four points (step st of a block), and
+// their products: NT = 4, the pair of blocks (ia, ib), or 3, the upper triangle
+// of block ia.  F: [re, im][16 points][R].
+template <int NT>
+struct AntOps64 {
+  double Ar[2], Ai[2], Br[NT == 4 ? 2 : 1], Bi[NT == 4 ? 2 : 1], sg;
+  __device__ __forceinline__ void load(const double *F, int R, int ia, int ib, int st, const double *am) {
+    const int lane = threadIdx.x & 63, j = 4 * st + (lane >> 4), r = lane & 15;
+    const double *re = F + j * R, *im = re + kAntK64 * R;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      Ar[i] = re[ia * kAntBlk + 16 * i + r];
+      Ai[i] = im[ia * kAntBlk + 16 * i + r];
+      if constexpr (NT == 4) {
+        Br[i] = re[ib * kAntBlk + 16 * i + r];
+        Bi[i] = im[ib * kAntBlk + 16 * i + r];
+      }
+    }
+    sg = am[j];
+  }
+  template <bool NEG>
+  __device__ __forceinline__ void products(AntTile64 (&t)[NT]) const {
+    double br[2], bi[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (NT == 4) {
+        br[i] = Br[i];
+        bi[i] = Bi[i];
+      } else {
+        br[i] = Ar[i];
+        bi[i] = Ai[i];
+      }
+      if constexpr (NEG) {
+        br[i] = ant_flip(br[i], sg);
+        bi[i] = ant_flip(bi[i], sg);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int p = i >> 1, q = NT == 4 ? i & 1 : (i + 1) >> 1;
+      t[i].re = ant_mfma64(Ar[p], br[q], t[i].re);
+      t[i].im = ant_mfma64(Ar[p], bi[q], t[i].im);
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int p = i >> 1, q = NT == 4 ? i & 1 : (i + 1) >> 1;
+      t[i].re = ant_mfma64(Ai[p], bi[q], t[i].re);
+      t[i].im = ant_mfma64(-Ai[p], br[q], t[i].im);
+    }
+  }
+};
+
+__device__ __forceinline__ void ant_zero64(AntTile64 &t) { t.re = t.im = double4a{0.0, 0.0, 0.0, 0.0}; }
+__device__ __forceinline__ AntSum ant_sum64(const AntTile64 &t) {
+  AntSum s;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    s.re[e] = t.re[e];
+    s.im[e] = t.im[e];
+  }
+  return s;
+}
+
+// 128 antennas, 14 times x 32 channels, 20,000 points: 15.3 ms (the vector
+// kernel: 39.6), 6.1 us per block and round of workgroups.  Four waves' MFMAs of
+// 64 cycles take 4.3 us of it where a SIMD has a triangle (24 a step) and a pair
+// (16); the rest is the factors, which the two waves of a SIMD mostly evaluate
+// at the same time, between barriers.
+// Error against 80-bit sums, 4,000 points: 6.6e-14 of the visibilities' norm
+// (1.7e-13 before, most of it from direction cosines with cancelling terms),
+// 6.4e-16 over a 0.1 degree field (5.6e-14).
+// ITEMS: (64 antennas) x (4 points) shares of the factors per wave and block.
+template <int ITEMS, bool NEG>
+__global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_ant_fp64(AntArgs a) {
+  extern __shared__ __align__(16) unsigned char ant_sm[];
+  const int tile = ant_xcd(blockIdx.x, gridDim.x);
+  const int mi = tile % a.nmac, kb = (tile / a.nmac) % a.nkb;
+  const int64_t t = tile / (a.nmac * a.nkb);
+  const AntMacro &mac = a.mac[mi];
+  const int R = mac.nsup * kAntBlk, k0 = kb * a.kpack;
+  AntPoints64 &pt = *(AntPoints64 *)ant_sm;
+  double *F = (double *)(ant_sm + sizeof(AntPoints64));  // [2 buffers][re, im][16 points][R]
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nc = (a.J + kAntK64 - 1) / kAntK64;
+
+  AntXyz X[ITEMS];
+  int gr[ITEMS], gg[ITEMS], gs[ITEMS];
+  bool on[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const int it = wave + i * kAntWaves, r = (it >> 2) * 64 + (tid & 63);
+    on[i] = r < R;
+    gr[i] = on[i] ? r : R - 1;
+    gg[i] = it & 3;
+    gs[i] = gr[i] >> 5;
+    const double *x = a.xyz + (t * a.npad + mac.blk[gs[i]] * kAntBlk + (gr[i] & 31)) * 3;
+    const double *xl = a.xyz_lo + (x - a.xyz);
+    const double f = a.fk[min(k0 + mac.dk[gs[i]], a.K - 1)];
+    X[i].xh = x[0] * f;
+    X[i].yh = x[1] * f;
+    X[i].zh = x[2] * f;
+    X[i].xl = fma(xl[0], f, fma(x[0], f, -X[i].xh));
+    X[i].yl = fma(xl[1], f, fma(x[1], f, -X[i].yh));
+    X[i].zl = fma(xl[2], f, fma(x[2], f, -X[i].zh));
+  }
+  // one point of a block a thread: position components for the first 48
+  // threads, amplitudes (per staged block) for the next 16 nsup
+  const int pj = tid & 15, pc = tid >> 4;
+  const bool is_pos = pc < 3, is_am = pc >= 3 && pc < 3 + mac.nsup;
+  const int ka = min(k0 + mac.dk[is_am ? pc - 3 : 0], a.K - 1);
+  auto fetch = [&](int c) {
+    const int j = (nc - 1 - min(c, nc - 1)) * kAntK64 + pj;  // faint points first
+    double v = 0.0;
+    if (is_pos) v = ((const double *)(a.pos + min(j, a.J - 1)))[pc];
+    if (is_am && j < a.J) v = a.flux64[(int64_t)j * a.Kpad + ka];
+    return v;
+  };
+  auto place = [&](int c, double v) {
+    if (is_pos) (pc == 0 ? pt.x[c & 1] : pc == 1 ? pt.y[c & 1] : pt.z[c & 1])[pj] = v;
+    if (is_am) pt.am[c & 3][pc - 3][pj] = copysign(sqrt(fabs(v)), v);
+  };
+  const int stride = 2 * kAntK64 * R;
+  // point e of this wave's four of block b
+  auto factor = [&](int i, int b, int e) {
+    const int j = 4 * gg[i] + e;
+    double c, s;
+    ant_sincos64(X[i], pt.x[b & 1][j], pt.y[b & 1][j], pt.z[b & 1][j], c, s);
+    const double m = fabs(pt.am[b & 3][gs[i]][j]);
+    if (on[i]) {
+      double *o = F + (b & 1) * stride + j * R + gr[i];
+      o[0] = m * c;
+      o[kAntK64 * R] = m * s;
+    }
+  };
+  place(0, fetch(0));
+  place(1, fetch(1));
+  double next = fetch(2);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    for (int e = 0; e < 4; ++e) factor(i, 0, e);
+  const int ia = mac.a[wave], ib = mac.b[wave];
+  // Iteration c multiplies block c and evaluates block c + 1 (at the end, the
+  // last block's points once more, into the buffer that is not read again).
+  auto head = [&](int c) {
+    __syncthreads();
+    place(c + 2, next);
+    next = fetch(c + 3);
+  };
+  auto side = [&](int c, int st) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) factor(i, c + 1, st);
+  };
+  // Each step's operands are read while the step before multiplies.
+  if (mac.tri[wave]) {
+    AntTile64 w[2][3];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) ant_zero64(w[i / 3][i % 3]);
+    for (int c = 0; c < nc; ++c) {
+      head(c);
+      const double *cur = F + (c & 1) * stride;
+      const int i1 = ib >= 0 ? ib : ia;
+      const double *am0 = pt.am[c & 3][ia], *am1 = pt.am[c & 3][i1];
+      AntOps64<3> o0, o1;
+      o0.load(cur, R, ia, ia, 0, am0);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        o1.load(cur, R, i1, i1, st, am1);
+        o0.template products<NEG>(w[0]);
+        if (st < 3) o0.load(cur, R, ia, ia, st + 1, am0);
+        if (ib >= 0) o1.template products<NEG>(w[1]);
+        side(c, st);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int b = i ? ib : ia;
+      if (b < 0) continue;
+      const int k = k0 + mac.dk[b], p = mac.blk[b] * kAntBlk;
+      if (k >= a.K) continue;
+      ant_store<true>(a, ant_sum64(w[i][0]), p, p, t, k);
+      ant_store<true>(a, ant_sum64(w[i][1]), p, p + 16, t, k);
+      ant_store<true>(a, ant_sum64(w[i][2]), p + 16, p + 16, t, k);
+    }
+  } else if (ia >= 0) {
+    AntTile64 w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ant_zero64(w[i]);
+    for (int c = 0; c < nc; ++c) {
+      head(c);
+      const double *cur = F + (c & 1) * stride, *am = pt.am[c & 3][ia];
+      AntOps64<4> o[2];
+      o[0].load(cur, R, ia, ib, 0, am);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        if (st < 3) o[(st + 1) & 1].load(cur, R, ia, ib, st + 1, am);
+        o[st & 1].template products<NEG>(w);
+        side(c, st);
+      }
+    }
+    const int k = k0 + mac.dk[ia], p = mac.blk[ia] * kAntBlk, q = mac.blk[ib] * kAntBlk;
+    if (k < a.K) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ant_store<true>(a, ant_sum64(w[i]), p + 16 * (i >> 1), q + 16 * (i & 1), t, k);
+    }
+  } else {
+    for (int c = 0; c < nc; ++c) {
+      head(c);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) side(c, st);
+    }
+  }
+}
+
 // Amplitudes of the factors: sign(S) sqrt|S| x scale per (channel, point),
 // zero past the last point (blocks of 32 points are taken whole).
 __global__ __launch_bounds__(256) void k_ant_amp(AntAmpArgs a) {
@@ -519,6 +863,26 @@ hipError_t launch_ant(const AntArgs &a, hipStream_t s) {
   const int R = a.max_sup * kAntBlk;
   const size_t sm = sizeof(AntPoints) + (size_t)2 * 16 * R * sizeof(half8);
   return R <= 16 * kAntWaves ? launch_ant_items<1>(a, (int)nt, sm, s) : launch_ant_items<2>(a, (int)nt, sm, s);
+}
+
+template <int ITEMS, bool NEG>
+static hipError_t launch_ant_fp64(const AntArgs &a, int nt, size_t sm, hipStream_t s) {
+  hipError_t e =
+      hipFuncSetAttribute((const void *)k_ant_fp64<ITEMS, NEG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_ant_fp64<ITEMS, NEG>), dim3((unsigned)nt), dim3(64 * kAntWaves), sm, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_ant64(const AntArgs &a, hipStream_t s) {
+  const int64_t nt = (int64_t)a.T * a.nkb * a.nmac;
+  if (nt <= 0) return hipSuccess;
+  if (nt > 0x7fffffff || a.J <= 0 || a.max_sup < 1 || a.max_sup > kAntSup) return hipErrorInvalidValue;
+  const int R = a.max_sup * kAntBlk;
+  const size_t sm = sizeof(AntPoints64) + (size_t)2 * 2 * kAntK64 * R * sizeof(double);
+  if (R <= 16 * kAntWaves)
+    return a.neg ? launch_ant_fp64<1, true>(a, (int)nt, sm, s) : launch_ant_fp64<1, false>(a, (int)nt, sm, s);
+  return a.neg ? launch_ant_fp64<2, true>(a, (int)nt, sm, s) : launch_ant_fp64<2, false>(a, (int)nt, sm, s);
 }
 
 }  // namespace vp

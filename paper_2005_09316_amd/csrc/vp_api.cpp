@@ -124,7 +124,24 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
 // 256 x 1,536.  The vector kernel's goes by points and rounds of three tiles
 // per CU: 0.32 us (128 antennas, 1,780 tiles), and not below 0.18 us for a few
 // tiles.
-static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision) {
+//
+// The FP64 path: where the antennas agree with the rows to 1e-12 turns (its bar
+// is 1e-11 of the flux), and not when complex64 data would take the Gaussians
+// in a pass of their own (a rounding more).  Per block of 16 points and round of
+// workgroups 6.2 us (measured at 128 to 256 antennas; 4.8 at 64 and 96, 2.7 at
+// up to 32: smaller macros), and the vector kernel 0.29 us a point and tile per
+// CU, 0.32 us at least (32 to 256 antennas, 1 to 14 times 8 to 32 channels).
+// 128 antennas, 14 times, 32 channels: 0.77 against 1.98 us a point.
+static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dtype) {
+  if (precision == kFP64 || precision == kLut) {
+    if (obs->ant_n == 0 || sky->P < kAntMinPoints || !(obs->ant_dev <= 1e-12) || !(obs->ant_reach <= 1e12)) return false;
+    if (dtype == VP_C64 && sky->G > 0) return false;
+    const double wgs = (double)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac;
+    const double blk_us = obs->ant_n <= 32 ? 2.7 : obs->ant_n <= 96 ? 4.8 : 6.2;
+    const double ant_us = std::ceil(wgs / 256.0) * ((sky->P + 15) / 16) * blk_us + 10.0;
+    const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
+    return ant_us < std::max(0.32, 0.29 * std::ceil(tiles / 256.0)) * sky->P;
+  }
   if (precision != kMixed && precision != kMixedBf16 && precision != kMixedBf16x2) return false;
   if (!ant_pair(sky, obs) || !(obs->ant_dev <= 1e-10) || !(obs->ant_reach <= 131072.0)) return false;
   const double wgs = (double)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac;
@@ -396,7 +413,8 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   a.uniform = precision == kFP64 || precision == kLut ? obs->uniform64 : obs->uniform;
   // A sky of shapelets only skips the point/Gaussian pass, which would only
   // write zeros (predict) or rewrite the data unchanged (subtract).
-  const bool ant = d.amp && use_ant(sky, obs, precision);
+  const bool ant64 = precision == kFP64 || precision == kLut;
+  const bool ant = (ant64 || d.amp) && use_ant(sky, obs, precision, dtype);
   const bool pg_pass = ant ? sky->G > 0 : sky->P + sky->G > 0 || sky->S == 0;
   a.skip_points = ant;
   a.fresh = !pg_pass && !ant && !subtract;
@@ -404,20 +422,21 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   if (ant) {
     AntArgs p;
     double scale = 1.0;
-    ant_pair(sky, obs, &scale);
+    if (!ant64) ant_pair(sky, obs, &scale);
     p.T = obs->T; p.B = obs->B; p.K = obs->K;
     p.npad = obs->ant_npad;
     p.J = sky->P; p.Jp = ant_jp(sky);
     p.nmac = obs->ant_nmac; p.max_sup = obs->ant_max_sup;
     p.kpack = obs->ant_kpack; p.nkb = (obs->K + p.kpack - 1) / p.kpack;
-    p.mac = obs->ant_mac; p.xyz = obs->ant_xyz; p.rowmap = obs->ant_rowmap;
+    p.mac = obs->ant_mac; p.xyz = obs->ant_xyz; p.xyz_lo = obs->ant_lo; p.rowmap = obs->ant_rowmap;
     p.fk = obs->fk; p.pos = d.pos; p.amp = d.amp;
+    p.flux64 = d.flux64; p.Kpad = obs->Kpad;
     p.unscale = 1.0 / (scale * scale);
     p.neg = sky->p_neg;
     p.fine = !obs->uniform;
     p.vis = vis; p.c64 = a.c64; p.conj = a.conj; p.subtract = subtract;
     ProfScope ps(prof, stream, 1);
-    e = launch_ant(p, stream);
+    e = ant64 ? launch_ant64(p, stream) : launch_ant(p, stream);
     if (kernels) ++*kernels;
   }
   if (e != hipSuccess) return hip_error(e, "launching the kernel of the points by antenna");
@@ -545,17 +564,18 @@ static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
   const int max_n = std::min(kAntMaxN, (int)(2.2 * std::sqrt((double)o->B)) + 8);
   const double f = o->f_hi / kLightSpeed;
   if (o->B > (int64_t)kAntMaxN * (kAntMaxN + 1) / 2) return hipSuccess;
-  const AntLayout L = find_antennas(o->T, o->B, uvw, 1e-10 / f, max_n);
+  const AntLayout L = find_antennas(o->T, o->B, uvw, 1e-10 / f, max_n, false);
   const int np = (L.n + kAntBlk - 1) / kAntBlk * kAntBlk;
   // (few baselines over very many times: the padding would outgrow the uvw)
   if (L.n == 0 || (np > o->B && (int64_t)o->T * np > 1 << 20)) return hipSuccess;
   const std::vector<AntMacro> mac = ant_macros(L.n, &o->ant_kpack);
-  // one buffer: coordinates, pair map, macros
+  // one buffer: largest disagreement, coordinates, their corrections, pair map, macros
   const size_t n_xyz = sizeof(double) * 3 * (size_t)o->T * np, n_map = sizeof(int32_t) * (size_t)np * np;
-  std::vector<char> buf(n_xyz + n_map + sizeof(AntMacro) * mac.size(), 0);
-  double *xyz = (double *)buf.data();
-  int32_t *map = (int32_t *)(buf.data() + n_xyz);
-  std::memcpy(buf.data() + n_xyz + n_map, mac.data(), sizeof(AntMacro) * mac.size());
+  const size_t o_xyz = 16, o_lo = o_xyz + n_xyz, o_map = o_lo + n_xyz, o_mac = o_map + n_map;
+  std::vector<char> buf(o_mac + sizeof(AntMacro) * mac.size(), 0);
+  double *xyz = (double *)(buf.data() + o_xyz);
+  int32_t *map = (int32_t *)(buf.data() + o_map);
+  std::memcpy(buf.data() + o_mac, mac.data(), sizeof(AntMacro) * mac.size());
   for (int b = 0; b < o->B; ++b) {
     const int p = L.p[b], q = L.q[b];
     if (p <= q)
@@ -566,16 +586,22 @@ static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
   for (int t = 0; t < o->T; ++t)
     std::copy(&L.xyz[(size_t)t * L.n * 3], &L.xyz[(size_t)t * L.n * 3] + 3 * (size_t)L.n, &xyz[(size_t)t * np * 3]);
   char *dev = nullptr;
-  const hipError_t e = upload(&dev, buf.data(), (int64_t)buf.size(), o->mem);
+  hipError_t e = upload(&dev, buf.data(), (int64_t)buf.size(), o->mem);
   if (e != hipSuccess) return e;
-  o->ant_xyz = (double *)dev;
-  o->ant_rowmap = (int32_t *)(dev + n_xyz);
-  o->ant_mac = (AntMacro *)(dev + n_xyz + n_map);
+  o->ant_xyz = (double *)(dev + o_xyz);
+  o->ant_lo = (double *)(dev + o_lo);
+  o->ant_rowmap = (int32_t *)(dev + o_map);
+  o->ant_mac = (AntMacro *)(dev + o_mac);
+  double worst = 0.0;
+  e = launch_ant_refine(o->T, o->B, L.n, np, o->uvw, o->ant_rowmap, o->ant_xyz, o->ant_lo, (unsigned long long *)dev, nullptr);
+  if (e == hipSuccess) e = hipMemcpy(&worst, dev, sizeof(worst), hipMemcpyDeviceToHost);
+  if (e != hipSuccess) return e;
+  if (!(worst * f <= 1e-10)) return hipSuccess;  // other time steps have other antennas
   o->ant_n = L.n;
   o->ant_npad = np;
   o->ant_nmac = (int)mac.size();
   for (const AntMacro &m : mac) o->ant_max_sup = std::max(o->ant_max_sup, (int)m.nsup);
-  o->ant_dev = L.dev * f;
+  o->ant_dev = worst * f;
   for (size_t i = 0; i < L.xyz.size(); i += 3)
     o->ant_reach = std::max(o->ant_reach, f * (std::fabs(L.xyz[i]) + std::fabs(L.xyz[i + 1]) + std::fabs(L.xyz[i + 2])));
   return hipSuccess;

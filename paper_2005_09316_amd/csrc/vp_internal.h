@@ -153,10 +153,13 @@ struct AntArgs {
   int kpack, nkb;         // channels per workgroup, workgroups over the channels
   const AntMacro *mac;
   const double *xyz;      // [T][npad][3] antenna coordinates, metres (zero in the padding)
+  const double *xyz_lo;   // [T][npad][3] what they are short of (FP64 path)
   const int32_t *rowmap;  // [npad][npad] row of pair (p, q) + 1, negative: conjugated, 0: none
   const double *fk;       // [Kpad] nu / c
   const double4 *pos;     // [J] l, m, n - 1
-  const float *amp;       // [Kpad][Jp]
+  const float *amp;       // [Kpad][Jp] (mixed path)
+  const double *flux64;   // [J][Kpad] (FP64 path)
+  int Kpad;
   double unscale;         // 1 / (the amplitudes' scale)^2
   int neg;                // 1: some fluxes are negative
   int fine;               // 1: the more exact factors (irregular channels)
@@ -231,6 +234,9 @@ bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp);
 hipError_t launch_lut_build(float *T, hipStream_t s);
 hipError_t launch_ant_amp(const AntAmpArgs &a, hipStream_t s);
 hipError_t launch_ant(const AntArgs &a, hipStream_t s);
+hipError_t launch_ant_refine(int T, int B, int n, int npad, const double *uvw, const int32_t *rowmap, const double *xyz,
+                             double *xyz_lo, unsigned long long *dev, hipStream_t s);
+hipError_t launch_ant64(const AntArgs &a, hipStream_t s);
 hipError_t launch_mark(ServeMark *m, uint64_t seq, hipStream_t s);
 hipError_t launch_gain(const GainArgs &a, hipStream_t s);
 hipError_t launch_gain_subtract(const GainArgs &a, hipStream_t s);

@@ -108,11 +108,13 @@ __device__ __forceinline__ void derive_one(const DeriveArgs &a, int j) {
   const double ra = a.ra[j], dec = a.dec[j];
   const double da = ra - a.ra0;
   const double sd = sin(dec), cd = cos(dec), sd0 = sin(a.dec0), cd0 = cos(a.dec0);
-  const double sda = sin(da), cda = cos(da);
-  const double l = cd * sda;
-  const double m = sd * cd0 - cd * sd0 * cda;
-  const double n = sd * sd0 + cd * cd0 * cda;
-  const double nm1 = -(l * l + m * m) / (1.0 + n);
+  // m = sin(dec) cos(dec0) - cos(dec) sin(dec0) cos(da) and n - 1 from
+  // differences and half angles, where nothing large cancels
+  const double dd = dec - a.dec0;
+  const double hda = sin(0.5 * da), hdd = sin(0.5 * dd);
+  const double l = cd * sin(da);
+  const double m = fma(2.0 * cd * sd0, hda * hda, sin(dd));
+  const double nm1 = -2.0 * fma(cd * cd0, hda * hda, hdd * hdd);
   a.d.pos[j] = make_double4(l, m, nm1, 0.0);
   if (j >= a.P && j < a.P + a.G) {
     // exponent of Eq. gauss-env in base 2:

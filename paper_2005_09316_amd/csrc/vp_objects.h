@@ -151,7 +151,7 @@ struct vp_obs {
   int ant_n = 0, ant_npad = 0, ant_nmac = 0, ant_max_sup = 0, ant_kpack = 1;
   double ant_dev = 0;           // their largest disagreement with a row, in turns at the highest frequency
   double ant_reach = 0;         // largest antenna coordinate (a sum of magnitudes), in wavelengths at the highest frequency
-  double *ant_xyz = nullptr;    // device [T][npad][3]
+  double *ant_xyz = nullptr, *ant_lo = nullptr;  // device [T][npad][3], [T][npad][3]
   int32_t *ant_rowmap = nullptr;  // device [npad][npad]
   vp::AntMacro *ant_mac = nullptr;
   int jobs = 0;           // pending serving jobs using it (guarded by ctx->mu)
