@@ -135,19 +135,107 @@ __global__ __launch_bounds__(256) void k_gain_tables(GainArgs a) {
   }
 }
 
+// The same tables for arrays of up to kGainPairs tiles, one entry a pair i < j
+// (pair_index order, X seen from tile j): xt [cell][pair], wf [cell][pair].
+// Workgroup (x, y): C consecutive cells, kGainPairRun pairs.  Every visibility is
+// read once, C adjacent channels at a time, and the rows written are contiguous.
+constexpr int kGainPairRun = 128;
+template <typename TT, typename VT2>
+__global__ __launch_bounds__(256) void k_gain_pairs(GainArgs a) {
+  typedef typename TabPair<TT>::type TT2;
+  constexpr int C = tab_cells<TT>(), R = kGainPairRun * C / 256;
+  __shared__ TT2 sx[C][kGainPairRun + 1];
+  __shared__ TT sw[C][kGainPairRun + 1];
+  const int np = a.n_ant * (a.n_ant - 1) / 2, p0 = blockIdx.y * kGainPairRun, c0 = blockIdx.x * C;
+  const int nc = min(C, a.ncell - c0), j = threadIdx.x % C;
+  const int cell = a.cell0 + c0 + min(j, nc - 1), t = cell / a.K, kc = cell - t * a.K;
+  int b[R];
+  VT2 mr[R], vr[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) b[r] = a.pair_bl[min(p0 + (int)threadIdx.x / C + r * (256 / C), np - 1)];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = ((int64_t)t * a.B + max(b[r], 0)) * a.K + kc;
+    mr[r] = ((const VT2 *)a.model)[i];
+    vr[r] = ((const VT2 *)a.data)[i];
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int q = threadIdx.x / C + r * (256 / C), bl = max(b[r], 0);
+    const double2 m = make_double2(mr[r].x, mr[r].y);
+    double2 xv = cmul(cconj(m), make_double2(vr[r].x, vr[r].y));
+    if (a.ant1[bl] < a.ant2[bl]) xv = cconj(xv);
+    TT2 x;
+    x.x = b[r] >= 0 ? (TT)xv.x : (TT)0;
+    x.y = b[r] >= 0 ? (TT)xv.y : (TT)0;
+    sx[j][q] = x;
+    sw[j][q] = b[r] >= 0 ? (TT)(m.x * m.x + m.y * m.y) : (TT)0;
+  }
+  __syncthreads();
+  TT2 *X = (TT2 *)a.xt;
+  TT *W = (TT *)a.wf;
+  const int nq = min(kGainPairRun, np - p0);
+  for (int e = threadIdx.x; e < nc * kGainPairRun; e += 256) {
+    const int c = e / kGainPairRun, q = e % kGainPairRun;
+    if (q >= nq) continue;
+    const int64_t off = (int64_t)(c0 + c) * np + p0 + q;
+    X[off] = sx[c][q];
+    W[off] = sw[c][q];
+  }
+}
+
+// Sums over a wave without LDS: halves, then rows of 16 lanes change places
+// between two registers (v_permlane32_swap, v_permlane16_swap), so that one add
+// folds two values at once, and four rotations sum within the rows.  A shuffle
+// (ds_bpermute) takes an LDS round trip a fold and value.
+__device__ __forceinline__ void swap32(double &a, double &b) {  // upper half of a with lower half of b
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  a = __hiloint2double((int)h[0], (int)l[0]);
+  b = __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ void swap16(double &a, double &b) {  // odd rows of a with even rows of b
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  a = __hiloint2double((int)h[0], (int)l[0]);
+  b = __hiloint2double((int)h[1], (int)l[1]);
+}
+template <int ROT>
+__device__ __forceinline__ double row_fold(double v) {  // plus the lane ROT further in its row
+  const int l = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + ROT, 0xf, 0xf, true);
+  const int h = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + ROT, 0xf, 0xf, true);
+  return v + __hiloint2double(h, l);
+}
+__device__ __forceinline__ double row_sum(double v) { return row_fold<1>(row_fold<2>(row_fold<4>(row_fold<8>(v)))); }
+__device__ __forceinline__ double lane_of(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ double3 wave_sum3(double u, double v, double w) {
+  swap32(u, v);
+  double uv = u + v, w2 = w;
+  swap32(w, w2);
+  double ww = w + w2;
+  swap16(uv, ww);
+  const double s = row_sum(uv + ww);  // rows: u, w, v, w
+  return make_double3(lane_of(s, 0), lane_of(s, 32), lane_of(s, 16));
+}
+__device__ __forceinline__ double2 wave_sum2(double u, double v) {
+  swap32(u, v);
+  double uv = u + v, uv2 = uv;
+  swap16(uv, uv2);
+  const double s = row_sum(uv + uv2);
+  return make_double2(lane_of(s, 0), lane_of(s, 32));
+}
+
 // Sums of two values over the workgroup (NT threads) in one pass, through
 // the scratch red[NT / 64].  One barrier: the caller alternates between two
 // scratch buffers, and a workgroup barrier separates the last reads of a
 // buffer from its next writes.
 template <int NT>
 __device__ __forceinline__ double2 block_sum2(double u, double v, double2 *red) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    u += __shfl_xor(u, o);
-    v += __shfl_xor(v, o);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = make_double2(u, v);
+  const double2 t = wave_sum2(u, v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
   __syncthreads();
   double2 s = make_double2(0.0, 0.0);
 #pragma unroll
@@ -162,16 +250,11 @@ __device__ __forceinline__ double2 block_sum2(double u, double v, double2 *red) 
 // pairs.
 template <int NT>
 __device__ __forceinline__ double3 block_sum3(double u, double v, double w, double2 *red) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    u += __shfl_xor(u, o);
-    v += __shfl_xor(v, o);
-    w += __shfl_xor(w, o);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[2 * wave] = make_double2(u, v);
-    red[2 * wave + 1] = make_double2(w, 0.0);
+  const double3 t = wave_sum3(u, v, w);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    red[2 * wave] = make_double2(t.x, t.y);
+    red[2 * wave + 1] = make_double2(t.z, 0.0);
   }
   __syncthreads();
   double3 s = make_double3(0.0, 0.0, 0.0);
@@ -448,6 +531,308 @@ __global__ __launch_bounds__(NT) void k_gain_solve(GainArgs a) {
   }
 }
 
+// 1 / x for normal x, to about an ulp: v_rcp_f64 and two Newton steps, half the
+// instructions of the division.
+__device__ __forceinline__ double gain_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// n entries from memory to LDS, 16 loads a thread in flight.
+template <int NT, typename T>
+__device__ __forceinline__ void gain_stage(T *to, const T *from, int n) {
+  for (int i0 = threadIdx.x; i0 < n; i0 += 16 * NT) {
+    T v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = from[min(i0 + q * NT, n - 1)];
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      if (i0 + q * NT < n) to[i0 + q * NT] = v[q];
+  }
+}
+
+// The solve for up to 64 RPL <= 128 tiles, mixed (TT float) and FP64 (double).
+// One workgroup of NW waves per cell.  Wave w takes the columns o of
+// [w OPW, (w + 1) OPW) and lane l the rows k = l + 64 j (j < RPL): W sits in
+// registers, RPL x OPW a thread, X in LDS, one entry a pair, both read from
+// memory once.  Every wave keeps the gains and the conjugate-gradient state of
+// all rows (lane l: its RPL tiles) and takes the same steps with the same
+// numbers, so that a step is one exchange of partial products through LDS, with
+// one barrier (two buffers in turn), and the sums that steer it stay within the
+// wave; all waves leave the loop together because what they compare is the same
+// bit for bit.  What bounds it: with few cells the chain of a step (direction
+// out and back through LDS, products, exchange, wave sums, two divisions), with
+// many the products' and the state's instructions.
+template <typename TT, int NW, int RPL>
+__global__ __launch_bounds__(64 * NW, sizeof(TT) == sizeof(float) ? 2 : 1) void k_gain_solve_rw(GainArgs a) {
+  typedef typename TabPair<TT>::type TT2;
+  constexpr int ROWS = 64 * RPL, OPW = ROWS / NW;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double2 *pa = (double2 *)smem;                             // [NW][ROWS] partial sums, or
+  TT2 *pt = (TT2 *)smem;                                     // [2][NW][ROWS] those of the operator
+  double2 *g = pa + NW * ROWS * (2 * sizeof(TT2) / sizeof(double2));  // [ROWS] gains
+  double *pv = (double *)(g + ROWS);                         // [ROWS] projection scratch
+  TT2 *y = (TT2 *)(pv + ROWS);                               // [ROWS] g_o u_o^*, by the wave whose columns they are
+  int *comp = (int *)(y + ROWS);                             // [ROWS] connected component of each tile
+  TT2 *P = (TT2 *)(comp + ROWS);                             // [n (n - 1) / 2 + 1] X of the pairs, and a zero
+
+  const int cl = blockIdx.x, cell = a.cell0 + cl;
+  const int t = cell / a.K, kc = cell % a.K;
+  const int n = a.n_ant, np = n * (n - 1) / 2, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ob = wv * OPW;
+  // entry of (k, o): before(o) + k or before(k) + o, the first tile's; np (a
+  // zero) where there is none
+  auto before = [&](int i) { return i * n - i * (i + 1) / 2 - i - 1; };
+  auto pair_at = [&](int k, int bk, int o, int bo) {
+    const int e = k > o ? bo + k : bk + o;
+    const bool none = (k == o) | (max(k, o) >= n);
+    return none ? np : e;
+  };
+
+  TT Wr[RPL][OPW];
+  {
+    const TT *Wf = (const TT *)a.wf + (int64_t)cl * np;
+    TT *Ws = (TT *)P;
+    gain_stage<64 * NW>(Ws, Wf, np);
+    if (tid == 0) Ws[np] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      const int k = lane + 64 * j, bk = before(k);
+#pragma unroll
+      for (int i = 0; i < OPW; ++i) {
+        Wr[j][i] = Ws[pair_at(k, bk, ob + i, before(ob + i))];
+        if (i % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();
+    const TT2 *X = (const TT2 *)a.xt + (int64_t)cl * np;
+    gain_stage<64 * NW>(P, X, np);
+    if (tid == 0) P[np].x = P[np].y = 0;
+  }
+  double2 gk[RPL];
+  int ck[RPL];
+#pragma unroll
+  for (int j = 0; j < RPL; ++j) {
+    const int k = lane + 64 * j;
+    gk[j] = make_double2(1.0, 0.0);
+    ck[j] = k < n ? a.comp[k] : -1;
+    if (wv == 0) {
+      g[k] = make_double2(k < n ? 1.0 : 0.0, 0.0);
+      comp[k] = ck[j];
+    }
+  }
+  __syncthreads();
+
+  // v <- v - i g (sum_C Im(g^* v)) / (sum_C |g|^2), C the tile's component
+  auto project = [&](double2 (&v)[RPL]) {
+    if (a.single_comp) {
+      double num = 0.0, den = 0.0;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        if (ck[j] < 0) continue;
+        num += gk[j].x * v[j].y - gk[j].y * v[j].x;
+        den += gk[j].x * gk[j].x + gk[j].y * gk[j].y;
+      }
+      const double2 s = wave_sum2(num, den);
+      const double c = s.y > 0.0 ? s.x / s.y : 0.0;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        if (ck[j] < 0) continue;
+        v[j].x += c * gk[j].y;
+        v[j].y -= c * gk[j].x;
+      }
+      return;
+    }
+    if (wv == 0) {
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) pv[lane + 64 * j] = ck[j] >= 0 ? gk[j].x * v[j].y - gk[j].y * v[j].x : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      double num = 0.0, den = 0.0;
+      for (int o = 0; o < n; ++o) {
+        if (comp[o] != ck[j]) continue;
+        const double2 go = g[o];
+        num += pv[o];
+        den += go.x * go.x + go.y * go.y;
+      }
+      if (ck[j] >= 0 && den > 0.0) {
+        const double c = num / den;
+        v[j].x += c * gk[j].y;
+        v[j].y -= c * gk[j].x;
+      }
+    }
+    __syncthreads();
+  };
+  // this lane's rows of the NW partial sums
+  auto gather = [&](const double2 (&part)[RPL], double2 (&sum)[RPL]) {
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) pa[wv * ROWS + lane + 64 * j] = part[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      sum[j] = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const double2 v = pa[w * ROWS + lane + 64 * j];
+        sum[j].x += v.x;
+        sum[j].y += v.y;
+      }
+    }
+    __syncthreads();
+  };
+
+  for (int it = 0; it < a.n_iter; ++it) {
+    // r_k = sum_o g_o X_ko - g_k D_k, D_k = sum_o W_ko |g_o|^2; aa: sum of
+    // |g_o X_ko|, for the rounding level of r_k
+    int row0 = lane, bk[RPL];
+    asm volatile("" : "+v"(row0));  // or every entry's position is kept from one iteration to the next, and spills
+    double2 sx[RPL], sd[RPL];
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      sx[j] = sd[j] = make_double2(0.0, 0.0);
+      bk[j] = before(row0 + 64 * j);
+    }
+#pragma unroll
+    for (int i = 0; i < OPW; ++i) {
+      const int o = ob + i, bo = before(o);
+      const double2 go = g[o];
+      const double g2 = go.x * go.x + go.y * go.y;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        const int k = row0 + 64 * j;
+        const TT2 xt = P[pair_at(k, bk[j], o, bo)];
+        if constexpr (sizeof(TT) == sizeof(float)) asm volatile("" : "+v"(Wr[j][i]));  // nor its FP64 copy
+        const double xr = (double)xt.x, xi = (double)(k < o ? -xt.y : xt.y);  // the entry is seen from the later tile
+        sx[j].x += go.x * xr - go.y * xi;
+        sx[j].y += go.x * xi + go.y * xr;
+        // the rounding level only: an FP32 square root will do
+        sd[j].y += (double)__builtin_amdgcn_sqrtf((float)((TT)g2 * (xt.x * xt.x + xt.y * xt.y)));
+        sd[j].x += g2 * (double)Wr[j][i];
+      }
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four columns' entries in flight, not all
+    }
+    double2 r[RPL], ds[RPL];
+    gather(sx, r);
+    gather(sd, ds);
+    double Dt[RPL], minv[RPL], rr0 = 0.0, sc2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      Dt[j] = ds[j].x;
+      r[j].x -= gk[j].x * Dt[j];
+      r[j].y -= gk[j].y * Dt[j];
+      const double sc = ds[j].y + sqrt(gk[j].x * gk[j].x + gk[j].y * gk[j].y) * Dt[j];
+      sc2 += sc * sc;
+      minv[j] = Dt[j] > 0.0 ? 1.0 / Dt[j] : 0.0;
+    }
+    project(r);
+    // conjugate gradients in the Chronopoulos-Gear form, as in k_gain_solve,
+    // with eta = delta - beta gam / alpha_old = delta - beta^2 eta_old
+    double2 x[RPL], u[RPL], pd[RPL], sv[RPL];
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      rr0 += r[j].x * r[j].x + r[j].y * r[j].y;
+      x[j] = pd[j] = sv[j] = make_double2(0.0, 0.0);
+      u[j] = make_double2(minv[j] * r[j].x, minv[j] * r[j].y);
+    }
+    const double2 s0 = wave_sum2(rr0, sc2);
+    const double floor2 = kGainFloor * kGainFloor * s0.y, tol2 = a.cg_tol2 * s0.x;
+    double gam_inv = 0.0, eta_old = 0.0;
+    int steps = 0;
+    for (int cg = 0; cg < a.max_cg; ++cg) {
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        const int k = lane + 64 * j;
+        if (k >= ob && k < ob + OPW) {
+          const double2 yk = cmul(gk[j], cconj(u[j]));
+          y[k].x = (TT)yk.x;
+          y[k].y = (TT)yk.y;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();  // written and read by this wave alone, in order
+      TT2 acc[RPL];
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) acc[j].x = acc[j].y = 0;
+#pragma unroll
+      for (int i = 0; i < OPW; ++i) {
+        const TT2 yo = y[ob + i];
+#pragma unroll
+        for (int j = 0; j < RPL; ++j) {
+          acc[j].x += Wr[j][i] * yo.x;
+          acc[j].y += Wr[j][i] * yo.y;
+        }
+      }
+      TT2 *const pb = pt + (cg & 1) * NW * ROWS;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) pb[wv * ROWS + lane + 64 * j] = acc[j];
+      __syncthreads();
+      double gt = 0.0, dt = 0.0, rt = 0.0;
+      double2 w[RPL];
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        double2 S = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          const TT2 v = pb[q * ROWS + lane + 64 * j];
+          S.x += v.x;
+          S.y += v.y;
+        }
+        const double2 gs = cmul(gk[j], S);
+        w[j] = make_double2(Dt[j] * u[j].x + gs.x, Dt[j] * u[j].y + gs.y);
+        gt += r[j].x * u[j].x + r[j].y * u[j].y;
+        dt += u[j].x * w[j].x + u[j].y * w[j].y;
+        rt += r[j].x * r[j].x + r[j].y * r[j].y;
+      }
+      const double3 s = wave_sum3(gt, dt, rt);
+      const double gam = s.x, rr = s.z;
+      if (!(rr > tol2) || !(rr > floor2) || !(gam > 0.0)) break;
+      const double beta = gam * gam_inv;
+      const double eta = s.y - beta * beta * eta_old;
+      if (!(eta > 0.0)) break;
+      const double alpha = gam * gain_rcp(eta);
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) {
+        pd[j] = make_double2(u[j].x + beta * pd[j].x, u[j].y + beta * pd[j].y);
+        sv[j] = make_double2(w[j].x + beta * sv[j].x, w[j].y + beta * sv[j].y);
+        x[j].x += alpha * pd[j].x;
+        x[j].y += alpha * pd[j].y;
+        r[j].x -= alpha * sv[j].x;
+        r[j].y -= alpha * sv[j].y;
+        u[j] = make_double2(minv[j] * r[j].x, minv[j] * r[j].y);
+      }
+      gam_inv = gain_rcp(gam);
+      eta_old = eta;
+      ++steps;
+    }
+    project(x);
+    __syncthreads();  // the last reads of the partial sums and, in project, of g
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      gk[j].x += x[j].x;
+      gk[j].y += x[j].y;
+      if (wv == 0 && lane + 64 * j < n) g[lane + 64 * j] = gk[j];
+    }
+    __syncthreads();
+    // no step taken: the gains did not change, so every further iteration
+    // would repeat this one exactly
+    if (steps == 0) break;
+  }
+
+  if (wv == 0) {
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      const int k = lane + 64 * j;
+      if (k >= n) continue;
+      if (a.gains) a.gains[(int64_t)cell * n + k] = gk[j];
+      a.gw[((int64_t)t * n + k) * a.K + kc] = gk[j];
+    }
+  }
+}
+
 // The mixed path's solve for large arrays (up to kPeelMaxAnt tiles), with W
 // held in registers instead of LDS.  One workgroup of 64 NW threads per cell.
 // Wave w takes the columns o of [w OPW, (w + 1) OPW) and lane l the rows
@@ -459,7 +844,7 @@ __global__ __launch_bounds__(NT) void k_gain_solve(GainArgs a) {
 // and arithmetic as k_gain_solve's mixed path (FP32 operator, FP64 sums and
 // state), with D_k summed from the same FP32 W.
 template <int NW, int RPL>
-__global__ __launch_bounds__(64 * NW) void k_gain_solve_rw(GainArgs a) {
+__global__ __launch_bounds__(64 * NW) void k_gain_solve_wide(GainArgs a) {
   // up to 64 RPL tiles: RPL rows per lane, NW column blocks of OPW
   constexpr int NT = 64 * NW, OPW = 64 * RPL / NW;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -685,6 +1070,15 @@ template <typename TT>
 static hipError_t launch_tables(const GainArgs &a, hipStream_t s) {
   constexpr int C = tab_cells<TT>();
   const size_t sm = (size_t)C * a.n_ant * (sizeof(typename TabPair<TT>::type) + sizeof(TT));
+  if (a.n_ant <= kGainPairs) {
+    const unsigned runs = (unsigned)((a.n_ant * (a.n_ant - 1) / 2 + kGainPairRun - 1) / kGainPairRun);
+    const dim3 grid((unsigned)((a.ncell + C - 1) / C), runs);
+    if (a.c64)
+      hipLaunchKernelGGL((k_gain_pairs<TT, float2>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_gain_pairs<TT, double2>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_gain_tables<TT>, dim3((unsigned)((a.ncell + C - 1) / C), (unsigned)a.n_ant), dim3(256), sm, s,
                      a);
   return hipGetLastError();
@@ -708,17 +1102,36 @@ size_t gain_rw_smem_bytes(int nw) {
 }
 
 template <int NW, int RPL>
-static hipError_t launch_solve_rw(const GainArgs &a, hipStream_t s) {
+static hipError_t launch_solve_wide(const GainArgs &a, hipStream_t s) {
   const size_t sm = gain_rw_smem_bytes(NW);
   hipError_t e =
-      hipFuncSetAttribute((const void *)k_gain_solve_rw<NW, RPL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+      hipFuncSetAttribute((const void *)k_gain_solve_wide<NW, RPL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_gain_solve_rw<NW, RPL>), dim3((unsigned)a.ncell), dim3(64 * NW), sm, s, a);
+  hipLaunchKernelGGL((k_gain_solve_wide<NW, RPL>), dim3((unsigned)a.ncell), dim3(64 * NW), sm, s, a);
   return hipGetLastError();
 }
 
+template <typename TT, int NW, int RPL>
+static hipError_t launch_solve_pairs(const GainArgs &a, hipStream_t s) {
+  typedef typename TabPair<TT>::type TT2;
+  constexpr int ROWS = 64 * RPL;
+  const size_t sm = ROWS * (2 * NW * sizeof(TT2) + sizeof(double2) + sizeof(double) + sizeof(TT2) + sizeof(int)) +
+                    ((size_t)a.n_ant * (a.n_ant - 1) / 2 + 1) * sizeof(TT2);
+  static_assert(NW * ROWS * sizeof(double2) <= 2 * NW * ROWS * sizeof(TT2), "one buffer serves both sums");
+  hipError_t e = hipFuncSetAttribute((const void *)k_gain_solve_rw<TT, NW, RPL>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_gain_solve_rw<TT, NW, RPL>), dim3((unsigned)a.ncell), dim3(64 * NW), sm, s, a);
+  return hipGetLastError();
+}
+
+// Entries of the tables X and W a cell.
+static size_t gain_entries(int n_ant) {
+  return n_ant <= kGainPairs ? (size_t)n_ant * (n_ant - 1) / 2 : (size_t)n_ant * n_ant;
+}
+size_t gain_x_bytes(int n_ant, bool w32) { return gain_entries(n_ant) * (w32 ? sizeof(float2) : sizeof(double2)); }
 size_t gain_cell_bytes(int n_ant, bool w32) {
-  return (size_t)n_ant * n_ant * (w32 ? sizeof(float2) + sizeof(float) : sizeof(double2) + sizeof(double));
+  return gain_x_bytes(n_ant, w32) + gain_entries(n_ant) * (w32 ? sizeof(float) : sizeof(double));
 }
 
 hipError_t launch_gain(const GainArgs &a, hipStream_t s) {
@@ -727,9 +1140,15 @@ hipError_t launch_gain(const GainArgs &a, hipStream_t s) {
     return hipErrorInvalidValue;
   hipError_t e = a.w32 ? launch_tables<float>(a, s) : launch_tables<double>(a, s);
   if (e != hipSuccess) return e;
-  // the mixed path (FP32 tables): W in registers, 128 tiles per 4 waves or
-  // 256 per 8 waves; the FP64 path: W in LDS, FP64 while it fits
-  if (a.w32) return a.n_ant <= 128 ? launch_solve_rw<4, 2>(a, s) : launch_solve_rw<8, 4>(a, s);
+  // up to kGainPairs tiles both tables of a cell fit its workgroup (LDS for X:
+  // 127 KB in FP64 at 128 tiles); above, X streams from memory once per
+  // iteration, with W in registers (mixed, 8 waves) or in LDS (FP64 while it fits)
+  if (a.n_ant <= kGainPairs) {
+    const bool one = a.n_ant <= 64;
+    if (a.w32) return one ? launch_solve_pairs<float, 4, 1>(a, s) : launch_solve_pairs<float, 4, 2>(a, s);
+    return one ? launch_solve_pairs<double, 4, 1>(a, s) : launch_solve_pairs<double, 4, 2>(a, s);
+  }
+  if (a.w32) return launch_solve_wide<8, 4>(a, s);
   if (gain_smem_bytes(a.n_ant, true, 1024) <= kPeelSmemMax) return launch_solve<double, 1024>(a, s);
   return launch_solve<float, 1024>(a, s);
 }

@@ -183,6 +183,7 @@ struct ServeMark {
 constexpr int kProfClasses = 4;
 
 // Peel calibration (vp_calib.hip).
+constexpr int kGainPairs = 128;           // up to this many, the solve keeps both tables of a cell on chip
 constexpr int kPeelMaxAnt = 256;          // tiles per observation (one thread each)
 constexpr size_t kPeelSmemMax = 163840;  // LDS per workgroup on gfx950
 constexpr size_t kPeelWsMax = size_t(1) << 30;  // per-cell tables of one launch, bytes (at least one cell)
@@ -200,8 +201,10 @@ struct GainArgs {
   double2 *gains;         // [T][K][n_ant] output, or null
   double2 *gw;            // [T][n_ant][K] gains of every cell (workspace, read by the subtract pass)
   int cell0, ncell;       // the launch covers cells cell0 .. cell0 + ncell - 1 (cell = t K + k)
-  void *xt;               // workspace [ncell][n_ant][n_ant] complex X (float2 when w32, else double2)
-  void *wf;               // workspace [ncell][n_ant][n_ant] |I|^2 (float when w32, else double)
+  // workspace: complex X and |I|^2 (float when w32, else double), [ncell][pairs]
+  // up to kGainPairs tiles, else [ncell][n_ant][n_ant]
+  void *xt;
+  void *wf;
   int w32;                // 1 (mixed path): FP32 tables and FP32 W in the step's operator, FP64 sums
   int single_comp;        // 1: every tile with a baseline is in one connected component
 };
@@ -242,7 +245,8 @@ hipError_t launch_gain(const GainArgs &a, hipStream_t s);
 hipError_t launch_gain_subtract(const GainArgs &a, hipStream_t s);
 bool gain_supported(int n_ant);
 size_t gain_smem_bytes(int n_ant, bool w64, int threads);
-size_t gain_cell_bytes(int n_ant, bool w32);  // workspace bytes per cell
+size_t gain_x_bytes(int n_ant, bool w32);     // of table X per cell
+size_t gain_cell_bytes(int n_ant, bool w32);  // of tables X and W per cell
 
 // sizes of per-shapelet tile storage
 inline int64_t a32_floats(int nmax) { return (int64_t)shp_pairs(nmax) * kA32PerPair; }

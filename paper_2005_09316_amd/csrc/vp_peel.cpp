@@ -133,7 +133,7 @@ int vp_peel(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, const int32_t *an
   a.w32 = w32;
   a.single_comp = single ? 1 : 0;
   a.xt = w.ws;
-  a.wf = (char *)w.ws + (size_t)chunk * n_ant * n_ant * (w32 ? sizeof(float2) : sizeof(double2));
+  a.wf = (char *)w.ws + (size_t)chunk * gain_x_bytes(n_ant, w32);
   {
     ProfScope ps(ctx, s, 3);
     for (int64_t c0 = 0; c0 < cells && e == hipSuccess; c0 += chunk) {
