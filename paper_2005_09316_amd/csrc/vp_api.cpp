@@ -392,7 +392,7 @@ static int get_lut(vp_ctx *ctx, hipStream_t stream, const float **out) {
 }
 
 int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
-                  int subtract, hipStream_t stream, const Derived &d, const float *lut, int *kernels) {
+                  int subtract, hipStream_t stream, const Derived &d, const float *lut, int *kernels, bool nodes) {
   TileArgs a;
   a.nrows = (int64_t)obs->T * obs->B;
   a.K = obs->K;
@@ -450,7 +450,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
     a.n_cb = (obs->K + kShpChan - 1) / kShpChan;
     ProfScope ps(prof, stream, 2);
     const int path = precision == kFP64 ? 1 : precision == kFP32 || precision == kLut ? -1 : 0;
-    const NodePlan plan = path >= 0 && d.interp[path] ? node_plan(sky, obs, path) : NodePlan{0, 0, 0.0, 0.0};
+    const NodePlan plan = nodes && path >= 0 && d.interp[path] ? node_plan(sky, obs, path) : NodePlan{0, 0, 0.0, 0.0};
     if (plan.M > 0)
       e = launch_shp_nodes(a, plan, precision, sky->max_nmax, stream);
     else
@@ -463,7 +463,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
 }
 
 int run_tiles(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
-              int subtract, hipStream_t stream) {
+              int subtract, hipStream_t stream, bool nodes) {
   DerivedEntry *d = nullptr;
   int rc = get_derived(ctx, sky, obs, stream, false, &d);
   if (rc != VP_OK) return rc;
@@ -472,7 +472,7 @@ int run_tiles(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, 
     rc = get_lut(ctx, stream, &lut);
     if (rc != VP_OK) return rc;
   }
-  return launch_passes(ctx, sky, obs, precision, dtype, vis, subtract, stream, d->d, lut);
+  return launch_passes(ctx, sky, obs, precision, dtype, vis, subtract, stream, d->d, lut, nullptr, nodes);
 }
 
 int check_call(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis) {

@@ -90,15 +90,16 @@ struct DeviceGuard {
 int set_error(int code, const char *fmt, ...);
 int hip_error(hipError_t e, const char *what);
 int run_tiles(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
-              void *vis, int subtract, hipStream_t stream);
+              void *vis, int subtract, hipStream_t stream, bool nodes = true);
 int check_call(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
                void *vis);
 // Launch the passes over the visibility tiles with the pair's tables `d`.
 // prof: the context whose profiling records the launches, or null; *kernels
-// (when given) grows by the number of kernels launched.
+// (when given) grows by the number of kernels launched; nodes: shapelets may go
+// by nodes.
 int launch_passes(vp_ctx *prof, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
                   void *vis, int subtract, hipStream_t stream, const Derived &d, const float *lut,
-                  int *kernels = nullptr);
+                  int *kernels = nullptr, bool nodes = true);
 // Per-(sky, observation) tables, built on `stream` at first use and cached;
 // later callers on other streams wait for the build.  serving: the caller is
 // an admitted job, counted in the entry's users until serve_release_derived.

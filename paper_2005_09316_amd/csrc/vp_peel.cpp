@@ -106,7 +106,13 @@ int vp_peel(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, const int32_t *an
   e = hipMemcpy(w.tab, tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_error(e, "uploading the baseline tables");
   hipStream_t s = (hipStream_t)hip_stream;
-  rc = run_tiles(ctx, sky, obs, precision, dtype, w.model, 0, s);
+  // On the mixed path the model stays the contraction channel by channel.  Both
+  // ways are 4e-8 of the model off, in errors of their own, and the residual
+  // shows them multiplied by |data| / |residual|: measured up to 510 for two
+  // bright lobes under noise of 1 Jy, so that a residual by nodes would lie 3e-5
+  // from one by channels.  By nodes the model of such a peel takes 0.36 ms, by
+  // channels 2.4 ms.
+  rc = run_tiles(ctx, sky, obs, precision, dtype, w.model, 0, s, precision == VP_PREC_FP64);
   if (rc != VP_OK) return rc;
   GainArgs a;
   a.T = obs->T;
