@@ -13,6 +13,7 @@
 // (w/2)^M / M! with w = (N + 1/2) x the band's half-width over its lower end.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 
 namespace vp {
@@ -40,6 +41,32 @@ inline int shp_nodes(int nmax, double f_lo, double f_hi, double tol) {
     if (m >= w && t * std::exp(-0.25 * w * w / (m + 1)) <= tol) return m;
   }
   return 0;
+}
+
+// Points and Gaussians.  Along a baseline a component is S(nu) 2^(-Q nu^2)
+// e^(2 pi i t0 nu / c), so that a row's sum over components in a narrow field,
+// where every t0 is short, is determined by its values at a few frequencies too.
+// w: the largest phase, in radians, from the band's middle to its end; delta:
+// the band's half-width over its middle; amax: the largest |spectral index|.
+// On the ellipse with foci -1, 1 and semi-axes a, b = (rho +- 1 / rho) / 2 (the
+// band's variable being z in [-1, 1]) a term is at most e^(w b) (1 - delta
+// a)^-amax of its flux at the middle, Gaussian envelopes and beam staying below 1
+// while delta^2 (a^2 + b^2) <= 1, and Chebyshev interpolation at M nodes errs by
+// at most 4 rho^(1 - M) / (rho - 1) of that.  The least M over the ellipses tried
+// that brings it to tol, or 0 when kPgNodesMax do not.
+constexpr int kPgNodesMax = 48;
+inline int pg_nodes(double w, double delta, double amax, double tol) {
+  if (!(w >= 0.0) || !(w <= kPgNodesMax) || !(delta >= 0.0) || !(amax >= 0.0)) return 0;
+  int best = 0;
+  for (double rho = 1.2; rho < 1e4; rho *= 1.15) {
+    const double a = 0.5 * (rho + 1.0 / rho), b = 0.5 * (rho - 1.0 / rho);
+    if (delta * delta * (a * a + b * b) > 0.9) break;
+    const double lg = std::log(4.0 / ((rho - 1.0) * tol)) + w * b - amax * std::log(1.0 - delta * a);
+    if (!(lg <= kPgNodesMax * std::log(rho))) continue;
+    const int M = 1 + (int)std::ceil(std::max(0.0, lg) / std::log(rho));
+    if (M <= kPgNodesMax && (best == 0 || M < best)) best = M;
+  }
+  return best;
 }
 
 }  // namespace vp

@@ -47,9 +47,13 @@ DeviceGuard::~DeviceGuard() {
 }
 
 static bool finite_all(const double *p, int64_t n) {
-  for (int64_t i = 0; i < n; ++i)
-    if (!std::isfinite(p[i])) return false;
-  return true;
+  uint64_t all = 0;  // (no early exit, so that it vectorises)
+  for (int64_t i = 0; i < n; ++i) {
+    uint64_t u;
+    std::memcpy(&u, p + i, sizeof(u));
+    all |= (u & 0x7fffffffffffffffull) + 0x0010000000000000ull;  // an exponent of ones carries into the sign
+  }
+  return all >> 63 == 0;
 }
 
 template <typename T>
@@ -83,18 +87,47 @@ void DeviceMem::release() {
 // Shapelets by nodes where that saves a sixth of the envelopes or more: a
 // channel's interpolation, phase and flux cost about 0.035 of an envelope.
 // (The highest order's nodes serve all of the sky's shapelets.)
+static int shapelet_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
+  if (sky->S == 0) return 0;
+  const int M = shp_nodes(sky->max_nmax, obs->f_lo, obs->f_hi, i == 0 ? kNodesTolMixed : kNodesTolFp64);
+  if (M + 0.035 * obs->K > 0.85 * obs->K) return 0;
+  return shp_nodes_fit(i == 0 ? kMixed : kFP64, sky->max_nmax, sky->S, (M + 3) / 4 * 4) ? M : 0;
+}
+
+// Points and Gaussians by nodes where three channels or more go to a node.  A
+// row's phase per component is at most its length times the distance between the
+// component's direction and the phase centre, bounded here through the sky's middle.
+static int pg_sum_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
+  if (sky->P + sky->G == 0 || obs->K < 12) return 0;
+  const double half = 0.5 * (obs->f_hi - obs->f_lo) / kLightSpeed, mid = 0.5 * (obs->f_lo + obs->f_hi) / kLightSpeed;
+  // |s - s'|^2 = 4 sin^2(d dec / 2) + 4 cos(dec) cos(dec') sin^2(d ra / 2)
+  const double sd = std::sin(0.5 * (sky->pg_dec - obs->dec0)), sa = std::sin(0.5 * (sky->pg_ra - obs->ra0));
+  const double to_mid = 2.0 * std::sqrt(sd * sd + std::fabs(std::cos(sky->pg_dec) * std::cos(obs->dec0)) * sa * sa);
+  const double reach = obs->b_max * std::min(2.0, to_mid + sky->pg_reach) * (1.0 + 1e-9);
+  if (!(reach * obs->f_hi / kLightSpeed <= 262144.0)) return 0;  // the mixed kernel's phases are fixed-point, up to 2^19 turns
+  const double w = 6.283185307179586477 * reach * half;
+  const int M = pg_nodes(w, half / mid, sky->pg_amax, i == 2 ? kNodesTolMixed : kNodesTolFp64);
+  return 3 * M <= obs->K ? M : 0;
+}
+
 NodePlan node_plan(const vp_sky *sky, const vp_obs *obs, int i) {
   NodePlan p{0, 0, 0.0, 0.0};
-  if (sky->S == 0 || obs->K > kNodesMaxChan) return p;
-  const int M = shp_nodes(sky->max_nmax, obs->f_lo, obs->f_hi, i == 0 ? kNodesTolMixed : kNodesTolFp64);
-  if (M == 0 || M + 0.035 * obs->K > 0.85 * obs->K) return p;
+  if (obs->K > kNodesMaxChan) return p;
+  const int M = i < 2 ? shapelet_nodes(sky, obs, i) : pg_sum_nodes(sky, obs, i);
+  if (M == 0) return p;
   const int Mp = (M + 3) / 4 * 4;
-  if (!shp_nodes_fit(i == 0 ? kMixed : kFP64, sky->max_nmax, sky->S, Mp)) return p;
   p.M = M;
   p.Mp = Mp;
   p.mid = 0.5 * (obs->f_lo + obs->f_hi) / kLightSpeed;
   p.half = 0.5 * (obs->f_hi - obs->f_lo) / kLightSpeed;
   return p;
+}
+
+uint64_t plan_bytes(const vp_obs *obs, const NodePlan &p) {
+  return p.M > 0 ? sizeof(double) * (uint64_t)node_doubles(obs->K, p.Mp) : 0;
+}
+uint64_t nflux_bytes(const vp_sky *sky, const NodePlan &p, int i) {
+  return i >= 2 && p.M > 0 ? sizeof(double) * (uint64_t)(sky->P + sky->G) * p.Mp : 0;
 }
 
 // Points by antenna: whole blocks of 32 points.
@@ -120,10 +153,10 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
 // to 3e-8) and lie within 2^17 wavelengths (fixed-point phases hold 2^19 turns;
 // |n - 1| <= 2), and the matrix kernel is the faster.  Its time goes by blocks
 // of 32 points and rounds of one workgroup per CU, a workgroup being a (time,
-// channels, macro): 2.2 us each, measured at 128 antennas x 448 workgroups and
-// 256 x 1,536.  The vector kernel's goes by points and rounds of three tiles
-// per CU: 0.32 us (128 antennas, 1,780 tiles), and not below 0.18 us for a few
-// tiles.
+// channels, macro): 2.1 us each (128 antennas, one round and six; 256, six; 1.8
+// at 64 and 96, 1.3 at up to 32).  The vector kernel's goes by points and rounds
+// of three tiles per CU: 0.32 us (128 antennas, 1,780 tiles), and not below 0.18
+// us for a few tiles.
 //
 // The FP64 path: where the antennas agree with the rows to 1e-12 turns (its bar
 // is 1e-11 of the flux), and not when complex64 data would take the Gaussians
@@ -132,7 +165,15 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
 // up to 32: smaller macros), and the vector kernel 0.29 us a point and tile per
 // CU, 0.32 us at least (32 to 256 antennas, 1 to 14 times 8 to 32 channels).
 // 128 antennas, 14 times, 32 channels: 0.77 against 1.98 us a point.
-static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dtype) {
+//
+// Where the points may go by nodes instead (plan), that kernel's time decides:
+// 2.3e6 values (row, node, point) a us on the mixed path, 0.47e6 in FP64 (32,512
+// rows x 30 and 36 nodes), and not below 0.1 and 0.3 us a point.  128 antennas,
+// 4 times x 384 channels: 0.41 us a point by nodes, 0.39 by antenna.
+static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dtype, const NodePlan &plan) {
+  const bool f64 = precision == kFP64 || precision == kLut;
+  const double rows = (double)obs->T * obs->B;
+  const double node_us = plan.M == 0 ? 1e30 : sky->P * (f64 ? std::max(0.3, rows * plan.Mp / 0.47e6) : std::max(0.1, rows * plan.Mp / 2.3e6));
   if (precision == kFP64 || precision == kLut) {
     if (obs->ant_n == 0 || sky->P < kAntMinPoints || !(obs->ant_dev <= 1e-12) || !(obs->ant_reach <= 1e12)) return false;
     if (dtype == VP_C64 && sky->G > 0) return false;
@@ -140,15 +181,16 @@ static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dty
     const double blk_us = obs->ant_n <= 32 ? 2.7 : obs->ant_n <= 96 ? 4.8 : 6.2;
     const double ant_us = std::ceil(wgs / 256.0) * ((sky->P + 15) / 16) * blk_us + 10.0;
     const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
-    return ant_us < std::max(0.32, 0.29 * std::ceil(tiles / 256.0)) * sky->P;
+    return ant_us < std::min(node_us, std::max(0.32, 0.29 * std::ceil(tiles / 256.0)) * sky->P);
   }
   if (precision != kMixed && precision != kMixedBf16 && precision != kMixedBf16x2) return false;
   if (!ant_pair(sky, obs) || !(obs->ant_dev <= 1e-10) || !(obs->ant_reach <= 131072.0)) return false;
   const double wgs = (double)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac;
-  const double ant_us = std::ceil(wgs / 256.0) * ant_jp(sky) / 32.0 * 2.2 + 8.0;
+  const double blk_us = obs->ant_n <= 32 ? 1.3 : obs->ant_n <= 96 ? 1.8 : 2.1;
+  const double ant_us = std::ceil(wgs / 256.0) * ant_jp(sky) / 32.0 * blk_us + 8.0;
   const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
   const double vec_us = std::max(0.18, 0.32 * tiles / 768.0) * sky->P;
-  return ant_us < vec_us;
+  return ant_us < std::min(node_us, vec_us);
 }
 
 static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **out) {
@@ -160,9 +202,11 @@ static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **ou
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.sframe, sizeof(double) * 12 * Sc);
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.flux32, sizeof(float) * (size_t)Jc * obs->Kpad);
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.flux64, sizeof(double) * (size_t)Jc * obs->Kpad);
-  for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-    const NodePlan p = node_plan(sky, obs, i);
-    if (p.M > 0) e = d->mem.alloc((void **)&d->d.interp[i], sizeof(double) * node_doubles(obs->K, p.Mp));
+  for (int i = 0; i < kPlans && e == hipSuccess; ++i) {
+    const NodePlan p = d->d.plan[i] = node_plan(sky, obs, i);
+    if (p.M == 0) continue;
+    e = d->mem.alloc((void **)&d->d.interp[i], plan_bytes(obs, p));
+    if (e == hipSuccess && i >= 2) e = d->mem.alloc((void **)&d->d.nflux[i - 2], nflux_bytes(sky, p, i));
   }
   if (e == hipSuccess && ant_pair(sky, obs))
     e = d->mem.alloc((void **)&d->d.amp, sizeof(float) * (size_t)ant_jp(sky) * obs->Kpad);
@@ -184,10 +228,6 @@ DeriveArgs make_derive_args(const vp_sky *sky, const vp_obs *obs, const Derived 
   da.ra0 = obs->ra0; da.dec0 = obs->dec0;
   da.K = obs->K;
   da.fk = obs->fk;
-  for (int i = 0; i < 2; ++i) {
-    da.plan[i] = node_plan(sky, obs, i);
-    if (!d.interp[i]) da.plan[i].M = 0;
-  }
   da.d = d;
   return da;
 }
@@ -414,7 +454,8 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   // A sky of shapelets only skips the point/Gaussian pass, which would only
   // write zeros (predict) or rewrite the data unchanged (subtract).
   const bool ant64 = precision == kFP64 || precision == kLut;
-  const bool ant = (ant64 || d.amp) && use_ant(sky, obs, precision, dtype);
+  const bool by_nodes = d.plan[2 + ant64].M > 0 && precision != kFP32 && (nodes || ant64);
+  const bool ant = (ant64 || d.amp) && use_ant(sky, obs, precision, dtype, by_nodes ? d.plan[2 + ant64] : NodePlan{0, 0, 0.0, 0.0});
   const bool pg_pass = ant ? sky->G > 0 : sky->P + sky->G > 0 || sky->S == 0;
   a.skip_points = ant;
   a.fresh = !pg_pass && !ant && !subtract;
@@ -442,7 +483,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   if (e != hipSuccess) return hip_error(e, "launching the kernel of the points by antenna");
   if (pg_pass) {
     ProfScope ps(prof, stream, 1);
-    e = launch_pg(a, precision, stream);
+    e = by_nodes ? launch_pg_nodes(a, precision, stream) : launch_pg(a, precision, stream);
     if (kernels) ++*kernels;
   }
   if (e != hipSuccess) return hip_error(e, "launching the point/Gaussian kernel");
@@ -450,9 +491,8 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
     a.n_cb = (obs->K + kShpChan - 1) / kShpChan;
     ProfScope ps(prof, stream, 2);
     const int path = precision == kFP64 ? 1 : precision == kFP32 || precision == kLut ? -1 : 0;
-    const NodePlan plan = nodes && path >= 0 && d.interp[path] ? node_plan(sky, obs, path) : NodePlan{0, 0, 0.0, 0.0};
-    if (plan.M > 0)
-      e = launch_shp_nodes(a, plan, precision, sky->max_nmax, stream);
+    if (nodes && path >= 0 && d.plan[path].M > 0)
+      e = launch_shp_nodes(a, d.plan[path], precision, sky->max_nmax, stream);
     else
       e = launch_shp(a, precision, sky->max_nmax, stream);
     if (kernels) ++*kernels;
@@ -641,6 +681,13 @@ int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out) {
   o->h_freq.assign(desc->freq_hz, desc->freq_hz + desc->n_chan);
   o->f_lo = *std::min_element(o->h_freq.begin(), o->h_freq.end());
   o->f_hi = *std::max_element(o->h_freq.begin(), o->h_freq.end());
+  double longest[4] = {0, 0, 0, 0};  // (four chains: one would wait on itself)
+  for (int64_t r = 0; r < nrows; r += 4)
+    for (int64_t i = 0; i < 4; ++i) {
+      const double *b = desc->uvw_m + 3 * std::min(r + i, nrows - 1), l = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+      longest[i] = l > longest[i] ? l : longest[i];
+    }
+  o->b_max = std::sqrt(*std::max_element(longest, longest + 4));
   std::vector<double> fk(o->Kpad);
   for (int k = 0; k < o->Kpad; ++k) fk[k] = desc->freq_hz[std::min(k, o->K - 1)] / kLightSpeed;
   if (o->K >= 2) {
@@ -797,6 +844,29 @@ int vp_create_sky(vp_ctx *ctx, const vp_sky_desc *d, vp_sky **out) {
     ra[i] = d->p_ra[j]; dec[i] = d->p_dec[j]; sref[i] = d->p_sref[j]; alpha[i] = d->p_alpha[j];
   }
   for (int i = 0; i < G; ++i) { ra[P + i] = d->g_ra[i]; dec[P + i] = d->g_dec[i]; sref[P + i] = d->g_sref[i]; alpha[P + i] = d->g_alpha[i]; }
+  if (P + G > 0) {
+    auto turn = [](double x) {  // (one turn at most: right ascensions further out only loosen the bound)
+      return x - (x > 3.141592653589793 ? 6.283185307179586477 : x < -3.141592653589793 ? -6.283185307179586477 : 0.0);
+    };
+    double ra_lo = 0, ra_hi = 0, dec_lo = dec[0], dec_hi = dec[0], r2 = 0;
+    for (int i = 0; i < P + G; ++i) {
+      const double x = turn(ra[i] - ra[0]);
+      ra_lo = std::min(ra_lo, x);
+      ra_hi = std::max(ra_hi, x);
+      dec_lo = std::min(dec_lo, dec[i]);
+      dec_hi = std::max(dec_hi, dec[i]);
+      k->pg_amax = std::max(k->pg_amax, std::fabs(alpha[i]));
+    }
+    k->pg_ra = ra[0] + 0.5 * (ra_lo + ra_hi);
+    k->pg_dec = 0.5 * (dec_lo + dec_hi);
+    // |s - s'|^2 <= (d dec)^2 + cos(dec) cos(dec') (d ra)^2, cos(dec) <= cos(dec') + |d dec|
+    const double c = std::fabs(std::cos(k->pg_dec));
+    for (int i = 0; i < P + G; ++i) {
+      const double da = turn(ra[i] - k->pg_ra), dd = std::fabs(dec[i] - k->pg_dec);
+      r2 = std::max(r2, dd * dd + c * (c + dd) * da * da);
+    }
+    k->pg_reach = std::sqrt(r2);
+  }
   bool terms = false;
   for (int i = 0; i < S; ++i) {
     const int s = src[i];
@@ -930,10 +1000,13 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
   d.sframe = (double *)(base + o_sf);
   d.flux32 = (float *)(base + o_f32);
   d.flux64 = (double *)(base + o_f64);
-  for (int i = 0; i < 2; ++i)
-    d.interp[i] = node_plan(sky, obs, i).M > 0
-                      ? (double *)(base + kNoAllocScratchBytes + kNoAllocAmpBytes + i * (kNoAllocNodeBytes / 2))
-                      : nullptr;
+  char *part = base + kNoAllocScratchBytes + kNoAllocAmpBytes;
+  for (int i = 0; i < kPlans; ++i) {
+    d.plan[i] = node_plan(sky, obs, i);
+    if (nflux_bytes(sky, d.plan[i], i) > kNoAllocNfluxBytes / 2) d.plan[i].M = 0;
+    d.interp[i] = (double *)(part + i * (kNoAllocNodeBytes / kPlans));
+    if (i >= 2) d.nflux[i - 2] = (double *)(part + kNoAllocNodeBytes + (i - 2) * (kNoAllocNfluxBytes / 2));
+  }
   d.amp = ant_pair(sky, obs) && sizeof(float) * (uint64_t)ant_jp(sky) * Kp <= kNoAllocAmpBytes
               ? (float *)(base + kNoAllocScratchBytes)
               : nullptr;

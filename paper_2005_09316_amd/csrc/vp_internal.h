@@ -44,6 +44,21 @@ constexpr double kLutXMax = 32.0;
 constexpr int kLutStride = 100;
 constexpr size_t kLutBytes = (size_t)(kLutSamples + 2) * kLutStride * sizeof(float);
 
+// By nodes: shapelet envelopes, or the sums of points and Gaussians, are
+// evaluated at M Chebyshev nodes of the band and interpolated to the channels (M =
+// 0: evaluated at every channel).
+// Table: the nodes nu / c [kNodesStride], then the interpolation matrix as
+// operands of 16 channels x 4 nodes: [K / 16][M / 4][64], both rounded up, lane
+// l of a block holding channel 4 (l mod 4) + (l mod 16) / 4 and node l / 16 of it.
+struct NodePlan {
+  int M, Mp;                 // nodes, padded to a multiple of 4 (zero columns)
+  double mid, half;          // the band in nu / c
+};
+constexpr int kPlans = 4;
+constexpr int kNodesStride = 64;
+inline size_t node_doubles(int K, int Mp) { return kNodesStride + (size_t)((K + 15) / 16) * 16 * Mp; }
+constexpr int kNodesMaxChan = 4096;
+
 // Per-(sky, observation) tables, built on the device.
 struct Derived {
   double4 *pos;   // [J] (l, m, n-1, 0), components in order points, Gaussians, shapelets
@@ -51,7 +66,12 @@ struct Derived {
   double *sframe; // [S][12] a-vector(3), b-vector(3), (l, m, n-1)(3), pad(3)
   float *flux32;  // [J][Kpad]
   double *flux64; // [J][Kpad]
-  double *interp[2];  // shapelet nodes and interpolation of the mixed and the FP64 path (NodePlan), or null
+  // Nodes and interpolation (NodePlan; M = 0: none): [0] shapelets on the mixed
+  // and [1] on the FP64 path, [2] points and Gaussians on the mixed and [3] on
+  // the FP64 path, these with their fluxes at the nodes, [P + G][Mp].
+  NodePlan plan[kPlans];
+  double *interp[kPlans];
+  double *nflux[2];
   float *amp;     // [Kpad][Jp] sign(S) sqrt|S| x scale of the points, by antenna (null: not taken by antenna)
 };
 
@@ -67,19 +87,6 @@ struct ShpTiles {
   const int32_t *nmax;     // [S]
 };
 
-// Shapelets by nodes: the envelopes are evaluated at M Chebyshev nodes of the
-// band and interpolated to the channels (M = 0: evaluated at every channel).
-// Table: the nodes nu / c [kNodesStride], then the interpolation matrix as
-// operands of 16 channels x 4 nodes: [K / 16][M / 4][64], both rounded up, lane
-// l of a block holding channel 4 (l mod 4) + (l mod 16) / 4 and node l / 16 of it.
-struct NodePlan {
-  int M, Mp;                 // nodes, padded to a multiple of 4 (zero columns)
-  double mid, half;          // the band in nu / c
-};
-constexpr int kNodesStride = 64;
-inline size_t node_doubles(int K, int Mp) { return kNodesStride + (size_t)((K + 15) / 16) * 16 * Mp; }
-constexpr int kNodesMaxChan = 4096;
-
 struct DeriveArgs {
   int P, G, S;
   const double *ra, *dec;          // [J]
@@ -88,7 +95,6 @@ struct DeriveArgs {
   double ra0, dec0;
   int K;                           // the interpolation tables (below), for plans with M > 0
   const double *fk;                // [Kpad] nu / c
-  NodePlan plan[2];
   Derived d;
 };
 
@@ -102,7 +108,7 @@ struct FluxArgs {
   double beam_fwhm, beam_nu_ref;
   int j0;                      // first shapelet component
   const int32_t *lpow;         // [J - j0] power q of ln(nu / nu_ref) multiplying a shapelet's flux, or null
-  Derived d;
+  Derived d;                   // (its plans 2 and 3: fluxes at the nodes for the components before j0)
 };
 
 struct TileBuildArgs {
@@ -224,7 +230,10 @@ constexpr uint64_t kNoAllocScratchBytes = 64ull << 20;
 constexpr uint64_t kNoAllocAmpBytes = 48ull << 20;
 // A third part holds the interpolation tables of both paths (at most
 // kNodesMaxChan channels x kNodesStride nodes each).
-constexpr uint64_t kNoAllocNodeBytes = 2ull * (kNodesMaxChan + 16) * kNodesStride * 8;
+constexpr uint64_t kNoAllocNodeBytes = (uint64_t)kPlans * (kNodesMaxChan + 16) * kNodesStride * 8;
+// A fourth, points' and Gaussians' fluxes at the nodes, half for each path (where
+// they do not fit, those are taken channel by channel).
+constexpr uint64_t kNoAllocNfluxBytes = 16ull << 20;
 
 // Host-side launchers (vp_kernels.hip).
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s);
@@ -232,6 +241,7 @@ hipError_t launch_flux(const FluxArgs &a, hipStream_t s);
 hipError_t launch_tiles_build(const TileBuildArgs &a, int max_nmax, hipStream_t s);
 hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s);
 hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s);
+hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s);
 hipError_t launch_shp_nodes(const TileArgs &a, const NodePlan &p, int prec, int max_nmax, hipStream_t s);
 bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp);
 hipError_t launch_lut_build(float *T, hipStream_t s);

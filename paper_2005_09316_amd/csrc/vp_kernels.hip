@@ -40,9 +40,11 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
+#include "shp_nodes.h"
 #include "vp_internal.h"
 
 namespace vp {
@@ -75,6 +77,14 @@ __device__ __forceinline__ int xcd_tile(int b, int nt) {
 // [0, 1), then the FP32 transcendental unit (which takes turns).
 __device__ __forceinline__ void turns_sincos_mixed(double t, float &c, float &s) {
   const float r = (float)__builtin_amdgcn_fract(t);
+  s = __builtin_amdgcn_sinf(r);
+  c = __builtin_amdgcn_cosf(r);
+}
+
+// The same of t0 f, |t0 f| < 2^19, by one fused multiply-add onto 1.5 2^20: the
+// low word of the sum is the fraction in units of 2^-32, signed.
+__device__ __forceinline__ void turns_sincos_fixed(double t0, double f, float &c, float &s) {
+  const float r = (float)__double2loint(fma(t0, f, 1572864.0)) * 2.3283064365386963e-10f;
   s = __builtin_amdgcn_sinf(r);
   c = __builtin_amdgcn_cosf(r);
 }
@@ -153,17 +163,23 @@ __device__ __forceinline__ void derive_one(const DeriveArgs &a, int j) {
   }
 }
 
+// Node m of a plan (nu / c), and the sine of its angle.
+__device__ __forceinline__ double node_at(const NodePlan &p, int m, double &sn) {
+  double cs;
+  sincospi((2 * m + 1) / (2.0 * p.M), &sn, &cs);
+  return fma(p.half, cs, p.mid);
+}
+
 // Row k (a channel) of the interpolation matrix of plan i, one wave a row and
 // one lane a node: barycentric weights of the Chebyshev nodes, normalised; a
 // channel on a node takes that node alone.  Channels past the last and padding
 // nodes are zero.
 __device__ __forceinline__ void interp_row(const DeriveArgs &a, int i, int k) {
-  const NodePlan &p = a.plan[i];
+  const NodePlan &p = a.d.plan[i];
   const int m = threadIdx.x & 63;
   double *tab = a.d.interp[i];
-  double sn, cs;
-  sincospi((2 * m + 1) / (2.0 * p.M), &sn, &cs);
-  const double fm = fma(p.half, cs, p.mid);
+  double sn;
+  const double fm = node_at(p, m, sn);
   if (k == 0) tab[m] = m < p.M ? fm : p.mid;
   double w = 0.0;
   if (k < a.K) {
@@ -195,8 +211,8 @@ __global__ __launch_bounds__(128) void k_derive(DeriveArgs a) {
   int row = 2 * ((int)blockIdx.x - nj) + (int)(threadIdx.x >> 6);
   const int K16 = (a.K + 15) / 16 * 16;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    if (a.plan[i].M == 0) continue;
+  for (int i = 0; i < kPlans; ++i) {
+    if (a.d.plan[i].M == 0) continue;
     if (row < K16) {
       interp_row(a, i, row);
       return;
@@ -205,36 +221,52 @@ __global__ __launch_bounds__(128) void k_derive(DeriveArgs a) {
   }
 }
 
-// S_j(nu_k) = S_ref (nu_k / nu_ref)^alpha * B_j(nu_k) for flat index
-// idx = j * Kpad + k (zero in the channel padding).
-__device__ __forceinline__ void flux_one(const FluxArgs &a, int64_t idx) {
-  const int j = (int)(idx / a.Kpad), k = (int)(idx % a.Kpad);
-  double S = 0.0;
-  if (k < a.K) {
-    const double nu = a.freq[k];
-    S = a.sref[j] * pow(nu / a.nu_ref, a.alpha[j]);
-    if (a.lpow && j >= a.j0) {
-      // spectral term q of a shapelet's coefficients: ln(nu / nu_ref)^q
-      const double x = log(nu / a.nu_ref);
-      for (int q = a.lpow[j - a.j0]; q > 0; --q) S *= x;
-    }
-    if (a.beam_fwhm > 0.0) {
-      // distance from the phase centre: sin(rho) = sqrt(l^2 + m^2)
-      const double dec = a.dec[j], da = a.ra[j] - a.ra0;
-      const double l = cos(dec) * sin(da);
-      const double m = sin(dec) * cos(a.dec0) - cos(dec) * sin(a.dec0) * cos(da);
-      const double rho = asin(sqrt(l * l + m * m));
-      const double th = a.beam_fwhm * a.beam_nu_ref / nu;
-      S *= exp(-4.0 * 0.69314718055994530942 * rho * rho / (th * th));
-    }
+// S_j(nu) = S_ref (nu / nu_ref)^alpha * B_j(nu).
+__device__ __forceinline__ double flux_at(const FluxArgs &a, int j, double nu) {
+  double S = a.sref[j] * pow(nu / a.nu_ref, a.alpha[j]);
+  if (a.lpow && j >= a.j0) {
+    // spectral term q of a shapelet's coefficients: ln(nu / nu_ref)^q
+    const double x = log(nu / a.nu_ref);
+    for (int q = a.lpow[j - a.j0]; q > 0; --q) S *= x;
   }
-  a.d.flux32[idx] = (float)S;
-  a.d.flux64[idx] = S;
+  if (a.beam_fwhm > 0.0) {
+    // distance from the phase centre: sin(rho) = sqrt(l^2 + m^2)
+    const double dec = a.dec[j], da = a.ra[j] - a.ra0;
+    const double l = cos(dec) * sin(da);
+    const double m = sin(dec) * cos(a.dec0) - cos(dec) * sin(a.dec0) * cos(da);
+    const double rho = asin(sqrt(l * l + m * m));
+    const double th = a.beam_fwhm * a.beam_nu_ref / nu;
+    S *= exp(-4.0 * 0.69314718055994530942 * rho * rho / (th * th));
+  }
+  return S;
 }
 
+// The channels' table, flat index j * Kpad + k (zero in the channel padding),
+// then the nodes', j * Mp + m (zero in the node padding).
 __global__ void k_flux(FluxArgs a) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < (int64_t)a.J * a.Kpad) flux_one(a, idx);
+  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n = (int64_t)a.J * a.Kpad;
+  if (idx < n) {
+    const int j = (int)(idx / a.Kpad), k = (int)(idx % a.Kpad);
+    const double S = k < a.K ? flux_at(a, j, a.freq[k]) : 0.0;
+    a.d.flux32[idx] = (float)S;
+    a.d.flux64[idx] = S;
+    return;
+  }
+  idx -= n;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const NodePlan &p = a.d.plan[2 + i];
+    if (p.M == 0) continue;
+    const int64_t nn = (int64_t)a.j0 * p.Mp;
+    if (idx < nn) {
+      const int j = (int)(idx / p.Mp), m = (int)(idx % p.Mp);
+      double sn;
+      a.d.nflux[i][idx] = m < p.M ? flux_at(a, j, node_at(p, m, sn) * kLightSpeed) : 0.0;
+      return;
+    }
+    idx -= nn;
+  }
 }
 
 // Coefficient tiles.  Signed coefficients C''[n1][n2] = C[n1][n2] (-1)^floor((n1+n2)/2),
@@ -1749,6 +1781,172 @@ __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)
 
 // A serving job's mark on its stream (see ServeMark): the clock, then the
 // sequence number that tells the host that the clock is there.
+// ---------------------------------------------------------------------------
+// points and Gaussians by nodes
+// ---------------------------------------------------------------------------
+//
+// In a narrow field a row's sum over points and Gaussians is a smooth function
+// of frequency (see pg_nodes in shp_nodes.h): it is summed at M Chebyshev nodes
+// of the band and interpolated to the channels.  A workgroup takes LR rows; wave
+// i holds nodes kPgNB i .. kPgNB (i + 1) - 1, lane l row l % LR and every
+// (64 / LR)-th component (fewer rows where more workgroups are wanted), sums as
+// on the tile of channels (FP32 partials of kFlush components into FP64 on the
+// mixed path, Kahan sums on the FP64 path).  The sums go to LDS and each wave
+// interpolates 16 rows x 16 channels at a time on v_mfma_f64_16x16x4f64.
+//
+// What bounds it: vector instructions, 8 a value of a point (phase, sine and
+// cosine, two multiply-adds), 12 of a Gaussian.  128 antennas x 4 times, 384
+// channels by 28 nodes (0.5 degrees): 1,791 Gaussians 1.08 ms for 7.07 on
+// channels, 4,540 points 1.85 ms for 10.7 (1.75 by antenna); FP64 6.4 and 11.1 ms
+// for 19.6 and 30.6.  Six nodes a lane hold five waves a SIMD (96 registers);
+// at four, 1,016 workgroups took two rounds: 1.43 ms and 2.57.
+constexpr int kPgNB = 6;
+constexpr int kPgNodeWaves = kPgNodesMax / kPgNB;
+
+struct PgNodeLds {
+  double4 pos[kChunk], gq[kChunk];
+};
+
+template <bool F64>
+__global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_eu(F64 ? 3 : 5))) void k_pg_nodes(TileArgs a, int LR) {
+  typedef typename std::conditional<F64, double, float>::type T;
+  extern __shared__ __align__(16) unsigned char node_sm[];
+  const NodePlan &p = a.d.plan[2 + F64];
+  const double *tab = a.d.interp[2 + F64], *nf = a.d.nflux[F64];
+  const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x, nw = nt / 64, FS = kPgNB * nw;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  PgNodeLds &sm = *(PgNodeLds *)node_sm;
+  T *s_flux = (T *)(node_sm + sizeof(PgNodeLds));       // [kChunk][FS]
+  double *xr = (double *)(s_flux + kChunk * FS), *xi = xr + p.Mp * LR;  // [Mp][LR] each
+  const int64_t row0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * LR;
+  const int rr = lane % LR, sub = lane / LR, nsub = 64 / LR;
+  const int64_t row = min(row0 + rr, a.nrows - 1);
+  const double u = a.uvw[3 * row], v = a.uvw[3 * row + 1], w = a.uvw[3 * row + 2];
+  double f[kPgNB], sre[kPgNB], sim[kPgNB], cre[kPgNB], cim[kPgNB];
+  T f2[kPgNB], pre[kPgNB], pim[kPgNB];
+#pragma unroll
+  for (int k = 0; k < kPgNB; ++k) {
+    f[k] = tab[min(wave * kPgNB + k, kNodesStride - 1)];
+    f2[k] = (T)(f[k] * f[k]);
+    sre[k] = sim[k] = cre[k] = cim[k] = 0.0;
+    pre[k] = pim[k] = 0;
+  }
+  const T uu = (T)(u * u), vv = (T)(v * v), uv = (T)(u * v);
+  const int J0[2] = {a.skip_points ? a.P : 0, a.P}, JN[2] = {a.P, a.P + a.G};
+#pragma unroll
+  for (int kind = 0; kind < 2; ++kind) {  // 0: points, 1: Gaussians
+    for (int j0 = J0[kind]; j0 < JN[kind]; j0 += kChunk) {
+      const int n = min(kChunk, JN[kind] - j0);
+      __syncthreads();
+      for (int i = tid; i < n; i += nt) {
+        sm.pos[i] = a.d.pos[j0 + i];
+        if (kind == 1) sm.gq[i] = a.d.gq[j0 - a.P + i];
+      }
+      for (int i = tid; i < n * FS; i += nt) {
+        const int jj = i / FS, m = i - jj * FS;
+        s_flux[i] = m < p.Mp ? (T)nf[(int64_t)(j0 + jj) * p.Mp + m] : (T)0;
+      }
+      __syncthreads();
+      auto term = [&](int jj) {
+        const double4 q = sm.pos[jj];
+        T Q = 0;
+        if (kind == 1) {
+          const double4 g = sm.gq[jj];
+          Q = fma((T)g.x, uu, fma((T)g.y, vv, (T)g.z * uv));
+        }
+        const double t0 = fma(u, q.x, fma(v, q.y, w * q.z));
+        const T *fl = s_flux + jj * FS + wave * kPgNB;
+#pragma unroll
+        for (int k = 0; k < kPgNB; ++k) {
+          T c, s, S = fl[k];
+          if constexpr (F64) {
+            turns_sincos_f64(t0 * f[k], c, s);
+            if (kind == 1) S *= exp2(-Q * f2[k]);
+          } else {
+            turns_sincos_fixed(t0, f[k], c, s);
+            if (kind == 1) S *= __builtin_amdgcn_exp2f(-Q * f2[k]);
+          }
+          pre[k] = fma(S, c, pre[k]);
+          pim[k] = fma(S, s, pim[k]);
+        }
+      };
+      auto flush = [&]() {
+#pragma unroll
+        for (int k = 0; k < kPgNB; ++k) {
+          if constexpr (F64) {
+            kahan_add(sre[k], cre[k], pre[k]);
+            kahan_add(sim[k], cim[k], pim[k]);
+          } else {
+            sre[k] += (double)pre[k];
+            sim[k] += (double)pim[k];
+          }
+          pre[k] = pim[k] = 0;
+        }
+      };
+      int jj = sub;
+      constexpr int kUnroll = F64 ? 1 : 4;
+      for (; jj + (kFlush - 1) * nsub < n; jj += kFlush * nsub) {
+#pragma unroll kUnroll
+        for (int i = 0; i < kFlush; ++i) term(jj + i * nsub);
+        flush();
+      }
+      for (; jj < n; jj += nsub) term(jj);
+      flush();
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kPgNB; ++k) {
+    const int m = wave * kPgNB + k;
+    double re = sre[k] - cre[k], im = sim[k] - cim[k];
+    for (int o = LR; o < 64; o *= 2) {
+      re += __shfl_xor(re, o);
+      im += __shfl_xor(im, o);
+    }
+    if (sub == 0 && m < p.Mp) {
+      xr[m * LR + rr] = re;
+      xi[m * LR + rr] = im;
+    }
+  }
+  __syncthreads();
+  const int n16 = lane & 15, g = lane >> 4, ncb = (a.K + 15) / 16, steps = p.Mp / 4;
+  for (int task = wave; task < (LR / 16) * ncb; task += nw) {
+    const int rg = task / ncb, cb = task - rg * ncb, ro = rg * 16 + n16, k = cb * 16 + 4 * g;
+    const double *L = tab + kNodesStride + (size_t)cb * steps * 64 + lane;
+    double4w er = {0, 0, 0, 0}, ei = {0, 0, 0, 0};
+    for (int s = 0; s < steps; ++s) {
+      const double l = L[64 * s];
+      const int at = (4 * s + g) * LR + ro;
+      er = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xr[at], er, 0, 0, 0);
+      ei = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xi[at], ei, 0, 0, 0);
+    }
+    if (row0 + ro >= a.nrows) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (k + r >= a.K) break;
+      const int64_t idx = (row0 + ro) * a.K + k + r;
+      double re = a.subtract ? -er[r] : er[r], im = a.subtract != a.conj ? -ei[r] : ei[r];
+      const bool add = a.subtract || a.skip_points;
+      if (a.c64) {
+        float2 *o = (float2 *)a.vis + idx;
+        if (add) {
+          const float2 d = *o;
+          re += d.x;
+          im += d.y;
+        }
+        *o = make_float2((float)re, (float)im);
+      } else {
+        double2 *o = (double2 *)a.vis + idx;
+        if (add) {
+          const double2 d = *o;
+          re += d.x;
+          im += d.y;
+        }
+        *o = make_double2(re, im);
+      }
+    }
+  }
+}
+
 __global__ void k_mark(ServeMark *m, uint64_t seq) {
   __hip_atomic_store(&m->clk, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&m->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1783,7 +1981,8 @@ static hipError_t init_constants() {
 // call), one array per device for the life of the process.  In host code the
 // name is only a stand-in: its device address, which differs per device, is
 // looked up once per device below and used everywhere instead.
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocAmpBytes + kNoAllocNodeBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocAmpBytes + kNoAllocNodeBytes +
+                                                              kNoAllocNfluxBytes];
 static void *g_scratch[kMaxDevices];
 
 hipError_t device_init(int dev) {
@@ -1816,13 +2015,16 @@ static hipError_t upload_tables() {
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s) {
   const int J = a.P + a.G + a.S;
   if (J == 0) return hipSuccess;
-  const int rows = ((a.plan[0].M > 0) + (a.plan[1].M > 0)) * ((a.K + 15) / 16 * 16);
+  int rows = 0;
+  for (const NodePlan &p : a.d.plan) rows += p.M > 0 ? (a.K + 15) / 16 * 16 : 0;
   hipLaunchKernelGGL(k_derive, dim3((J + 127) / 128 + (rows + 1) / 2), dim3(128), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_flux(const FluxArgs &a, hipStream_t s) {
-  const int64_t n = (int64_t)a.J * a.Kpad;
+  int64_t n = (int64_t)a.J * a.Kpad;
+  for (int i = 0; i < 2; ++i)
+    if (a.d.plan[2 + i].M > 0) n += (int64_t)a.j0 * a.d.plan[2 + i].Mp;
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_flux, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
@@ -1912,6 +2114,39 @@ static int node_rows(int prec, int max_nmax, int S, int Mp, int64_t nrows) {
   if (base + node_lds(S, Mp, R) * sizeof(double) > all) return 0;
   while (R > 16 && (nrows + R - 1) / R < 512) R /= 2;
   return R;
+}
+
+hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
+  const bool f64 = prec == kFP64 || prec == kLut;
+  const NodePlan &p = a.d.plan[2 + f64];
+  if (p.M < 1 || p.M > kPgNodesMax || p.M > p.Mp || p.Mp > kNodesStride || p.Mp % 4 || a.K > kNodesMaxChan)
+    return hipErrorInvalidValue;
+  // Rows of a workgroup: those whose rounds of workgroups (as many as the CUs
+  // hold at the kernel's registers) end soonest, a component's staging and reads
+  // weighing the more the fewer rows share them.
+  const int nw = (p.Mp + kPgNB - 1) / kPgNB;
+  const int64_t slots = 256 * std::max(1, 4 * (f64 ? 3 : 5) / nw);
+  int LR = 64;
+  double best = 0.0;
+  for (int r = 64; r >= 16; r /= 2) {
+    const int64_t wgs = (a.nrows + r - 1) / r;
+    const double t = (double)((wgs + slots - 1) / slots) * (r + 4);
+    if (best == 0.0 || t < best) {
+      best = t;
+      LR = r;
+    }
+  }
+  const int64_t nt = (a.nrows + LR - 1) / LR;
+  if (nt > 0x7fffffff) return hipErrorInvalidValue;
+  const size_t sm = sizeof(PgNodeLds) + (size_t)kChunk * kPgNB * nw * (f64 ? 8 : 4) + (size_t)2 * p.Mp * LR * 8;
+  const void *k = f64 ? (const void *)k_pg_nodes<true> : (const void *)k_pg_nodes<false>;
+  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  if (e != hipSuccess) return e;
+  if (f64)
+    hipLaunchKernelGGL(k_pg_nodes<true>, dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR);
+  else
+    hipLaunchKernelGGL(k_pg_nodes<false>, dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR);
+  return hipGetLastError();
 }
 
 bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) { return node_rows(prec, max_nmax, S, Mp, 1 << 20) > 0; }

@@ -115,8 +115,11 @@ void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d);
 // uses, and their release (hipFree: waits for the device).
 uint64_t serve_evictable_bytes(vp_ctx *ctx);
 void serve_evict(vp_ctx *ctx);
-// The pair's plan for shapelets by nodes: i = 0 mixed, 1 FP64 (M = 0: none).
+// The pair's plans by nodes (Derived::plan; M = 0: none).
 NodePlan node_plan(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int i);
+// Bytes of a plan's tables: nodes and interpolation, and the fluxes at the nodes.
+uint64_t plan_bytes(const struct ::vp_obs *obs, const NodePlan &p);
+uint64_t nflux_bytes(const struct ::vp_sky *sky, const NodePlan &p, int i);
 // Whether the pair's points may be taken by antenna, on any path (a property of
 // the pair: its tables then hold the amplitudes, Jp x Kpad of them).
 bool ant_pair(const struct ::vp_sky *sky, const struct ::vp_obs *obs, double *scale = nullptr);
@@ -148,6 +151,7 @@ struct vp_obs {
   int uniform64 = 0;      // ... to 1e-15 of nu/c (enough for the FP64 path)
   std::vector<double> h_freq;
   double f_lo = 0, f_hi = 0;  // lowest and highest channel frequency, Hz
+  double b_max = 0;           // longest row, metres
   // antennas behind the baselines (ant_layout.h); ant_n 0: none found
   int ant_n = 0, ant_npad = 0, ant_nmac = 0, ant_max_sup = 0, ant_kpack = 1;
   double ant_dev = 0;           // their largest disagreement with a row, in turns at the highest frequency
@@ -168,6 +172,9 @@ struct vp_sky {
   std::vector<int32_t> h_nmax;
   double p_smax = 0, p_amax = 0;  // points: largest |S_ref| and largest |spectral index|
   int p_neg = 0;                  // points: 1 if an S_ref is negative
+  // points and Gaussians: a direction in their middle, a bound on their distance
+  // from it (of unit vectors), and the largest |spectral index|
+  double pg_ra = 0, pg_dec = 0, pg_reach = 0, pg_amax = 0;
   double *ra = nullptr, *dec = nullptr, *sref = nullptr, *alpha = nullptr;  // device [J]
   double *g_maj = nullptr, *g_min = nullptr, *g_pa = nullptr;               // device [G]
   double *s_beta1 = nullptr, *s_beta2 = nullptr, *s_pa = nullptr;          // device [S]

@@ -35,9 +35,9 @@ namespace vp {
 
 static uint64_t node_table_bytes(const vp_sky *sky, const vp_obs *obs) {
   uint64_t b = 0;
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < kPlans; ++i) {
     const NodePlan p = node_plan(sky, obs, i);
-    if (p.M > 0) b += sizeof(double) * node_doubles(obs->K, p.Mp);
+    b += plan_bytes(obs, p) + nflux_bytes(sky, p, i);
   }
   return b;
 }
