@@ -1708,9 +1708,7 @@ __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)
     const int c = i / ((p.Mp - p.M) * R), e = i % ((p.Mp - p.M) * R);
     xs[(size_t)c * p.Mp * R + (size_t)p.M * R + e] = 0.0;
   }
-  const int lr = R < 64 ? R : 64;                    // rows of a wave's share
-  const int per = 64 / lr, groups = R / lr;          // nodes of it, row groups
-  const int items = groups * ((p.M + per - 1) / per);
+  const int pairs = R * p.M;  // (row, node), 64 of them a wave's share
   for (int j = 0; j < a.S; ++j) {
     const int N = a.t.nmax[j];
     const int npairs = shp_pairs(N);
@@ -1722,18 +1720,18 @@ __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)
     __syncthreads();
     const double *fr = a.d.sframe + 12 * j;
     double *xr_s = xs + node_lds(j, p.Mp, R), *xi_s = xr_s + (size_t)p.Mp * R;
-    for (int it = wave; it < items; it += kNodeThreads / 64) {
-      const int rr = (it % groups) * lr + lane % lr, m = (it / groups) * per + lane / lr;
+    for (int i0 = 64 * wave; i0 < pairs; i0 += kNodeThreads) {
+      const int i = min(i0 + lane, pairs - 1), m = i / R, rr = i - m * R;
       const int64_t row = min(row0 + rr, a.nrows - 1);
-      const double f = tab[min(m, p.M - 1)];
+      const double f = tab[m];
       const double u = a.uvw[3 * row], v = a.uvw[3 * row + 1], w = a.uvw[3 * row + 2];
       const double am = fma(fr[0], u, fma(fr[1], v, fr[2] * w));
       const double bm = fma(fr[3], u, fma(fr[4], v, fr[5] * w));
       double xr, xi;
       shp_eval_bf<CM>(am * f, bm * f, N, (const __bf16 *)sA, npairs * kAbfPerPair, xr, xi);
-      if (m < p.M) {
-        xr_s[m * R + rr] = xr;
-        xi_s[m * R + rr] = xi;
+      if (i0 + lane < pairs) {
+        xr_s[i] = xr;
+        xi_s[i] = xi;
       }
     }
   }
@@ -1779,8 +1777,6 @@ __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)
   node_outputs(a, p.Mp, tab, xs, R, row0, __builtin_amdgcn_readfirstlane(tid >> 6), kNodeThreads / 64);
 }
 
-// A serving job's mark on its stream (see ServeMark): the clock, then the
-// sequence number that tells the host that the clock is there.
 // ---------------------------------------------------------------------------
 // points and Gaussians by nodes
 // ---------------------------------------------------------------------------
@@ -1947,6 +1943,8 @@ __global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_
   }
 }
 
+// A serving job's mark on its stream (see ServeMark): the clock, then the
+// sequence number that tells the host that the clock is there.
 __global__ void k_mark(ServeMark *m, uint64_t seq) {
   __hip_atomic_store(&m->clk, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&m->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2103,17 +2101,35 @@ static size_t node_base_bytes(int prec, int max_nmax) {
   return (size_t)(prec == kMixedBf16x2 ? 2 : 3) * shp_pairs(max_nmax) * kAbfPerPair * sizeof(uint16_t);
 }
 
-// Rows of a workgroup: as many as leave two workgroups on a CU (half of its
-// LDS) and, of those, few enough for two workgroups per CU to be had; 16 rows
-// (the outputs' tile) with all of the LDS where half is too little.  0: not even
-// those.
-static int node_rows(int prec, int max_nmax, int S, int Mp, int64_t nrows) {
+// Rows of a workgroup, a multiple of 16 (the outputs' tile): those with which
+// the last workgroups end soonest.  A workgroup takes as many passes of its
+// threads over the envelopes as its (row, node) pairs need (quads of nodes on
+// the FP64 path), staging and outputs beside them; two workgroups share a CU
+// (registers) where the LDS holds both, and one alone there runs some 1.5 times as
+// fast.  The costs, in cycles, are rough: they have to tell a last pass or round
+// nearly empty from a full one (113,792 rows, 9 nodes of two shapelets of order
+// 70: 112 rows, 98% of the lanes and 99% of two rounds at work, where 128 left
+// 10% and 13%).  0: LDS for not even 16.
+static int node_rows(int prec, int max_nmax, int S, int M, int Mp, int64_t nrows) {
   const size_t base = node_base_bytes(prec, max_nmax), half = 81920, all = 163840;
-  int R = 128;
-  while (R > 16 && base + node_lds(S, Mp, R) * sizeof(double) > half) R /= 2;
-  if (base + node_lds(S, Mp, R) * sizeof(double) > all) return 0;
-  while (R > 16 && (nrows + R - 1) / R < 512) R /= 2;
-  return R;
+  const bool f64 = prec == kFP64;
+  const double eval = f64 ? 12.5 * (max_nmax + 1) * (max_nmax + 2) : 2200.0 * shp_pairs(max_nmax);
+  int best_r = 0;
+  double best = 0.0;
+  for (int R = 16; R <= 128; R += 16) {
+    const size_t lds = base + node_lds(S, Mp, R) * sizeof(double);
+    if (lds > all) break;
+    const int64_t items = f64 ? (int64_t)R * (Mp / 4) : (int64_t)R * M, wgs = (nrows + R - 1) / R;
+    const double work = S * ((double)((items + kNodeThreads - 1) / kNodeThreads) * eval + 3000.0 + 75.0 * R);
+    const int64_t slots = lds <= half ? 512 : 256, rest = wgs % slots;
+    const double one = 1.0 / 1.5;
+    const double t = work * ((wgs / slots) * (slots == 512 ? 1.0 : one) + (rest == 0 ? 0.0 : rest > 256 ? 1.0 : one));
+    if (best_r == 0 || t < best) {
+      best = t;
+      best_r = R;
+    }
+  }
+  return best_r;
 }
 
 hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
@@ -2149,7 +2165,9 @@ hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
   return hipGetLastError();
 }
 
-bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) { return node_rows(prec, max_nmax, S, Mp, 1 << 20) > 0; }
+bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) {
+  return node_base_bytes(prec, max_nmax) + node_lds(S, Mp, 16) * sizeof(double) <= 163840;
+}
 
 template <typename K, typename... A>
 static hipError_t launch_node_kernel(K k, unsigned grid, size_t sm, hipStream_t s, A... args) {
@@ -2162,7 +2180,7 @@ static hipError_t launch_node_kernel(K k, unsigned grid, size_t sm, hipStream_t 
 hipError_t launch_shp_nodes(const TileArgs &a, const NodePlan &p, int prec, int max_nmax, hipStream_t s) {
   hipError_t e = upload_tables();
   if (e != hipSuccess) return e;
-  const int R = node_rows(prec, max_nmax, a.S, p.Mp, a.nrows);
+  const int R = node_rows(prec, max_nmax, a.S, p.M, p.Mp, a.nrows);
   if (R == 0 || p.M < 1 || p.M > p.Mp || p.Mp > kNodesStride || p.Mp % 4 || max_nmax < 0 || max_nmax > kNmaxLimit)
     return hipErrorInvalidValue;
   const int64_t nt = (a.nrows + R - 1) / R;
