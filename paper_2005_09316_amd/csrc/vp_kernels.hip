@@ -108,6 +108,40 @@ __device__ __forceinline__ void kahan_add(T &sum, T &cmp, T x) {
   sum = t;
 }
 
+// Four channels of one row, from k on (n of them within the row): vis = (add ?
+// vis : 0) + (re, im).  complex64 goes as two 16-byte accesses where every such
+// group is aligned (wide: even rows on a 16-byte base); as single values, lanes
+// apart by rows, each access leaves most of its sectors unused (119 -> 74 us of
+// outputs at 32,640 rows x 384 channels).
+__device__ __forceinline__ bool vis_wide(const TileArgs &a) { return a.c64 && a.K % 2 == 0 && ((uintptr_t)a.vis & 15) == 0; }
+__device__ __forceinline__ void vis_put4(const TileArgs &a, bool wide, bool add, int64_t idx, int n, const double (&re)[4],
+                                         const double (&im)[4]) {
+  if (wide && n >= 4) {
+    float4 *o = (float4 *)((float2 *)a.vis + idx);
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+    if (add) {
+      x = o[0];
+      y = o[1];
+    }
+    o[0] = make_float4((float)(re[0] + x.x), (float)(im[0] + x.y), (float)(re[1] + x.z), (float)(im[1] + x.w));
+    o[1] = make_float4((float)(re[2] + y.x), (float)(im[2] + y.y), (float)(re[3] + y.z), (float)(im[3] + y.w));
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (r >= n) break;
+    if (a.c64) {
+      float2 *o = (float2 *)a.vis + idx + r;
+      const float2 d = add ? *o : make_float2(0.f, 0.f);
+      *o = make_float2((float)(re[r] + d.x), (float)(im[r] + d.y));
+    } else {
+      double2 *o = (double2 *)a.vis + idx + r;
+      const double2 d = add ? *o : make_double2(0.0, 0.0);
+      *o = make_double2(re[r] + d.x, im[r] + d.y);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // per-(sky, observation) tables
 // ---------------------------------------------------------------------------
@@ -613,40 +647,20 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
   }
 
   if (!valid) return;
-  const int64_t base = row * a.K;
+  const bool wide = vis_wide(a), add = a.subtract || a.skip_points;
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
+  for (int k = 0; k < KB; k += 4) {
     if (k0 + k >= a.K) break;
-    const int64_t idx = base + k0 + k;
-    const double tre = PREC == kMixed ? dsum_re[k] : (double)sum_re[k] - (double)cmp_re[k];
-    const double tim = PREC == kMixed ? dsum_im[k] : (double)sum_im[k] - (double)cmp_im[k];
-    if (a.c64) {
-      float re = (float)tre, im = (float)tim;
-      if (a.conj) im = -im;
-      float2 *o = (float2 *)a.vis + idx;
-      if (a.subtract) {
-        const float2 d = *o;
-        *o = make_float2(d.x - re, d.y - im);
-      } else if (a.skip_points) {
-        const float2 d = *o;
-        *o = make_float2((float)((double)d.x + tre), (float)((double)d.y + (a.conj ? -tim : tim)));
-      } else {
-        *o = make_float2(re, im);
-      }
-    } else {
-      double re = tre, im = tim;
-      if (a.conj) im = -im;
-      double2 *o = (double2 *)a.vis + idx;
-      if (a.subtract) {
-        const double2 d = *o;
-        *o = make_double2(d.x - re, d.y - im);
-      } else if (a.skip_points) {
-        const double2 d = *o;
-        *o = make_double2(d.x + re, d.y + im);
-      } else {
-        *o = make_double2(re, im);
-      }
+    double re[4], im[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = k + r;
+      re[r] = PREC == kMixed ? dsum_re[c] : (double)sum_re[c] - (double)cmp_re[c];
+      im[r] = PREC == kMixed ? dsum_im[c] : (double)sum_im[c] - (double)cmp_im[c];
+      if (a.subtract) re[r] = -re[r];
+      if (a.subtract != a.conj) im[r] = -im[r];
     }
+    vis_put4(a, wide, add, row * a.K + k0 + k, a.K - k0 - k, re, im);
   }
 }
 
@@ -1174,8 +1188,8 @@ __device__ __forceinline__ void shp_eval_bf(double xa, double xb, int N, const _
 //     walks its own first-axis recurrence over the block and folds the rows
 //     into FP64 sums.  No row value crosses lanes.
 // The first axis is walked from order 0 in each chunk, carried from one
-// block into the next (only a chunk's last block is partial).  Sums start
-// from what the point/Gaussian pass left (from zero without one).
+// block into the next (only a chunk's last block is partial).  The sums are
+// added to what the point/Gaussian pass left (with one).
 template <int CM>
 __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, ShpSmem<CM> &sm) {
   static_assert(CM == kCmBf16x3 || CM == kCmBf16x2, "BF16-split contraction modes only");
@@ -1189,23 +1203,7 @@ __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, S
   const int K = a.K;
 
 #pragma unroll
-  for (int c = 0; c < KB; ++c) {
-    double sr = 0, si = 0;
-    if (valid && k0 + c < K && !a.fresh) {
-      const int64_t idx = row * K + k0 + c;
-      if (a.c64) {
-        const float2 x = ((const float2 *)a.vis)[idx];
-        sr = x.x;
-        si = a.conj ? -x.y : x.y;
-      } else {
-        const double2 x = ((const double2 *)a.vis)[idx];
-        sr = x.x;
-        si = a.conj ? -x.y : x.y;
-      }
-    }
-    sm.acc_re[c][tid] = sr;
-    sm.acc_im[c][tid] = si;
-  }
+  for (int c = 0; c < KB; ++c) sm.acc_re[c][tid] = sm.acc_im[c][tid] = 0.0;
 
   const double sgn = a.subtract ? -1 : 1;
   for (int j = 0; j < a.S; ++j) {
@@ -1241,16 +1239,14 @@ __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, S
     }
   }
   if (!valid) return;
+  static_assert(KB == 4, "one vis_put4");
+  double re[4], im[4];
 #pragma unroll
   for (int c = 0; c < KB; ++c) {
-    if (k0 + c >= K) break;
-    const int64_t idx = row * K + k0 + c;
-    const double re = sm.acc_re[c][tid], im = sm.acc_im[c][tid];
-    if (a.c64)
-      ((float2 *)a.vis)[idx] = make_float2((float)re, (float)(a.conj ? -im : im));
-    else
-      ((double2 *)a.vis)[idx] = make_double2(re, a.conj ? -im : im);
+    re[c] = sm.acc_re[c][tid];
+    im[c] = a.conj ? -sm.acc_im[c][tid] : sm.acc_im[c][tid];
   }
+  vis_put4(a, vis_wide(a), !a.fresh, row * K + k0, K - k0, re, im);
 }
 
 template <int CM>
@@ -1619,6 +1615,7 @@ __device__ __forceinline__ void node_outputs(const TileArgs &a, int Mp, const do
                                              int64_t row0, int wave, int nwaves) {
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int ncb = (a.K + 15) / 16, ntask = (R / 16) * ncb, steps = Mp / 4;
+  const bool wide = vis_wide(a);
   for (int task = wave; task < ntask; task += nwaves) {
     const int rg = task / ncb, cb = task - rg * ncb;
     const int rr = rg * 16 + n, k = cb * 16 + 4 * g;  // this lane's row and first of four channels
@@ -1666,28 +1663,10 @@ __device__ __forceinline__ void node_outputs(const TileArgs &a, int Mp, const do
     if (!valid) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (k + r >= a.K) break;
-      const int64_t idx = row * a.K + k + r;
-      double re = a.subtract ? -sre[r] : sre[r], im = a.subtract ? -sim[r] : sim[r];
-      if (a.conj) im = -im;
-      if (a.c64) {
-        float2 *o = (float2 *)a.vis + idx;
-        if (!a.fresh) {
-          const float2 d = *o;
-          re += d.x;
-          im += d.y;
-        }
-        *o = make_float2((float)re, (float)im);
-      } else {
-        double2 *o = (double2 *)a.vis + idx;
-        if (!a.fresh) {
-          const double2 d = *o;
-          re += d.x;
-          im += d.y;
-        }
-        *o = make_double2(re, im);
-      }
+      if (a.subtract) sre[r] = -sre[r];
+      if (a.subtract != a.conj) sim[r] = -sim[r];
     }
+    vis_put4(a, wide, !a.fresh, row * a.K + k, a.K - k, sre, sim);
   }
 }
 
@@ -1905,6 +1884,7 @@ __global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_
   }
   __syncthreads();
   const int n16 = lane & 15, g = lane >> 4, ncb = (a.K + 15) / 16, steps = p.Mp / 4;
+  const bool wide = vis_wide(a);
   for (int task = wave; task < (LR / 16) * ncb; task += nw) {
     const int rg = task / ncb, cb = task - rg * ncb, ro = rg * 16 + n16, k = cb * 16 + 4 * g;
     const double *L = tab + kNodesStride + (size_t)cb * steps * 64 + lane;
@@ -1916,30 +1896,13 @@ __global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_
       ei = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xi[at], ei, 0, 0, 0);
     }
     if (row0 + ro >= a.nrows) continue;
+    double re[4], im[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (k + r >= a.K) break;
-      const int64_t idx = (row0 + ro) * a.K + k + r;
-      double re = a.subtract ? -er[r] : er[r], im = a.subtract != a.conj ? -ei[r] : ei[r];
-      const bool add = a.subtract || a.skip_points;
-      if (a.c64) {
-        float2 *o = (float2 *)a.vis + idx;
-        if (add) {
-          const float2 d = *o;
-          re += d.x;
-          im += d.y;
-        }
-        *o = make_float2((float)re, (float)im);
-      } else {
-        double2 *o = (double2 *)a.vis + idx;
-        if (add) {
-          const double2 d = *o;
-          re += d.x;
-          im += d.y;
-        }
-        *o = make_double2(re, im);
-      }
+      re[r] = a.subtract ? -er[r] : er[r];
+      im[r] = a.subtract != a.conj ? -ei[r] : ei[r];
     }
+    vis_put4(a, wide, a.subtract || a.skip_points, (row0 + ro) * a.K + k, a.K - k, re, im);
   }
 }
 
