@@ -456,7 +456,13 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   const bool ant64 = precision == kFP64 || precision == kLut;
   const bool by_nodes = d.plan[2 + ant64].M > 0 && precision != kFP32 && (nodes || ant64);
   const bool ant = (ant64 || d.amp) && use_ant(sky, obs, precision, dtype, by_nodes ? d.plan[2 + ant64] : NodePlan{0, 0, 0.0, 0.0});
-  const bool pg_pass = ant ? sky->G > 0 : sky->P + sky->G > 0 || sky->S == 0;
+  const int path = precision == kFP64 ? 1 : precision == kFP32 || precision == kLut ? -1 : 0;
+  const bool shp_by_nodes = sky->S > 0 && nodes && path >= 0 && d.plan[path].M > 0;
+  // A handful of points goes along with the shapelets' outputs by nodes, as
+  // envelopes of 1: some 4 us each where a pass of their own over the data takes 26
+  // (113,792 rows x 32 channels).
+  a.out_points = shp_by_nodes && !ant && sky->G == 0 && sky->P <= kOutPoints ? sky->P : 0;
+  const bool pg_pass = a.out_points > 0 ? false : ant ? sky->G > 0 : sky->P + sky->G > 0 || sky->S == 0;
   a.skip_points = ant;
   a.fresh = !pg_pass && !ant && !subtract;
   hipError_t e = hipSuccess;
@@ -490,8 +496,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   if (sky->S > 0) {
     a.n_cb = (obs->K + kShpChan - 1) / kShpChan;
     ProfScope ps(prof, stream, 2);
-    const int path = precision == kFP64 ? 1 : precision == kFP32 || precision == kLut ? -1 : 0;
-    if (nodes && path >= 0 && d.plan[path].M > 0)
+    if (shp_by_nodes)
       e = launch_shp_nodes(a, d.plan[path], precision, sky->max_nmax, stream);
     else
       e = launch_shp(a, precision, sky->max_nmax, stream);

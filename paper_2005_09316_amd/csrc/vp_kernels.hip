@@ -1628,22 +1628,24 @@ __device__ __forceinline__ void node_outputs(const TileArgs &a, int Mp, const do
 #pragma unroll
     for (int r = 0; r < 4; ++r) f[r] = a.fk[min(k + r, a.Kpad - 1)];
     double sre[4] = {0, 0, 0, 0}, sim[4] = {0, 0, 0, 0};
-    for (int j = 0; j < a.S; ++j) {
-      const double *xr = xs + node_lds(j, Mp, R), *xi = xr + (size_t)Mp * R;
+    for (int j = 0; j < a.S + a.out_points; ++j) {
+      const bool pt = j >= a.S;  // a point: an envelope of 1
+      const double *xr = xs + node_lds(pt ? 0 : j, Mp, R), *xi = xr + (size_t)Mp * R;
       const double *L = tab + kNodesStride + (size_t)cb * steps * 64 + lane;
-      double4w er = {0, 0, 0, 0}, ei = {0, 0, 0, 0};
-      for (int s = 0; s < steps; ++s) {
+      const double one = pt ? 1.0 : 0.0;
+      double4w er = {one, one, one, one}, ei = {0, 0, 0, 0};
+      for (int s = 0; s < (pt ? 0 : steps); ++s) {
         const double l = L[64 * s];
         const int at = (4 * s + g) * R + rr;
         er = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xr[at], er, 0, 0, 0);
         ei = __builtin_amdgcn_mfma_f64_16x16x4f64(l, xi[at], ei, 0, 0, 0);
       }
-      const double *fr = a.d.sframe + 12 * j;
-      const double t0 = fma(fr[6], u, fma(fr[7], v, fr[8] * w));
+      const double *fr = pt ? (const double *)(a.d.pos + (j - a.S)) : a.d.sframe + 12 * j + 6;
+      const double t0 = fma(fr[0], u, fma(fr[1], v, fr[2] * w));
       double c, s, cd = 0, sd = 0;
       turns_sincos_f64(t0 * f[0], c, s);
       if (a.uniform) turns_sincos_f64(t0 * a.dfk, cd, sd);
-      const double *fl = a.d.flux64 + (int64_t)(a.P + a.G + j) * a.Kpad;
+      const double *fl = a.d.flux64 + (int64_t)(pt ? j - a.S : a.P + a.G + j) * a.Kpad;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (r > 0) {

@@ -104,3 +104,30 @@ def test_nodes_match_oracle(name, prec, dtype, bar):
             assert np.all(np.isfinite(got)) and err <= bar
     finally:
         vp.vp_destroy_ctx(ctx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_point", [1, 4, 5])
+@pytest.mark.parametrize("prec,dtype,bar", [(0, 0, 1e-11), (1, 0, 1e-6), (1, 1, 1e-6), (0, 1, 1e-6)])
+def test_points_beside_nodes(n_point, prec, dtype, bar):
+    """A few points go along with the shapelets' outputs (up to four), on
+    regular and irregular channels, added to data and on their own."""
+    import oracle
+    from paper_2005_09316_amd import vp
+    from tests.helpers import Handles, run
+    ctx = vp.vp_create_ctx(0, 0)
+    try:
+        for name in ("narrow-17", "irregular"):
+            tiles, times, orders, freqs = CASES[name]
+            obs, sky = synth.make_config(1, seed=78, n_tiles=tiles, n_time=times, n_chan=len(freqs), n_point=n_point,
+                                         n_gauss=0, shapelet_nmax=orders, freq_hz=freqs)
+            ref = oracle.predict(obs, sky)
+            data = synth.noise_c64(ref.shape, 5).astype(np.complex128)
+            with Handles(ctx, obs, sky) as h:
+                got = run(ctx, h.obs, h.sky, obs, prec, dtype)
+                res = run(ctx, h.obs, h.sky, obs, prec, dtype, data=data)
+            e1, e2 = oracle.error_metric(got, ref, obs, sky), oracle.error_metric(res, data - ref, obs, sky)
+            print(name, n_point, "prec", prec, "dtype", dtype, "error / total flux %.2e %.2e" % (e1, e2), flush=True)
+            assert e1 <= bar and e2 <= bar
+    finally:
+        vp.vp_destroy_ctx(ctx)
