@@ -91,6 +91,11 @@ static int shapelet_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
   if (sky->S == 0) return 0;
   const int M = shp_nodes(sky->max_nmax, obs->f_lo, obs->f_hi, i == 0 ? kNodesTolMixed : kNodesTolFp64);
   if (M + 0.035 * obs->K > 0.85 * obs->K) return 0;
+  // Nor where the channels' own tiles run side by side, all in a first round of
+  // two workgroups per CU (513 rows x 201 channels, order 92, FP64: 93 us, by nodes
+  // 101).
+  const int64_t n_rb = ((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows;
+  if (n_rb * (i == 0 ? obs->K : (obs->K + kShpChan - 1) / kShpChan) <= 512) return 0;
   return shp_nodes_fit(i == 0 ? kMixed : kFP64, sky->max_nmax, sky->S, (M + 3) / 4 * 4) ? M : 0;
 }
 
@@ -154,16 +159,17 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
 // |n - 1| <= 2), and the matrix kernel is the faster.  Its time goes by blocks
 // of 32 points and rounds of one workgroup per CU, a workgroup being a (time,
 // channels, macro): 2.1 us each (128 antennas, one round and six; 256, six; 1.8
-// at 64 and 96, 1.3 at up to 32).  The vector kernel's goes by points and rounds
-// of three tiles per CU: 0.32 us (128 antennas, 1,780 tiles), and not below 0.18
-// us for a few tiles.
+// at 64 and 96, 1.3 at up to 32).  The vector kernels' goes by points and tiles:
+// 0.32 us per point and 768 (128 antennas, 1,780 tiles), or 0.0005 a tile, 0.045
+// at least, where few tiles split their components.
 //
 // The FP64 path: where the antennas agree with the rows to 1e-12 turns (its bar
 // is 1e-11 of the flux), and not when complex64 data would take the Gaussians
 // in a pass of their own (a rounding more).  Per block of 16 points and round of
 // workgroups 6.2 us (measured at 128 to 256 antennas; 4.8 at 64 and 96, 2.7 at
-// up to 32: smaller macros), and the vector kernel 0.29 us a point and tile per
-// CU, 0.32 us at least (32 to 256 antennas, 1 to 14 times 8 to 32 channels).
+// up to 32: smaller macros), and the vector kernels 0.29 us a point and tile
+// per CU (32 to 256 antennas, 1 to 14 times 8 to 32 channels), or 0.0012 a tile,
+// 0.09 at least, where few tiles split their components.
 // 128 antennas, 14 times, 32 channels: 0.77 against 1.98 us a point.
 //
 // Where the points may go by nodes instead (plan), that kernel's time decides:
@@ -181,7 +187,7 @@ static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dty
     const double blk_us = obs->ant_n <= 32 ? 2.7 : obs->ant_n <= 96 ? 4.8 : 6.2;
     const double ant_us = std::ceil(wgs / 256.0) * ((sky->P + 15) / 16) * blk_us + 10.0;
     const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
-    return ant_us < std::min(node_us, std::max(0.32, 0.29 * std::ceil(tiles / 256.0)) * sky->P);
+    return ant_us < std::min(node_us, sky->P * (tiles <= kPgSplitTiles ? std::max(0.09, 0.02 + 0.0012 * tiles) : 0.29 * std::ceil(tiles / 256.0)));
   }
   if (precision != kMixed && precision != kMixedBf16 && precision != kMixedBf16x2) return false;
   if (!ant_pair(sky, obs) || !(obs->ant_dev <= 1e-10) || !(obs->ant_reach <= 131072.0)) return false;
@@ -189,7 +195,7 @@ static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dty
   const double blk_us = obs->ant_n <= 32 ? 1.3 : obs->ant_n <= 96 ? 1.8 : 2.1;
   const double ant_us = std::ceil(wgs / 256.0) * ant_jp(sky) / 32.0 * blk_us + 8.0;
   const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
-  const double vec_us = std::max(0.18, 0.32 * tiles / 768.0) * sky->P;
+  const double vec_us = sky->P * (tiles <= kPgSplitTiles ? std::max(0.045, 0.015 + 0.0005 * tiles) : 0.32 * tiles / 768.0);
   return ant_us < std::min(node_us, vec_us);
 }
 
@@ -449,6 +455,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   a.n_rb = (int)((a.nrows + kTileRows - 1) / kTileRows);
   a.n_cb = obs->Kpad / kPgChan;
   a.lut = lut;
+  a.shp_chan = kShpChan;
   a.dfk = obs->dfk;
   a.uniform = precision == kFP64 || precision == kLut ? obs->uniform64 : obs->uniform;
   // A sky of shapelets only skips the point/Gaussian pass, which would only
@@ -1012,7 +1019,9 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
     d.interp[i] = (double *)(part + i * (kNoAllocNodeBytes / kPlans));
     if (i >= 2) d.nflux[i - 2] = (double *)(part + kNoAllocNodeBytes + (i - 2) * (kNoAllocNfluxBytes / 2));
   }
-  d.amp = ant_pair(sky, obs) && sizeof(float) * (uint64_t)ant_jp(sky) * Kp <= kNoAllocAmpBytes
+  const bool f64 = precision == kFP64;
+  const bool ant = !f64 && use_ant(sky, obs, precision, dtype, precision == kFP32 ? NodePlan{0, 0, 0.0, 0.0} : d.plan[2]);
+  d.amp = ant && sizeof(float) * (uint64_t)ant_jp(sky) * Kp <= kNoAllocAmpBytes
               ? (float *)(base + kNoAllocScratchBytes)
               : nullptr;
   const hipStream_t stream = (hipStream_t)hip_stream;

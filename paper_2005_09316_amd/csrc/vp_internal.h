@@ -125,6 +125,7 @@ struct TileBuildArgs {
   const int64_t *abf_off;
 };
 
+constexpr int kPgSplitTiles = 640;  // up to this many tiles of points and Gaussians, the components are split too
 constexpr int kOutPoints = 4;  // points that may go along with the outputs of shapelets by nodes
 
 // Arguments common to the visibility tile kernels.
@@ -145,6 +146,7 @@ struct TileArgs {
   const float *lut;    // basis table of the lookup-table variant, or null
   double dfk;          // (nu_{k+1} - nu_k) / c when the channels are uniformly spaced
   int uniform;         // 1: channels uniformly spaced (the mixed path rotates phasors by dfk)
+  int shp_chan;        // channels of a workgroup of the mixed shapelet tile
   int out_points;      // points that the outputs of shapelets by nodes take along
   int fresh;           // 1: the shapelet pass starts from zero instead of reading vis (a
                        //    predict with no point/Gaussian pass before it)

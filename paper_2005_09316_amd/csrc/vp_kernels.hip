@@ -426,9 +426,13 @@ struct PgSmem {
 // with at most one rotation between a channel and an evaluated phasor.  On
 // the FP64 path channel 0 and the step are evaluated and channels 1-7 are
 // reached by successive rotations.
-template <int PREC, bool UNI = false>
+// SPLIT (observations of a few tiles): the workgroup's four waves take the same
+// 64 rows and a quarter of the components each, their sums meeting in LDS (part),
+// so that four times as many workgroups have a quarter of the work.
+template <int PREC, bool UNI = false, bool SPLIT = false>
 __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
-                                        PgSmem<typename PgTypes<PREC>::acc_t> &sm) {
+                                        PgSmem<typename PgTypes<PREC>::acc_t> &sm,
+                                        double (*part)[kPgChan][64][2] = nullptr) {
   static_assert(!UNI || ((PREC == kMixed || PREC == kFP64) && kPgChan == 8),
                 "channel rotation: mixed and FP64 paths, 8-channel tiles");
   typedef typename PgTypes<PREC>::acc_t acc_t;
@@ -437,8 +441,8 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
   double4 *s_gq = sm.gq;
   auto &s_flux = sm.flux;
   const int k0 = cb * KB;
-  const int tid = threadIdx.x;
-  const int64_t row = (int64_t)rb * kTileRows + tid;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row = SPLIT ? (int64_t)rb * 64 + (tid & 63) : (int64_t)rb * kTileRows + tid;
   const bool valid = row < a.nrows;
   const int64_t rowc = valid ? row : a.nrows - 1;
   const double u = a.uvw[3 * rowc], v = a.uvw[3 * rowc + 1], w = a.uvw[3 * rowc + 2];
@@ -625,10 +629,10 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
       };
       // groups of kGroup components, unrolled, then the remainder
       constexpr int kGroup = PREC == kMixed ? kFlushMixed : kFlush;
-      int jg = 0;
+      int jg = SPLIT ? wave * kGroup : 0;
       // FP64 terms hold twice the registers: two at a time keep two waves per SIMD
       constexpr int kUnroll = PREC == kFP64 ? 2 : kGroup;
-      for (; jg + kGroup <= n; jg += kGroup) {
+      for (; jg + kGroup <= n; jg += SPLIT ? 4 * kGroup : kGroup) {
 #pragma unroll kUnroll
         for (int jo = 0; jo < kGroup; ++jo) {
           if (kGroup > kFlush && jo == kFlush) hold_partials();
@@ -636,7 +640,7 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
         }
         flush_partials();
       }
-      if (jg < n) {
+      if (jg < n) {  // (split: the wave whose group is the incomplete one)
         for (int jj = jg; jj < n; ++jj) {
           if (kGroup > kFlush && jj - jg == kFlush) hold_partials();
           term(jj);
@@ -646,6 +650,29 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
     }
   }
 
+  double tre[KB], tim[KB];
+#pragma unroll
+  for (int c = 0; c < KB; ++c) {
+    tre[c] = PREC == kMixed ? dsum_re[c] : (double)sum_re[c] - (double)cmp_re[c];
+    tim[c] = PREC == kMixed ? dsum_im[c] : (double)sum_im[c] - (double)cmp_im[c];
+  }
+  if constexpr (SPLIT) {
+    if (wave > 0) {
+#pragma unroll
+      for (int c = 0; c < KB; ++c) {
+        part[wave - 1][c][tid & 63][0] = tre[c];
+        part[wave - 1][c][tid & 63][1] = tim[c];
+      }
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int c = 0; c < KB; ++c)
+      for (int q = 0; q < 3; ++q) {
+        tre[c] += part[q][c][tid][0];
+        tim[c] += part[q][c][tid][1];
+      }
+  }
   if (!valid) return;
   const bool wide = vis_wide(a), add = a.subtract || a.skip_points;
 #pragma unroll
@@ -655,8 +682,8 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int c = k + r;
-      re[r] = PREC == kMixed ? dsum_re[c] : (double)sum_re[c] - (double)cmp_re[c];
-      im[r] = PREC == kMixed ? dsum_im[c] : (double)sum_im[c] - (double)cmp_im[c];
+      re[r] = tre[c];
+      im[r] = tim[c];
       if (a.subtract) re[r] = -re[r];
       if (a.subtract != a.conj) im[r] = -im[r];
     }
@@ -669,6 +696,13 @@ __global__ __launch_bounds__(kTileRows) void k_pg_tile(TileArgs a) {
   __shared__ PgSmem<typename PgTypes<PREC>::acc_t> sm;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   pg_tile<PREC, UNI>(a, tile % a.n_rb, tile / a.n_rb, sm);
+}
+template <int PREC, bool UNI>
+__global__ __launch_bounds__(kTileRows) void k_pg_split(TileArgs a, int n_rb) {
+  __shared__ PgSmem<typename PgTypes<PREC>::acc_t> sm;
+  __shared__ double part[3][kPgChan][64][2];
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  pg_tile<PREC, UNI, true>(a, tile % n_rb, tile / n_rb, sm, part);
 }
 
 // ---------------------------------------------------------------------------
@@ -1166,8 +1200,8 @@ __device__ __forceinline__ void shp_eval_bf(double xa, double xb, int N, const _
   xi = (si[0] + si[1]) + (si[2] + si[3]);
 }
 
-// One tile of the mixed path's shapelet pass: kTileRows rows x kShpChan
-// channels starting at channel block cb.  Lane l of wave w owns row 64 w + l
+// One tile of the mixed path's shapelet pass: kTileRows rows x a.shp_chan (up
+// to kShpChan) channels of channel block cb.  Lane l of wave w owns row 64 w + l
 // and runs both Hermite recurrences of its visibility in FP64 (rescaled,
 // psi_next).  The MFMA's N dimension is 32 visibilities: group 0 is the lower
 // half-wave's, group 1 the upper's.  M is a 32-row block of the first axis, K
@@ -1195,7 +1229,7 @@ __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, S
   static_assert(CM == kCmBf16x3 || CM == kCmBf16x2, "BF16-split contraction modes only");
   constexpr int KB = kShpChan;
   constexpr int parts = CM == kCmBf16x3 ? 3 : 2;
-  const int k0 = cb * KB;
+  const int kc = a.shp_chan, k0 = cb * kc;
   const int tid = threadIdx.x;
   const int64_t row = (int64_t)rb * kTileRows + tid;
   const bool valid = row < a.nrows;
@@ -1225,7 +1259,7 @@ __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, S
     const int jg = a.P + a.G + j;
     const __bf16 *Ab = (const __bf16 *)&sm.A[0];
     const int part_stride = npairs * kAbfPerPair;
-    for (int c = 0; c < KB; ++c) {
+    for (int c = 0; c < kc; ++c) {
       if (k0 + c >= K) break;
       const double f = a.fk[k0 + c];
       const double S = a.d.flux64[(int64_t)jg * a.Kpad + k0 + c];
@@ -1246,7 +1280,7 @@ __device__ __forceinline__ void shp_tile_bf(const TileArgs &a, int rb, int cb, S
     re[c] = sm.acc_re[c][tid];
     im[c] = a.conj ? -sm.acc_im[c][tid] : sm.acc_im[c][tid];
   }
-  vis_put4(a, vis_wide(a), !a.fresh, row * K + k0, K - k0, re, im);
+  vis_put4(a, vis_wide(a), !a.fresh, row * K + k0, min(kc, K - k0), re, im);
 }
 
 template <int CM>
@@ -1778,32 +1812,42 @@ __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)
 // for 19.6 and 30.6.  Six nodes a lane hold five waves a SIMD (96 registers);
 // at four, 1,016 workgroups took two rounds: 1.43 ms and 2.57.
 constexpr int kPgNB = 6;
-constexpr int kPgNodeWaves = kPgNodesMax / kPgNB;
+// Waves of a workgroup, at most.
+constexpr int pg_node_waves(bool f64, bool nodes) { return nodes || f64 ? kPgNodesMax / kPgNB : 16; }
 
 struct PgNodeLds {
   double4 pos[kChunk], gq[kChunk];
 };
 
-template <bool F64>
-__global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_eu(F64 ? 3 : 5))) void k_pg_nodes(TileArgs a, int LR) {
+// NODES false: the same split over channels instead of nodes, without
+// interpolation, for observations whose tiles (256 rows x 8 channels a workgroup)
+// would leave most CUs idle: workgroup (x, y) takes LR rows and the y-th kPgNB nw
+// channels, CS groups of nw waves sharing the components.  2,524 rows x 13
+// channels, 90 Gaussians: 14.5 us for 33.5 on tiles; 496 rows x 4 channels in
+// FP64, 100 points and 10 Gaussians: 16 us for 26 (points by antenna) and 9.4.
+template <bool F64, bool NODES>
+__global__ __launch_bounds__(64 * pg_node_waves(F64, NODES)) __attribute__((amdgpu_waves_per_eu(F64 ? 3 : NODES ? 5 : 4))) void k_pg_nodes(
+    TileArgs a, int LR, int CS) {
   typedef typename std::conditional<F64, double, float>::type T;
   extern __shared__ __align__(16) unsigned char node_sm[];
   const NodePlan &p = a.d.plan[2 + F64];
   const double *tab = a.d.interp[2 + F64], *nf = a.d.nflux[F64];
-  const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x, nw = nt / 64, FS = kPgNB * nw;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
+  const int nw = NODES ? nt / 64 : nt / 64 / CS, FS = kPgNB * nw;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6), wave = NODES ? wid : wid % nw, cp = NODES ? 0 : wid / nw;
   PgNodeLds &sm = *(PgNodeLds *)node_sm;
   T *s_flux = (T *)(node_sm + sizeof(PgNodeLds));       // [kChunk][FS]
   double *xr = (double *)(s_flux + kChunk * FS), *xi = xr + p.Mp * LR;  // [Mp][LR] each
+  const int k0 = NODES ? 0 : blockIdx.y * FS;
   const int64_t row0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * LR;
-  const int rr = lane % LR, sub = lane / LR, nsub = 64 / LR;
+  const int rr = lane % LR, sub = lane / LR + 64 / LR * cp, nsub = 64 / LR * (NODES ? 1 : CS);
   const int64_t row = min(row0 + rr, a.nrows - 1);
   const double u = a.uvw[3 * row], v = a.uvw[3 * row + 1], w = a.uvw[3 * row + 2];
   double f[kPgNB], sre[kPgNB], sim[kPgNB], cre[kPgNB], cim[kPgNB];
   T f2[kPgNB], pre[kPgNB], pim[kPgNB];
 #pragma unroll
   for (int k = 0; k < kPgNB; ++k) {
-    f[k] = tab[min(wave * kPgNB + k, kNodesStride - 1)];
+    f[k] = NODES ? tab[min(wave * kPgNB + k, kNodesStride - 1)] : a.fk[min(k0 + wave * kPgNB + k, a.Kpad - 1)];
     f2[k] = (T)(f[k] * f[k]);
     sre[k] = sim[k] = cre[k] = cim[k] = 0.0;
     pre[k] = pim[k] = 0;
@@ -1821,7 +1865,12 @@ __global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_
       }
       for (int i = tid; i < n * FS; i += nt) {
         const int jj = i / FS, m = i - jj * FS;
-        s_flux[i] = m < p.Mp ? (T)nf[(int64_t)(j0 + jj) * p.Mp + m] : (T)0;
+        if (NODES)
+          s_flux[i] = m < p.Mp ? (T)nf[(int64_t)(j0 + jj) * p.Mp + m] : (T)0;
+        else if (F64)
+          s_flux[i] = k0 + m < a.K ? (T)a.d.flux64[(int64_t)(j0 + jj) * a.Kpad + k0 + m] : (T)0;
+        else
+          s_flux[i] = k0 + m < a.K ? (T)a.d.flux32[(int64_t)(j0 + jj) * a.Kpad + k0 + m] : (T)0;
       }
       __syncthreads();
       auto term = [&](int jj) {
@@ -1840,7 +1889,10 @@ __global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_
             turns_sincos_f64(t0 * f[k], c, s);
             if (kind == 1) S *= exp2(-Q * f2[k]);
           } else {
-            turns_sincos_fixed(t0, f[k], c, s);
+            if (NODES)
+              turns_sincos_fixed(t0, f[k], c, s);
+            else
+              turns_sincos_mixed(t0 * f[k], c, s);
             if (kind == 1) S *= __builtin_amdgcn_exp2f(-Q * f2[k]);
           }
           pre[k] = fma(S, c, pre[k]);
@@ -1879,10 +1931,46 @@ __global__ __launch_bounds__(64 * kPgNodeWaves) __attribute__((amdgpu_waves_per_
       re += __shfl_xor(re, o);
       im += __shfl_xor(im, o);
     }
-    if (sub == 0 && m < p.Mp) {
+    if (NODES && sub == 0 && m < p.Mp) {
       xr[m * LR + rr] = re;
       xi[m * LR + rr] = im;
     }
+    if (!NODES) {
+      sre[k] = re;
+      sim[k] = im;
+    }
+  }
+  if constexpr (!NODES) {
+    // the waves' shares of the components, [CS - 1][nw][kPgNB][LR] each
+    double *ex = (double *)(s_flux + kChunk * FS), *ey = ex + (CS - 1) * nw * kPgNB * LR;
+    if (cp > 0 && lane < LR) {
+#pragma unroll
+      for (int k = 0; k < kPgNB; ++k) {
+        const int at = (((cp - 1) * nw + wave) * kPgNB + k) * LR + rr;
+        ex[at] = sre[k];
+        ey[at] = sim[k];
+      }
+    }
+    __syncthreads();
+    const int k = k0 + wave * kPgNB;
+    if (cp > 0 || lane >= LR || row0 + rr >= a.nrows || k >= a.K) return;
+#pragma unroll
+    for (int i = 0; i < kPgNB; ++i) {
+      for (int c = 1; c < CS; ++c) {
+        const int at = (((c - 1) * nw + wave) * kPgNB + i) * LR + rr;
+        sre[i] += ex[at];
+        sim[i] += ey[at];
+      }
+      if (a.subtract) sre[i] = -sre[i];
+      if (a.subtract != a.conj) sim[i] = -sim[i];
+    }
+    static_assert(kPgNB == 6, "four channels and two");
+    const double r0[4] = {sre[0], sre[1], sre[2], sre[3]}, i0[4] = {sim[0], sim[1], sim[2], sim[3]};
+    const double r1[4] = {sre[4], sre[5], 0, 0}, i1[4] = {sim[4], sim[5], 0, 0};
+    const bool wide = vis_wide(a), add = a.subtract || a.skip_points;
+    vis_put4(a, wide, add, row * a.K + k, min(4, a.K - k), r0, i0);
+    vis_put4(a, wide, add, row * a.K + k + 4, min(2, a.K - k - 4), r1, i1);
+    return;
   }
   __syncthreads();
   const int n16 = lane & 15, g = lane >> 4, ncb = (a.K + 15) / 16, steps = p.Mp / 4;
@@ -2000,12 +2088,43 @@ hipError_t launch_tiles_build(const TileBuildArgs &a, int max_nmax, hipStream_t 
   return hipGetLastError();
 }
 
+// Whether an observation is so small that rows, channels and components are all
+// split (k_pg_nodes over channels).  1,000 Gaussians, us each, against the tiles
+// with split components: mixed, 2 tiles 0.040 for 0.068, 32 tiles 0.064 for
+// 0.069, 128 tiles 0.21 for 0.12; FP64, where the tiles rotate phasors between
+// channels, 0.13 for 0.15, then 0.26 for 0.15, and on irregular channels 0.26 for
+// 0.34 at 32 tiles.
+static bool pg_small(const TileArgs &a, int prec) {
+  const int64_t nt = (int64_t)a.n_rb * (a.Kpad / kPgChan);
+  if (prec == kFP64 || prec == kLut) return nt <= (a.uniform ? 4 : 64);
+  return prec != kFP32 && nt <= 40;
+}
+static hipError_t launch_pg_small(const TileArgs &a, bool f64, hipStream_t s);
+
 hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s) {
   hipError_t e = upload_tables();
   if (e != hipSuccess) return e;
   const int64_t nt = (int64_t)a.n_rb * a.n_cb;
   if (nt <= 0) return hipSuccess;
   if (nt > 0x7fffffff) return hipErrorInvalidValue;
+  if (pg_small(a, prec)) return launch_pg_small(a, prec == kFP64 || prec == kLut, s);
+  // Components split over a workgroup's waves, us a Gaussian: mixed 0.12 for 0.29
+  // at 128 tiles, 0.20 for 0.29 at 256, 0.36 for 0.41 at 508; FP64 0.29 for 0.55,
+  // 0.53 for 0.57, the same at 508.
+  if (nt <= kPgSplitTiles && prec != kFP32) {
+    const int n_rb = (int)((a.nrows + 63) / 64);
+    const dim3 g((unsigned)((int64_t)n_rb * a.n_cb)), b(kTileRows);
+    if (prec == kFP64 || prec == kLut) {
+      if (a.uniform)
+        hipLaunchKernelGGL((k_pg_split<kFP64, true>), g, b, 0, s, a, n_rb);
+      else
+        hipLaunchKernelGGL((k_pg_split<kFP64, false>), g, b, 0, s, a, n_rb);
+    } else if (a.uniform)
+      hipLaunchKernelGGL((k_pg_split<kMixed, true>), g, b, 0, s, a, n_rb);
+    else
+      hipLaunchKernelGGL((k_pg_split<kMixed, false>), g, b, 0, s, a, n_rb);
+    return hipGetLastError();
+  }
   switch (prec) {
     case kFP64:
     case kLut:  // the lookup-table variant differs from the FP64 path in the shapelet basis only
@@ -2048,11 +2167,20 @@ hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s) 
       break;
     case kMixed:
     case kMixedBf16:
-      hipLaunchKernelGGL(k_shp_mfma<kCmBf16x3>, g, b, 0, s, a);
+    case kMixedBf16x2: {
+      // fewer channels a workgroup where the tiles would leave CUs without one
+      // (2,524 rows x 13 channels: 40 workgroups of four channels, 48 us, 130 of
+      // one, 17 us)
+      TileArgs t = a;
+      while (t.shp_chan > 1 && (int64_t)t.n_rb * ((a.K + t.shp_chan - 1) / t.shp_chan) < 256) t.shp_chan /= 2;
+      t.n_cb = (a.K + t.shp_chan - 1) / t.shp_chan;
+      const dim3 gt((unsigned)((int64_t)t.n_rb * t.n_cb));
+      if (prec == kMixedBf16x2)
+        hipLaunchKernelGGL(k_shp_mfma<kCmBf16x2>, gt, b, 0, s, t);
+      else
+        hipLaunchKernelGGL(k_shp_mfma<kCmBf16x3>, gt, b, 0, s, t);
       break;
-    case kMixedBf16x2:
-      hipLaunchKernelGGL(k_shp_mfma<kCmBf16x2>, g, b, 0, s, a);
-      break;
+    }
     default:
       return hipErrorNotSupported;
   }
@@ -2120,13 +2248,34 @@ hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
   const int64_t nt = (a.nrows + LR - 1) / LR;
   if (nt > 0x7fffffff) return hipErrorInvalidValue;
   const size_t sm = sizeof(PgNodeLds) + (size_t)kChunk * kPgNB * nw * (f64 ? 8 : 4) + (size_t)2 * p.Mp * LR * 8;
-  const void *k = f64 ? (const void *)k_pg_nodes<true> : (const void *)k_pg_nodes<false>;
+  const void *k = f64 ? (const void *)k_pg_nodes<true, true> : (const void *)k_pg_nodes<false, true>;
   hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
   if (e != hipSuccess) return e;
   if (f64)
-    hipLaunchKernelGGL(k_pg_nodes<true>, dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR);
+    hipLaunchKernelGGL((k_pg_nodes<true, true>), dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR, 1);
   else
-    hipLaunchKernelGGL(k_pg_nodes<false>, dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR);
+    hipLaunchKernelGGL((k_pg_nodes<false, true>), dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR, 1);
+  return hipGetLastError();
+}
+
+// Points and Gaussians of a small observation, channel by channel.
+static hipError_t launch_pg_small(const TileArgs &a, bool f64, hipStream_t s) {
+  const int nw = std::min(4, (a.K + kPgNB - 1) / kPgNB), ny = (a.K + kPgNB * nw - 1) / (kPgNB * nw);
+  // fewer rows a wave, then more waves to the components, until two waves a SIMD
+  const int comps = a.G + (a.skip_points ? 0 : a.P);
+  int LR = 64, CS = 1;
+  while (LR > 16 && (a.nrows + LR - 1) / LR * ny < 512) LR /= 2;
+  const int64_t wgs = (a.nrows + LR - 1) / LR * ny;
+  while (2 * CS * nw <= pg_node_waves(f64, false) && wgs * nw * CS < 2048 && comps >= 64 / LR * CS * 4) CS *= 2;
+  const dim3 g((unsigned)((a.nrows + LR - 1) / LR), (unsigned)ny), b(64 * nw * CS);
+  const size_t sm = sizeof(PgNodeLds) + (size_t)kChunk * kPgNB * nw * (f64 ? 8 : 4) + (size_t)2 * (CS - 1) * nw * kPgNB * LR * 8;
+  const void *k = f64 ? (const void *)k_pg_nodes<true, false> : (const void *)k_pg_nodes<false, false>;
+  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  if (e != hipSuccess) return e;
+  if (f64)
+    hipLaunchKernelGGL((k_pg_nodes<true, false>), g, b, sm, s, a, LR, CS);
+  else
+    hipLaunchKernelGGL((k_pg_nodes<false, false>), g, b, sm, s, a, LR, CS);
   return hipGetLastError();
 }
 

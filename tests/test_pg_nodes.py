@@ -126,3 +126,33 @@ def test_points_and_gaussians_by_nodes_match_oracle(name, prec, dtype, bar):
     e1, e2 = oracle.error_metric(got, ref, obs, sky), oracle.error_metric(res, data - ref, obs, sky)
     print(name, "precision", prec, "dtype", dtype, "error / total flux: predict %.2e, subtract %.2e" % (e1, e2), flush=True)
     assert e1 <= bar and e2 <= bar
+
+
+# Observations of a few tiles, whose components are split over waves and lanes:
+# (tiles, times, channels, points, Gaussians); 256 rows x 8 channels are a tile,
+# and the kernels change at 4, 40 and 64 of them.
+SMALL = [(5, 1, 3, 3, 2), (24, 1, 31, 1, 0), (40, 1, 7, 63, 64), (30, 1, 100, 17, 130), (40, 2, 50, 17, 47),
+         (60, 2, 33, 0, 65), (90, 2, 41, 63, 1)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", SMALL, ids=["-".join(map(str, s)) for s in SMALL])
+@pytest.mark.parametrize("prec,dtype,bar", [(1, 0, 1e-6), (1, 1, 1e-6), (0, 0, 1e-11), (0, 1, 1e-6)])
+def test_small_observations_match_oracle(size, prec, dtype, bar):
+    import oracle
+    from paper_2005_09316_amd import vp
+    from tests.helpers import Handles, run
+    ctx = vp.vp_create_ctx(0, 0)
+    try:
+        for odd in (False, True):
+            obs, sky = _case(*size, radius=0.2, odd=odd, wrap=True, nmax=[12])
+            ref = oracle.predict(obs, sky)
+            data = synth.noise_c64(ref.shape, 5).astype(np.complex128)
+            with Handles(ctx, obs, sky) as h:
+                got = run(ctx, h.obs, h.sky, obs, prec, dtype)
+                res = run(ctx, h.obs, h.sky, obs, prec, dtype, data=data)
+            e1, e2 = oracle.error_metric(got, ref, obs, sky), oracle.error_metric(res, data - ref, obs, sky)
+            print(size, odd, "precision", prec, "dtype", dtype, "error / total flux %.2e %.2e" % (e1, e2), flush=True)
+            assert e1 <= bar and e2 <= bar
+    finally:
+        vp.vp_destroy_ctx(ctx)
