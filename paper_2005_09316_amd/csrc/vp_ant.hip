@@ -597,8 +597,10 @@ hipError_t launch_ant_refine(int T, int B, int n, int npad, const double *uvw, c
   return hipGetLastError();
 }
 
+// Sums over points of Ar Br, Ai Bi and (Ar + Ai)(Bi - Br), for conj(A) B with three
+// real products instead of four.
 struct AntTile64 {
-  double4a re, im;
+  double4a rr, ii, mx;
 };
 
 __device__ __forceinline__ double4a ant_mfma64(double a, double b, double4a c) {
@@ -648,37 +650,37 @@ struct AntOps64 {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int p = i >> 1, q = NT == 4 ? i & 1 : (i + 1) >> 1;
-      t[i].re = ant_mfma64(Ar[p], br[q], t[i].re);
-      t[i].im = ant_mfma64(Ar[p], bi[q], t[i].im);
+      t[i].rr = ant_mfma64(Ar[p], br[q], t[i].rr);
+      t[i].ii = ant_mfma64(Ai[p], bi[q], t[i].ii);
     }
+    const double sa[2] = {Ar[0] + Ai[0], Ar[1] + Ai[1]}, db[2] = {bi[0] - br[0], bi[1] - br[1]};
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int p = i >> 1, q = NT == 4 ? i & 1 : (i + 1) >> 1;
-      t[i].re = ant_mfma64(Ai[p], bi[q], t[i].re);
-      t[i].im = ant_mfma64(-Ai[p], br[q], t[i].im);
+      t[i].mx = ant_mfma64(sa[p], db[q], t[i].mx);
     }
   }
 };
 
-__device__ __forceinline__ void ant_zero64(AntTile64 &t) { t.re = t.im = double4a{0.0, 0.0, 0.0, 0.0}; }
+__device__ __forceinline__ void ant_zero64(AntTile64 &t) { t.rr = t.ii = t.mx = double4a{0.0, 0.0, 0.0, 0.0}; }
 __device__ __forceinline__ AntSum ant_sum64(const AntTile64 &t) {
   AntSum s;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    s.re[e] = t.re[e];
-    s.im[e] = t.im[e];
+    s.re[e] = t.rr[e] + t.ii[e];
+    s.im[e] = t.mx[e] + (t.rr[e] - t.ii[e]);
   }
   return s;
 }
 
-// 128 antennas, 14 times x 32 channels, 20,000 points: 15.3 ms (the vector
-// kernel: 39.6), 6.1 us per block and round of workgroups.  Four waves' MFMAs of
-// 64 cycles take 4.3 us of it where a SIMD has a triangle (24 a step) and a pair
-// (16); the rest is the factors, which the two waves of a SIMD mostly evaluate
-// at the same time, between barriers.
+// 128 antennas, 14 times x 32 channels, 20,000 points: 12.9 ms (the vector
+// kernel: 39.6; 15.3 with four real products), 5.2 us per block and round of
+// workgroups.  The MFMAs of 64 cycles take 3.2 us of it where a SIMD has a triangle
+// (18 a step) and a pair (12); the rest is the factors, which the two waves of a
+// SIMD mostly evaluate at the same time, between barriers.
 // Error against 80-bit sums, 4,000 points: 6.6e-14 of the visibilities' norm
 // (1.7e-13 before, most of it from direction cosines with cancelling terms),
-// 6.4e-16 over a 0.1 degree field (5.6e-14).
+// 6.4e-16 over a 0.1 degree field (5.6e-14), with four real products and with three.
 // ITEMS: (64 antennas) x (4 points) shares of the factors per wave and block.
 template <int ITEMS, bool NEG>
 __global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_ant_fp64(AntArgs a) {

@@ -166,11 +166,11 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
 // The FP64 path: where the antennas agree with the rows to 1e-12 turns (its bar
 // is 1e-11 of the flux), and not when complex64 data would take the Gaussians
 // in a pass of their own (a rounding more).  Per block of 16 points and round of
-// workgroups 6.2 us (measured at 128 to 256 antennas; 4.8 at 64 and 96, 2.7 at
+// workgroups 5.4 us (measured at 128 to 256 antennas; 4.1 at 64 and 96, 2.7 at
 // up to 32: smaller macros), and the vector kernels 0.29 us a point and tile
 // per CU (32 to 256 antennas, 1 to 14 times 8 to 32 channels), or 0.0012 a tile,
 // 0.09 at least, where few tiles split their components.
-// 128 antennas, 14 times, 32 channels: 0.77 against 1.98 us a point.
+// 128 antennas, 14 times, 32 channels: 0.65 against 1.98 us a point.
 //
 // Where the points may go by nodes instead (plan), that kernel's time decides:
 // 2.3e6 values (row, node, point) a us on the mixed path, 0.47e6 in FP64 (32,512
@@ -184,7 +184,7 @@ static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dty
     if (obs->ant_n == 0 || sky->P < kAntMinPoints || !(obs->ant_dev <= 1e-12) || !(obs->ant_reach <= 1e12)) return false;
     if (dtype == VP_C64 && sky->G > 0) return false;
     const double wgs = (double)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac;
-    const double blk_us = obs->ant_n <= 32 ? 2.7 : obs->ant_n <= 96 ? 4.8 : 6.2;
+    const double blk_us = obs->ant_n <= 32 ? 2.7 : obs->ant_n <= 96 ? 4.1 : 5.4;
     const double ant_us = std::ceil(wgs / 256.0) * ((sky->P + 15) / 16) * blk_us + 10.0;
     const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
     return ant_us < std::min(node_us, sky->P * (tiles <= kPgSplitTiles ? std::max(0.09, 0.02 + 0.0012 * tiles) : 0.29 * std::ceil(tiles / 256.0)));

@@ -19,18 +19,19 @@
 // own size that the iteration amplifies into a drift of the global phase.
 // The solve also stops once the residual is at the rounding level of r.
 // With X_ko = I^* V seen from tile k (a per-cell table built once), the
-// right-hand side is r_k = sum_o g_o X_ko - g_k D_k; X streams from HBM once
-// per Gauss-Newton iteration as a full n x n table, coalesced over k.  The
-// conjugate gradients take one operator application and one workgroup
-// reduction per step (Chronopoulos-Gear form).  On the FP64 path the tables
-// are FP64, D_k is summed from the FP64 W table, and the operator's W sits
-// in LDS, packed, FP64 while it fits (up to 183 tiles) and FP32 beyond: that
-// changes the step's operator at the 1e-7 level, not the right-hand side, so
-// not the fixed point.  On the mixed path the tables hold X and W rounded to
-// FP32 (sums and steps stay FP64, so the solution moves by the tables'
-// rounding, ~1e-7 relative), each thread holds its block of W in registers,
-// the operator's products are FP32 (its W is FP32 already) and each step's
-// solve stops at a relative residual of 1e-6 instead of 1e-12.
+// right-hand side is r_k = sum_o g_o X_ko - g_k D_k.  Up to kGainPairs tiles a
+// cell's tables hold one entry a pair and stay on chip (k_gain_solve_rw: X in
+// LDS, W in registers); above, X streams from memory once per Gauss-Newton
+// iteration as a full n x n table, coalesced over k (k_gain_solve_wide,
+// k_gain_solve).  The conjugate gradients take one operator application and
+// one reduction per step (Chronopoulos-Gear form).  On the FP64 path the tables
+// are FP64, D_k is summed from the FP64 W table, and so is the operator's W up
+// to 183 tiles (FP32 beyond: that changes the step's operator at the 1e-7 level,
+// not the right-hand side, so not the fixed point).  On the mixed path the tables
+// hold X and W rounded to FP32 (sums and steps stay FP64, so the solution moves
+// by the tables' rounding, ~1e-7 relative), the operator's products are FP32 (its
+// W is FP32 already) and each step's solve stops at a relative residual of 1e-6
+// instead of 1e-12.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -563,7 +564,11 @@ __device__ __forceinline__ void gain_stage(T *to, const T *from, int n) {
 // wave; all waves leave the loop together because what they compare is the same
 // bit for bit.  What bounds it: with few cells the chain of a step (direction
 // out and back through LDS, products, exchange, wave sums, two divisions), with
-// many the products' and the state's instructions.
+// many the products' and the state's instructions.  48 cells of 48 tiles, FP64:
+// 0.17 ms (1,500 cycles a step; with 1,024 threads a cell, W and the shuffled sums
+// in LDS 9,200 and 0.95 ms).  1,536 cells of 128 tiles, mixed: 0.83 ms (1.19 with X
+// from memory, 33,000 of 76,000 cycles a cell and CU); its products on
+// v_mfma_f32_4x4x1 measured 0.99.
 template <typename TT, int NW, int RPL>
 __global__ __launch_bounds__(64 * NW, sizeof(TT) == sizeof(float) ? 2 : 1) void k_gain_solve_rw(GainArgs a) {
   typedef typename TabPair<TT>::type TT2;

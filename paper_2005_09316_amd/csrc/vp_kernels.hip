@@ -3,10 +3,14 @@
 // Direct-Fourier visibility prediction (Line et al., Sec. 3): for every
 // (time, baseline, channel) visibility, sum over point, Gaussian and shapelet
 // components of flux x uv-envelope x phase term (Eqs. measure_eq_discrete,
-// env_visi_def, gauss-env, shape-env).  The work is split in two kernels per
-// call, each over tiles of 256 (time, baseline) rows x a block of channels:
+// env_visi_def, gauss-env, shape-env).  A call takes its points on the matrix
+// cores where that pays (vp_ant.hip), then points and Gaussians, then shapelets,
+// each over tiles of (time, baseline) rows x a block of channels, or at a few
+// frequencies of the band with interpolation to the channels (k_pg_nodes,
+// k_shp_nodes, below):
 //
-//   k_pg_tile   points then Gaussians.  One thread owns one row and
+//   k_pg_tile   points then Gaussians (k_pg_split: few tiles, the components
+//               shared by four waves).  One thread owns one row and
 //               kPgChan channels; component lists are staged through LDS in
 //               chunks and read as wave-uniform broadcasts.  Phase per
 //               (row, component) is t0 = u l + v m + w (n-1) in metres (FP64);
@@ -111,7 +115,7 @@ __device__ __forceinline__ void kahan_add(T &sum, T &cmp, T x) {
 // Four channels of one row, from k on (n of them within the row): vis = (add ?
 // vis : 0) + (re, im).  complex64 goes as two 16-byte accesses where every such
 // group is aligned (wide: even rows on a 16-byte base); as single values, lanes
-// apart by rows, each access leaves most of its sectors unused (119 -> 74 us of
+// apart by rows, each access leaves most of its sectors unused (119 -> 96 us of
 // outputs at 32,640 rows x 384 channels).
 __device__ __forceinline__ bool vis_wide(const TileArgs &a) { return a.c64 && a.K % 2 == 0 && ((uintptr_t)a.vis & 15) == 0; }
 __device__ __forceinline__ void vis_put4(const TileArgs &a, bool wide, bool add, int64_t idx, int n, const double (&re)[4],

@@ -113,9 +113,53 @@ def test_points_by_antenna_match_oracle(name, prec, dtype, bar):
     assert e1 <= bar and e2 <= bar
 
 
+# Sizes that both paths' rules give to the antennas (smaller ones go to kernels
+# that split rows, channels and components): blocks of 32 antennas from one to
+# eight, one more and one fewer, points around multiples of 32 and 16.
+BY_ANTENNA = {
+    "one-block": dict(n_tiles=32, n_time=14, n_chan=40, n_point=1504),
+    "one-block-ragged": dict(n_tiles=31, n_time=15, n_chan=41, n_point=1489, keep=0.97),
+    "two-blocks": dict(n_tiles=40, n_time=14, n_chan=36, n_point=1471, negative=True),
+    "three-blocks": dict(n_tiles=96, n_time=4, n_chan=32, n_point=703),
+    "three-irregular": dict(n_tiles=70, n_time=5, n_chan=33, n_point=609, odd=True),
+    "four-blocks": dict(n_tiles=128, n_time=4, n_chan=26, n_point=240, negative=True, nmax=[11]),
+    "five-blocks": dict(n_tiles=129, n_time=4, n_chan=64, n_point=321),
+    "eight-blocks": dict(n_tiles=230, n_time=1, n_chan=30, n_point=399, odd=True, negative=True),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(BY_ANTENNA))
+@pytest.mark.parametrize("prec,dtype,bar", [(1, 0, 1e-6), (1, 1, 1e-6), (0, 0, 1e-11)])
+def test_points_by_antenna_where_taken(name, prec, dtype, bar):
+    """Against the oracle, and the points have a launch of their own beside the
+    Gaussians'."""
+    import oracle
+    from paper_2005_09316_amd import vp
+    from tests.helpers import Handles, run
+    obs, sky = _case(gauss=5, **BY_ANTENNA[name])
+    ref = oracle.predict(obs, sky)
+    ctx = vp.vp_create_ctx(0, 0)
+    try:
+        with Handles(ctx, obs, sky) as h:
+            vp.vp_profile(ctx, True)
+            vp.vp_profile_read(ctx)
+            got = run(ctx, h.obs, h.sky, obs, prec, dtype)
+            counts, _ = vp.vp_profile_read(ctx)
+    finally:
+        vp.vp_destroy_ctx(ctx)
+    err = oracle.error_metric(got, ref, obs, sky)
+    print(name, "precision", prec, "dtype", dtype, "error / total flux %.2e" % err, flush=True)
+    assert counts[1] == 2, counts
+    assert err <= bar
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("kw", [dict(n_tiles=128, n_chan=4, n_time=4, n_point=3000),
-                                dict(n_tiles=40, n_chan=32, n_time=4, n_point=2000, odd=True)], ids=["128", "40-irregular"])
+                                dict(n_tiles=40, n_chan=32, n_time=4, n_point=2000, odd=True),
+                                dict(n_tiles=128, n_chan=26, n_time=4, n_point=3000),
+                                dict(n_tiles=40, n_chan=40, n_time=14, n_point=2000, odd=True)],
+                         ids=["128", "40-irregular", "128-by-antenna", "40-by-antenna-irregular"])
 def test_fp64_points_against_80_bits(kw):
     """The FP64 path on sampled rows, against numpy's extended precision.  A
     point's phase is good to the rounding of its direction (4 ulp of each of l,
