@@ -8,10 +8,11 @@ mixed-precision path; the FP64 path is timed beside it.  Shapelets count as
 their (N+1)(N+2)/2 basis functions.
 
 The JSON line carries:
-  roofline     -- the point/Gaussian tile kernel (the dominant kernel here),
-                  vector-ALU bound: algorithmic VALU issue slots per launch /
-                  its mean duration (HIP events on the launch stream) against
-                  the chip's VALU issue peak;
+  roofline     -- the points by antenna (the dominant kernel here), matrix-core
+                  bound: MFMA FLOPs issued per launch / its mean duration (HIP
+                  events on the launch stream) against the dense FP16 peak; and
+                  under "gaussians" the Gaussian tile kernel, vector-ALU bound:
+                  algorithmic VALU issue slots against the chip's issue peak;
   cpu_baseline -- the FP64 oracle on a bounded sample of rows, on the host's
                   cores, which also checks the GPU output on those rows;
   shapelet_contraction -- the shapelet kernel alone on the Fornax-like
@@ -75,16 +76,9 @@ VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # phasor of 3 channels of each 8 and the channel step, and rotates the others:
 #   per 8 channels: 4 x (phase scale 1 + reduction 1 + convert 1 + sin 1 + cos 1)
 #                   + 5 complex rotations x 4 + 8 complex MACs x 2 = 56
-#   point:    56 / 8                                                       = 7
-#   Gaussian: point + exponent scale 1 + exp2 1 + flux x envelope 1        = 10
+#   Gaussian: 56 / 8 + exponent scale 1 + exp2 1 + flux x envelope 1       = 10
 #   per (row, component): u l + v m + w (n - 1), 3 FMAs shared by the row's channels
-SLOTS_POINT, SLOTS_GAUSS, SLOTS_ROW_COMP = 7, 10, 3
-
-# HBM bytes per launch of the point/Gaussian kernel on this workload, from
-# rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a 1 GiB copy (summary in
-# profiles/k_pg_tile_mwa-like_hbm-traffic.md), valid for the kernel source
-# whose hash is recorded; reported as null once that source changes.
-PG_TRAFFIC = {"bytes": 128.0e6 + 29.1e6, "source_sha256_16": "ce22dd23a7358942"}
+SLOTS_GAUSS, SLOTS_ROW_COMP = 10, 3
 
 
 # dense MFMA peaks and the FP64 vector peak (TFLOP/s)
@@ -108,6 +102,17 @@ def _shp_mfma_flops(nmax, n_vis, mode):
                 else:
                     total += 2 * (6 if mode == "bf16x3" else 3) * 32768
     return total * n_vis / 32.0
+
+
+def _shp_nodes(nmax, f_lo, f_hi, tol):
+    """Frequencies at which the library evaluates a shapelet's envelope (the rule
+    of csrc/shp_nodes.h)."""
+    w, t = (nmax + 7.0) * 0.5 * (f_hi - f_lo) / f_lo, 2.0
+    for m in range(1, 65):
+        t *= 0.5 * w / m
+        if m >= w and t * math.exp(-0.25 * w * w / (m + 1)) <= tol:
+            return m
+    return 0
 
 
 def shapelet_contraction(reps=5):
@@ -152,19 +157,26 @@ def shapelet_contraction(reps=5):
         vp.vp_profile(ctx, False)
         ms = float(t[2] / max(c[2], 1))
         err = oracle.error_metric(out.cpu().numpy(), ref, obs, sky)
-        r = {"kernel_ms": round(ms, 4),
-             "algorithmic_tflops": round(alg_flops / ms / 1e9, 2),
-             "frac_of_fp32_mfma_peak": round(alg_flops / ms / 1e9 / MFMA_PEAK_F32, 4),
+        # by nodes, the contraction is done at M frequencies in place of K
+        M = {"mixed_bf16x3": 1e-10, "mixed_bf16x2": 1e-10, "fp64_valu": 2e-15}.get(name)
+        M = _shp_nodes(max(int(n) for n in sky.s_nmax), min(obs.freq_hz), max(obs.freq_hz), M) if M else K
+        if M == 0 or M + 0.035 * K > 0.85 * K:
+            M = K
+        done = alg_flops * M / K
+        r = {"kernel_ms": round(ms, 4), "frequencies": M,
+             "nominal_tflops": round(alg_flops / ms / 1e9, 2),
+             "algorithmic_tflops": round(done / ms / 1e9, 2),
+             "frac_of_fp32_mfma_peak": round(done / ms / 1e9 / MFMA_PEAK_F32, 4),
              "own_peak_tflops": peak,
              "max_err_vs_oracle": err,
              "gate": {"mixed_bf16x3": 1e-6, "fp64_valu": 1e-11}.get(name)}
         if mode is not None:
-            issued = _shp_mfma_flops(sky.s_nmax, obs.n_vis, mode)
+            issued = _shp_mfma_flops(sky.s_nmax, obs.n_vis * M / K, mode)
             r["issued_mfma_tflops"] = round(issued / ms / 1e9, 2)
             r["issued_frac_of_own_peak"] = round(issued / ms / 1e9 / peak, 4)
         else:
             # vector-ALU paths: FP64 contraction against the FP64 vector peak
-            r["frac_of_own_peak"] = round(alg_flops / ms / 1e9 / peak, 4)
+            r["frac_of_own_peak"] = round(done / ms / 1e9 / peak, 4)
         res["modes"][name] = r
         _log("shapelet kernel %s: %.3f ms, %.1f TFLOP/s algorithmic (%.1f%% of FP32 MFMA peak), "
              "max err %.2e" % (name, ms, r["algorithmic_tflops"], 100 * r["frac_of_fp32_mfma_peak"], err))
@@ -530,13 +542,6 @@ def large_peel(check_rows=64, full_rows=4, reps=3):
     return res
 
 
-def _pg_source_hash():
-    import hashlib
-    src = open(os.path.join(ROOT, "paper_2005_09316_amd", "csrc", "vp_kernels.hip")).read()
-    a, b = src.index("// point + Gaussian tile kernel"), src.index("// shapelet tile on MFMA")
-    return hashlib.sha256(src[a:b].encode()).hexdigest()[:16]
-
-
 def _log(*a):
     print(*a, file=sys.stderr, flush=True)
 
@@ -854,10 +859,29 @@ def main():
     vp.vp_profile(ctx, False)
     ms_step = (t1 - t0) * 1e3 / args.steps
     value = nominal / (ms_step * 1e-3)
-    pg_ms = tot_ms[1] / max(counts[1], 1)
+    pg_ms = tot_ms[1] / max(args.steps, 1)
     shp_ms = tot_ms[2] / max(counts[2], 1)
-    _log("mixed: %.3f ms/step, %.3e evals/s; pg kernel %.3f ms, shapelet kernel %.3f ms"
+    _log("mixed: %.3f ms/step, %.3e evals/s; point and Gaussian kernels %.3f ms, shapelet kernel %.3f ms"
          % (ms_step, value, pg_ms, shp_ms))
+
+    # ---- the points and the Gaussians by themselves, for the rooflines ----
+    kind_ms = {}
+    for kind, part in (("points", synth.select_components(sky, gauss=[], shapelets=[])),
+                       ("gaussians", synth.select_components(sky, points=[], shapelets=[]))):
+        ph = vp.vp_create_sky(ctx, part)
+        for rep in range(4):
+            if rep == 1:
+                torch.cuda.synchronize()
+                vp.vp_profile(ctx, True)
+                vp.vp_profile_read(ctx)
+            vp.vp_predict(ctx, ph, oh, vp.VP_PREC_MIXED, vp.VP_C64, out.data_ptr(), stream.cuda_stream)
+        torch.cuda.synchronize()
+        c, t = vp.vp_profile_read(ctx)
+        vp.vp_profile(ctx, False)
+        kind_ms[kind] = t[1] / max(c[1], 1)
+        vp.vp_destroy_sky(ph)
+    step(vp.VP_PREC_MIXED, out, vp.VP_C64)  # the whole sky again, for the check below
+    torch.cuda.synchronize()
 
     # ---- FP64 path, for the speedup ----
     out64 = torch.empty((obs.n_time, obs.n_bl, obs.n_chan), dtype=torch.complex128, device="cuda")
@@ -873,18 +897,23 @@ def main():
         value64 = nominal / (ms64 * 1e-3)
         _log("fp64: %.3f ms/step, %.3e evals/s" % (ms64, value64))
 
-    # ---- roofline of the point/Gaussian kernel ----
-    pg_evals_pt = nrows * K * sky.n_point
-    pg_evals_g = nrows * K * sky.n_gauss
-    slots = (pg_evals_pt * SLOTS_POINT + pg_evals_g * SLOTS_GAUSS
-             + nrows * (sky.n_point + sky.n_gauss) * SLOTS_ROW_COMP)
-    achieved = slots / (pg_ms * 1e-3) / 1e12
-    roofline = {"bound": "alu", "kernel": "k_pg_tile<mixed, uniform channels>", "achieved": round(achieved, 3),
-                "peak": round(VALU_PEAK_TOPS, 3), "unit": "Tops/s (VALU issue slots)",
-                "frac": round(achieved / VALU_PEAK_TOPS, 4),
-                "traffic": PG_TRAFFIC["bytes"] if _pg_source_hash() == PG_TRAFFIC["source_sha256_16"] else None,
-                "traffic_unit": "bytes per launch (HBM read + write)",
-                "kernel_ms": round(pg_ms, 4), "shapelet_kernel_ms": round(shp_ms, 4)}
+    # ---- rooflines of the point and Gaussian kernels ----
+    # Per 32 points, time, channel and tile of 16 x 16 antenna pairs: 12 matrix
+    # instructions of 16 x 16 x 32 (three products of FP16 pairs for each of four
+    # real products of the complex one), tiles below the diagonal left out.
+    blocks = (int(round((1 + math.sqrt(1 + 8 * obs.n_bl)) / 2)) + 31) // 32 * 2
+    flops = (obs.n_time * K * ((sky.n_point + 31) // 32) * (blocks * (blocks + 1) // 2)) * 12 * 2.0 * 16 * 16 * 32
+    tf = flops / (kind_ms["points"] * 1e-3) / 1e12
+    slots = nrows * K * sky.n_gauss * SLOTS_GAUSS + nrows * sky.n_gauss * SLOTS_ROW_COMP
+    achieved = slots / (kind_ms["gaussians"] * 1e-3) / 1e12
+    roofline = {"bound": "mfma", "kernel": "k_ant_mixed", "achieved": round(tf, 2), "peak": MFMA_PEAK_BF16,
+                "unit": "TFLOP/s (FP16 MFMA issued)", "frac": round(tf / MFMA_PEAK_BF16, 4),
+                "kernel_ms": round(kind_ms["points"], 4),
+                "gaussians": {"bound": "alu", "kernel": "k_pg_tile<mixed, uniform channels>",
+                              "achieved": round(achieved, 3), "peak": round(VALU_PEAK_TOPS, 3),
+                              "unit": "Tops/s (VALU issue slots)", "frac": round(achieved / VALU_PEAK_TOPS, 4),
+                              "kernel_ms": round(kind_ms["gaussians"], 4)},
+                "point_and_gaussian_ms": round(pg_ms, 4), "shapelet_kernel_ms": round(shp_ms, 4)}
 
     # ---- sampled parity + CPU baseline (oracle) ----
     cpu = None

@@ -185,7 +185,8 @@ int vp_predict(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision,
  * the same output), but the per-(sky, observation) tables (direction
  * cosines, Gaussian quadratic forms, shapelet frames, flux per component and
  * channel) are rebuilt on every call into a fixed scratch array of
- * 64 MiB that the library holds on each device until the process ends,
+ * 64 MiB that the library holds on each device until the process ends (beside
+ * it 105 MiB for what those of its kernels need that work by antenna and by nodes),
  * instead of being allocated and cached.  Limit: 32 B per component, 32 B
  * per Gaussian, 96 B per shapelet and 12 B per (component, channel padded to
  * a multiple of 8), each part rounded up to 256 B, at most 64 MiB in all

@@ -236,9 +236,11 @@ constexpr uint64_t kNoAllocAmpBytes = 48ull << 20;
 // A third part holds the interpolation tables of both paths (at most
 // kNodesMaxChan channels x kNodesStride nodes each).
 constexpr uint64_t kNoAllocNodeBytes = (uint64_t)kPlans * (kNodesMaxChan + 16) * kNodesStride * 8;
-// A fourth, points' and Gaussians' fluxes at the nodes, half for each path (where
-// they do not fit, those are taken channel by channel).
-constexpr uint64_t kNoAllocNfluxBytes = 16ull << 20;
+// A fourth, points' and Gaussians' fluxes at the nodes, half for each path: room
+// for every pair that the tables hold (12 bytes per component and padded channel
+// in 64 MiB, 8 per component and node, at most half as many nodes as padded
+// channels), so that the calls take the same kernels as vp_predict.
+constexpr uint64_t kNoAllocNfluxBytes = 48ull << 20;
 
 // Host-side launchers (vp_kernels.hip).
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s);
