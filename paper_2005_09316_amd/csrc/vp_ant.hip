@@ -139,12 +139,13 @@ template <bool F64 = false>
 __device__ __forceinline__ void ant_store(const AntArgs &a, const AntSum &s, int p0, int q0, int64_t t, int k) {
   const int lane = threadIdx.x & 63;
   const int q = q0 + (lane & 15);
+  const double un = F64 ? 1.0 : a.unscale[k];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int p = p0 + (F64 ? 4 * i + (lane >> 4) : 4 * (lane >> 4) + i);
     const int m = a.rowmap[(int64_t)p * a.npad + q];
     if (m == 0) continue;
-    const double re = s.re[i] * a.unscale, im0 = s.im[i] * a.unscale;
+    const double re = s.re[i] * un, im0 = s.im[i] * un;
     const double im = (m < 0) != (a.conj != 0) ? -im0 : im0;
     const int64_t idx = (t * a.B + (m < 0 ? -m : m) - 1) * a.K + k;
     if (a.c64) {
@@ -825,20 +826,49 @@ __global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// The points' largest |S| in each channel, beam and spectrum in it (as the bits
+// of a non-negative double; k_flux cleared it).  Workgroup (x, y): 8 channels,
+// runs of kPeakRows points; memory bound.
+constexpr int kPeakRows = 1024;
+__global__ __launch_bounds__(256) void k_ant_peak(AntAmpArgs a) {
+  const int k = blockIdx.x * 8 + (threadIdx.x & 7);
+  double m = 0.0;
+  for (int64_t j0 = (int64_t)blockIdx.y * kPeakRows; j0 < a.J; j0 += (int64_t)gridDim.y * kPeakRows) {
+    const int64_t j1 = min(j0 + kPeakRows, (int64_t)a.J);
+#pragma unroll 4
+    for (int64_t j = j0 + (threadIdx.x >> 3); j < j1; j += 32) m = fmax(m, fabs(a.d.flux64[j * a.Kpad + k]));
+  }
+#pragma unroll
+  for (int o = 8; o < 64; o *= 2) m = fmax(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) < 8)
+    atomicMax((unsigned long long *)(a.d.amp_peak + k), (unsigned long long)__double_as_longlong(m));
+}
+
 // Amplitudes of the factors: sign(S) sqrt|S| x scale per (channel, point),
-// zero past the last point (blocks of 32 points are taken whole).
+// zero past the last point (blocks of 32 points are taken whole).  The factors
+// are FP16 pairs (2^-24 .. 2^16): a channel's scale is the power of two that
+// brings the largest of its amplitudes to 2^11 .. 2^12, whatever beam and
+// spectrum have left of it.
 __global__ __launch_bounds__(256) void k_ant_amp(AntAmpArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= (int64_t)a.Jp * a.Kpad) return;
   const int j = (int)(i / a.Kpad), k = (int)(i % a.Kpad);
+  const double peak = a.d.amp_peak[k];
+  int e = 12;
+  if (peak > 0.0) (void)frexp(sqrt(peak), &e);
   double s = 0.0;
-  if (j < a.J) s = a.flux64[(int64_t)j * a.Kpad + k];
-  a.amp[(int64_t)k * a.Jp + j] = (float)copysign(sqrt(fabs(s)) * a.scale, s);
+  if (j < a.J) s = a.d.flux64[(int64_t)j * a.Kpad + k];
+  a.d.amp[(int64_t)k * a.Jp + j] = (float)copysign(ldexp(sqrt(fabs(s)), 12 - e), s);
+  if (j == 0) a.d.amp_unscale[k] = ldexp(1.0, 2 * (e - 12));
 }
 
 hipError_t launch_ant_amp(const AntAmpArgs &a, hipStream_t s) {
   const int64_t n = (int64_t)a.Jp * a.Kpad;
   if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_ant_peak, dim3((unsigned)(a.Kpad / 8), (unsigned)min(1024, (a.J - 1) / kPeakRows + 1)), dim3(256), 0, s,
+                     a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_ant_amp, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }

@@ -137,20 +137,25 @@ uint64_t nflux_bytes(const vp_sky *sky, const NodePlan &p, int i) {
 
 // Points by antenna: whole blocks of 32 points.
 int ant_jp(const vp_sky *sky) { return (sky->P + 31) / 32 * 32; }
+uint64_t ant_amp_bytes(const vp_sky *sky, const vp_obs *obs) {
+  return (sizeof(float) * (uint64_t)ant_jp(sky) + 2 * sizeof(double)) * obs->Kpad;
+}
+static void place_amp(Derived &d, char *at, const vp_sky *sky, const vp_obs *obs) {
+  d.amp = (float *)at;
+  d.amp_peak = (double *)(d.amp + (size_t)ant_jp(sky) * obs->Kpad);
+  d.amp_unscale = d.amp_peak + obs->Kpad;
+}
 
-bool ant_pair(const vp_sky *sky, const vp_obs *obs, double *scale) {
+bool ant_pair(const vp_sky *sky, const vp_obs *obs) {
   if (obs->ant_n == 0 || sky->P < kAntMinPoints) return false;
-  // The factors are FP16 pairs (2^-24 .. 2^16): sqrt|S| is scaled so that the
-  // largest stays below 2^13.  The bound on the largest flux takes the largest
-  // S_ref and the largest spectral index together (the beam is at most 1);
-  // where that leaves the true one further than 2^20 behind, the headroom is
-  // gone and the vector path takes the points.
+  // Every channel's amplitudes are scaled by their own largest (k_ant_amp), so
+  // that beam and spectrum may take any share of the fluxes; these have to be
+  // finite (as a product of the largest S_ref and the largest growth), and not so
+  // steep that the points' order by S_ref, bright to faint, says nothing about
+  // the order in the band.
   const double x = std::max(std::fabs(std::log(obs->f_lo / sky->nu_ref)), std::fabs(std::log(obs->f_hi / sky->nu_ref)));
   const double grow = std::exp(sky->p_amax * x);
-  const double top = sky->p_smax * grow;
-  if (!(sky->p_smax >= 1e-30) || !(top <= 1e30) || !(grow <= 1048576.0)) return false;
-  if (scale) *scale = std::ldexp(1.0, 13 - (int)std::ceil(std::log2(std::sqrt(top))) - 1);
-  return true;
+  return sky->p_smax >= 1e-30 && sky->p_smax * grow <= 1e30 && grow <= 1048576.0;
 }
 
 // Whether a call takes the points by antenna: the mixed paths, where the
@@ -214,8 +219,11 @@ static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **ou
     e = d->mem.alloc((void **)&d->d.interp[i], plan_bytes(obs, p));
     if (e == hipSuccess && i >= 2) e = d->mem.alloc((void **)&d->d.nflux[i - 2], nflux_bytes(sky, p, i));
   }
-  if (e == hipSuccess && ant_pair(sky, obs))
-    e = d->mem.alloc((void **)&d->d.amp, sizeof(float) * (size_t)ant_jp(sky) * obs->Kpad);
+  if (e == hipSuccess && ant_pair(sky, obs)) {
+    char *amp = nullptr;
+    e = d->mem.alloc((void **)&amp, ant_amp_bytes(sky, obs));
+    if (e == hipSuccess) place_amp(d->d, amp, sky, obs);
+  }
   if (e != hipSuccess) {
     d->mem.release();
     delete d;
@@ -251,11 +259,10 @@ FluxArgs make_flux_args(const vp_sky *sky, const vp_obs *obs, const Derived &d) 
 }
 
 static hipError_t build_amp(const vp_sky *sky, const vp_obs *obs, const Derived &d, hipStream_t stream) {
+  if (!d.amp) return hipSuccess;
   AntAmpArgs a;
-  if (!d.amp || !ant_pair(sky, obs, &a.scale)) return hipSuccess;
   a.J = sky->P; a.Jp = ant_jp(sky); a.Kpad = obs->Kpad;
-  a.flux64 = d.flux64;
-  a.amp = d.amp;
+  a.d = d;
   return launch_ant_amp(a, stream);
 }
 
@@ -475,8 +482,6 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   hipError_t e = hipSuccess;
   if (ant) {
     AntArgs p;
-    double scale = 1.0;
-    if (!ant64) ant_pair(sky, obs, &scale);
     p.T = obs->T; p.B = obs->B; p.K = obs->K;
     p.npad = obs->ant_npad;
     p.J = sky->P; p.Jp = ant_jp(sky);
@@ -485,7 +490,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
     p.mac = obs->ant_mac; p.xyz = obs->ant_xyz; p.xyz_lo = obs->ant_lo; p.rowmap = obs->ant_rowmap;
     p.fk = obs->fk; p.pos = d.pos; p.amp = d.amp;
     p.flux64 = d.flux64; p.Kpad = obs->Kpad;
-    p.unscale = 1.0 / (scale * scale);
+    p.unscale = d.amp_unscale;
     p.neg = sky->p_neg;
     p.fine = !obs->uniform;
     p.vis = vis; p.c64 = a.c64; p.conj = a.conj; p.subtract = subtract;
@@ -1006,7 +1011,7 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
   if (!g.ok) return set_error(VP_EDEVICE, "cannot select device %d", ctx->device);
   char *base = (char *)noalloc_scratch(ctx->device);
   if (!base) return set_error(VP_EDEVICE, "no scratch address for device %d", ctx->device);
-  Derived d;
+  Derived d{};
   d.pos = (double4 *)base;
   d.gq = (double4 *)(base + o_gq);
   d.sframe = (double *)(base + o_sf);
@@ -1021,9 +1026,7 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
   }
   const bool f64 = precision == kFP64;
   const bool ant = !f64 && use_ant(sky, obs, precision, dtype, precision == kFP32 ? NodePlan{0, 0, 0.0, 0.0} : d.plan[2]);
-  d.amp = ant && sizeof(float) * (uint64_t)ant_jp(sky) * Kp <= kNoAllocAmpBytes
-              ? (float *)(base + kNoAllocScratchBytes)
-              : nullptr;
+  if (ant && ant_amp_bytes(sky, obs) <= kNoAllocAmpBytes) place_amp(d, base + kNoAllocScratchBytes, sky, obs);
   const hipStream_t stream = (hipStream_t)hip_stream;
   // every entry the tile kernels read is written here first (the flux table
   // includes its zero padding), so nothing is cleared

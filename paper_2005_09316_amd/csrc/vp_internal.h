@@ -72,7 +72,10 @@ struct Derived {
   NodePlan plan[kPlans];
   double *interp[kPlans];
   double *nflux[2];
-  float *amp;     // [Kpad][Jp] sign(S) sqrt|S| x scale of the points, by antenna (null: not taken by antenna)
+  // Points by antenna (null: not taken by antenna): sign(S) sqrt|S| x the
+  // channel's scale [Kpad][Jp], then the largest |S| and 1 / scale^2 [Kpad] each.
+  float *amp;
+  double *amp_peak, *amp_unscale;
 };
 
 // Shapelet coefficient tiles (depend on the sky only).
@@ -171,7 +174,7 @@ struct AntArgs {
   const float *amp;       // [Kpad][Jp] (mixed path)
   const double *flux64;   // [J][Kpad] (FP64 path)
   int Kpad;
-  double unscale;         // 1 / (the amplitudes' scale)^2
+  const double *unscale;  // [Kpad] 1 / (the amplitudes' scale)^2 (mixed path)
   int neg;                // 1: some fluxes are negative
   int fine;               // 1: the more exact factors (irregular channels)
   void *vis;              // [T][B][K]
@@ -179,9 +182,7 @@ struct AntArgs {
 };
 struct AntAmpArgs {
   int J, Jp, Kpad;
-  const double *flux64;   // [J][Kpad]
-  double scale;
-  float *amp;             // [Kpad][Jp]
+  Derived d;
 };
 
 // A serving job's mark: its sequence number, and the device wall clock when it

@@ -286,6 +286,7 @@ __global__ void k_flux(FluxArgs a) {
   const int64_t n = (int64_t)a.J * a.Kpad;
   if (idx < n) {
     const int j = (int)(idx / a.Kpad), k = (int)(idx % a.Kpad);
+    if (j == 0 && a.d.amp) a.d.amp_peak[k] = 0.0;  // k_ant_peak, next on the stream, takes the maximum
     const double S = k < a.K ? flux_at(a, j, a.freq[k]) : 0.0;
     a.d.flux32[idx] = (float)S;
     a.d.flux64[idx] = S;

@@ -121,9 +121,11 @@ NodePlan node_plan(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int i
 uint64_t plan_bytes(const struct ::vp_obs *obs, const NodePlan &p);
 uint64_t nflux_bytes(const struct ::vp_sky *sky, const NodePlan &p, int i);
 // Whether the pair's points may be taken by antenna, on any path (a property of
-// the pair: its tables then hold the amplitudes, Jp x Kpad of them).
-bool ant_pair(const struct ::vp_sky *sky, const struct ::vp_obs *obs, double *scale = nullptr);
+// the pair: its tables then hold the amplitudes, Jp x Kpad of them, and two
+// doubles a channel beside them).
+bool ant_pair(const struct ::vp_sky *sky, const struct ::vp_obs *obs);
 int ant_jp(const struct ::vp_sky *sky);
+uint64_t ant_amp_bytes(const struct ::vp_sky *sky, const struct ::vp_obs *obs);
 DeriveArgs make_derive_args(const struct ::vp_sky *sky, const struct ::vp_obs *obs, const Derived &d);
 FluxArgs make_flux_args(const struct ::vp_sky *sky, const struct ::vp_obs *obs, const Derived &d);
 void drop_derived(vp_ctx *ctx, uint64_t sky_id, uint64_t obs_id);

@@ -47,7 +47,7 @@ uint64_t job_footprint(const vp_sky *sky, const vp_obs *obs, int dtype) {
   const uint64_t J = (uint64_t)sky->P + sky->G + sky->S;
   const uint64_t tables = 32 * (J ? J : 1) + 32 * (sky->G ? sky->G : 1) + 96 * (sky->S ? sky->S : 1) +
                           12 * (J ? J : 1) * (uint64_t)obs->Kpad +
-                          node_table_bytes(sky, obs) + (ant_pair(sky, obs) ? 4 * (uint64_t)ant_jp(sky) * obs->Kpad : 0);
+                          node_table_bytes(sky, obs) + (ant_pair(sky, obs) ? ant_amp_bytes(sky, obs) : 0);
   return nvis * (dtype == VP_C64 ? 8 : 16) + tables;
 }
 
