@@ -108,10 +108,18 @@ static int pg_sum_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
   // |s - s'|^2 = 4 sin^2(d dec / 2) + 4 cos(dec) cos(dec') sin^2(d ra / 2)
   const double sd = std::sin(0.5 * (sky->pg_dec - obs->dec0)), sa = std::sin(0.5 * (sky->pg_ra - obs->ra0));
   const double to_mid = 2.0 * std::sqrt(sd * sd + std::fabs(std::cos(sky->pg_dec) * std::cos(obs->dec0)) * sa * sa);
-  const double reach = obs->b_max * std::min(2.0, to_mid + sky->pg_reach) * (1.0 + 1e-9);
+  const double apart = std::min(2.0, to_mid + sky->pg_reach);  // of unit vectors
+  const double reach = obs->b_max * apart * (1.0 + 1e-9);
   if (!(reach * obs->f_hi / kLightSpeed <= 262144.0)) return 0;  // the mixed kernel's phases are fixed-point, up to 2^19 turns
-  const double w = 6.283185307179586477 * reach * half;
-  const int M = pg_nodes(w, half / mid, sky->pg_amax, i == 2 ? kNodesTolMixed : kNodesTolFp64);
+  const double w = 6.283185307179586477 * reach * half, delta = half / mid;
+  double beam = 0.0;  // exponent of the beam, furthest component, middle of the band (see flux_at)
+  if (obs->beam_fwhm > 0.0) {
+    const double rho = std::min(1.57079632679489662, 2.0 * std::asin(0.5 * apart) * (1.0 + 1e-9));
+    const double x = rho * mid * kLightSpeed / (obs->beam_fwhm * obs->beam_nu_ref);
+    beam = 4.0 * 0.69314718055994530942 * x * x;
+  }
+  if (!(pg_spread(delta, sky->pg_amax, beam) <= (i == 2 ? kPgSpreadMixed : kPgSpreadFp64))) return 0;
+  const int M = pg_nodes(w, delta, sky->pg_amax, i == 2 ? kNodesTolMixed : kNodesTolFp64, beam);
   return 3 * M <= obs->K ? M : 0;
 }
 
