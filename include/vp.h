@@ -175,7 +175,11 @@ int vp_destroy_sky(vp_sky *sky); /* VP_EBUSY while a pending job uses it */
  * caller-owned device memory `vis_dev`, asynchronously on `hip_stream`
  * (a hipStream_t; NULL = the null stream).  `precision` is a VP_PREC_* path.
  * Returns once the work is enqueued; faults of the asynchronous work surface
- * as VP_EDEVICE from a later call.  Errors: VP_EINVAL, VP_EDEVICE, VP_ENOMEM. */
+ * as VP_EDEVICE from a later call.  Mixed calls into complex64 whose points go by
+ * antenna beside Gaussians sum both in FP64 through one of up to four workspaces of
+ * 64 to 256 MiB that the context keeps; without memory for one, and on a stream
+ * under graph capture, such a call takes its points with its Gaussians instead.
+ * Errors: VP_EINVAL, VP_EDEVICE, VP_ENOMEM. */
 int vp_predict(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype,
                void *vis_dev, void *hip_stream);
 
@@ -186,7 +190,7 @@ int vp_predict(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision,
  * cosines, Gaussian quadratic forms, shapelet frames, flux per component and
  * channel) are rebuilt on every call into a fixed scratch array of
  * 64 MiB that the library holds on each device until the process ends (beside
- * it 105 MiB for what those of its kernels need that work by antenna and by nodes),
+ * it 169 MiB for what those of its kernels need that work by antenna and by nodes),
  * instead of being allocated and cached.  Limit: 32 B per component, 32 B
  * per Gaussian, 96 B per shapelet and 12 B per (component, channel padded to
  * a multiple of 8), each part rounded up to 256 B, at most 64 MiB in all

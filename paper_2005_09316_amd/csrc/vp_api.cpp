@@ -452,8 +452,93 @@ static int get_lut(vp_ctx *ctx, hipStream_t stream, const float **out) {
   return VP_OK;
 }
 
+void SumsPool::release() {
+  for (Slot &s : slot) {
+    if (s.done) {
+      (void)hipEventSynchronize(s.done);
+      (void)hipEventDestroy(s.done);
+    }
+    if (s.p) (void)hipFree(s.p);
+    s = Slot();
+  }
+}
+
+SumsSpace SumsLease::take(SumsPool &pool, uint64_t want, hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return {nullptr, 0};
+  }
+  uint64_t bytes = kSumsMin;
+  while (bytes < want && bytes < kSumsMax) bytes *= 2;
+  std::unique_lock<std::mutex> lk(pool.mu);
+  SumsPool::Slot *s = nullptr;
+  for (SumsPool::Slot &x : pool.slot)  // this stream's own: nothing to wait for
+    if (!s && x.used && x.last == stream) s = &x;
+  for (SumsPool::Slot &x : pool.slot)
+    if (!s && !x.p) s = &x;
+  if (!s) {
+    s = &pool.slot[pool.next];
+    pool.next = (pool.next + 1) % SumsPool::kSlots;
+  }
+  hipError_t e = s->done ? hipSuccess : hipEventCreateWithFlags(&s->done, hipEventDisableTiming);
+  if (e == hipSuccess && s->bytes < bytes) {
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) {
+      if (s->p) {
+        (void)hipEventSynchronize(s->done);
+        (void)hipFree(s->p);
+      }
+      s->p = p;
+      s->bytes = bytes;
+    } else {
+      (void)hipGetLastError();  // the smaller one, if there is one, will do in parts
+    }
+  }
+  if (e == hipSuccess && s->used) e = hipStreamWaitEvent(stream, s->done, 0);
+  if (e != hipSuccess || !s->p) {
+    (void)hipGetLastError();
+    return {nullptr, 0};
+  }
+  lk_ = std::move(lk);
+  slot_ = s;
+  stream_ = stream;
+  return {(double2 *)s->p, s->bytes};
+}
+
+SumsLease::~SumsLease() {
+  if (!slot_) return;
+  if (hipEventRecord(slot_->done, stream_) != hipSuccess) (void)hipStreamSynchronize(stream_);
+  slot_->last = stream_;
+  slot_->used = true;
+}
+
+// How a call's points and Gaussians go.
+struct PgRoute {
+  bool by_nodes;  // Gaussians, and points unless by antenna
+  bool ant;       // points by antenna
+  bool sums;      // their sums go to the Gaussians through a workspace
+  int step;       // channels by which parts of a time step are counted
+};
+static PgRoute pg_route(const vp_sky *sky, const vp_obs *obs, int precision, int dtype, const Derived &d, bool nodes) {
+  PgRoute r;
+  const bool ant64 = precision == kFP64 || precision == kLut;
+  r.by_nodes = d.plan[2 + ant64].M > 0 && precision != kFP32 && (nodes || ant64);
+  r.ant = (ant64 || d.amp) && use_ant(sky, obs, precision, dtype, r.by_nodes ? d.plan[2 + ant64] : NodePlan{0, 0, 0.0, 0.0});
+  r.sums = r.ant && !ant64 && dtype == VP_C64 && sky->G > 0;
+  r.step = r.by_nodes ? 16 : 8;
+  if (r.sums && sizeof(double2) * (uint64_t)obs->B * std::min(r.step, obs->K) > kSumsMin) r.ant = r.sums = false;
+  return r;
+}
+
+uint64_t sums_bytes(const vp_sky *sky, const vp_obs *obs, int precision, int dtype, const Derived &d, bool nodes) {
+  if (!pg_route(sky, obs, precision, dtype, d, nodes).sums) return 0;
+  return sizeof(double2) * (uint64_t)obs->T * obs->B * obs->K;
+}
+
 int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
-                  int subtract, hipStream_t stream, const Derived &d, const float *lut, int *kernels, bool nodes) {
+                  int subtract, hipStream_t stream, const Derived &d, const float *lut, SumsSpace sums, int *kernels,
+                  bool nodes) {
   TileArgs a;
   a.nrows = (int64_t)obs->T * obs->B;
   a.K = obs->K;
@@ -471,13 +556,18 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   a.n_cb = obs->Kpad / kPgChan;
   a.lut = lut;
   a.shp_chan = kShpChan;
+  a.ld = a.K;
+  a.chan0 = 0;
+  a.call_rows = a.nrows;
+  a.sums = nullptr;
   a.dfk = obs->dfk;
   a.uniform = precision == kFP64 || precision == kLut ? obs->uniform64 : obs->uniform;
   // A sky of shapelets only skips the point/Gaussian pass, which would only
   // write zeros (predict) or rewrite the data unchanged (subtract).
   const bool ant64 = precision == kFP64 || precision == kLut;
-  const bool by_nodes = d.plan[2 + ant64].M > 0 && precision != kFP32 && (nodes || ant64);
-  const bool ant = (ant64 || d.amp) && use_ant(sky, obs, precision, dtype, by_nodes ? d.plan[2 + ant64] : NodePlan{0, 0, 0.0, 0.0});
+  PgRoute route = pg_route(sky, obs, precision, dtype, d, nodes);
+  if (route.sums && !sums.p) route.ant = route.sums = false;
+  const bool by_nodes = route.by_nodes, ant = route.ant;
   const int path = precision == kFP64 ? 1 : precision == kFP32 || precision == kLut ? -1 : 0;
   const bool shp_by_nodes = sky->S > 0 && nodes && path >= 0 && d.plan[path].M > 0;
   // A handful of points goes along with the shapelets' outputs by nodes, as
@@ -488,8 +578,8 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   a.skip_points = ant;
   a.fresh = !pg_pass && !ant && !subtract;
   hipError_t e = hipSuccess;
+  AntArgs p;
   if (ant) {
-    AntArgs p;
     p.T = obs->T; p.B = obs->B; p.K = obs->K;
     p.npad = obs->ant_npad;
     p.J = sky->P; p.Jp = ant_jp(sky);
@@ -502,17 +592,57 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
     p.neg = sky->p_neg;
     p.fine = !obs->uniform;
     p.vis = vis; p.c64 = a.c64; p.conj = a.conj; p.subtract = subtract;
-    ProfScope ps(prof, stream, 1);
-    e = ant64 ? launch_ant64(p, stream) : launch_ant(p, stream);
-    if (kernels) ++*kernels;
   }
-  if (e != hipSuccess) return hip_error(e, "launching the kernel of the points by antenna");
-  if (pg_pass) {
+  auto points = [&](const AntArgs &x) {
     ProfScope ps(prof, stream, 1);
-    e = by_nodes ? launch_pg_nodes(a, precision, stream) : launch_pg(a, precision, stream);
     if (kernels) ++*kernels;
+    return ant64 ? launch_ant64(x, stream) : launch_ant(x, stream);
+  };
+  auto gaussians = [&](const TileArgs &x) {  // (and the points, if not by antenna)
+    ProfScope ps(prof, stream, 1);
+    if (kernels) ++*kernels;
+    return by_nodes ? launch_pg_nodes(x, precision, stream) : launch_pg(x, precision, stream);
+  };
+  if (route.sums) {
+    // parts of the call, of like sizes: whole time steps, or channels of one
+    const uint64_t chan = sizeof(double2) * (uint64_t)obs->B, whole = chan * obs->K;
+    int tc = 1, kc = obs->K;
+    if (whole <= sums.bytes) {
+      tc = (int)std::min<uint64_t>(obs->T, sums.bytes / whole);
+      const int parts = (obs->T + tc - 1) / tc;
+      tc = (obs->T + parts - 1) / parts;
+    } else {
+      const int most = (int)(sums.bytes / chan) / route.step * route.step, parts = (obs->K + most - 1) / most;
+      kc = ((obs->K + parts - 1) / parts + route.step - 1) / route.step * route.step;
+    }
+    const size_t vis_size = a.c64 ? sizeof(float2) : sizeof(double2);
+    for (int t0 = 0; t0 < obs->T && e == hipSuccess; t0 += tc)
+      for (int k0 = 0; k0 < obs->K && e == hipSuccess; k0 += kc) {
+        const int nt = std::min(tc, obs->T - t0), nk = std::min(kc, obs->K - k0);
+        AntArgs x = p;
+        x.T = nt; x.K = nk;
+        x.nkb = (nk + x.kpack - 1) / x.kpack;
+        x.xyz += (size_t)t0 * x.npad * 3; x.xyz_lo += (size_t)t0 * x.npad * 3;
+        x.fk += k0; x.amp += (size_t)k0 * x.Jp; x.unscale += k0; x.flux64 += k0;
+        x.vis = sums.p; x.c64 = 0; x.subtract = 0;
+        e = points(x);
+        TileArgs y = a;
+        const int64_t row0 = (int64_t)t0 * obs->B;
+        y.nrows = (int64_t)nt * obs->B; y.K = nk; y.chan0 = k0;
+        y.n_rb = (int)((y.nrows + kTileRows - 1) / kTileRows);
+        y.n_cb = (nk + kPgChan - 1) / kPgChan;
+        y.uvw += 3 * row0; y.fk += k0; y.d.flux32 += k0; y.d.flux64 += k0;
+        y.vis = (char *)vis + vis_size * (row0 * obs->K + k0);
+        y.sums = sums.p;
+        if (e == hipSuccess) e = gaussians(y);
+      }
+    if (e != hipSuccess) return hip_error(e, "launching the points by antenna and the Gaussians");
+  } else {
+    if (ant) e = points(p);
+    if (e != hipSuccess) return hip_error(e, "launching the kernel of the points by antenna");
+    if (pg_pass) e = gaussians(a);
+    if (e != hipSuccess) return hip_error(e, "launching the point/Gaussian kernel");
   }
-  if (e != hipSuccess) return hip_error(e, "launching the point/Gaussian kernel");
   if (sky->S > 0) {
     a.n_cb = (obs->K + kShpChan - 1) / kShpChan;
     ProfScope ps(prof, stream, 2);
@@ -537,7 +667,10 @@ int run_tiles(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, 
     rc = get_lut(ctx, stream, &lut);
     if (rc != VP_OK) return rc;
   }
-  return launch_passes(ctx, sky, obs, precision, dtype, vis, subtract, stream, d->d, lut, nullptr, nodes);
+  SumsLease lease;
+  const uint64_t want = sums_bytes(sky, obs, precision, dtype, d->d, nodes);
+  const SumsSpace sums = want ? lease.take(ctx->sums, want, stream) : SumsSpace{nullptr, 0};
+  return launch_passes(ctx, sky, obs, precision, dtype, vis, subtract, stream, d->d, lut, sums, nullptr, nodes);
 }
 
 int check_call(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis) {
@@ -616,6 +749,7 @@ int vp_destroy_ctx(vp_ctx *ctx) {
     ctx->peel->mem.release();
     delete ctx->peel;
   }
+  ctx->sums.release();
   ctx->lut_mem.release();
   delete ctx;
   return VP_OK;
@@ -1042,7 +1176,8 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
   if (e == hipSuccess) e = launch_flux(make_flux_args(sky, obs, d), stream);
   if (e == hipSuccess) e = build_amp(sky, obs, d, stream);
   if (e != hipSuccess) return hip_error(e, "building the tables in the scratch array");
-  return launch_passes(nullptr, sky, obs, precision, dtype, vis_dev, 0, stream, d, nullptr);
+  const SumsSpace sums = {(double2 *)(part + kNoAllocNodeBytes + kNoAllocNfluxBytes), kSumsMin};
+  return launch_passes(nullptr, sky, obs, precision, dtype, vis_dev, 0, stream, d, nullptr, sums);
 }
 
 int vp_subtract(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *data_dev,

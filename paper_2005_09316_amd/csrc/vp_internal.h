@@ -144,6 +144,13 @@ struct TileArgs {
   void *vis;           // output (predict) or data (subtract), [nrows][K] complex
   int subtract;        // 0: vis = V; 1: vis = vis - V
   int skip_points;     // 1: the points were taken by antenna; the Gaussians add to vis (or subtract from it)
+  // The point/Gaussian kernels may take a part of the rows and channels (the
+  // pointers above begin there, K and nrows are the part's): channels of a row of
+  // vis, the part's first channel (a multiple of 16 by nodes), and the call's rows,
+  // by which kernel and workgroups are chosen whatever the part.
+  int ld, chan0;
+  int64_t call_rows;
+  const double2 *sums; // [nrows][K] the points' sums, to be added to the Gaussians' (null: they are in vis)
   int c64;             // 1: complex64, 0: complex128
   int conj;            // 1 when the exponent sign is -1
   const float *lut;    // basis table of the lookup-table variant, or null
@@ -183,6 +190,17 @@ struct AntArgs {
 struct AntAmpArgs {
   int J, Jp, Kpad;
   Derived d;
+};
+
+// Where the data are complex64, points by antenna hand their sums to the
+// Gaussians' pass in FP64 (written to vis, they would be rounded to complex64
+// between the two): through a workspace of [rows][channels] complex128, whole time
+// steps at a time or, where one does not fit, some of the channels of one.  Such
+// workspaces hold kSumsMin to kSumsMax bytes; a call's least part fits the former.
+constexpr uint64_t kSumsMin = 64ull << 20, kSumsMax = 256ull << 20;
+struct SumsSpace {
+  double2 *p;
+  uint64_t bytes;
 };
 
 // A serving job's mark: its sequence number, and the device wall clock when it
@@ -242,6 +260,8 @@ constexpr uint64_t kNoAllocNodeBytes = (uint64_t)kPlans * (kNodesMaxChan + 16) *
 // in 64 MiB, 8 per component and node, at most half as many nodes as padded
 // channels), so that the calls take the same kernels as vp_predict.
 constexpr uint64_t kNoAllocNfluxBytes = 48ull << 20;
+
+// A fifth, the points' sums on their way to the Gaussians (kSumsMin bytes).
 
 // Host-side launchers (vp_kernels.hip).
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s);

@@ -117,7 +117,7 @@ __device__ __forceinline__ void kahan_add(T &sum, T &cmp, T x) {
 // group is aligned (wide: even rows on a 16-byte base); as single values, lanes
 // apart by rows, each access leaves most of its sectors unused (119 -> 96 us of
 // outputs at 32,640 rows x 384 channels).
-__device__ __forceinline__ bool vis_wide(const TileArgs &a) { return a.c64 && a.K % 2 == 0 && ((uintptr_t)a.vis & 15) == 0; }
+__device__ __forceinline__ bool vis_wide(const TileArgs &a) { return a.c64 && a.ld % 2 == 0 && ((uintptr_t)a.vis & 15) == 0; }
 __device__ __forceinline__ void vis_put4(const TileArgs &a, bool wide, bool add, int64_t idx, int n, const double (&re)[4],
                                          const double (&im)[4]) {
   if (wide && n >= 4) {
@@ -143,6 +143,19 @@ __device__ __forceinline__ void vis_put4(const TileArgs &a, bool wide, bool add,
       const double2 d = add ? *o : make_double2(0.0, 0.0);
       *o = make_double2(re[r] + d.x, im[r] + d.y);
     }
+  }
+}
+
+// (re, im) -= or += the points' sums of four channels of one row, from k on
+// (signs as the Gaussians' in re, im).
+__device__ __forceinline__ void add_sums(const TileArgs &a, int64_t row, int k, double (&re)[4], double (&im)[4]) {
+  if (!a.sums) return;
+  const double2 *s = a.sums + row * a.K;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double2 x = s[min(k + r, a.K - 1)];
+    re[r] += a.subtract ? -x.x : x.x;
+    im[r] += a.subtract ? -x.y : x.y;
   }
 }
 
@@ -679,7 +692,7 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
       }
   }
   if (!valid) return;
-  const bool wide = vis_wide(a), add = a.subtract || a.skip_points;
+  const bool wide = vis_wide(a), add = a.subtract || (a.skip_points && !a.sums);
 #pragma unroll
   for (int k = 0; k < KB; k += 4) {
     if (k0 + k >= a.K) break;
@@ -692,7 +705,8 @@ __device__ __forceinline__ void pg_tile(const TileArgs &a, int rb, int cb,
       if (a.subtract) re[r] = -re[r];
       if (a.subtract != a.conj) im[r] = -im[r];
     }
-    vis_put4(a, wide, add, row * a.K + k0 + k, a.K - k0 - k, re, im);
+    add_sums(a, row, k0 + k, re, im);
+    vis_put4(a, wide, add, row * a.ld + k0 + k, a.K - k0 - k, re, im);
   }
 }
 
@@ -1970,19 +1984,21 @@ __global__ __launch_bounds__(64 * pg_node_waves(F64, NODES)) __attribute__((amdg
       if (a.subtract != a.conj) sim[i] = -sim[i];
     }
     static_assert(kPgNB == 6, "four channels and two");
-    const double r0[4] = {sre[0], sre[1], sre[2], sre[3]}, i0[4] = {sim[0], sim[1], sim[2], sim[3]};
-    const double r1[4] = {sre[4], sre[5], 0, 0}, i1[4] = {sim[4], sim[5], 0, 0};
-    const bool wide = vis_wide(a), add = a.subtract || a.skip_points;
-    vis_put4(a, wide, add, row * a.K + k, min(4, a.K - k), r0, i0);
-    vis_put4(a, wide, add, row * a.K + k + 4, min(2, a.K - k - 4), r1, i1);
+    double r0[4] = {sre[0], sre[1], sre[2], sre[3]}, i0[4] = {sim[0], sim[1], sim[2], sim[3]};
+    double r1[4] = {sre[4], sre[5], 0, 0}, i1[4] = {sim[4], sim[5], 0, 0};
+    const bool wide = vis_wide(a), add = a.subtract || (a.skip_points && !a.sums);
+    add_sums(a, row, k, r0, i0);
+    add_sums(a, row, k + 4, r1, i1);
+    vis_put4(a, wide, add, row * a.ld + k, min(4, a.K - k), r0, i0);
+    vis_put4(a, wide, add, row * a.ld + k + 4, min(2, a.K - k - 4), r1, i1);
     return;
   }
   __syncthreads();
-  const int n16 = lane & 15, g = lane >> 4, ncb = (a.K + 15) / 16, steps = p.Mp / 4;
+  const int n16 = lane & 15, g = lane >> 4, ncb = (a.K + 15) / 16, cb0 = a.chan0 / 16, steps = p.Mp / 4;
   const bool wide = vis_wide(a);
   for (int task = wave; task < (LR / 16) * ncb; task += nw) {
     const int rg = task / ncb, cb = task - rg * ncb, ro = rg * 16 + n16, k = cb * 16 + 4 * g;
-    const double *L = tab + kNodesStride + (size_t)cb * steps * 64 + lane;
+    const double *L = tab + kNodesStride + (size_t)(cb0 + cb) * steps * 64 + lane;
     double4w er = {0, 0, 0, 0}, ei = {0, 0, 0, 0};
     for (int s = 0; s < steps; ++s) {
       const double l = L[64 * s];
@@ -1997,7 +2013,8 @@ __global__ __launch_bounds__(64 * pg_node_waves(F64, NODES)) __attribute__((amdg
       re[r] = a.subtract ? -er[r] : er[r];
       im[r] = a.subtract != a.conj ? -ei[r] : ei[r];
     }
-    vis_put4(a, wide, a.subtract || a.skip_points, (row0 + ro) * a.K + k, a.K - k, re, im);
+    add_sums(a, row0 + ro, k, re, im);
+    vis_put4(a, wide, a.subtract || (a.skip_points && !a.sums), (row0 + ro) * a.ld + k, a.K - k, re, im);
   }
 }
 
@@ -2038,7 +2055,7 @@ static hipError_t init_constants() {
 // name is only a stand-in: its device address, which differs per device, is
 // looked up once per device below and used everywhere instead.
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocAmpBytes + kNoAllocNodeBytes +
-                                                              kNoAllocNfluxBytes];
+                                                              kNoAllocNfluxBytes + kSumsMin];
 static void *g_scratch[kMaxDevices];
 
 hipError_t device_init(int dev) {
@@ -2099,8 +2116,9 @@ hipError_t launch_tiles_build(const TileBuildArgs &a, int max_nmax, hipStream_t 
 // 0.069, 128 tiles 0.21 for 0.12; FP64, where the tiles rotate phasors between
 // channels, 0.13 for 0.15, then 0.26 for 0.15, and on irregular channels 0.26 for
 // 0.34 at 32 tiles.
+static int64_t pg_tiles(const TileArgs &a) { return (a.call_rows + kTileRows - 1) / kTileRows * (a.Kpad / kPgChan); }
 static bool pg_small(const TileArgs &a, int prec) {
-  const int64_t nt = (int64_t)a.n_rb * (a.Kpad / kPgChan);
+  const int64_t nt = pg_tiles(a);
   if (prec == kFP64 || prec == kLut) return nt <= (a.uniform ? 4 : 64);
   return prec != kFP32 && nt <= 40;
 }
@@ -2116,7 +2134,7 @@ hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s) {
   // Components split over a workgroup's waves, us a Gaussian: mixed 0.12 for 0.29
   // at 128 tiles, 0.20 for 0.29 at 256, 0.36 for 0.41 at 508; FP64 0.29 for 0.55,
   // 0.53 for 0.57, the same at 508.
-  if (nt <= kPgSplitTiles && prec != kFP32) {
+  if (pg_tiles(a) <= kPgSplitTiles && prec != kFP32) {
     const int n_rb = (int)((a.nrows + 63) / 64);
     const dim3 g((unsigned)((int64_t)n_rb * a.n_cb)), b(kTileRows);
     if (prec == kFP64 || prec == kLut) {
@@ -2243,7 +2261,7 @@ hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
   int LR = 64;
   double best = 0.0;
   for (int r = 64; r >= 16; r /= 2) {
-    const int64_t wgs = (a.nrows + r - 1) / r;
+    const int64_t wgs = (a.call_rows + r - 1) / r;
     const double t = (double)((wgs + slots - 1) / slots) * (r + 4);
     if (best == 0.0 || t < best) {
       best = t;

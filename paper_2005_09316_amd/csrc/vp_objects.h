@@ -43,6 +43,40 @@ struct PeelWork {
   hipEvent_t done = nullptr;
 };
 
+// Workspaces for points' sums (SumsSpace) of the calls on one context: up to
+// kSlots, each in use by one call's kernels at a time (the event of the last one's
+// end orders the next, on whatever stream), freed with the context.
+struct SumsPool {
+  static constexpr int kSlots = 4;
+  struct Slot {
+    void *p = nullptr;
+    uint64_t bytes = 0;
+    hipEvent_t done = nullptr;
+    hipStream_t last = nullptr;
+    bool used = false;  // done was recorded, on last
+  };
+  std::mutex mu;
+  Slot slot[kSlots];
+  int next = 0;
+  void release();
+};
+
+// One call's hold on a workspace while it enqueues its kernels.
+class SumsLease {
+ public:
+  // Up to `want` bytes, at least kSumsMin of it, for work enqueued on `stream`
+  // from here until the lease ends; p null when there is none to have: memory is
+  // short, or the stream is being captured (the graph would use the workspace
+  // beside later calls).
+  SumsSpace take(SumsPool &pool, uint64_t want, hipStream_t stream);
+  ~SumsLease();
+
+ private:
+  std::unique_lock<std::mutex> lk_;
+  SumsPool::Slot *slot_ = nullptr;
+  hipStream_t stream_ = nullptr;
+};
+
 struct DerivedEntry {
   Derived d{};
   DeviceMem mem;
@@ -94,12 +128,17 @@ int run_tiles(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *ob
 int check_call(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
                void *vis);
 // Launch the passes over the visibility tiles with the pair's tables `d`.
-// prof: the context whose profiling records the launches, or null; *kernels
-// (when given) grows by the number of kernels launched; nodes: shapelets may go
-// by nodes.
+// prof: the context whose profiling records the launches, or null; sums: the
+// workspace that sums_bytes asks for, or {null, 0} (the points then go with the
+// Gaussians); *kernels (when given) grows by the number of kernels launched;
+// nodes: shapelets may go by nodes.
 int launch_passes(vp_ctx *prof, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
-                  void *vis, int subtract, hipStream_t stream, const Derived &d, const float *lut,
+                  void *vis, int subtract, hipStream_t stream, const Derived &d, const float *lut, SumsSpace sums,
                   int *kernels = nullptr, bool nodes = true);
+// Bytes of workspace with which a call takes one pass over its sums (fewer:
+// several), 0 when it needs none.
+uint64_t sums_bytes(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype, const Derived &d,
+                    bool nodes = true);
 // Per-(sky, observation) tables, built on `stream` at first use and cached;
 // later callers on other streams wait for the build.  serving: the caller is
 // an admitted job, counted in the entry's users until serve_release_derived.
@@ -201,6 +240,7 @@ struct vp_ctx {
   // created by the first vp_submit (under mu), read by vp_poll without it
   std::atomic<vp::Scheduler *> sched{nullptr};
   vp::PeelWork *peel = nullptr;
+  vp::SumsPool sums;
   float *lut = nullptr;    // basis table of VP_PREC_LUT, built at its first use (guarded by mu)
   vp::DeviceMem lut_mem;
 };

@@ -143,8 +143,11 @@ int HipExecutor::admit(CoreJob &j) {
     rc = hip_error(e, "starting a serving job");
   } else {
     x.kernels = x.built ? 2 : 0;
+    SumsLease lease;
+    const uint64_t want = sums_bytes(x.job.sky, x.job.obs, x.job.precision, x.job.dtype, d->d);
+    const SumsSpace sums = want ? lease.take(ctx->sums, want, st) : SumsSpace{nullptr, 0};
     rc = launch_passes(nullptr, x.job.sky, x.job.obs, x.job.precision, x.job.dtype, x.job.vis_dev,
-                       x.job.kind == VP_JOB_SUBTRACT, st, d->d, nullptr, &x.kernels);
+                       x.job.kind == VP_JOB_SUBTRACT, st, d->d, nullptr, sums, &x.kernels);
   }
   if (rc == VP_OK) {
     e = launch_mark(&H_dev->finished[slot], x.seq, st);
