@@ -646,6 +646,7 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
   if (sky->S > 0) {
     a.n_cb = (obs->K + kShpChan - 1) / kShpChan;
     ProfScope ps(prof, stream, 2);
+    a.uniform = obs->uniform64;  // (the outputs by nodes turn FP64 phasors by dfk)
     if (shp_by_nodes)
       e = launch_shp_nodes(a, d.plan[path], precision, sky->max_nmax, stream);
     else
