@@ -9,7 +9,9 @@ namespace vp {
 namespace {
 
 // Points in space, looked up by coordinate to a tolerance: open addressing on
-// the first coordinate's cell.
+// the cell of a projection whose weights no array's symmetry knows (rows of one
+// list may well share one or two coordinates).  Points that coincide share a cell
+// all the same: probes() counts what the look-ups touched, for the caller to bound.
 class Places {
  public:
   Places(double tol, int most) : tol_(tol), cell_(std::max(1e-3, 8.0 * tol)) {
@@ -19,13 +21,10 @@ class Places {
     slot_.assign((size_t)1 << bits, -1);
     pos_.reserve(3 * (size_t)most);
   }
-  void add(const double *x) {
-    size_t h = hash(cell(x[0]));
-    while (slot_[h] >= 0) h = next(h);
-    slot_[h] = size();
-    pos_.insert(pos_.end(), x, x + 3);
-  }
+  void add(const double *x) { put(x, false); }
+  void add_once(const double *x) { put(x, true); }  // not beside one within tol (of the same cell)
   int size() const { return (int)(pos_.size() / 3); }
+  int64_t probes() const { return probes_; }
   const double *at(int i) const { return &pos_[3 * (size_t)i]; }
   bool near(int i, const double *x) const {
     const double *y = at(i);
@@ -34,22 +33,44 @@ class Places {
   // Calls f(index) for every point within tol of x until it returns true.
   template <typename F>
   bool each(const double *x, F f) const {
-    const int64_t lo = cell(x[0] - tol_), hi = cell(x[0] + tol_);
+    const double k = key(x);
+    const int64_t lo = cell(k - kReach * tol_), hi = cell(k + kReach * tol_);
     for (int64_t c = lo; c <= hi; ++c)
-      for (size_t h = hash(c); slot_[h] >= 0; h = next(h))
-        if (near(slot_[h], x) && cell(at(slot_[h])[0]) == c && f(slot_[h])) return true;
+      for (size_t h = hash(c); slot_[h] >= 0; h = next(h)) {
+        ++probes_;
+        if (near(slot_[h], x) && cell(key(at(slot_[h]))) == c && f(slot_[h])) return true;
+      }
     return false;
   }
 
  private:
+  static constexpr double kReach = 2.5;  // above the sum of the weights
+  static double key(const double *x) { return x[0] + 0.7548776662466927 * x[1] + 0.5698402909980532 * x[2]; }
   int64_t cell(double v) const { return (int64_t)std::floor(v / cell_); }
   size_t hash(int64_t c) const { return (size_t)(((uint64_t)c * 0x9e3779b97f4a7c15ull) >> shift_); }
   size_t next(size_t h) const { return (h + 1) & (slot_.size() - 1); }
+  void put(const double *x, bool once) {
+    size_t h = hash(cell(key(x)));
+    for (; slot_[h] >= 0; h = next(h)) {
+      ++probes_;
+      if (once && near(slot_[h], x)) return;
+    }
+    slot_[h] = size();
+    pos_.insert(pos_.end(), x, x + 3);
+  }
   double tol_, cell_;
   int shift_;
   std::vector<int> slot_;
   std::vector<double> pos_;
+  mutable int64_t probes_ = 0;
 };
+
+// Probes of the tables that a search over b rows may have made: a list in general
+// position takes some 2 a row, and up to 50 a new antenna and candidate for its
+// place (5e6 at 900 antennas with gaps).  Where many antennas coincide, or
+// baselines repeat, the tables degenerate into lists, and the search, quadratic
+// then, is given up.
+int64_t most_probes(int64_t b) { return 40 * b + 4000000; }
 
 void plus(const double *x, const double *d, double *y) {
   for (int c = 0; c < 3; ++c) y[c] = x[c] + d[c];
@@ -137,6 +158,7 @@ struct Pass {
       }
       // lists in no order cost a search of every antenna per row: left alone
       if (looks > 3 * (int64_t)b + 2 * (int64_t)n * n + 1024) return false;
+      if (places.probes() + (rows ? rows->probes() : 0) > most_probes(b)) return false;
       used[(size_t)std::min(p, q) * max_n + std::max(p, q)] = 1;
       P[b] = p;
       Q[b] = q;
@@ -161,9 +183,13 @@ AntLayout find_antennas(int T, int B, const double *uvw, double tol, int max_n, 
   if (!ok || (B != n0 * (n0 - 1) / 2 && B != n0 * (n0 + 1) / 2)) {
     // not a complete list: place its antennas by vote
     Places rows(tol, B);
-    for (int b = 0; b < B; ++b) rows.add(uvw + 3 * (size_t)b);
+    bool fits = true;
+    for (int b = 0; b < B && fits; ++b) {
+      rows.add_once(uvw + 3 * (size_t)b);  // (asked for their presence only)
+      fits = rows.probes() <= most_probes(b);
+    }
     Pass v;
-    if (v.run(B, uvw, tol, max_n, &rows) && (!ok || v.from.size() < s.from.size())) {
+    if (fits && v.run(B, uvw, tol, max_n, &rows) && (!ok || v.from.size() < s.from.size())) {
       s = v;
       ok = true;
     }
