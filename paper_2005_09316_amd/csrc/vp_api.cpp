@@ -275,11 +275,12 @@ static hipError_t build_amp(const vp_sky *sky, const vp_obs *obs, const Derived 
 }
 
 int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t stream, bool serving,
-                DerivedEntry **out, bool *built) {
+                DerivedEntry **out, bool *built, int *kernels) {
   const auto key = std::make_pair(sky->id, obs->id);
   std::lock_guard<std::mutex> lk(ctx->mu);
   auto it = ctx->derived.find(key);
   if (built) *built = it == ctx->derived.end();
+  if (kernels) *kernels = 0;
   if (it != ctx->derived.end()) {
     DerivedEntry *d = it->second;
     if (d->ready && d->ready_stream != stream) {
@@ -311,6 +312,7 @@ int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t s
     delete d;
     return hip_error(e, "building per-(sky, observation) tables");
   }
+  if (kernels) *kernels = (sky->P + sky->G + sky->S > 0 ? 2 : 0) + (d->d.amp ? 2 : 0);
   d->ready_stream = stream;
   d->serve_built = serving;
   d->serve_users = serving ? 1 : 0;

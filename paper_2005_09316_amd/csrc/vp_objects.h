@@ -142,9 +142,10 @@ uint64_t sums_bytes(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int 
 // Per-(sky, observation) tables, built on `stream` at first use and cached;
 // later callers on other streams wait for the build.  serving: the caller is
 // an admitted job, counted in the entry's users until serve_release_derived.
-// *built (when given): whether this call enqueued the build.
+// *built (when given): whether this call enqueued the build, *kernels: of how many
+// kernels.
 int get_derived(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, hipStream_t stream, bool serving,
-                DerivedEntry **out, bool *built = nullptr);
+                DerivedEntry **out, bool *built = nullptr, int *kernels = nullptr);
 // A serving job is done with the pair's tables.
 void serve_release_derived(vp_ctx *ctx, DerivedEntry *d);
 // The tables a serving job was to build may never have been built (its work

@@ -28,6 +28,7 @@
 
 #include "../../include/vp.h"
 #include "serve_core.h"
+#include "serve_spans.h"
 #include "vp_internal.h"
 #include "vp_objects.h"
 
@@ -79,6 +80,7 @@ struct JobExt {
   int kernels = 0;         // kernels launched for it
   DerivedEntry *d = nullptr;
   bool built = false;      // this job enqueued the build of the pair's tables
+  uint64_t floor = 0;      // SpanUnion's, from its admission
 };
 
 static JobExt &ext(CoreJob &j) { return *(JobExt *)j.payload; }
@@ -112,11 +114,9 @@ class HipExecutor : public ServeExecutor {
   void retired(CoreJob &j) override;
 
  private:
-  std::mutex stats_mu;     // the three below, read by vp_serve_stats
+  std::mutex stats_mu;     // the two below, read by vp_serve_stats
   uint64_t launches = 0;   // kernels of finished jobs
-  uint64_t merged_ticks = 0;  // device time covered by the intervals merged so far
-  std::vector<std::pair<uint64_t, uint64_t>> spans;  // finished jobs' device intervals, not yet merged
-  void merge_spans();
+  SpanUnion spans;         // their device intervals
 };
 
 struct Scheduler {
@@ -132,7 +132,7 @@ int HipExecutor::admit(CoreJob &j) {
   hipStream_t st = streams[si];
   TraceRange tr("vp_serve: job");
   DerivedEntry *d = nullptr;
-  int rc = get_derived(ctx, x.job.sky, x.job.obs, st, true, &d, &x.built);
+  int rc = get_derived(ctx, x.job.sky, x.job.obs, st, true, &d, &x.built, &x.kernels);
   if (rc != VP_OK) return rc;
   const int slot = free_slots.back();
   hipError_t e = hipSuccess;
@@ -142,7 +142,6 @@ int HipExecutor::admit(CoreJob &j) {
   if (e != hipSuccess) {
     rc = hip_error(e, "starting a serving job");
   } else {
-    x.kernels = x.built ? 2 : 0;
     SumsLease lease;
     const uint64_t want = sums_bytes(x.job.sky, x.job.obs, x.job.precision, x.job.dtype, d->d);
     const SumsSpace sums = want ? lease.take(ctx->sums, want, st) : SumsSpace{nullptr, 0};
@@ -165,6 +164,8 @@ int HipExecutor::admit(CoreJob &j) {
   x.stream = si;
   x.d = d;
   ++in_flight[si];
+  std::lock_guard<std::mutex> lk(stats_mu);
+  x.floor = spans.admit();
   return VP_OK;
 }
 
@@ -199,8 +200,7 @@ void HipExecutor::finished(CoreJob &j) {
   {
     std::lock_guard<std::mutex> lk(stats_mu);
     launches += (uint64_t)x.kernels;
-    spans.emplace_back(j.dev_start, j.dev_done);
-    if (spans.size() >= 4096) merge_spans();
+    spans.finish(x.floor, j.dev_start, j.dev_done);
   }
   --in_flight[x.stream];
   free_slots.push_back(x.slot);
@@ -218,23 +218,10 @@ void HipExecutor::retired(CoreJob &j) {
   j.payload = nullptr;
 }
 
-// Adds the device time that the kept intervals cover together (stats_mu held).
-void HipExecutor::merge_spans() {
-  std::sort(spans.begin(), spans.end());
-  uint64_t end = 0;
-  for (const auto &s : spans) {
-    const uint64_t from = std::max(s.first, end);
-    if (s.second > from) merged_ticks += s.second - from;
-    end = std::max(end, s.second);
-  }
-  spans.clear();
-}
-
 void HipExecutor::stats(uint64_t *n, double *ms) {
   std::lock_guard<std::mutex> lk(stats_mu);
-  merge_spans();
   *n = launches;
-  *ms = (double)merged_ticks / ticks_per_ms;
+  *ms = (double)spans.ticks() / ticks_per_ms;
 }
 
 // The device failed under the running jobs: they end with that error.  Their
@@ -251,6 +238,8 @@ void HipExecutor::abandon(const std::vector<CoreJob *> &running, int rc) {
   for (CoreJob *j : running) {
     free_slots.push_back(ext(*j).slot);
     --in_flight[ext(*j).stream];
+    std::lock_guard<std::mutex> lk(stats_mu);
+    spans.drop(ext(*j).floor);
   }
 }
 
