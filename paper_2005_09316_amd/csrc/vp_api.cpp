@@ -125,7 +125,10 @@ static int pg_sum_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
 
 NodePlan node_plan(const vp_sky *sky, const vp_obs *obs, int i) {
   NodePlan p{0, 0, 0.0, 0.0};
-  if (obs->K > kNodesMaxChan) return p;
+  if (obs->K > kNodesMaxChan || (int64_t)obs->T * obs->B > kNodesMaxRows) return p;
+  // the fluxes at the nodes lengthen the flux tables' grid
+  if (i >= 2 && !grid_fits(((int64_t)(sky->P + sky->G + sky->S) * obs->Kpad + 2ll * (sky->P + sky->G) * kNodesStride) / 256 + 1, 256))
+    return p;
   const int M = i < 2 ? shapelet_nodes(sky, obs, i) : pg_sum_nodes(sky, obs, i);
   if (M == 0) return p;
   const int Mp = (M + 3) / 4 * 4;
@@ -161,6 +164,7 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs) {
   // finite (as a product of the largest S_ref and the largest growth), and not so
   // steep that the points' order by S_ref, bright to faint, says nothing about
   // the order in the band.
+  if (!grid_fits((int64_t)ant_jp(sky) * obs->Kpad / 256 + 1, 256)) return false;
   const double x = std::max(std::fabs(std::log(obs->f_lo / sky->nu_ref)), std::fabs(std::log(obs->f_hi / sky->nu_ref)));
   const double grow = std::exp(sky->p_amax * x);
   return sky->p_smax >= 1e-30 && sky->p_smax * grow <= 1e30 && grow <= 1048576.0;
@@ -191,6 +195,7 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs) {
 // 4 times x 384 channels: 0.41 us a point by nodes, 0.39 by antenna.
 static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dtype, const NodePlan &plan) {
   const bool f64 = precision == kFP64 || precision == kLut;
+  if (!grid_fits((int64_t)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac, 64 * kAntWaves)) return false;
   const double rows = (double)obs->T * obs->B;
   const double node_us = plan.M == 0 ? 1e30 : sky->P * (f64 ? std::max(0.3, rows * plan.Mp / 0.47e6) : std::max(0.1, rows * plan.Mp / 2.3e6));
   if (precision == kFP64 || precision == kLut) {
@@ -765,7 +770,7 @@ static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
   // flagged, n = 2 sqrt(B)
   const int max_n = std::min(kAntMaxN, (int)(2.2 * std::sqrt((double)o->B)) + 8);
   const double f = o->f_hi / kLightSpeed;
-  if (o->B > (int64_t)kAntMaxN * (kAntMaxN + 1) / 2) return hipSuccess;
+  if (o->B > (int64_t)kAntMaxN * (kAntMaxN + 1) / 2 || !grid_fits(o->T, 256)) return hipSuccess;
   const AntLayout L = find_antennas(o->T, o->B, uvw, 1e-10 / f, max_n, false);
   const int np = (L.n + kAntBlk - 1) / kAntBlk * kAntBlk;
   // (few baselines over very many times: the padding would outgrow the uvw)

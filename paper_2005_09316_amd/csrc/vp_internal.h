@@ -162,6 +162,10 @@ struct TileArgs {
                        //    predict with no point/Gaussian pass before it)
 };
 
+// Whether HIP takes a grid of so many workgroups (its threads are counted in 32 bits).
+inline bool grid_fits(int64_t blocks, int threads) { return blocks <= 0xffffffffll / threads; }
+constexpr int64_t kNodesMaxRows = 1ll << 28;  // so many, by nodes, whatever rows a workgroup takes (16 x 256 threads at the least)
+
 // Points by antenna (vp_ant.hip).
 constexpr int kAntMinPoints = 64;  // two blocks of 32 points: below, padding is most of the work
 constexpr int kAntMaxN = 1024;     // antennas (the pair map takes 4 n^2 bytes)

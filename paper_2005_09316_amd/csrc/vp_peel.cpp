@@ -80,7 +80,8 @@ int vp_peel(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, const int32_t *an
   // the FP64 path keeps its tables and the operator in FP64 (the latter where it fits)
   const bool w32 = precision != VP_PREC_FP64;
   const size_t cell_bytes = gain_cell_bytes(n_ant, w32);
-  const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(cells, (int64_t)(kPeelWsMax / cell_bytes)));
+  // (a workgroup of up to 1,024 threads a cell, and HIP counts a grid's in 32 bits)
+  const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>({cells, (int64_t)(kPeelWsMax / cell_bytes), 1 << 21}));
   const size_t wsbytes = (size_t)chunk * cell_bytes;
   const size_t gwbytes = (size_t)cells * n_ant * sizeof(double2);
   if (mbytes > w.model_bytes || tab.size() > w.tab_n || wsbytes > w.ws_bytes || gwbytes > w.gw_bytes) {
