@@ -486,9 +486,9 @@ __global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(
 // FP64 path
 // ---------------------------------------------------------------------------
 //
-// The same product in FP64 on v_mfma_f64_16x16x4f64, 16 points at a time, from
-// faint points to bright, so that the running sums stay small for longest.  The
-// factors' phases are dots of
+// The same product in FP64 on v_mfma_f64_16x16x4f64, 16 points at a time (they
+// come from faint to bright, so that the running sums stay small for longest).
+// The factors' phases are dots of
 // coordinates (wavelengths) with (l, m, n - 1): each product is taken with its
 // rounding error and reduced to a fraction of a turn before the sum, so that
 // the phase is good to an ulp of a turn and not of the whole phase (the error of
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(
   const bool is_pos = pc < 3, is_am = pc >= 3 && pc < 3 + mac.nsup;
   const int ka = min(k0 + mac.dk[is_am ? pc - 3 : 0], a.K - 1);
   auto fetch = [&](int c) {
-    const int j = (nc - 1 - min(c, nc - 1)) * kAntK64 + pj;  // faint points first
+    const int j = min(c, nc - 1) * kAntK64 + pj;
     double v = 0.0;
     if (is_pos) v = ((const double *)(a.pos + min(j, a.J - 1)))[pc];
     if (is_am && j < a.J) v = a.flux64[(int64_t)j * a.Kpad + ka];

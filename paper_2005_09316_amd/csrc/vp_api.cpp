@@ -905,19 +905,21 @@ int vp_destroy_obs(vp_obs *obs) {
   return VP_OK;
 }
 
-// The points from bright to faint, to a quarter of an octave (a counting sort
+// The points from faint to bright, to a quarter of an octave (a counting sort
 // on the leading bits; points of one bin keep their order).  The kernels sum
 // points in short FP32 groups, on the matrix cores with roundings of ~1.3 units
 // of the group's largest term: groups of one brightness keep a bright point's
 // rounding off the faint ones' sum (MWA-like points by antenna: 2.1e-7 of the
-// result's norm as given).
+// result's norm as given), and a point much brighter than all others comes last
+// in its group, after which nothing is rounded at its size (first, it costs a
+// rounding for each that follows).  FP64 sums stay small for longest, too.
 static std::vector<int32_t> by_flux(const double *s, int n) {
   constexpr int kBins = 2048 << 2;  // exponent and two bits of the mantissa
   std::vector<int32_t> at(kBins + 1, 0), ord(n);
   auto bin = [&](int i) {
     uint64_t u;
     std::memcpy(&u, &s[i], 8);
-    return kBins - 1 - (int)((u << 1) >> 51);
+    return (int)((u << 1) >> 51);
   };
   for (int i = 0; i < n; ++i) ++at[bin(i) + 1];
   for (int b = 0; b < kBins; ++b) at[b + 1] += at[b];
