@@ -159,7 +159,8 @@ int vp_destroy_obs(vp_obs *obs); /* VP_EBUSY while a pending job uses it */
 /* Copy a sky model to the device.  Host arrays are read during the call and
  * may be freed on return.  Per-(sky, observation) tables (direction cosines,
  * frames, flux per channel, coefficient tiles) are built on the device by the
- * first predict/subtract that pairs them, and cached.  A shapelet is kept to
+ * first predict/subtract that pairs them, and cached (what the precision paths'
+ * kernels need beside them, by the first call on each path).  A shapelet is kept to
  * its effective order, the highest n1 + n2 with a non-zero coefficient
  * (zero coefficients above it contribute nothing; the shapelet kernels' work
  * follows the order, so truncating high orders saves time while truncating
@@ -190,7 +191,7 @@ int vp_predict(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision,
  * cosines, Gaussian quadratic forms, shapelet frames, flux per component and
  * channel) are rebuilt on every call into a fixed scratch array of
  * 64 MiB that the library holds on each device until the process ends (beside
- * it 169 MiB for what those of its kernels need that work by antenna and by nodes),
+ * it 126 MiB for what those of its kernels need that work by antenna and by nodes),
  * instead of being allocated and cached.  Limit: 32 B per component, 32 B
  * per Gaussian, 96 B per shapelet and 12 B per (component, channel padded to
  * a multiple of 8), each part rounded up to 256 B, at most 64 MiB in all

@@ -217,6 +217,44 @@ static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dty
   return ant_us < std::min(node_us, vec_us);
 }
 
+// Whether any mixed call on the pair may take its points by antenna: by nodes
+// allowed or not (use_ant asks for the type on the FP64 path only).
+bool ant_mixed(const vp_sky *sky, const vp_obs *obs) {
+  const NodePlan none{0, 0, 0.0, 0.0};
+  return use_ant(sky, obs, kMixed, VP_C128, node_plan(sky, obs, 2)) || use_ant(sky, obs, kMixed, VP_C128, none);
+}
+
+// The path whose tables by nodes and by antenna a precision works with: 0 mixed,
+// 1 FP64, -1 none.
+static int table_path(int precision) {
+  return precision == kFP32 ? -1 : precision == kFP64 || precision == kLut ? 1 : 0;
+}
+
+// One path's tables by nodes and by antenna, into d.
+static hipError_t alloc_path(const vp_sky *sky, const vp_obs *obs, int path, Derived &d, DeviceMem &mem) {
+  hipError_t e = hipSuccess;
+  for (int i = path; i < kPlans && e == hipSuccess; i += 2) {
+    const NodePlan p = d.plan[i] = node_plan(sky, obs, i);
+    if (p.M == 0) continue;
+    e = mem.alloc((void **)&d.interp[i], plan_bytes(obs, p));
+    if (e == hipSuccess && i >= 2) e = mem.alloc((void **)&d.nflux[i - 2], nflux_bytes(sky, p, i));
+  }
+  if (path == 0 && e == hipSuccess && ant_mixed(sky, obs)) {
+    char *amp = nullptr;
+    e = mem.alloc((void **)&amp, ant_amp_bytes(sky, obs));
+    if (e == hipSuccess) place_amp(d, amp, sky, obs);
+  }
+  return e;
+}
+
+// d with the tables of one path only (-1: of none).
+static Derived of_path(Derived d, int path) {
+  for (int i = 0; i < kPlans; ++i)
+    if (path < 0 || i % 2 != path) d.plan[i].M = 0;
+  if (path != 0) d.amp = nullptr;
+  return d;
+}
+
 static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **out) {
   DerivedEntry *d = new DerivedEntry();
   const int J = sky->P + sky->G + sky->S;
@@ -226,17 +264,6 @@ static int alloc_derived(const vp_sky *sky, const vp_obs *obs, DerivedEntry **ou
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.sframe, sizeof(double) * 12 * Sc);
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.flux32, sizeof(float) * (size_t)Jc * obs->Kpad);
   if (e == hipSuccess) e = d->mem.alloc((void **)&d->d.flux64, sizeof(double) * (size_t)Jc * obs->Kpad);
-  for (int i = 0; i < kPlans && e == hipSuccess; ++i) {
-    const NodePlan p = d->d.plan[i] = node_plan(sky, obs, i);
-    if (p.M == 0) continue;
-    e = d->mem.alloc((void **)&d->d.interp[i], plan_bytes(obs, p));
-    if (e == hipSuccess && i >= 2) e = d->mem.alloc((void **)&d->d.nflux[i - 2], nflux_bytes(sky, p, i));
-  }
-  if (e == hipSuccess && ant_pair(sky, obs)) {
-    char *amp = nullptr;
-    e = d->mem.alloc((void **)&amp, ant_amp_bytes(sky, obs));
-    if (e == hipSuccess) place_amp(d->d, amp, sky, obs);
-  }
   if (e != hipSuccess) {
     d->mem.release();
     delete d;
@@ -279,63 +306,119 @@ static hipError_t build_amp(const vp_sky *sky, const vp_obs *obs, const Derived 
   return launch_ant_amp(a, stream);
 }
 
-int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t stream, bool serving,
-                DerivedEntry **out, bool *built, int *kernels) {
-  const auto key = std::make_pair(sky->id, obs->id);
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  auto it = ctx->derived.find(key);
-  if (built) *built = it == ctx->derived.end();
-  if (kernels) *kernels = 0;
-  if (it != ctx->derived.end()) {
-    DerivedEntry *d = it->second;
-    if (d->ready && d->ready_stream != stream) {
-      hipError_t e = hipStreamWaitEvent(stream, d->ready, 0);
-      if (e != hipSuccess) return hip_error(e, "hipStreamWaitEvent");
-    }
-    if (serving)
-      d->serve_users += 1;
-    else
-      d->serve_built = false;  // a direct call's kernels may read it from now on: never evicted by serving
-    *out = d;
-    return VP_OK;
-  }
-  DerivedEntry *d = nullptr;
-  int rc = alloc_derived(sky, obs, &d);
-  if (rc != VP_OK) return rc;
-  hipError_t e = hipEventCreateWithFlags(&d->ready, hipEventDisableTiming);
-  if (e == hipSuccess) {
-    ProfScope ps(serving ? nullptr : ctx, stream, 0);
-    e = launch_derive(make_derive_args(sky, obs, d->d), stream);
-    if (e == hipSuccess) e = launch_flux(make_flux_args(sky, obs, d->d), stream);
-    if (e == hipSuccess) e = build_amp(sky, obs, d->d, stream);
-    ps.end();
-  }
-  if (e == hipSuccess) e = hipEventRecord(d->ready, stream);
-  if (e != hipSuccess) {
-    if (d->ready) (void)hipEventDestroy(d->ready);
-    d->mem.release();
-    delete d;
-    return hip_error(e, "building per-(sky, observation) tables");
-  }
-  if (kernels) *kernels = (sky->P + sky->G + sky->S > 0 ? 2 : 0) + (d->d.amp ? 2 : 0);
-  d->ready_stream = stream;
-  d->serve_built = serving;
-  d->serve_users = serving ? 1 : 0;
-  ctx->derived[key] = d;
-  ctx->lib_bytes += d->mem.total;
-  *out = d;
-  return VP_OK;
-}
+static uint64_t entry_bytes(const DerivedEntry *d) { return d->mem.total + d->path[0].mem.total + d->path[1].mem.total; }
 
 static void free_entry(vp_ctx *ctx, DerivedEntry *d) {
   // caller holds ctx->mu and has removed d from ctx->derived
-  if (d->ready) {
-    (void)hipEventSynchronize(d->ready);
-    (void)hipEventDestroy(d->ready);
-  }
-  ctx->lib_bytes -= d->mem.total;
+  ctx->lib_bytes -= entry_bytes(d);
+  for (hipEvent_t e : {d->ready, d->path[0].ready, d->path[1].ready})
+    if (e) {
+      (void)hipEventSynchronize(e);
+      (void)hipEventDestroy(e);
+    }
+  d->path[0].mem.release();
+  d->path[1].mem.release();
   d->mem.release();
   delete d;
+}
+
+int get_derived(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, hipStream_t stream, int precision, bool serving,
+                Derived *out, DerivedEntry **entry, int *built, int *kernels) {
+  const auto key = std::make_pair(sky->id, obs->id);
+  const int path = table_path(precision);
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  auto it = ctx->derived.find(key);
+  const bool base = it == ctx->derived.end();
+  DerivedEntry *d = nullptr;
+  if (base) {
+    int rc = alloc_derived(sky, obs, &d);
+    if (rc != VP_OK) return rc;
+  } else {
+    d = it->second;
+  }
+  DerivedEntry::Path *x = path >= 0 ? &d->path[path] : nullptr;
+  hipError_t e = hipSuccess;
+  bool own = false;  // this call builds the path's tables
+  if (x && !x->built) {
+    // Not under capture, where they would be built by the graph: the call then does
+    // without them, as it does without the memory for them.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    own = base || (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone);
+    x->mem.release();
+    if (own && alloc_path(sky, obs, path, d->d, x->mem) != hipSuccess) {
+      x->mem.release();
+      own = false;
+    }
+    if (!own) (void)hipGetLastError();
+  }
+  // before the path's tables, too: the amplitudes come from the components' fluxes
+  if (!base && d->ready_stream != stream) e = hipStreamWaitEvent(stream, d->ready, 0);
+  if (e == hipSuccess && !own && x && x->built && x->ready && x->ready_stream != stream)
+    e = hipStreamWaitEvent(stream, x->ready, 0);
+  if (e != hipSuccess) {
+    if (own) x->mem.release();
+    return hip_error(e, "hipStreamWaitEvent");
+  }
+  int n = 0;
+  if (base || own) {
+    const Derived part = of_path(d->d, own ? path : -1);
+    DeriveArgs da = make_derive_args(sky, obs, part);
+    FluxArgs fa = make_flux_args(sky, obs, part);
+    bool any = base && fa.J > 0;
+    for (int i = 0; i < kPlans; ++i) any = any || part.plan[i].M > 0;
+    if (!base) {  // the components' own are there, and may be being read
+      da.P = da.G = da.S = 0;
+      fa.J = 0;
+    }
+    ProfScope ps(serving || !(any || part.amp) ? nullptr : ctx, stream, 0);
+    if (any) {
+      e = launch_derive(da, stream);
+      if (e == hipSuccess) e = launch_flux(fa, stream);
+      n += 2;
+    } else if (part.amp) {
+      e = launch_flux(fa, stream);  // (clears the peaks)
+      n += 1;
+    }
+    if (e == hipSuccess && part.amp) {
+      e = build_amp(sky, obs, part, stream);
+      n += 2;
+    }
+    ps.end();
+    if (e == hipSuccess && base) {
+      e = hipEventCreateWithFlags(&d->ready, hipEventDisableTiming);
+      if (e == hipSuccess) e = hipEventRecord(d->ready, stream);
+      d->ready_stream = stream;
+    } else if (e == hipSuccess && n > 0) {
+      if (!x->ready) e = hipEventCreateWithFlags(&x->ready, hipEventDisableTiming);
+      if (e == hipSuccess) e = hipEventRecord(x->ready, stream);
+      x->ready_stream = stream;
+    }
+    if (e != hipSuccess) {
+      (void)hipStreamSynchronize(stream);
+      if (base) {
+        ctx->lib_bytes += entry_bytes(d);  // (free_entry takes it off)
+        free_entry(ctx, d);
+      } else {
+        x->mem.release();
+      }
+      return hip_error(e, "building per-(sky, observation) tables");
+    }
+    if (own) x->built = true;
+    ctx->lib_bytes += base ? entry_bytes(d) : x->mem.total;
+  }
+  if (base) {
+    d->serve_built = serving;
+    ctx->derived[key] = d;
+  }
+  if (serving)
+    d->serve_users += 1;
+  else
+    d->serve_built = false;  // a direct call's kernels may read it from now on: never evicted by serving
+  if (built) *built = (base ? kBuiltBase : 0) | (own ? kBuiltPath : 0);
+  if (kernels) *kernels = n;
+  *out = of_path(d->d, x && x->built ? path : -1);
+  if (entry) *entry = d;
+  return VP_OK;
 }
 
 void serve_release_derived(vp_ctx *ctx, DerivedEntry *d) {
@@ -343,9 +426,15 @@ void serve_release_derived(vp_ctx *ctx, DerivedEntry *d) {
   d->serve_users -= 1;
 }
 
-void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d) {
+void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d, int built) {
   std::lock_guard<std::mutex> lk(ctx->mu);
   d->serve_users -= 1;
+  if (!(built & kBuiltBase)) {
+    ctx->lib_bytes -= d->path[0].mem.total;
+    d->path[0].built = false;  // serving is mixed; the next call builds them anew
+    d->path[0].mem.release();
+    return;
+  }
   for (auto it = ctx->derived.begin(); it != ctx->derived.end(); ++it)
     if (it->second == d) {
       ctx->derived.erase(it);
@@ -358,7 +447,7 @@ uint64_t serve_evictable_bytes(vp_ctx *ctx) {
   std::lock_guard<std::mutex> lk(ctx->mu);
   uint64_t b = 0;
   for (auto &kv : ctx->derived)
-    if (kv.second->serve_built && kv.second->serve_users == 0) b += kv.second->mem.total;
+    if (kv.second->serve_built && kv.second->serve_users == 0) b += entry_bytes(kv.second);
   return b;
 }
 
@@ -379,14 +468,9 @@ void drop_derived(vp_ctx *ctx, uint64_t sky_id, uint64_t obs_id) {
   // caller holds ctx->mu; an id of 0 matches nothing
   for (auto it = ctx->derived.begin(); it != ctx->derived.end();) {
     if ((sky_id && it->first.first == sky_id) || (obs_id && it->first.second == obs_id)) {
-      if (it->second->ready) {
-        (void)hipEventSynchronize(it->second->ready);
-        (void)hipEventDestroy(it->second->ready);
-      }
-      ctx->lib_bytes -= it->second->mem.total;
-      it->second->mem.release();
-      delete it->second;
+      DerivedEntry *d = it->second;
       it = ctx->derived.erase(it);
+      free_entry(ctx, d);
     } else {
       ++it;
     }
@@ -395,15 +479,7 @@ void drop_derived(vp_ctx *ctx, uint64_t sky_id, uint64_t obs_id) {
 
 void drop_all_derived(vp_ctx *ctx) {
   // caller holds ctx->mu
-  for (auto &kv : ctx->derived) {
-    if (kv.second->ready) {
-      (void)hipEventSynchronize(kv.second->ready);
-      (void)hipEventDestroy(kv.second->ready);
-    }
-    ctx->lib_bytes -= kv.second->mem.total;
-    kv.second->mem.release();
-    delete kv.second;
-  }
+  for (auto &kv : ctx->derived) free_entry(ctx, kv.second);
   ctx->derived.clear();
 }
 
@@ -667,8 +743,8 @@ int launch_passes(vp_ctx *prof, const vp_sky *sky, const vp_obs *obs, int precis
 
 int run_tiles(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis,
               int subtract, hipStream_t stream, bool nodes) {
-  DerivedEntry *d = nullptr;
-  int rc = get_derived(ctx, sky, obs, stream, false, &d);
+  Derived d;
+  int rc = get_derived(ctx, sky, obs, stream, precision, false, &d);
   if (rc != VP_OK) return rc;
   const float *lut = nullptr;
   if (precision == kLut && sky->S > 0) {
@@ -676,9 +752,9 @@ int run_tiles(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, 
     if (rc != VP_OK) return rc;
   }
   SumsLease lease;
-  const uint64_t want = sums_bytes(sky, obs, precision, dtype, d->d, nodes);
+  const uint64_t want = sums_bytes(sky, obs, precision, dtype, d, nodes);
   const SumsSpace sums = want ? lease.take(ctx->sums, want, stream) : SumsSpace{nullptr, 0};
-  return launch_passes(ctx, sky, obs, precision, dtype, vis, subtract, stream, d->d, lut, sums, nullptr, nodes);
+  return launch_passes(ctx, sky, obs, precision, dtype, vis, subtract, stream, d, lut, sums, nullptr, nodes);
 }
 
 int check_call(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int precision, int dtype, void *vis) {
@@ -1170,15 +1246,15 @@ int vp_predict_noalloc(vp_ctx *ctx, const vp_sky *sky, const vp_obs *obs, int pr
   d.flux32 = (float *)(base + o_f32);
   d.flux64 = (double *)(base + o_f64);
   char *part = base + kNoAllocScratchBytes + kNoAllocAmpBytes;
-  for (int i = 0; i < kPlans; ++i) {
+  const int path = table_path(precision);
+  for (int i = path; path >= 0 && i < kPlans; i += 2) {
     d.plan[i] = node_plan(sky, obs, i);
-    if (nflux_bytes(sky, d.plan[i], i) > kNoAllocNfluxBytes / 2) d.plan[i].M = 0;
-    d.interp[i] = (double *)(part + i * (kNoAllocNodeBytes / kPlans));
-    if (i >= 2) d.nflux[i - 2] = (double *)(part + kNoAllocNodeBytes + (i - 2) * (kNoAllocNfluxBytes / 2));
+    if (nflux_bytes(sky, d.plan[i], i) > kNoAllocNfluxBytes) d.plan[i].M = 0;
+    d.interp[i] = (double *)(part + i / 2 * (kNoAllocNodeBytes / 2));
+    if (i >= 2) d.nflux[i - 2] = (double *)(part + kNoAllocNodeBytes);
   }
-  const bool f64 = precision == kFP64;
-  const bool ant = !f64 && use_ant(sky, obs, precision, dtype, precision == kFP32 ? NodePlan{0, 0, 0.0, 0.0} : d.plan[2]);
-  if (ant && ant_amp_bytes(sky, obs) <= kNoAllocAmpBytes) place_amp(d, base + kNoAllocScratchBytes, sky, obs);
+  if (path == 0 && use_ant(sky, obs, precision, dtype, d.plan[2]) && ant_amp_bytes(sky, obs) <= kNoAllocAmpBytes)
+    place_amp(d, base + kNoAllocScratchBytes, sky, obs);
   const hipStream_t stream = (hipStream_t)hip_stream;
   // every entry the tile kernels read is written here first (the flux table
   // includes its zero padding), so nothing is cleared

@@ -253,17 +253,18 @@ void *noalloc_scratch(int dev);
 // Size of that array: per-(sky, observation) tables of vp_predict_noalloc.
 constexpr uint64_t kNoAllocScratchBytes = 64ull << 20;
 // A second part of the array, behind the first, holds the points' amplitudes
-// by antenna: 4 of the 12 bytes per (component, channel) above, and less than
-// twice the points in padding, so that no pair the first part takes exceeds it.
-constexpr uint64_t kNoAllocAmpBytes = 48ull << 20;
-// A third part holds the interpolation tables of both paths (at most
-// kNodesMaxChan channels x kNodesStride nodes each).
-constexpr uint64_t kNoAllocNodeBytes = (uint64_t)kPlans * (kNodesMaxChan + 16) * kNodesStride * 8;
-// A fourth, points' and Gaussians' fluxes at the nodes, half for each path: room
-// for every pair that the tables hold (12 bytes per component and padded channel
-// in 64 MiB, 8 per component and node, at most half as many nodes as padded
-// channels), so that the calls take the same kernels as vp_predict.
-constexpr uint64_t kNoAllocNfluxBytes = 48ull << 20;
+// by antenna: 4 of the 12 bytes per (component, channel) above for the points
+// padded to 32 (of 64 at the least) and 16 a channel, 6.2 bytes in place of 12,
+// so that no pair the first part takes exceeds it.
+constexpr uint64_t kNoAllocAmpBytes = 34ull << 20;
+// A third part holds the interpolation tables of one path, shapelets' and points'
+// (at most kNodesMaxChan channels x kNodesStride nodes each).
+constexpr uint64_t kNoAllocNodeBytes = (uint64_t)kPlans / 2 * (kNodesMaxChan + 16) * kNodesStride * 8;
+// A fourth, points' and Gaussians' fluxes at its nodes: room for every pair that the
+// tables hold (12 bytes per component and padded channel in 64 MiB, 8 per
+// component and node, at most half as many nodes as padded channels), so that the
+// calls take the same kernels as vp_predict.
+constexpr uint64_t kNoAllocNfluxBytes = 24ull << 20;
 
 // A fifth, the points' sums on their way to the Gaussians (kSumsMin bytes).
 

@@ -297,9 +297,9 @@ __device__ __forceinline__ double flux_at(const FluxArgs &a, int j, double nu) {
 __global__ void k_flux(FluxArgs a) {
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = (int64_t)a.J * a.Kpad;
+  if (a.d.amp && idx < a.Kpad) a.d.amp_peak[idx] = 0.0;  // k_ant_peak, next on the stream, takes the maximum
   if (idx < n) {
     const int j = (int)(idx / a.Kpad), k = (int)(idx % a.Kpad);
-    if (j == 0 && a.d.amp) a.d.amp_peak[k] = 0.0;  // k_ant_peak, next on the stream, takes the maximum
     const double S = k < a.K ? flux_at(a, j, a.freq[k]) : 0.0;
     a.d.flux32[idx] = (float)S;
     a.d.flux64[idx] = S;
@@ -2087,9 +2087,9 @@ static hipError_t upload_tables() {
 
 hipError_t launch_derive(const DeriveArgs &a, hipStream_t s) {
   const int J = a.P + a.G + a.S;
-  if (J == 0) return hipSuccess;
   int rows = 0;
   for (const NodePlan &p : a.d.plan) rows += p.M > 0 ? (a.K + 15) / 16 * 16 : 0;
+  if (J == 0 && rows == 0) return hipSuccess;
   hipLaunchKernelGGL(k_derive, dim3((J + 127) / 128 + (rows + 1) / 2), dim3(128), 0, s, a);
   return hipGetLastError();
 }
@@ -2098,6 +2098,7 @@ hipError_t launch_flux(const FluxArgs &a, hipStream_t s) {
   int64_t n = (int64_t)a.J * a.Kpad;
   for (int i = 0; i < 2; ++i)
     if (a.d.plan[2 + i].M > 0) n += (int64_t)a.j0 * a.d.plan[2 + i].Mp;
+  if (a.d.amp) n = std::max<int64_t>(n, a.Kpad);
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_flux, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();

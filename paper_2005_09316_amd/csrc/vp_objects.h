@@ -82,6 +82,14 @@ struct DerivedEntry {
   DeviceMem mem;
   hipEvent_t ready = nullptr;  // recorded after the kernels that build the tables
   hipStream_t ready_stream = nullptr;
+  // What one path's kernels by nodes and by antenna need beside the components'
+  // own: [0] mixed, [1] FP64, each built by the first call that works on it.
+  struct Path {
+    DeviceMem mem;
+    bool built = false;
+    hipEvent_t ready = nullptr;  // null: built with the components' own
+    hipStream_t ready_stream = nullptr;
+  } path[2];
   bool serve_built = false;    // built for serving and not handed to a direct call since (guarded by ctx->mu)
   int serve_users = 0;         // admitted serving jobs that use the tables (guarded by ctx->mu)
 };
@@ -139,18 +147,21 @@ int launch_passes(vp_ctx *prof, const struct ::vp_sky *sky, const struct ::vp_ob
 // several), 0 when it needs none.
 uint64_t sums_bytes(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype, const Derived &d,
                     bool nodes = true);
-// Per-(sky, observation) tables, built on `stream` at first use and cached;
-// later callers on other streams wait for the build.  serving: the caller is
-// an admitted job, counted in the entry's users until serve_release_derived.
-// *built (when given): whether this call enqueued the build, *kernels: of how many
-// kernels.
-int get_derived(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, hipStream_t stream, bool serving,
-                DerivedEntry **out, bool *built = nullptr, int *kernels = nullptr);
+// Per-(sky, observation) tables, built on `stream` at first use and cached, those
+// by nodes and by antenna for the path that `precision` works on; later callers on
+// other streams wait for the build.  *out: the tables as this call may use them
+// (without a path's, which a capture or short memory kept from being built, the
+// call goes by channels and rows).  serving: the caller is an admitted job, counted
+// in the entry's users until serve_release_derived.  *built (when given): what this
+// call enqueued the build of, *kernels: in how many kernels.
+constexpr int kBuiltBase = 1, kBuiltPath = 2;
+int get_derived(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *obs, hipStream_t stream, int precision,
+                bool serving, Derived *out, DerivedEntry **entry = nullptr, int *built = nullptr, int *kernels = nullptr);
 // A serving job is done with the pair's tables.
 void serve_release_derived(vp_ctx *ctx, DerivedEntry *d);
 // The tables a serving job was to build may never have been built (its work
 // was abandoned): drop them, so that no later call finds them ready.
-void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d);
+void serve_abandon_derived(vp_ctx *ctx, DerivedEntry *d, int built);
 // Bytes of tables that serving jobs built and no admitted job or direct call
 // uses, and their release (hipFree: waits for the device).
 uint64_t serve_evictable_bytes(vp_ctx *ctx);
@@ -160,10 +171,12 @@ NodePlan node_plan(const struct ::vp_sky *sky, const struct ::vp_obs *obs, int i
 // Bytes of a plan's tables: nodes and interpolation, and the fluxes at the nodes.
 uint64_t plan_bytes(const struct ::vp_obs *obs, const NodePlan &p);
 uint64_t nflux_bytes(const struct ::vp_sky *sky, const NodePlan &p, int i);
-// Whether the pair's points may be taken by antenna, on any path (a property of
-// the pair: its tables then hold the amplitudes, Jp x Kpad of them, and two
-// doubles a channel beside them).
+// Whether the pair's points may be taken by antenna on the mixed paths, were it the
+// faster.  Its tables then hold the amplitudes, Jp x Kpad of them, and two doubles a
+// channel beside them.
 bool ant_pair(const struct ::vp_sky *sky, const struct ::vp_obs *obs);
+// Whether a mixed call on the pair may do so.
+bool ant_mixed(const struct ::vp_sky *sky, const struct ::vp_obs *obs);
 int ant_jp(const struct ::vp_sky *sky);
 uint64_t ant_amp_bytes(const struct ::vp_sky *sky, const struct ::vp_obs *obs);
 DeriveArgs make_derive_args(const struct ::vp_sky *sky, const struct ::vp_obs *obs, const Derived &d);

@@ -36,7 +36,7 @@ namespace vp {
 
 static uint64_t node_table_bytes(const vp_sky *sky, const vp_obs *obs) {
   uint64_t b = 0;
-  for (int i = 0; i < kPlans; ++i) {
+  for (int i = 0; i < kPlans; i += 2) {  // (serving is mixed)
     const NodePlan p = node_plan(sky, obs, i);
     b += plan_bytes(obs, p) + nflux_bytes(sky, p, i);
   }
@@ -48,7 +48,7 @@ uint64_t job_footprint(const vp_sky *sky, const vp_obs *obs, int dtype) {
   const uint64_t J = (uint64_t)sky->P + sky->G + sky->S;
   const uint64_t tables = 32 * (J ? J : 1) + 32 * (sky->G ? sky->G : 1) + 96 * (sky->S ? sky->S : 1) +
                           12 * (J ? J : 1) * (uint64_t)obs->Kpad +
-                          node_table_bytes(sky, obs) + (ant_pair(sky, obs) ? ant_amp_bytes(sky, obs) : 0);
+                          node_table_bytes(sky, obs) + (ant_mixed(sky, obs) ? ant_amp_bytes(sky, obs) : 0);
   return nvis * (dtype == VP_C64 ? 8 : 16) + tables;
 }
 
@@ -79,7 +79,7 @@ struct JobExt {
   uint64_t seq = 0;        // the job's sequence number in its slot's marks
   int kernels = 0;         // kernels launched for it
   DerivedEntry *d = nullptr;
-  bool built = false;      // this job enqueued the build of the pair's tables
+  int built = 0;           // what this job enqueued the build of (kBuiltBase, kBuiltPath)
   uint64_t floor = 0;      // SpanUnion's, from its admission
 };
 
@@ -132,7 +132,8 @@ int HipExecutor::admit(CoreJob &j) {
   hipStream_t st = streams[si];
   TraceRange tr("vp_serve: job");
   DerivedEntry *d = nullptr;
-  int rc = get_derived(ctx, x.job.sky, x.job.obs, st, true, &d, &x.built, &x.kernels);
+  Derived tables;
+  int rc = get_derived(ctx, x.job.sky, x.job.obs, st, x.job.precision, true, &tables, &d, &x.built, &x.kernels);
   if (rc != VP_OK) return rc;
   const int slot = free_slots.back();
   hipError_t e = hipSuccess;
@@ -143,10 +144,10 @@ int HipExecutor::admit(CoreJob &j) {
     rc = hip_error(e, "starting a serving job");
   } else {
     SumsLease lease;
-    const uint64_t want = sums_bytes(x.job.sky, x.job.obs, x.job.precision, x.job.dtype, d->d);
+    const uint64_t want = sums_bytes(x.job.sky, x.job.obs, x.job.precision, x.job.dtype, tables);
     const SumsSpace sums = want ? lease.take(ctx->sums, want, st) : SumsSpace{nullptr, 0};
     rc = launch_passes(nullptr, x.job.sky, x.job.obs, x.job.precision, x.job.dtype, x.job.vis_dev,
-                       x.job.kind == VP_JOB_SUBTRACT, st, d->d, nullptr, sums, &x.kernels);
+                       x.job.kind == VP_JOB_SUBTRACT, st, tables, nullptr, sums, &x.kernels);
   }
   if (rc == VP_OK) {
     e = launch_mark(&H_dev->finished[slot], x.seq, st);
@@ -234,7 +235,7 @@ void HipExecutor::abandon(const std::vector<CoreJob *> &running, int rc) {
   for (CoreJob *j : running)
     if (!ext(*j).built) serve_release_derived(ctx, ext(*j).d);
   for (CoreJob *j : running)
-    if (ext(*j).built) serve_abandon_derived(ctx, ext(*j).d);
+    if (ext(*j).built) serve_abandon_derived(ctx, ext(*j).d, ext(*j).built);
   for (CoreJob *j : running) {
     free_slots.push_back(ext(*j).slot);
     --in_flight[ext(*j).stream];
