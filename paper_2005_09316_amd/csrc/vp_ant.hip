@@ -875,8 +875,7 @@ hipError_t launch_ant_amp(const AntAmpArgs &a, hipStream_t s) {
 
 template <int ITEMS, bool NEG, bool FINE>
 static hipError_t launch_ant_mixed(const AntArgs &a, int nt, size_t sm, hipStream_t s) {
-  hipError_t e = hipFuncSetAttribute((const void *)k_ant_mixed<ITEMS, NEG, FINE>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds((const void *)k_ant_mixed<ITEMS, NEG, FINE>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_ant_mixed<ITEMS, NEG, FINE>), dim3((unsigned)nt), dim3(64 * kAntWaves), sm, s, a);
   return hipGetLastError();
@@ -899,8 +898,7 @@ hipError_t launch_ant(const AntArgs &a, hipStream_t s) {
 
 template <int ITEMS, bool NEG>
 static hipError_t launch_ant_fp64(const AntArgs &a, int nt, size_t sm, hipStream_t s) {
-  hipError_t e =
-      hipFuncSetAttribute((const void *)k_ant_fp64<ITEMS, NEG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds((const void *)k_ant_fp64<ITEMS, NEG>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_ant_fp64<ITEMS, NEG>), dim3((unsigned)nt), dim3(64 * kAntWaves), sm, s, a);
   return hipGetLastError();

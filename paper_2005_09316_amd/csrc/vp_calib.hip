@@ -1064,8 +1064,7 @@ size_t gain_smem_bytes(int n_ant, bool w64, int threads) {
 template <typename WT, int NT>
 static hipError_t launch_solve(const GainArgs &a, hipStream_t s) {
   const size_t sm = gain_smem_bytes(a.n_ant, sizeof(WT) == sizeof(double), NT);
-  hipError_t e = hipFuncSetAttribute((const void *)k_gain_solve<WT, NT>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds((const void *)k_gain_solve<WT, NT>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_gain_solve<WT, NT>), dim3((unsigned)a.ncell), dim3(NT), sm, s, a);
   return hipGetLastError();
@@ -1109,8 +1108,7 @@ size_t gain_rw_smem_bytes(int nw) {
 template <int NW, int RPL>
 static hipError_t launch_solve_wide(const GainArgs &a, hipStream_t s) {
   const size_t sm = gain_rw_smem_bytes(NW);
-  hipError_t e =
-      hipFuncSetAttribute((const void *)k_gain_solve_wide<NW, RPL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds((const void *)k_gain_solve_wide<NW, RPL>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_gain_solve_wide<NW, RPL>), dim3((unsigned)a.ncell), dim3(64 * NW), sm, s, a);
   return hipGetLastError();
@@ -1123,8 +1121,7 @@ static hipError_t launch_solve_pairs(const GainArgs &a, hipStream_t s) {
   const size_t sm = ROWS * (2 * NW * sizeof(TT2) + sizeof(double2) + sizeof(double) + sizeof(TT2) + sizeof(int)) +
                     ((size_t)a.n_ant * (a.n_ant - 1) / 2 + 1) * sizeof(TT2);
   static_assert(NW * ROWS * sizeof(double2) <= 2 * NW * ROWS * sizeof(TT2), "one buffer serves both sums");
-  hipError_t e = hipFuncSetAttribute((const void *)k_gain_solve_rw<TT, NW, RPL>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds((const void *)k_gain_solve_rw<TT, NW, RPL>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_gain_solve_rw<TT, NW, RPL>), dim3((unsigned)a.ncell), dim3(64 * NW), sm, s, a);
   return hipGetLastError();

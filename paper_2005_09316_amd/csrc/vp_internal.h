@@ -162,6 +162,13 @@ struct TileArgs {
                        //    predict with no point/Gaussian pass before it)
 };
 
+// Lets a kernel without LDS of its own be launched with up to a CU's whole.  The
+// setting is the kernel's, for every thread and context that launches it: always the
+// same value, so that a launch never meets another's smaller one.
+inline hipError_t whole_lds(const void *kernel) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
+}
+
 // Whether HIP takes a grid of so many workgroups (its threads are counted in 32 bits).
 inline bool grid_fits(int64_t blocks, int threads) { return blocks <= 0xffffffffll / threads; }
 constexpr int64_t kNodesMaxRows = 1ll << 28;  // so many, by nodes, whatever rows a workgroup takes (16 x 256 threads at the least)

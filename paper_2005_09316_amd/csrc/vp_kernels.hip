@@ -2273,7 +2273,7 @@ hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
   if (nt > 0x7fffffff) return hipErrorInvalidValue;
   const size_t sm = sizeof(PgNodeLds) + (size_t)kChunk * kPgNB * nw * (f64 ? 8 : 4) + (size_t)2 * p.Mp * LR * 8;
   const void *k = f64 ? (const void *)k_pg_nodes<true, true> : (const void *)k_pg_nodes<false, true>;
-  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds(k);
   if (e != hipSuccess) return e;
   if (f64)
     hipLaunchKernelGGL((k_pg_nodes<true, true>), dim3((unsigned)nt), dim3(64 * nw), sm, s, a, LR, 1);
@@ -2294,7 +2294,7 @@ static hipError_t launch_pg_small(const TileArgs &a, bool f64, hipStream_t s) {
   const dim3 g((unsigned)((a.nrows + LR - 1) / LR), (unsigned)ny), b(64 * nw * CS);
   const size_t sm = sizeof(PgNodeLds) + (size_t)kChunk * kPgNB * nw * (f64 ? 8 : 4) + (size_t)2 * (CS - 1) * nw * kPgNB * LR * 8;
   const void *k = f64 ? (const void *)k_pg_nodes<true, false> : (const void *)k_pg_nodes<false, false>;
-  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds(k);
   if (e != hipSuccess) return e;
   if (f64)
     hipLaunchKernelGGL((k_pg_nodes<true, false>), g, b, sm, s, a, LR, CS);
@@ -2309,7 +2309,7 @@ bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) {
 
 template <typename K, typename... A>
 static hipError_t launch_node_kernel(K k, unsigned grid, size_t sm, hipStream_t s, A... args) {
-  hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+  hipError_t e = whole_lds((const void *)k);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(grid), dim3(kNodeThreads), sm, s, args...);
   return hipGetLastError();
