@@ -84,43 +84,20 @@ void DeviceMem::release() {
 // derived (sky, obs) tables
 // ---------------------------------------------------------------------------
 
-// Shapelets by nodes where that saves a sixth of the envelopes or more: a
-// channel's interpolation, phase and flux cost about 0.035 of an envelope.
-// (The highest order's nodes serve all of the sky's shapelets.)
 static int shapelet_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
-  if (sky->S == 0) return 0;
-  const int M = shp_nodes(sky->max_nmax, obs->f_lo, obs->f_hi, i == 0 ? kNodesTolMixed : kNodesTolFp64);
-  if (M + 0.035 * obs->K > 0.85 * obs->K) return 0;
-  // Nor where the channels' own tiles run side by side, all in a first round of
-  // two workgroups per CU (513 rows x 201 channels, order 92, FP64: 93 us, by nodes
-  // 101).
-  const int64_t n_rb = ((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows;
-  if (n_rb * (i == 0 ? obs->K : (obs->K + kShpChan - 1) / kShpChan) <= 512) return 0;
-  return shp_nodes_fit(i == 0 ? kMixed : kFP64, sky->max_nmax, sky->S, (M + 3) / 4 * 4) ? M : 0;
+  double size = 0.0;
+  for (int j = 0; j < sky->S; ++j) size += shp_size(i == 0 ? kMixed : kFP64, sky->h_nmax[j]);
+  return shp_plan_nodes(i == 1, sky->S, sky->max_nmax, size, obs->f_lo, obs->f_hi, (int64_t)obs->T * obs->B, obs->K);
 }
 
-// Points and Gaussians by nodes where three channels or more go to a node.  A
-// row's phase per component is at most its length times the distance between the
-// component's direction and the phase centre, bounded here through the sky's middle.
 static int pg_sum_nodes(const vp_sky *sky, const vp_obs *obs, int i) {
-  if (sky->P + sky->G == 0 || obs->K < 12) return 0;
-  const double half = 0.5 * (obs->f_hi - obs->f_lo) / kLightSpeed, mid = 0.5 * (obs->f_lo + obs->f_hi) / kLightSpeed;
+  // the furthest direction, bounded through the sky's middle:
   // |s - s'|^2 = 4 sin^2(d dec / 2) + 4 cos(dec) cos(dec') sin^2(d ra / 2)
   const double sd = std::sin(0.5 * (sky->pg_dec - obs->dec0)), sa = std::sin(0.5 * (sky->pg_ra - obs->ra0));
   const double to_mid = 2.0 * std::sqrt(sd * sd + std::fabs(std::cos(sky->pg_dec) * std::cos(obs->dec0)) * sa * sa);
-  const double apart = std::min(2.0, to_mid + sky->pg_reach);  // of unit vectors
-  const double reach = obs->b_max * apart * (1.0 + 1e-9);
-  if (!(reach * obs->f_hi / kLightSpeed <= 262144.0)) return 0;  // the mixed kernel's phases are fixed-point, up to 2^19 turns
-  const double w = 6.283185307179586477 * reach * half, delta = half / mid;
-  double beam = 0.0;  // exponent of the beam, furthest component, middle of the band (see flux_at)
-  if (obs->beam_fwhm > 0.0) {
-    const double rho = std::min(1.57079632679489662, 2.0 * std::asin(0.5 * apart) * (1.0 + 1e-9));
-    const double x = rho * mid * kLightSpeed / (obs->beam_fwhm * obs->beam_nu_ref);
-    beam = 4.0 * 0.69314718055994530942 * x * x;
-  }
-  if (!(pg_spread(delta, sky->pg_amax, beam) <= (i == 2 ? kPgSpreadMixed : kPgSpreadFp64))) return 0;
-  const int M = pg_nodes(w, delta, sky->pg_amax, i == 2 ? kNodesTolMixed : kNodesTolFp64, beam);
-  return 3 * M <= obs->K ? M : 0;
+  return pg_plan_nodes(i == 3, sky->P, sky->G, std::min(2.0, to_mid + sky->pg_reach), obs->b_max, sky->pg_amax, obs->f_lo,
+                       obs->f_hi, obs->beam_fwhm, obs->beam_nu_ref, (int64_t)obs->T * obs->B, obs->K,
+                       i == 3 ? obs->uniform64 : obs->uniform);
 }
 
 NodePlan node_plan(const vp_sky *sky, const vp_obs *obs, int i) {

@@ -5,37 +5,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dispatch.h"
+
 namespace vp {
 
-constexpr double kLightSpeed = 299792458.0;  // m/s
-
-// Tile geometry.  A tile is kTileRows consecutive (time, baseline) rows times
-// a block of channels; one workgroup of kTileRows threads processes a tile.
-constexpr int kTileRows = 256;
-constexpr int kPgChan = 8;     // channels per point/Gaussian tile (per thread)
-constexpr int kShpChan = 4;    // channels per shapelet tile
-constexpr int kChunk = 64;     // components staged in LDS at a time
-constexpr int kFlush = 8;      // components summed plainly before a Kahan step
-constexpr int kFlushMixed = 16; // mixed path: components per FP64 add (two kFlush partials, summed in FP32)
-constexpr int kNmaxLimit = 96; // largest n1 + n2
-constexpr int kMBMax = 4;      // 32-row blocks of the n1 axis: ceil(97 / 32)
-
-// The MFMA shapelet kernels keep only the 32 x 32 blocks of the signed
-// coefficient matrix (32 rows of n1 by 32 orders of n2) that meet the
-// triangle n1 + n2 <= N: block (chunk ch, row block mb) with
-// 32 (ch + mb) <= N, chunk-major.  With q = N / 32 there are
-// (q + 1)(q + 2) / 2 of them.
-__host__ __device__ inline int shp_pairs(int nmax) {
-  const int q = nmax / 32;
-  return (q + 1) * (q + 2) / 2;
-}
 constexpr int kPairsMax = (kNmaxLimit / 32 + 1) * (kNmaxLimit / 32 + 2) / 2;
 constexpr int kA32PerPair = 2 * 8 * 64;  // floats: [parity][K step of 2 orders][lane]
-constexpr int kAbfPerPair = 2 * 64 * 8;  // BF16 values of one split part: [parity][lane][8]
-
-// Precision paths, numbered as VP_PREC_*; 5 (the FP32-MFMA contraction of the
-// mixed path) is retired and refused at the boundary.
-enum Prec : int { kFP64 = 0, kMixed = 1, kMixedBf16 = 2, kFP32 = 3, kMixedBf16x2 = 4, kLut = 6 };
 
 // Lookup table of the basis (the lookup-table variant): kLutSamples + 2 rows
 // of kLutStride FP32 values.
@@ -128,7 +103,6 @@ struct TileBuildArgs {
   const int64_t *abf_off;
 };
 
-constexpr int kPgSplitTiles = 640;  // up to this many tiles of points and Gaussians, the components are split too
 constexpr int kOutPoints = 4;  // points that may go along with the outputs of shapelets by nodes
 
 // Arguments common to the visibility tile kernels.
@@ -283,7 +257,6 @@ hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s);
 hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s);
 hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s);
 hipError_t launch_shp_nodes(const TileArgs &a, const NodePlan &p, int prec, int max_nmax, hipStream_t s);
-bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp);
 hipError_t launch_lut_build(float *T, hipStream_t s);
 hipError_t launch_ant_amp(const AntAmpArgs &a, hipStream_t s);
 hipError_t launch_ant(const AntArgs &a, hipStream_t s);

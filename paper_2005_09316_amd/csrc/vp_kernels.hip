@@ -45,6 +45,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -1392,7 +1393,6 @@ __device__ __forceinline__ void lut_chunk(const LutPos &q, int n0, float (&v)[32
 
 // Second-axis orders per chunk of the FP64 recurrence path: the values of a
 // chunk for the tile's four channels (4 x 16 FP64) stay in registers.
-constexpr int kF64Chunk = 16;
 
 // The envelopes of shapelet j (order N) at the four frequencies f4 (nu / c) of
 // this thread's row; sC: the workgroup's chunk of coefficients.  Every thread of
@@ -1661,9 +1661,6 @@ __global__ __launch_bounds__(kTileRows) __attribute__((amdgpu_waves_per_eu(2))) 
 // of an envelope.
 typedef double double4w __attribute__((ext_vector_type(4)));
 
-// Doubles of LDS the node values of S shapelets take.
-__host__ __device__ inline size_t node_lds(int S, int Mp, int R) { return (size_t)S * 2 * Mp * R; }
-
 __device__ __forceinline__ void node_outputs(const TileArgs &a, int Mp, const double *tab, const double *xs, int R,
                                              int64_t row0, int wave, int nwaves) {
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
@@ -1724,8 +1721,6 @@ __device__ __forceinline__ void node_outputs(const TileArgs &a, int Mp, const do
     vis_put4(a, wide, !a.fresh, row * a.K + k, a.K - k, sre, sim);
   }
 }
-
-constexpr int kNodeThreads = 256;
 
 template <int CM>
 __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_shp_nodes(
@@ -1830,7 +1825,6 @@ __global__ __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)
 // channels, 4,540 points 1.85 ms for 10.7 (1.75 by antenna); FP64 6.4 and 11.1 ms
 // for 19.6 and 30.6.  Six nodes a lane hold five waves a SIMD (96 registers);
 // at four, 1,016 workgroups took two rounds: 1.43 ms and 2.57.
-constexpr int kPgNB = 6;
 // Waves of a workgroup, at most.
 constexpr int pg_node_waves(bool f64, bool nodes) { return nodes || f64 ? kPgNodesMax / kPgNB : 16; }
 
@@ -2111,18 +2105,7 @@ hipError_t launch_tiles_build(const TileBuildArgs &a, int max_nmax, hipStream_t 
   return hipGetLastError();
 }
 
-// Whether an observation is so small that rows, channels and components are all
-// split (k_pg_nodes over channels).  1,000 Gaussians, us each, against the tiles
-// with split components: mixed, 2 tiles 0.040 for 0.068, 32 tiles 0.064 for
-// 0.069, 128 tiles 0.21 for 0.12; FP64, where the tiles rotate phasors between
-// channels, 0.13 for 0.15, then 0.26 for 0.15, and on irregular channels 0.26 for
-// 0.34 at 32 tiles.
 static int64_t pg_tiles(const TileArgs &a) { return (a.call_rows + kTileRows - 1) / kTileRows * (a.Kpad / kPgChan); }
-static bool pg_small(const TileArgs &a, int prec) {
-  const int64_t nt = pg_tiles(a);
-  if (prec == kFP64 || prec == kLut) return nt <= (a.uniform ? 4 : 64);
-  return prec != kFP32 && nt <= 40;
-}
 static hipError_t launch_pg_small(const TileArgs &a, bool f64, hipStream_t s);
 
 hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s) {
@@ -2131,11 +2114,10 @@ hipError_t launch_pg(const TileArgs &a, int prec, hipStream_t s) {
   const int64_t nt = (int64_t)a.n_rb * a.n_cb;
   if (nt <= 0) return hipSuccess;
   if (nt > 0x7fffffff) return hipErrorInvalidValue;
-  if (pg_small(a, prec)) return launch_pg_small(a, prec == kFP64 || prec == kLut, s);
-  // Components split over a workgroup's waves, us a Gaussian: mixed 0.12 for 0.29
-  // at 128 tiles, 0.20 for 0.29 at 256, 0.36 for 0.41 at 508; FP64 0.29 for 0.55,
-  // 0.53 for 0.57, the same at 508.
-  if (pg_tiles(a) <= kPgSplitTiles && prec != kFP32) {
+  const bool f64 = prec == kFP64 || prec == kLut;
+  const int points = a.skip_points ? 0 : a.P;
+  if (prec != kFP32 && pg_small(f64, pg_tiles(a), points + a.G, a.uniform)) return launch_pg_small(a, f64, s);
+  if (prec != kFP32 && pg_split(f64, pg_tiles(a), points, a.G)) {
     const int n_rb = (int)((a.nrows + 63) / 64);
     const dim3 g((unsigned)((int64_t)n_rb * a.n_cb)), b(kTileRows);
     if (prec == kFP64 || prec == kLut) {
@@ -2192,11 +2174,8 @@ hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s) 
     case kMixed:
     case kMixedBf16:
     case kMixedBf16x2: {
-      // fewer channels a workgroup where the tiles would leave CUs without one
-      // (2,524 rows x 13 channels: 40 workgroups of four channels, 48 us, 130 of
-      // one, 17 us)
       TileArgs t = a;
-      while (t.shp_chan > 1 && (int64_t)t.n_rb * ((a.K + t.shp_chan - 1) / t.shp_chan) < 256) t.shp_chan /= 2;
+      t.shp_chan = shp_channels(t.n_rb, a.K);
       t.n_cb = (a.K + t.shp_chan - 1) / t.shp_chan;
       const dim3 gt((unsigned)((int64_t)t.n_rb * t.n_cb));
       if (prec == kMixedBf16x2)
@@ -2211,64 +2190,13 @@ hipError_t launch_shp(const TileArgs &a, int prec, int max_nmax, hipStream_t s) 
   return hipGetLastError();
 }
 
-// LDS beside the node values: the mixed path's coefficient tiles, the FP64
-// path's chunk.
-static size_t node_base_bytes(int prec, int max_nmax) {
-  if (prec == kFP64) return (size_t)(kNmaxLimit + 1) * kF64Chunk * sizeof(double);
-  return (size_t)(prec == kMixedBf16x2 ? 2 : 3) * shp_pairs(max_nmax) * kAbfPerPair * sizeof(uint16_t);
-}
-
-// Rows of a workgroup, a multiple of 16 (the outputs' tile): those with which
-// the last workgroups end soonest.  A workgroup takes as many passes of its
-// threads over the envelopes as its (row, node) pairs need (quads of nodes on
-// the FP64 path), staging and outputs beside them; two workgroups share a CU
-// (registers) where the LDS holds both, and one alone there runs some 1.5 times as
-// fast.  The costs, in cycles, are rough: they have to tell a last pass or round
-// nearly empty from a full one (113,792 rows, 9 nodes of two shapelets of order
-// 70: 112 rows, 98% of the lanes and 99% of two rounds at work, where 128 left
-// 10% and 13%).  0: LDS for not even 16.
-static int node_rows(int prec, int max_nmax, int S, int M, int Mp, int64_t nrows) {
-  const size_t base = node_base_bytes(prec, max_nmax), half = 81920, all = 163840;
-  const bool f64 = prec == kFP64;
-  const double eval = f64 ? 12.5 * (max_nmax + 1) * (max_nmax + 2) : 2200.0 * shp_pairs(max_nmax);
-  int best_r = 0;
-  double best = 0.0;
-  for (int R = 16; R <= 128; R += 16) {
-    const size_t lds = base + node_lds(S, Mp, R) * sizeof(double);
-    if (lds > all) break;
-    const int64_t items = f64 ? (int64_t)R * (Mp / 4) : (int64_t)R * M, wgs = (nrows + R - 1) / R;
-    const double work = S * ((double)((items + kNodeThreads - 1) / kNodeThreads) * eval + 3000.0 + 75.0 * R);
-    const int64_t slots = lds <= half ? 512 : 256, rest = wgs % slots;
-    const double one = 1.0 / 1.5;
-    const double t = work * ((wgs / slots) * (slots == 512 ? 1.0 : one) + (rest == 0 ? 0.0 : rest > 256 ? 1.0 : one));
-    if (best_r == 0 || t < best) {
-      best = t;
-      best_r = R;
-    }
-  }
-  return best_r;
-}
-
 hipError_t launch_pg_nodes(const TileArgs &a, int prec, hipStream_t s) {
   const bool f64 = prec == kFP64 || prec == kLut;
   const NodePlan &p = a.d.plan[2 + f64];
   if (p.M < 1 || p.M > kPgNodesMax || p.M > p.Mp || p.Mp > kNodesStride || p.Mp % 4 || a.K > kNodesMaxChan)
     return hipErrorInvalidValue;
-  // Rows of a workgroup: those whose rounds of workgroups (as many as the CUs
-  // hold at the kernel's registers) end soonest, a component's staging and reads
-  // weighing the more the fewer rows share them.
-  const int nw = (p.Mp + kPgNB - 1) / kPgNB;
-  const int64_t slots = 256 * std::max(1, 4 * (f64 ? 3 : 5) / nw);
-  int LR = 64;
-  double best = 0.0;
-  for (int r = 64; r >= 16; r /= 2) {
-    const int64_t wgs = (a.call_rows + r - 1) / r;
-    const double t = (double)((wgs + slots - 1) / slots) * (r + 4);
-    if (best == 0.0 || t < best) {
-      best = t;
-      LR = r;
-    }
-  }
+  int64_t slots = 0;
+  const int nw = (p.Mp + kPgNB - 1) / kPgNB, LR = pg_node_rows(f64, p.Mp, a.call_rows, &slots);
   const int64_t nt = (a.nrows + LR - 1) / LR;
   if (nt > 0x7fffffff) return hipErrorInvalidValue;
   const size_t sm = sizeof(PgNodeLds) + (size_t)kChunk * kPgNB * nw * (f64 ? 8 : 4) + (size_t)2 * p.Mp * LR * 8;
@@ -2301,10 +2229,6 @@ static hipError_t launch_pg_small(const TileArgs &a, bool f64, hipStream_t s) {
   else
     hipLaunchKernelGGL((k_pg_nodes<false, false>), g, b, sm, s, a, LR, CS);
   return hipGetLastError();
-}
-
-bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) {
-  return node_base_bytes(prec, max_nmax) + node_lds(S, Mp, 16) * sizeof(double) <= 163840;
 }
 
 template <typename K, typename... A>
