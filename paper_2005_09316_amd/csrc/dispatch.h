@@ -172,14 +172,42 @@ inline int node_rows(int prec, int max_nmax, int S, int M, int Mp, int64_t nrows
   return best_r;
 }
 
-// Whether the node values of every shapelet fit the LDS for 16 rows.
-inline bool shp_nodes_fit(int prec, int max_nmax, int S, int Mp) {
-  return node_base_bytes(prec, max_nmax) + node_lds(S, Mp, 16) * sizeof(double) <= 163840;
+// Whether the shapelets of a sky (their sizes together, see shp_size) cost less by
+// nodes than by channels.  Both kernels evaluate envelopes in passes of 256 threads,
+// two workgroups a CU (one alone takes 0.67 to 0.78 of the time); by nodes a pass
+// holds as many (row, node) pairs as the LDS keeps rows of every shapelet's node
+// values, 16 at the least: with many shapelets most of its lanes repeat others.
+// Times in us a shapelet and round, fitted to 1 to 75 shapelets of order 8 to 70 on
+// 9,400 to 69,000 rows x 12 to 150 channels (rms 4 to 8%; no choice of them costs
+// over 3%).  20 of order 40, 32,512 rows x 20 channels in FP64: 1.80 ms by nodes, 1.00 by
+// channels; 45 of order 20, 12 channels, mixed: by nodes 2.2 times the channels'.
+inline bool shp_nodes_pay(int prec, int max_nmax, int S, double size, int M, int64_t nrows, int K) {
+  const int Mp = (M + 3) / 4 * 4;
+  const bool f64 = prec == kFP64;
+  const int R = node_rows(prec, max_nmax, S, M, Mp, nrows);
+  if (R == 0) return false;
+  auto rounds = [](int64_t wgs, int64_t slots, double alone) {
+    const int64_t rest = wgs % slots;
+    return (wgs / slots) * (slots == 512 ? 1.0 : alone) + (rest == 0 ? 0.0 : rest > 256 ? 1.0 : alone);
+  };
+  const size_t lds = node_base_bytes(prec, max_nmax) + node_lds(S, Mp, R) * sizeof(double);
+  const int64_t items = f64 ? (int64_t)R * (Mp / 4) : (int64_t)R * M;
+  const double passes = (double)((items + kNodeThreads - 1) / kNodeThreads), outs = R / 16 * ((K + 15) / 16) / 4.0;
+  const int64_t n_rb = (nrows + kTileRows - 1) / kTileRows;
+  if (f64) {
+    const double node = 13.6 + (passes * (4.05 * S + 15.7 * size) + 1.64 * S * outs) * rounds((nrows + R - 1) / R, lds <= 81920 ? 512 : 256, 0.67);
+    const double chan = 11.4 + (5.16 * S + 15.5 * size) * rounds(n_rb * ((K + kShpChan - 1) / kShpChan), 512, 0.66);
+    return node < chan;
+  }
+  const int kc = shp_channels(n_rb, K);
+  const double node = 8.5 + (passes * (0.9 * S + 1.85 * size) + 1.26 * S + 1.35 * S * outs) * rounds((nrows + R - 1) / R, lds <= 81920 ? 512 : 256, 0.78);
+  const double chan = 10.5 + (kc * (1.0 * S + 1.75 * size) + 1.4 * S) * rounds(n_rb * ((K + kc - 1) / kc), 512, 0.71);
+  return node < chan;
 }
 
 // Nodes of S shapelets (sizes together, see shp_size), or 0: where that saves a sixth
 // of the envelopes or more (a channel's interpolation, phase and flux cost about 0.035
-// of one).  The highest order's nodes
+// of one), and the kernel is the faster (shp_nodes_pay).  The highest order's nodes
 // serve all of the sky's shapelets.
 inline int shp_plan_nodes(bool f64, int S, int max_nmax, double size, double f_lo, double f_hi, int64_t nrows, int K) {
   if (S == 0) return 0;
@@ -190,8 +218,7 @@ inline int shp_plan_nodes(bool f64, int S, int max_nmax, double size, double f_l
   // 101).
   const int64_t n_rb = (nrows + kTileRows - 1) / kTileRows;
   if (n_rb * (f64 ? (K + kShpChan - 1) / kShpChan : K) <= 512) return 0;
-  (void)size;
-  return shp_nodes_fit(f64 ? kFP64 : kMixed, max_nmax, S, (M + 3) / 4 * 4) ? M : 0;
+  return shp_nodes_pay(f64 ? kFP64 : kMixed, max_nmax, S, size, M, nrows, K) ? M : 0;
 }
 
 }  // namespace vp
