@@ -96,3 +96,88 @@ def test_many_shapelets_in_fp64(rule, S, nodes):
     err = (np.abs(got[:1] - ref) / F).max()
     print(S, "shapelets, error %.2e" % err, flush=True)
     assert err <= 1e-11
+
+
+# (f64, points, Gaussians, rows, channels, field radius, by nodes): us by nodes and by channels as measured
+POINTS = [
+    (0, 1, 0, 2016, 384, 0.01, False),      # 16.6, 9.7
+    (1, 1, 0, 2016, 384, 0.01, False),      # 20.5, 11.5
+    (0, 8, 0, 2016, 384, 0.001, False),     # 15.2, 11.1
+    (1, 30, 10, 32512, 64, 0.009, False),   # 113, 68
+    (1, 60, 0, 8128, 64, 0.009, False),     # 31.8, 29.2
+    (0, 0, 300, 8128, 384, 0.003, True),
+    (0, 4540, 1791, 32512, 384, 0.009, True),  # 2900, 9000
+    (1, 4540, 1791, 32512, 384, 0.009, True),
+]
+
+
+@pytest.mark.parametrize("case", POINTS, ids=["-".join(map(str, c[:5])) for c in POINTS])
+def test_points_by_the_faster_kernel(rule, case):
+    f64, P, G, rows, K, radius, nodes = case
+    assert (rule("points", f64, P, G, radius, 3000.0, 1.0, *_band(K), 0.0, 0.0, rows, K, 1) > 0) == nodes
+
+
+def _pg_rule(rule, f64, obs, sky):
+    """The rule for a pair, from the bounds that creating them takes."""
+    ra, dec = np.concatenate([sky.p_ra, sky.g_ra]), np.concatenate([sky.p_dec, sky.g_dec])
+    x = np.mod(ra - ra[0] + np.pi, 2 * np.pi) - np.pi
+    mra, mdec = ra[0] + 0.5 * (x.min() + x.max()), 0.5 * (dec.min() + dec.max())
+    da, dd, c = np.mod(ra - mra + np.pi, 2 * np.pi) - np.pi, np.abs(dec - mdec), abs(math.cos(mdec))
+    reach = math.sqrt((dd * dd + c * (c + dd) * da * da).max())
+    sd, sa = math.sin(0.5 * (mdec - obs.dec0)), math.sin(0.5 * (mra - obs.ra0))
+    to_mid = 2 * math.sqrt(sd * sd + abs(math.cos(mdec) * math.cos(obs.dec0)) * sa * sa)
+    b_max = math.sqrt((obs.uvw_m ** 2).sum(axis=-1).max())
+    fk = obs.freq_hz / synth.C_LIGHT
+    dev = np.abs(fk - (fk[0] + np.arange(fk.size) * (fk[-1] - fk[0]) / (fk.size - 1))).max() / fk[0]
+    amax = np.abs(np.concatenate([sky.p_alpha, sky.g_alpha])).max()
+    return rule("points", f64, sky.n_point, sky.n_gauss, min(2.0, to_mid + reach), b_max, amax, obs.freq_hz.min(),
+                obs.freq_hz.max(), obs.beam_fwhm_rad, obs.beam_nu_ref_hz, obs.n_time * obs.n_bl, obs.n_chan,
+                dev <= (1e-15 if f64 else 1e-12))
+
+
+# The edges of k_pg_nodes at component counts that send both paths there: node counts around the waves' shares,
+# channels around multiples of 16, rows around the workgroup's, a sky beside the centre, across the origin of right
+# ascension, irregular and reversed channels, points by antenna beside, shapelets by nodes behind.
+BY_NODES = {
+    "points": dict(n_tiles=64, n_time=5, n_chan=96, n_point=150, n_gauss=0, radius=0.002),
+    "gauss": dict(n_tiles=65, n_time=5, n_chan=129, n_point=0, n_gauss=130, radius=0.003),
+    "one-chunk": dict(n_tiles=64, n_time=5, n_chan=200, n_point=64, n_gauss=0, radius=0.002, width=4e6),
+    "few-nodes": dict(n_tiles=64, n_time=6, n_chan=72, n_point=100, n_gauss=65, radius=1e-4),
+    "ragged-rows": dict(n_tiles=61, n_time=7, n_chan=143, n_point=121, n_gauss=127, radius=0.003, ragged=7),
+    "off-centre": dict(n_tiles=64, n_time=5, n_chan=160, n_point=80, n_gauss=140, radius=0.001, d_ra=0.004, d_dec=-0.003),
+    "across-zero": dict(n_tiles=64, n_time=5, n_chan=160, n_point=80, n_gauss=140, radius=0.003, wrap=True),
+    "many-nodes": dict(n_tiles=64, n_time=5, n_chan=300, n_point=100, n_gauss=130, radius=0.008, width=30e6),
+    "irregular": dict(n_tiles=63, n_time=5, n_chan=90, n_point=100, n_gauss=90, radius=0.003, odd=True, beam=False),
+    "reversed-shapelet": dict(n_tiles=64, n_time=5, n_chan=120, n_point=100, n_gauss=130, radius=0.002, reverse=True,
+                              nmax=[9], wrap=True),
+    "antennas-beside": dict(n_tiles=64, n_time=6, n_chan=96, n_point=900, n_gauss=165, radius=0.003),
+}
+_REF = {}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(BY_NODES))
+@pytest.mark.parametrize("prec,dtype,bar", [(1, 0, 1e-6), (1, 1, 1e-6), (0, 0, 1e-11), (0, 1, 1e-6)])
+def test_points_and_gaussians_where_by_nodes(rule, name, prec, dtype, bar):
+    import oracle
+    from paper_2005_09316_amd import vp
+    from tests.helpers import Handles, run
+    from tests.test_pg_nodes import _case
+    if name not in _REF:
+        _REF.clear()
+        obs, sky = _case(**BY_NODES[name])
+        _REF[name] = obs, sky, oracle.predict(obs, sky)
+    obs, sky, ref = _REF[name]
+    assert _pg_rule(rule, 1 - prec, obs, sky) > 0
+    data = synth.noise_c64(ref.shape, 5).astype(np.complex128)
+    ctx = vp.vp_create_ctx(0, 0)
+    try:
+        with Handles(ctx, obs, sky) as h:
+            got = run(ctx, h.obs, h.sky, obs, prec, dtype)
+            res = run(ctx, h.obs, h.sky, obs, prec, dtype, data=data)
+    finally:
+        vp.vp_destroy_ctx(ctx)
+    F = np.maximum(oracle.total_flux(obs, sky), np.abs(ref).max(axis=(0, 1)))
+    e1, e2 = (np.abs(got - ref) / F).max(), (np.abs(res - (data - ref)) / F).max()
+    print(name, "precision", prec, "dtype", dtype, "error: predict %.2e, subtract %.2e" % (e1, e2), flush=True)
+    assert e1 <= bar and e2 <= bar
