@@ -51,16 +51,30 @@ constexpr int kPgSplitTiles = 640;  // up to this many tiles, the components may
 // channels, 0.13 for 0.15, then 0.26 for 0.15, and on irregular channels 0.26 for
 // 0.34 at 32 tiles.
 inline bool pg_small(bool f64, int64_t nt, int n, bool uniform) {
-  (void)n;
+  // (a few components leave most lanes without one: a point on 2 tiles, 8.5 us for
+  // 5.9 on the tiles in FP64)
+  if (n < (f64 && !uniform ? 8 : 16)) return false;
   return nt <= (f64 ? (uniform ? 4 : 64) : 40);
 }
 
-// Components split over a workgroup's waves, us a Gaussian: mixed 0.12 for 0.29
-// at 128 tiles, 0.20 for 0.29 at 256, 0.36 for 0.41 at 508; FP64 0.29 for 0.55,
-// 0.53 for 0.57, the same at 508.
+// Whether the components are split over a workgroup's waves.  Per Gaussian, us: tiles
+// by workgroups a CU (1 / 2 / 3), mixed 0.295, 0.44, 0.59, FP64 0.57, 1.03, 1.5;
+// split, which fills the device evenly, 0.02 + 0.00079 a tile and 0.045 + 0.0021 (128
+// to 635 tiles).  A wave takes whole groups of a chunk: of a few components, most
+// waves have none, which costs about the root of the idle share (10 points, 508
+// tiles, FP64: split 30 us, tiles 15.6; mixed 15.2 and 12.0).
 inline bool pg_split(bool f64, int64_t nt, int P, int G) {
-  (void)f64, (void)P, (void)G;
-  return nt <= kPgSplitTiles;
+  const int n = P + G;
+  if (nt > kPgSplitTiles || n == 0) return false;
+  const int group = f64 ? kFlush : kFlushMixed;
+  auto slots = [&](int m) {  // of the waves' time, in components
+    const int rest = m % kChunk;
+    return m - rest + 4 * group * (((rest + group - 1) / group + 3) / 4);
+  };
+  const double idle = (double)(slots(P) + slots(G)) / n * (1.0 + 3.0 / n);
+  const int per_cu = (int)std::min<int64_t>(3, (nt + 255) / 256);
+  const double tile = f64 ? (per_cu == 1 ? 0.57 : per_cu == 2 ? 1.03 : 1.5) : (per_cu == 1 ? 0.295 : per_cu == 2 ? 0.44 : 0.59);
+  return (f64 ? 0.045 + 0.0021 * nt : 0.02 + 0.00079 * nt) * std::sqrt(idle) < tile;
 }
 
 // ---------------------------------------------------------------------------

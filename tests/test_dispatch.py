@@ -181,3 +181,62 @@ def test_points_and_gaussians_where_by_nodes(rule, name, prec, dtype, bar):
     e1, e2 = (np.abs(got - ref) / F).max(), (np.abs(res - (data - ref)) / F).max()
     print(name, "precision", prec, "dtype", dtype, "error: predict %.2e, subtract %.2e" % (e1, e2), flush=True)
     assert e1 <= bar and e2 <= bar
+
+
+# (f64, tiles, points, Gaussians, split): us split and on the tiles as measured
+SPLIT = [
+    (1, 508, 10, 0, False),   # 30.3, 15.6
+    (1, 508, 0, 300, False),  # 336, 325
+    (1, 128, 0, 300, True),   # 98, 172
+    (1, 381, 63, 0, True),    # 40.5, 46.8
+    (1, 576, 0, 300, True),   # 371, 433
+    (0, 508, 10, 0, False),   # 15.2, 12.0
+    (0, 477, 0, 30, False),   # 24.9, 20.4
+    (0, 477, 40, 100, False),  # 63.1, 59.4
+    (0, 128, 0, 30, True),    # 11.7, 15.0
+    (0, 508, 0, 300, True),   # 125, 134
+    (0, 672, 0, 300, False),
+    (1, 128, 0, 0, False),
+]
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=["-".join(map(str, c[:4])) for c in SPLIT])
+def test_components_split_where_it_pays(rule, case):
+    assert rule("split", *case[:4]) == case[4]
+
+
+@pytest.mark.parametrize("f64,nt,n,uniform,small", [(1, 2, 1, 1, 0), (1, 2, 110, 1, 1), (1, 5, 110, 1, 0), (1, 5, 110, 0, 1),
+                                                    (1, 16, 10, 0, 1), (0, 16, 10, 1, 0), (0, 40, 16, 1, 1), (0, 41, 16, 1, 0)])
+def test_small_observations_split_where_it_pays(rule, f64, nt, n, uniform, small):
+    assert rule("small", f64, nt, n, uniform) == small
+
+
+# Few components on either side of the rules' lines: (tiles, times, channels, points, Gaussians)
+FEW = [(16, 1, 8, 1, 0), (16, 1, 8, 15, 1), (45, 2, 16, 3, 2), (64, 2, 33, 16, 0), (100, 2, 25, 10, 0), (100, 2, 25, 0, 17),
+       (128, 2, 47, 9, 65), (128, 3, 49, 1, 0), (128, 3, 49, 33, 31)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", FEW, ids=["-".join(map(str, s)) for s in FEW])
+@pytest.mark.parametrize("prec,dtype,bar", [(1, 0, 1e-6), (1, 1, 1e-6), (0, 0, 1e-11), (0, 1, 1e-6)])
+def test_few_components_match_oracle(size, prec, dtype, bar):
+    import oracle
+    from paper_2005_09316_amd import vp
+    from tests.helpers import Handles, run
+    from tests.test_pg_nodes import _case
+    ctx = vp.vp_create_ctx(0, 0)
+    try:
+        for odd in (False, True):
+            obs, sky = _case(*size, radius=0.2, odd=odd)
+            ref = oracle.predict(obs, sky)
+            # (noise below the few components' flux, so that the residual's own rounding to complex64 is below the bar)
+            data = 0.1 * oracle.total_flux(obs, sky).min() * synth.noise_c64(ref.shape, 5).astype(np.complex128)
+            data = data.astype(np.complex64).astype(np.complex128)
+            with Handles(ctx, obs, sky) as h:
+                got = run(ctx, h.obs, h.sky, obs, prec, dtype)
+                res = run(ctx, h.obs, h.sky, obs, prec, dtype, data=data)
+            e1, e2 = oracle.error_metric(got, ref, obs, sky), oracle.error_metric(res, data - ref, obs, sky)
+            print(size, odd, "precision", prec, "dtype", dtype, "error / total flux %.2e %.2e" % (e1, e2), flush=True)
+            assert e1 <= bar and e2 <= bar
+    finally:
+        vp.vp_destroy_ctx(ctx)
