@@ -132,6 +132,16 @@ __device__ __forceinline__ void vis_put4(const TileArgs &a, bool wide, bool add,
     o[1] = make_float4((float)(re[2] + y.x), (float)(im[2] + y.y), (float)(re[3] + y.z), (float)(im[3] + y.w));
     return;
   }
+  if (!a.c64 && n >= 4) {  // (no test between the accesses: all four in flight)
+    double2 *o = (double2 *)a.vis + idx;
+    double2 d[4] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0), make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+    if (add)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d[r] = o[r];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = make_double2(re[r] + d[r].x, im[r] + d[r].y);
+    return;
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     if (r >= n) break;
