@@ -191,7 +191,14 @@ static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dty
   const double ant_us = std::ceil(wgs / 256.0) * ant_jp(sky) / 32.0 * blk_us + 8.0;
   const double tiles = (double)(((int64_t)obs->T * obs->B + kTileRows - 1) / kTileRows) * (obs->Kpad / kPgChan);
   const double vec_us = sky->P * (tiles <= kPgSplitTiles ? std::max(0.045, 0.015 + 0.0005 * tiles) : 0.32 * tiles / 768.0);
-  return ant_us < std::min(node_us, vec_us);
+  if (!(ant_us < std::min(node_us, vec_us))) return false;
+  // What either costs whatever the points: a round's first block, the visibilities
+  // (scattered by antenna, in rows by the vector kernels) and, beside Gaussians, a pass
+  // of their own over the data.  100 points and 20 Gaussians, 128 antennas, 4 times x 32
+  // channels: 49 us by antenna, 40 together; 64 points, 150 antennas, 2 x 100: 60, 43.
+  const double vis = 1e-6 * rows * obs->K;
+  return ant_us - 8.0 + 4.9 + 3.9 * std::ceil(wgs / 256.0) + 5.7 * vis + (sky->G > 0 ? 10.0 + 4.8 * vis : 0.0) <
+         vec_us * (obs->uniform ? 1.0 : 1.1) + 7.5 + 2.0 * vis;
 }
 
 // Whether any mixed call on the pair may take its points by antenna: by nodes

@@ -114,3 +114,26 @@ def test_points_alone_into_complex64(prec, bar):
     print("precision", prec, "error / total flux: predict %.2e, subtract %.2e" % (e1, e2), flush=True)
     assert e1 <= bar and e2 <= bar
     assert np.array_equal(got, wide.astype(np.complex64).astype(np.complex128))  # rounded once
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_point,n_gauss,launches", [(100, 20, 1), (1500, 20, 2)])
+def test_a_few_points_stay_with_the_gaussians(n_point, n_gauss, launches):
+    """128 antennas, 4 times x 32 channels: what a pass by antenna costs whatever its
+    points, a hundred do not bring in again (measured 49 us for 40)."""
+    import oracle
+    from paper_2005_09316_amd import vp
+    from tests.helpers import Handles, run
+    obs, sky = synth.make_config(1, seed=7, n_tiles=128, n_time=4, n_chan=32, n_point=n_point, n_gauss=n_gauss, shapelet_nmax=[],
+                                 freq_hz=synth.channels(182e6, 80e3, 32))
+    ctx = vp.vp_create_ctx(0, 0)
+    try:
+        with Handles(ctx, obs, sky) as h:
+            vp.vp_profile(ctx, True)
+            got = run(ctx, h.obs, h.sky, obs, vp.VP_PREC_MIXED, vp.VP_C64)
+            counts, _ = vp.vp_profile_read(ctx)
+    finally:
+        vp.vp_destroy_ctx(ctx)
+    assert counts[1] == launches, counts
+    one = dataclasses.replace(obs, n_time=1, uvw_m=np.ascontiguousarray(obs.uvw_m[:1]))
+    assert oracle.error_metric(got[:1], oracle.predict(one, sky), one, sky) <= 1e-6
