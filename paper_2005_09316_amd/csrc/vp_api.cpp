@@ -135,7 +135,7 @@ static void place_amp(Derived &d, char *at, const vp_sky *sky, const vp_obs *obs
 }
 
 bool ant_pair(const vp_sky *sky, const vp_obs *obs) {
-  if (obs->ant_n == 0 || sky->P < kAntMinPoints) return false;
+  if (sky->P < kAntMinPoints || obs->ant_n == 0) return false;
   // Every channel's amplitudes are scaled by their own largest (k_ant_amp), so
   // that beam and spectrum may take any share of the fluxes; these have to be
   // finite (as a product of the largest S_ref and the largest growth), and not so
@@ -172,11 +172,12 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs) {
 // 4 times x 384 channels: 0.41 us a point by nodes, 0.39 by antenna.
 static bool use_ant(const vp_sky *sky, const vp_obs *obs, int precision, int dtype, const NodePlan &plan) {
   const bool f64 = precision == kFP64 || precision == kLut;
+  if (sky->P < kAntMinPoints) return false;  // (first: such skies' observations may have their antennas found meanwhile)
   if (!grid_fits((int64_t)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac, 64 * kAntWaves)) return false;
   const double rows = (double)obs->T * obs->B;
   const double node_us = plan.M == 0 ? 1e30 : sky->P * (f64 ? std::max(0.3, rows * plan.Mp / 0.47e6) : std::max(0.1, rows * plan.Mp / 2.3e6));
   if (precision == kFP64 || precision == kLut) {
-    if (obs->ant_n == 0 || sky->P < kAntMinPoints || !(obs->ant_dev <= 1e-12) || !(obs->ant_reach <= 1e12)) return false;
+    if (obs->ant_n == 0 || !(obs->ant_dev <= 1e-12) || !(obs->ant_reach <= 1e12)) return false;
     if (dtype == VP_C64 && sky->G > 0) return false;
     const double wgs = (double)obs->T * ((obs->K + obs->ant_kpack - 1) / obs->ant_kpack) * obs->ant_nmac;
     const double blk_us = obs->ant_n <= 32 ? 2.7 : obs->ant_n <= 96 ? 4.1 : 5.4;
@@ -824,7 +825,10 @@ int vp_destroy_ctx(vp_ctx *ctx) {
 }
 
 // The antennas behind the rows, if there are any (see ant_layout.h), and the
-// tables by which the kernels work on them.
+// tables by which the kernels work on them.  The search and its upload take 20 us
+// (6 antennas) to 1 ms (256, a seventh of the baselines flagged), more than a
+// small sky's predictions, so they wait for a sky that may use them: done where
+// the second of the two is created, none is left to a call on them.
 static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
   // a complete list of n antennas has B = n (n - 1) / 2 rows; half of them
   // flagged, n = 2 sqrt(B)
@@ -872,6 +876,24 @@ static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
   for (size_t i = 0; i < L.xyz.size(); i += 3)
     o->ant_reach = std::max(o->ant_reach, f * (std::fabs(L.xyz[i]) + std::fabs(L.xyz[i + 1]) + std::fabs(L.xyz[i + 2])));
   return hipSuccess;
+}
+
+// uvw: the rows on the host, or NULL to read them back.
+static hipError_t look_for_antennas(vp_obs *o, const double *uvw) {
+  o->ant_looked = true;
+  hipError_t e = hipSuccess;
+  try {
+    std::vector<double> rows;
+    if (!uvw) {
+      rows.resize(3 * (size_t)o->T * o->B);
+      e = hipMemcpy(rows.data(), o->uvw, sizeof(double) * rows.size(), hipMemcpyDeviceToHost);
+      uvw = rows.data();
+    }
+    if (e == hipSuccess) e = upload_antennas(o, uvw);
+  } catch (const std::bad_alloc &) {  // without the antennas, points go the vector path
+    o->ant_n = 0;
+  }
+  return e;
 }
 
 int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out) {
@@ -933,17 +955,20 @@ int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out) {
   hipError_t e = upload(&o->uvw, desc->uvw_m, 3 * nrows, o->mem);
   if (e == hipSuccess) e = upload(&o->freq, desc->freq_hz, (int64_t)o->K, o->mem);
   if (e == hipSuccess) e = upload(&o->fk, fk.data(), (int64_t)o->Kpad, o->mem);
-  try {
-    if (e == hipSuccess) e = upload_antennas(o, desc->uvw_m);
-  } catch (const std::bad_alloc &) {  // without the antennas, points go the vector path
-    o->ant_n = 0;
+  bool look;
+  {
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    look = ctx->ant_skies > 0;
   }
+  if (e == hipSuccess && look) e = look_for_antennas(o, desc->uvw_m);
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  // (a first such sky may have come since)
+  if (e == hipSuccess && ctx->ant_skies > 0 && !o->ant_looked) e = look_for_antennas(o, desc->uvw_m);
   if (e != hipSuccess) {
     o->mem.release();
     delete o;
     return hip_error(e, "uploading the observation");
   }
-  std::lock_guard<std::mutex> lk(ctx->mu);
   o->id = ++ctx->next_id;
   ctx->obs.insert(o);
   ctx->lib_bytes += o->mem.total;
@@ -1166,6 +1191,24 @@ int vp_create_sky(vp_ctx *ctx, const vp_sky_desc *d, vp_sky **out) {
   k->tiles.abf = d_abf; k->tiles.abf_off = d_abfoff;
   k->tiles.nmax = d_nmax;
   std::lock_guard<std::mutex> lk(ctx->mu);
+  if (P >= kAntMinPoints) {
+    for (vp_obs *o : ctx->obs) {
+      if (o->ant_looked) continue;
+      const size_t before = o->mem.total;
+      e = look_for_antennas(o, nullptr);
+      ctx->lib_bytes += o->mem.total - before;
+      if (e == hipErrorOutOfMemory) {  // (the observation does without them)
+        (void)hipGetLastError();
+        e = hipSuccess;
+      }
+      if (e != hipSuccess) {
+        k->mem.release();
+        delete k;
+        return hip_error(e, "looking for the antennas of an observation");
+      }
+    }
+    ++ctx->ant_skies;
+  }
   k->id = ++ctx->next_id;
   ctx->skies.insert(k);
   ctx->lib_bytes += k->mem.total;
@@ -1181,6 +1224,7 @@ int vp_destroy_sky(vp_sky *sky) {
   if (sky->jobs > 0) return set_error(VP_EBUSY, "sky used by pending jobs");
   drop_derived(ctx, sky->id, 0);
   ctx->skies.erase(sky);
+  if (sky->P >= kAntMinPoints) --ctx->ant_skies;
   ctx->lib_bytes -= sky->mem.total;
   sky->mem.release();
   delete sky;

@@ -207,7 +207,10 @@ struct vp_obs {
   std::vector<double> h_freq;
   double f_lo = 0, f_hi = 0;  // lowest and highest channel frequency, Hz
   double b_max = 0;           // longest row, metres
-  // antennas behind the baselines (ant_layout.h); ant_n 0: none found
+  // antennas behind the baselines (ant_layout.h); ant_n 0: none found.  They are
+  // looked for once the context holds a sky that may use them (ant_looked, under
+  // the context's lock), and read only for such skies.
+  bool ant_looked = false;
   int ant_n = 0, ant_npad = 0, ant_nmac = 0, ant_max_sup = 0, ant_kpack = 1;
   double ant_dev = 0;           // their largest disagreement with a row, in turns at the highest frequency
   double ant_reach = 0;         // largest antenna coordinate (a sum of magnitudes), in wavelengths at the highest frequency
@@ -246,6 +249,7 @@ struct vp_ctx {
   uint64_t next_id = 0;
   std::set<vp_obs *> obs;
   std::set<vp_sky *> skies;
+  int ant_skies = 0;  // of these, skies with kAntMinPoints points or more
   std::map<std::pair<uint64_t, uint64_t>, vp::DerivedEntry *> derived;
   uint64_t lib_bytes = 0;
   bool profile = false;
