@@ -251,7 +251,7 @@ def truncation_sweep(check_rows=8, fracs=(1.0, 0.95, 0.9, 0.8, 0.7, 0.5), orders
             r = {"rule": rule, "param": param, "kept": int(n), "of": int(ntot),
                  "kept_frac": round(n / ntot, 4), "flux_frac": round(frac, 5),
                  "gpu_ms": round(wall, 3),
-                 "kernel_ms": round(float((tk[1] + tk[2]) / max(c[1], 1)), 3),
+                 "kernel_ms": round(float((tk[1] + tk[2]) / reps), 3),
                  "err_vs_full_model": err}
             if name == "shapelet":
                 r["effective_order"] = eff_order(t)

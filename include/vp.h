@@ -30,8 +30,8 @@
  *                 fitted per (time, channel) as in Sec. 5.1 (vp_peel).
  *
  * Conventions: angles in radians, FWHMs and beta as FWHM in radians, PA east of
- * north, fluxes in Jy, frequencies in Hz.  n - 1 is formed as
- * -(l^2 + m^2) / (1 + n).  The exponent sign is -1 in the paper; +1 yields the
+ * north, fluxes in Jy, frequencies in Hz.  l, m and n - 1 are formed from the
+ * sines of half the differences in RA and Dec, where nothing large cancels.  The exponent sign is -1 in the paper; +1 yields the
  * exact complex conjugate.  Coefficients are used as given (the paper's
  * C <- C / I convention, Sec. 3.2): no extra prefactor is applied.
  *
@@ -65,7 +65,9 @@ extern "C" {
 /* precision paths */
 #define VP_PREC_FP64 0        /* FP64 everywhere (phase, sincos, envelopes, recurrence, contraction, sums) */
 #define VP_PREC_MIXED 1       /* FP64 phase + range reduction; FP32 sincos/envelopes, FP32 partial
-                                 sums of 8 terms added into FP64;
+                                 sums of 8 terms added into FP64; points whose rows are differences
+                                 of antennas: factors per antenna in FP32, split into pairs of FP16
+                                 (23 bits), products on MFMA, every 32 points' sum added into FP64;
                                  FP64 Hermite recurrence; shapelet contraction on MFMA with the
                                  coefficients and Hermite values split into 3 BF16 parts from their
                                  FP64 values (6 products, FP32 accumulation, folded into FP64 per
@@ -150,7 +152,10 @@ int vp_create_ctx(int hip_device, uint64_t hbm_budget_bytes, vp_ctx **out);
 int vp_destroy_ctx(vp_ctx *ctx);
 
 /* Copy an observation to the device.  Host arrays are read during the call
- * and may be freed on return.  Errors: VP_EINVAL for n <= 0, NULL arrays,
+ * and may be freed on return.  Once the context holds a sky of 64 points or more,
+ * the antennas whose differences the rows are, if they are that, are looked for:
+ * by this call, or by the vp_create_sky that brings the first such sky, for the
+ * observations there are (no call on a pair has it left to do).  Errors: VP_EINVAL for n <= 0, NULL arrays,
  * non-finite uvw/frequencies, frequencies <= 0, |sign| != 1, beam FWHM < 0 or
  * a positive FWHM with beam_nu_ref_hz <= 0; VP_ENOMEM; VP_EDEVICE. */
 int vp_create_obs(vp_ctx *ctx, const vp_obs_desc *desc, vp_obs **out);

@@ -46,10 +46,12 @@ typedef uint32_t uint4w __attribute__((ext_vector_type(4)));
 // matrix instructions (108 of 16 cycles) in turn: beside other work an MFMA
 // still holds the issue of about two vector instructions.  Evaluation and
 // products therefore share each wave's instruction stream.  MWA-like points
-// (128 antennas, 14 x 32 (time, channel), 20,000 points): 2.7 ms, against 14.7
-// ms on the vector path; 256 antennas x 384 channels x 100,000: 39 ms against
-// 233 ms.  Error against FP64 over the result's norm: 1.27e-7 (vector path
-// 1.43e-7), irregular channels 1.12e-7 (1.18e-7).
+// (128 antennas, 14 x 32 (time, channel), 20,000 points): 2.5 ms, against 14.7
+// ms on the vector path (vector instructions hold 0.47 of the SIMDs' cycles, matrix
+// instructions 0.33, in sum 0.95 of those with a workgroup on the CU); 256 antennas
+// x 384 channels x 100,000: 42 ms against 233 ms.  Error against FP64 over the
+// result's norm: 1.27e-7 (vector path 1.43e-7), irregular channels 1.12e-7
+// (1.18e-7).
 constexpr int kAntK = 32;  // points per block
 
 __device__ __forceinline__ int ant_xcd(int b, int nt) {
@@ -493,9 +495,9 @@ __global__ __launch_bounds__(64 * kAntWaves) __attribute__((amdgpu_waves_per_eu(
 // rounding error and reduced to a fraction of a turn before the sum, so that
 // the phase is good to an ulp of a turn and not of the whole phase (the error of
 // two factors would otherwise exceed that of the vector path's one phase).
-// What bounds it: the matrix cores (16 MFMAs per four tiles and 4 points, 60
-// TFLOP/s at best against 47 to 63 measured for plain products), with ~55
-// vector instructions per factor beside them.
+// What bounds it: the matrix cores (12 MFMAs of 64 cycles per four tiles and 4
+// points: 0.58 of the cycles in which a CU holds a workgroup), with ~55 vector
+// instructions per factor (0.23) and what the two wait for each other.
 typedef double double4a __attribute__((ext_vector_type(4)));
 constexpr int kAntK64 = 16;  // points per block
 

@@ -139,7 +139,7 @@ bool ant_pair(const vp_sky *sky, const vp_obs *obs) {
   // Every channel's amplitudes are scaled by their own largest (k_ant_amp), so
   // that beam and spectrum may take any share of the fluxes; these have to be
   // finite (as a product of the largest S_ref and the largest growth), and not so
-  // steep that the points' order by S_ref, bright to faint, says nothing about
+  // steep that the points' order by S_ref, faint to bright, says nothing about
   // the order in the band.
   if (!grid_fits((int64_t)ant_jp(sky) * obs->Kpad / 256 + 1, 256)) return false;
   const double x = std::max(std::fabs(std::log(obs->f_lo / sky->nu_ref)), std::fabs(std::log(obs->f_hi / sky->nu_ref)));

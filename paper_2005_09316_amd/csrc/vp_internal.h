@@ -143,7 +143,8 @@ inline hipError_t whole_lds(const void *kernel) {
   return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
 }
 
-// Whether HIP takes a grid of so many workgroups (its threads are counted in 32 bits).
+// Whether a grid of so many workgroups runs whole (its threads are counted in 32 bits:
+// HIP launches a larger one cut short, without an error).
 inline bool grid_fits(int64_t blocks, int threads) { return blocks <= 0xffffffffll / threads; }
 constexpr int64_t kNodesMaxRows = 1ll << 28;  // so many, by nodes, whatever rows a workgroup takes (16 x 256 threads at the least)
 

@@ -139,7 +139,8 @@ int check_call(vp_ctx *ctx, const struct ::vp_sky *sky, const struct ::vp_obs *o
 // prof: the context whose profiling records the launches, or null; sums: the
 // workspace that sums_bytes asks for, or {null, 0} (the points then go with the
 // Gaussians); *kernels (when given) grows by the number of kernels launched;
-// nodes: shapelets may go by nodes.
+// nodes = false (vp_peel except in FP64): summed channel by channel (of the
+// lookup-table path, whose points and Gaussians are FP64, only the shapelets).
 int launch_passes(vp_ctx *prof, const struct ::vp_sky *sky, const struct ::vp_obs *obs, int precision, int dtype,
                   void *vis, int subtract, hipStream_t stream, const Derived &d, const float *lut, SumsSpace sums,
                   int *kernels = nullptr, bool nodes = true);

@@ -6,7 +6,8 @@ gaps still give the array's own antennas, rows that are no antenna differences
 are refused, and the tiling covers every pair once.  On the GPU: the path
 against the oracle at the edges of its blocks (32 antennas, 32 points, packed
 channels), with flagged, reversed and automatic baselines, negative fluxes and
-Gaussians and shapelets behind the points.  Bars: the paths' own, 1e-6 and
+Gaussians and shapelets behind the points; test_antenna_rows_gpu.py has the sizes
+at which the rule takes the path that these leave to the vector kernels.  Bars: the paths' own, 1e-6 and
 1e-11 of the total flux (1e-6 for complex64)."""
 import dataclasses
 import os

@@ -1,5 +1,5 @@
-"""Calls whose kernels would take a grid of 2^32 threads or more, which HIP refuses:
-a small array with very many (time, channel) cells."""
+"""Calls whose kernels would take a grid of 2^32 threads or more, which HIP
+launches cut short, without an error: a small array with very many (time, channel) cells."""
 import math
 
 import numpy as np

@@ -1,10 +1,11 @@
 """Points and Gaussians by nodes (csrc/shp_nodes.h, pg_nodes; k_pg_nodes): on
 the CPU, the number of Chebyshev nodes that the library takes for a field and a
 band suffices for every phase, spectral index and envelope within its bounds; on
-the GPU, the path against the oracle where it can go wrong: node counts around
-the waves' shares, channels around multiples of 16, rows around the workgroup's,
-few components, a sky beside the phase centre and across the origin of right
-ascension, irregular and reversed channels.  Bars: the paths' own, 1e-6 and
+the GPU, points and Gaussians against the oracle: node counts around the waves'
+shares, channels around multiples of 16, rows around the workgroup's, few
+components, a sky beside the phase centre and across the origin of right ascension,
+irregular and reversed channels.  The smallest of these go to the kernels by channels
+(csrc/dispatch.h, whose lines test_dispatch.py holds).  Bars: the paths' own, 1e-6 and
 1e-11 of the total flux (1e-6 for complex64)."""
 import dataclasses
 import os

@@ -1,8 +1,8 @@
-"""Serving (continuous batching) on the GPU: jobs submitted together share
-the persistent kernel tile by tile; each job's result must equal the same
-job run alone through vp_predict / vp_subtract (bitwise: the tile device
-functions and per-visibility operation order are the same), admission must
-respect the HBM budget in FIFO order, and error paths must isolate."""
+"""Serving (continuous batching) on the GPU: jobs submitted together run on a
+few streams side by side; each job's result must equal the same job run alone
+through vp_predict / vp_subtract (bitwise: the kernels are the same), admission
+must respect the HBM budget in FIFO order, and error paths must isolate.  (The
+kernel counts of vp_serve_stats: test_serve_spans.py.)"""
 import sys
 import time
 

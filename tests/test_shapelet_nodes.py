@@ -1,9 +1,9 @@
 """Shapelets by nodes (csrc/shp_nodes.h): the number of Chebyshev nodes that the
 library takes for an order and a band suffices for every Hermite function up to
-that order along every line, on the CPU; on the GPU the path against the oracle
-where it can go wrong: node counts around multiples of 4, channels around
-multiples of 16, rows around the workgroup's, many shapelets, spectral terms,
-irregular channels, one of them on a node."""
+that order along every line, on the CPU; on the GPU shapelets against the oracle on
+channels around multiples of 16, with many shapelets, spectral terms, irregular
+channels.  Observations as small as these go to the kernels by channels (csrc/dispatch.h):
+test_shapelet_node_outputs.py has the sizes that the node kernels take."""
 import dataclasses
 import os
 import subprocess
