@@ -76,6 +76,18 @@ void ServeCore::end_job(CoreJob *j, int status) {
   ex_->retired(*j);
 }
 
+// The budget covers running jobs and the leftovers of finished ones (the executor's
+// evictable bytes), which are released when they stand in the way.
+bool ServeCore::fits(const CoreJob &j) {
+  if (!ex_->has_room(j)) return false;
+  if (in_use_ + j.footprint > budget_) return false;
+  if (in_use_ + ex_->evictable_bytes() + j.footprint > budget_) {
+    ex_->evict();
+    if (in_use_ + ex_->evictable_bytes() + j.footprint > budget_) return false;
+  }
+  return true;
+}
+
 void ServeCore::loop() {
   ex_->thread_start();
   std::unique_lock<std::mutex> lk(mu_);
@@ -94,27 +106,26 @@ void ServeCore::loop() {
       }
     }
     // admissions, strictly first come first served: the head of the queue
-    // waits for room and budget, and nothing overtakes it.  The budget
-    // covers running jobs and the leftovers of finished ones (the executor's
-    // evictable bytes), which are released when they stand in the way.
-    while (!queue_.empty()) {
+    // waits for room and budget, and nothing overtakes it.  One at a time, so
+    // that jobs which end meanwhile are seen between two, and without the lock:
+    // an admission launches its job's kernels (10 us and more), for which neither
+    // submit() nor poll() waits.
+    if (!queue_.empty() && fits(*queue_.front())) {
       CoreJob *j = queue_.front();
-      if (!ex_->has_room(*j)) break;
-      if (in_use_ + j->footprint > budget_) break;
-      if (in_use_ + ex_->evictable_bytes() + j->footprint > budget_) {
-        ex_->evict();
-        if (in_use_ + ex_->evictable_bytes() + j->footprint > budget_) break;
-      }
       queue_.pop_front();
       j->t_admit = clock_();
       j->state = kRunning;
+      in_use_ += j->footprint;
+      running_.push_back(j);
+      lk.unlock();
       const int rc = ex_->admit(*j);
+      lk.lock();
       if (rc != VP_OK) {
+        running_.pop_back();
+        in_use_ -= j->footprint;
         end_job(j, rc);
-      } else {
-        in_use_ += j->footprint;
-        running_.push_back(j);
       }
+      continue;
     }
     if (!running_.empty()) {
       const int rc = ex_->kick();
@@ -136,9 +147,7 @@ void ServeCore::loop() {
       // follows (a clock step only stretches one idle period)
       cv_.wait_until(lk, std::chrono::system_clock::now() + std::chrono::milliseconds(2));
     } else {
-      lk.unlock();
-      std::this_thread::sleep_for(std::chrono::microseconds(20));
-      lk.lock();
+      cv_.wait_until(lk, std::chrono::system_clock::now() + std::chrono::microseconds(20));
     }
   }
 }

@@ -32,9 +32,9 @@ struct CoreJob {
   void *payload = nullptr;  // the executor's per-job state
 };
 
-// Device side of the scheduler.  Every call comes from the core's thread with
-// the core's lock held, so an executor needs no locking of its own for state
-// that only these calls touch.
+// Device side of the scheduler.  Every call comes from the core's thread (with the
+// core's lock held, but for admit), so an executor needs no locking of its own for
+// state that only these calls touch.
 class ServeExecutor {
  public:
   virtual ~ServeExecutor() = default;
@@ -46,7 +46,7 @@ class ServeExecutor {
   virtual uint64_t evictable_bytes() = 0;
   virtual void evict() = 0;
   // Starts the job: VP_OK (it runs), or an error code that ends this job
-  // alone (the executor has undone whatever it started).
+  // alone (the executor has undone whatever it started).  Without the core's lock.
   virtual int admit(CoreJob &j) = 0;
   // Advances a running job; true once it is done (status, t_start and the
   // device timestamps filled in).
@@ -88,6 +88,7 @@ class ServeCore {
 
  private:
   void loop();
+  bool fits(const CoreJob &j);           // lock held: room and budget for it
   void end_job(CoreJob *j, int status);  // lock held
 
   ServeExecutor *ex_;
