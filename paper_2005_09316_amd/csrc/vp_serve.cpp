@@ -65,7 +65,7 @@ static int check_job(vp_ctx *ctx, const vp_job *job) {
 }
 
 constexpr int kServeSlots = 1024;  // jobs in flight
-constexpr int kServeStreams = 4;   // the hardware queues of a process
+constexpr int kServeStreams = 4;   // as many as a process has hardware queues
 
 // What the device tells the host about each slot's job (host-mapped, coherent).
 struct ServeHost {
