@@ -834,7 +834,6 @@ static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
   // flagged, n = 2 sqrt(B)
   const int max_n = std::min(kAntMaxN, (int)(2.2 * std::sqrt((double)o->B)) + 8);
   const double f = o->f_hi / kLightSpeed;
-  if (o->B > (int64_t)kAntMaxN * (kAntMaxN + 1) / 2 || !grid_fits(o->T, 256)) return hipSuccess;
   const AntLayout L = find_antennas(o->T, o->B, uvw, 1e-10 / f, max_n, false);
   const int np = (L.n + kAntBlk - 1) / kAntBlk * kAntBlk;
   // (few baselines over very many times: the padding would outgrow the uvw)
@@ -881,6 +880,7 @@ static hipError_t upload_antennas(vp_obs *o, const double *uvw) {
 // uvw: the rows on the host, or NULL to read them back.
 static hipError_t look_for_antennas(vp_obs *o, const double *uvw) {
   o->ant_looked = true;
+  if (o->B > (int64_t)kAntMaxN * (kAntMaxN + 1) / 2 || !grid_fits(o->T, 256)) return hipSuccess;
   hipError_t e = hipSuccess;
   try {
     std::vector<double> rows;
